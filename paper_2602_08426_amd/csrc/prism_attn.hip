@@ -687,7 +687,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 }
 
 // =====================================================================================
-// The same computation with 64 queries per wave (B = 128, whole blocks, clean lists): workgroup =
+// The same computation with 64 queries per wave (B = 128, d = 128, clean lists): workgroup =
 // 2 waves = one (q-head, q-block) row, one wave per SIMD, two workgroups per CU.  Every K / V^T
 // fragment read from LDS feeds two MFMAs, K and V^T travel as 64-key half tiles through two LDS
 // buffers each, and the row loop (software-pipelined over half-steps, softmax in the shadow of the
@@ -718,6 +718,8 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   const uint32_t k_bytes = (uint32_t)L * kHeadDim * 2;
   const uint32_t vt_bytes = (uint32_t)N * 128u * kHeadDim * 2;
+  const int ragged_block = L < N * 128 ? N - 1 : -1;
+  const int tail1 = causal ? 0 : L - (N - 1) * 128 - 1;       // last token of the last block
 
   int pulled = 0;
   if (t == 0) pulled = atomicAdd(counter + my_queue, 1);
@@ -780,13 +782,18 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
 
     const size_t tok0 = (size_t)u * 128 + (size_t)wave * 64;                    // this wave's first query
     const size_t row0 = (size_t)hq * hs.q + tok0 * kHeadDim;                     // its element offset in Q / O
+    // rows of this wave that exist (a ragged last block may end in front of or inside the wave's 64)
+    const int rows_left = L - (int)tok0;
+    const int rows_here = __builtin_amdgcn_readfirstlane(rows_left < 0 ? 0 : (rows_left > 64 ? 64 : rows_left));
     if (it >= end) {
       // a row without entries: o = 0, lse = -inf
       const int r = lane;                                   // 64 rows per wave, one per lane
-      uint16_t* op = out + row0 + (size_t)r * kHeadDim;
+      if (r < rows_here) {
+        uint16_t* op = out + row0 + (size_t)r * kHeadDim;
 #pragma unroll
-      for (int c = 0; c < 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
-      if (lse != nullptr) lse[(size_t)hq * hs.lse + tok0 + r] = -INFINITY;
+        for (int c = 0; c < 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
+        if (lse != nullptr) lse[(size_t)hq * hs.lse + tok0 + r] = -INFINITY;
+      }
       if (t == 0) pulled = atomicAdd(counter + my_queue, 1);
       continue;
     }
@@ -799,6 +806,8 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     const int32_t* col_row = col_idx + it;
     const int n_entries = end - it;
     int32_t* pull_counter = counter + my_queue;
+    // the one block of the row that has hidden keys: the diagonal, or a ragged last block
+    const int mask_block = causal ? u : ragged_block;
     int pulled_next;
 #include "prism_attn_w64_body.inc"
     if (t == 0) pulled = pulled_next;
@@ -1072,12 +1081,10 @@ using namespace prism;
 // ---- workspace layout: [ V image | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
 //                            bins[2*h*kClasses] | parts[h_kv*kClasses*8] | plan[24] ] ----
 struct AttnWs {
-  size_t image, items, row_rank, row_part, bins, parts, plan, image16, range_flags, pair_items, pair_plan, total;
+  size_t image, items, row_rank, row_part, bins, parts, plan, image16, range_flags, pair_items, pair_plan, total, least;
 };
 // the fp16 image exists where the 64-queries-per-wave kernel can take the call
-static bool w64_shape(const prism_params* p) {
-  return p->block == 128 && p->head_dim == kHeadDim && p->seq_len % 128 == 0;
-}
+static bool w64_shape(const prism_params* p) { return p->block == 128 && p->head_dim == kHeadDim; }
 
 // B = 64 with an even number of blocks: a second plan over pairs of q-blocks for the pair kernel
 static bool pair_shape(const prism_params* p) { return p->block == 64 && n_blocks(p) % 2 == 0; }
@@ -1110,12 +1117,26 @@ static AttnWs attn_ws(const prism_params* p) {
     off = align_up(off + kPlanInts * sizeof(int32_t), 256);
   }
   w.total = off;
+  // A ragged length can do without the fp16 image: a caller with only this much runs the general kernel.
+  w.least = w64_shape(p) && p->seq_len % 128 != 0 ? w.image16 : off;
   return w;
+}
+
+// Does the 64-queries-per-wave kernel take this call?  Decided by the shape and the size of the buffer, in
+// the same way when the V image is written and when it is read.
+// A ragged length takes it too (20 011 tokens, 32 / 8 heads: 704 -> 646 us per layer; 19 290 tokens, 16 heads,
+// bidirectional: 695 -> 640 us against the general kernel), except in calls of so few rows that the list check
+// and the second attention launch cost more than it saves (a batch of eight prompts, five of them ragged with
+// 32 to 1280 rows: 1403 -> 1422 us).
+constexpr int kRaggedW64MinRows = 2048;
+static bool w64_call(const prism_params* p, size_t bytes) {
+  if (!w64_shape(p) || bytes < attn_ws(p).total) return false;
+  return p->seq_len % 128 == 0 || p->n_q_heads * n_blocks(p) >= kRaggedW64MinRows;
 }
 
 static int check_image(const prism_params* params, const void* img, size_t bytes) {
   if (img == nullptr || (reinterpret_cast<uintptr_t>(img) & 255u) != 0 ||
-      bytes < attn_ws(params).total)
+      bytes < attn_ws(params).least)
     return PRISM_ERR_WORKSPACE;
   return PRISM_OK;
 }
@@ -1169,10 +1190,11 @@ static void launch_vt_image(const prism_params* p, const HeadStrides& hs, const 
 }
 
 static int v_image_core(const prism_params* params, const HeadStrides& hs, const void* v_bf16, char* ws,
-                        hipStream_t st) {
+                        size_t ws_bytes, hipStream_t st) {
   const AttnWs W = attn_ws(params);
-  uint16_t* vt16 = w64_shape(params) ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
-  int32_t* range_flags = w64_shape(params) ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
+  const bool w64 = w64_call(params, ws_bytes);
+  uint16_t* vt16 = w64 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
+  int32_t* range_flags = w64 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
   const uint16_t* v = (const uint16_t*)v_bf16;
   uint16_t* vt = reinterpret_cast<uint16_t*>(ws + W.image);
   if (params->block == 128) {
@@ -1195,7 +1217,7 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
   return v_image_core(params, contiguous_heads(params), v_bf16, static_cast<char*>(v_image),
-                      static_cast<hipStream_t>(stream));
+                      v_image_bytes, static_cast<hipStream_t>(stream));
 }
 
 template <int BLK, bool kStreamOnly, int D, bool kPair = false>
@@ -1222,8 +1244,8 @@ static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t*
 
 // Queue build + attention kernels of one sequence (arguments already validated).
 static int attn_core(const prism_params* params, const HeadStrides& hs, const void* q_bf16, const void* k_bf16,
-                     char* ws, const int32_t* row_ptr, const int32_t* col_idx, int64_t col_count,
-                     void* out_bf16, float* lse, hipStream_t st) {
+                     char* ws, size_t ws_bytes, const int32_t* row_ptr, const int32_t* col_idx,
+                     int64_t col_count, void* out_bf16, float* lse, hipStream_t st) {
   const int N = n_blocks(params);
   const int h = params->n_q_heads, h_kv = params->n_kv_heads, L = params->seq_len, d = params->head_dim;
   const int R = h * N;
@@ -1268,10 +1290,10 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const vo
   const uint16_t* kp = (const uint16_t*)k_bf16;
   const uint16_t* vp = reinterpret_cast<const uint16_t*>(ws + W.image);
   uint16_t* op = (uint16_t*)out_bf16;
-  // Whole blocks of 128 tokens go through the 64-queries-per-wave kernel when every list is clean
+  // Blocks of 128 tokens go through the 64-queries-per-wave kernel when every list is clean
   // (decided on the device, so the general kernel is queued behind it and returns at once unless
   // the lists turn out to need it).
-  const bool w64 = w64_shape(params) && !stream_only &&
+  const bool w64 = w64_call(params, ws_bytes) && !stream_only &&
                    !(params->flags & PRISM_FLAG_GENERAL_KERNEL);
   // B = 64 with an even number of blocks: the pair kernel (two q-blocks per workgroup sharing the tiles of
   // the union of their lists) takes the call when every list is ascending and clean; decided on the
@@ -1346,8 +1368,8 @@ extern "C" int prism_sparse_attn_pre(const prism_params* params, const void* q_b
     return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
-  return attn_core(params, contiguous_heads(params), q_bf16, k_bf16, static_cast<char*>(v_image), row_ptr,
-                   col_idx, col_count, out_bf16, lse, static_cast<hipStream_t>(stream));
+  return attn_core(params, contiguous_heads(params), q_bf16, k_bf16, static_cast<char*>(v_image), v_image_bytes,
+                   row_ptr, col_idx, col_count, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16, const void* k_bf16,
@@ -1367,31 +1389,38 @@ extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16,
 }
 
 // ---- packed variable-length batches: one sequence after the other on the stream ---------
-extern "C" int prism_sparse_attn_varlen_workspace_bytes(const prism_params* params, const int32_t* cu_seqlens,
-                                                        int n_seqs, size_t* bytes) {
+static int varlen_workspace(const prism_params* params, const int32_t* cu_seqlens, int n_seqs, size_t* bytes,
+                            size_t* least_bytes) {
   if (bytes == nullptr) return PRISM_ERR_INVALID_ARG;
   int rc = prism_varlen_layout(params, cu_seqlens, n_seqs, nullptr, nullptr, nullptr);
   if (rc != PRISM_OK) return rc;
-  size_t need = 0;
+  size_t need = 0, least = 0;
   for (int s = 0; s < n_seqs; ++s) {
     prism_params ps = *params;
     ps.seq_len = cu_seqlens[s + 1] - cu_seqlens[s];
-    const size_t b = attn_ws(&ps).total;
-    need = b > need ? b : need;
+    const AttnWs w = attn_ws(&ps);
+    need = w.total > need ? w.total : need;
+    least = w.least > least ? w.least : least;
   }
+  if (least_bytes != nullptr) *least_bytes = least;
   *bytes = need;
   return PRISM_OK;
+}
+
+extern "C" int prism_sparse_attn_varlen_workspace_bytes(const prism_params* params, const int32_t* cu_seqlens,
+                                                        int n_seqs, size_t* bytes) {
+  return varlen_workspace(params, cu_seqlens, n_seqs, bytes, nullptr);
 }
 
 extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_t* cu_seqlens, int n_seqs,
                                         const void* q_bf16, const void* k_bf16, const void* v_bf16,
                                         const int32_t* row_ptr, const int32_t* col_idx, void* out_bf16,
                                         float* lse, void* workspace, size_t workspace_bytes, void* stream) {
-  size_t need = 0;
-  int rc = prism_sparse_attn_varlen_workspace_bytes(params, cu_seqlens, n_seqs, &need);
+  size_t need = 0, least = 0;
+  int rc = varlen_workspace(params, cu_seqlens, n_seqs, &need, &least);
   if (rc != PRISM_OK) return rc;
   if (!q_bf16 || !k_bf16 || !v_bf16 || !row_ptr || !col_idx || !out_bf16) return PRISM_ERR_INVALID_ARG;
-  if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
+  if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < least)
     return PRISM_ERR_WORKSPACE;
   const size_t d = params->head_dim, T = params->seq_len;
   const HeadStrides hs{T * d, T * d, T};
@@ -1403,10 +1432,10 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
     const int64_t N = n_blocks(&ps), h = ps.n_q_heads;
     const int64_t cap = (ps.flags & PRISM_FLAG_BIDIRECTIONAL) ? h * N * N : h * N * (N + 1) / 2;
     const size_t tok = (size_t)cu_seqlens[s];
-    rc = v_image_core(&ps, hs, (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), st);
+    rc = v_image_core(&ps, hs, (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), workspace_bytes, st);
     if (rc != PRISM_OK) return rc;
     rc = attn_core(&ps, hs, (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
-                   static_cast<char*>(workspace), row_ptr + ro, col_idx + co, cap, (uint16_t*)out_bf16 + tok * d,
+                   static_cast<char*>(workspace), workspace_bytes, row_ptr + ro, col_idx + co, cap, (uint16_t*)out_bf16 + tok * d,
                    lse != nullptr ? lse + tok : nullptr, st);
     if (rc != PRISM_OK) return rc;
     ro += h * N + 1;
