@@ -32,20 +32,15 @@ namespace prism {
 // exact there; smaller magnitudes lose at most 2^-25 absolute.  A block holding a finite value beyond
 // the fp16 range sets range_flags[kv head * N + block] = 1 (else 0): such inputs go through the
 // general kernel and the bf16 image.
-template <int BLK, int D>
-__global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restrict__ v,
-                                                       uint16_t* __restrict__ vt, int L, int N,
-                                                       size_t kv_head_stride,
-                                                       uint16_t* __restrict__ vt16,
-                                                       int32_t* __restrict__ range_flags) {
-  __shared__ uint16_t tile[BLK][D + 2];
-  __shared__ int s_over;
-  const int blk = blockIdx.x, kvh = blockIdx.y, t = threadIdx.x;
-  const uint16_t* src = v + (size_t)kvh * kv_head_stride + (size_t)blk * BLK * D;
-  const int cnt = min(BLK, L - blk * BLK);
+template <int BLK, int D, int kThreads>
+__device__ __forceinline__ void vt_image_tile(uint16_t (&tile)[BLK][D + 2], int& s_over,
+                                              const uint16_t* __restrict__ src, int cnt,
+                                              uint16_t* __restrict__ dstb, uint16_t* __restrict__ dst16,
+                                              int32_t* __restrict__ range_flag) {
+  const int t = threadIdx.x;
   if (t == 0) s_over = 0;
   constexpr int RCH = D / 8;                         // 16-byte chunks per token row
-  for (int idx = t; idx < BLK * RCH; idx += 256) {
+  for (int idx = t; idx < BLK * RCH; idx += kThreads) {
     const int row = idx / RCH, c = idx % RCH;
     u32x4 x = {0u, 0u, 0u, 0u};                       // V is read once: streaming (non-temporal) loads
     if (row < cnt) x = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (size_t)row * D + c * 8));
@@ -54,9 +49,8 @@ __global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restric
   }
   __syncthreads();
   constexpr int CPR = BLK / 8;                       // 16-byte chunks per image row
-  uint16_t* dstb = vt + ((size_t)kvh * N + blk) * (size_t)D * BLK;
   bool over = false;
-  for (int idx = t; idx < D * CPR; idx += 256) {
+  for (int idx = t; idx < D * CPR; idx += kThreads) {
     const int d = idx / CPR, c = idx % CPR;
     uint32_t w[4], w16[4];
 #pragma unroll
@@ -67,7 +61,7 @@ __global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restric
       const int k1 = (p1 & ~15) + 8 * ((p1 >> 2) & 1) + 4 * ((p1 >> 3) & 1) + (p1 & 3);
       const uint32_t a = tile[k0][d], b = tile[k1][d];
       w[e >> 1] = a | (b << 16);
-      if (vt16 != nullptr) {
+      if (dst16 != nullptr) {
         const float fa = bf16_bits_to_float(a), fb = bf16_bits_to_float(b);
         over |= (fabsf(fa) > 65504.f && fabsf(fa) < INFINITY) || (fabsf(fb) > 65504.f && fabsf(fb) < INFINITY);
         const _Float16 ha = (_Float16)fa, hb = (_Float16)fb;
@@ -75,15 +69,70 @@ __global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restric
       }
     }
     *reinterpret_cast<uint4*>(dstb + (size_t)d * BLK + c * 8) = make_uint4(w[0], w[1], w[2], w[3]);
-    if (vt16 != nullptr)
-      *reinterpret_cast<uint4*>(vt16 + ((size_t)kvh * N + blk) * (size_t)D * BLK + (size_t)d * BLK + c * 8) =
-          make_uint4(w16[0], w16[1], w16[2], w16[3]);
+    if (dst16 != nullptr)
+      *reinterpret_cast<uint4*>(dst16 + (size_t)d * BLK + c * 8) = make_uint4(w16[0], w16[1], w16[2], w16[3]);
   }
-  if (vt16 != nullptr) {
+  if (dst16 != nullptr) {
     if (over) s_over = 1;                            // benign race: every writer stores 1
     __syncthreads();
-    if (t == 0) range_flags[kvh * N + blk] = s_over;
+    if (t == 0) *range_flag = s_over;
   }
+}
+
+template <int BLK, int D>
+__global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restrict__ v,
+                                                       uint16_t* __restrict__ vt, int L, int N,
+                                                       size_t kv_head_stride,
+                                                       uint16_t* __restrict__ vt16,
+                                                       int32_t* __restrict__ range_flags) {
+  __shared__ uint16_t tile[BLK][D + 2];
+  __shared__ int s_over;
+  const int blk = blockIdx.x, kvh = blockIdx.y;
+  const size_t at = ((size_t)kvh * N + blk) * (size_t)D * BLK;
+  vt_image_tile<BLK, D, 256>(tile, s_over, v + (size_t)kvh * kv_head_stride + (size_t)blk * BLK * D,
+                             min(BLK, L - blk * BLK), vt + at, vt16 != nullptr ? vt16 + at : nullptr,
+                             vt16 != nullptr ? range_flags + kvh * N + blk : nullptr);
+}
+
+// =====================================================================================
+// The sequences of one launch.  A call on one sequence has one entry; a packed variable-length batch is
+// taken in groups of up to kMaxGroupSeqs sequences that share every launch.
+// =====================================================================================
+constexpr int kMaxGroupSeqs = 16;
+struct SeqInfo {
+  int32_t tok0;      // first token inside the packed tensors
+  int32_t L, N;      // tokens, blocks
+  int32_t blk0;      // blocks of the sequences in front of it in the group
+  int32_t cap;       // entries of its col_idx part
+  int32_t pad;
+  int64_t row0;      // its part of row_ptr ...
+  int64_t col0;      // ... and of col_idx starts here
+};
+struct SeqTable {
+  int32_t n;         // sequences
+  int32_t nsum;      // blocks of all of them
+  SeqInfo s[kMaxGroupSeqs];
+};
+// A queue entry names its sequence in the high bits of the head number (only where a group holds several).
+constexpr int kSeqShift = 20;
+
+// What decides, on the device, whether the lists and values of a call suit the specialised attention kernels:
+// the call is "dirty" when any word of the two arrays is not zero.
+struct DirtyFlags {
+  const int32_t* a;
+  const int32_t* b;
+  int32_t na, nb;
+};
+template <int kThreads>
+__device__ __forceinline__ bool call_is_dirty(const DirtyFlags& f, int& shared_word) {
+  if (threadIdx.x == 0) shared_word = 0;
+  int bad = 0;
+  for (int i = threadIdx.x; i < f.na; i += kThreads) bad |= f.a[i];
+  for (int i = threadIdx.x; i < f.nb; i += kThreads) bad |= f.b[i];
+  __syncthreads();
+  if (bad != 0) shared_word = 1;                     // every writer stores 1
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(shared_word) != 0;
 }
 
 // =====================================================================================
@@ -245,28 +294,30 @@ __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len,
 // kPair (B = 64, an even number of blocks, every list ascending and clean): items and plan describe PAIR
 // rows (q-blocks 2u' and 2u' + 1 of a head, whose two lists lie one behind the other in col_idx); the
 // workgroup walks the union of the two lists in ascending order, copies every tile of the union once,
-// and the waves of a q-block compute only in the steps whose block their own list names.  `dirty_flag`
-// is the flag word the list check wrote: the pair kernel returns at once when it is set, the plain
-// kernel launched behind it (only_dirty) returns at once when it is not.
+// and the waves of a q-block compute only in the steps whose block their own list names.  `flags` is what
+// the list check found: the pair kernel returns at once on a dirty call, the plain
+// kernel launched behind it (only_dirty) returns at once on a clean one.
 template <int BLK, bool kStreamOnly, int D, bool kPair>
 __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D, kPair>::kWavesPerSimd)) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const int4* __restrict__ items,
-    int32_t* __restrict__ plan, const int32_t* __restrict__ dirty_flag,
-    uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv, int L, int N,
+    int32_t* __restrict__ plan, DirtyFlags flags,
+    uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv, SeqTable seqs,
     HeadStrides hs, int causal, int only_dirty) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's signature
   using C = AttnCfg<BLK, D, kPair>;
   constexpr int KS = C::kKSteps, DT = C::kDTiles;
-  if (kPair) {
-    if ((dirty_flag[0] & kFlagDirtyLists) != 0) return;     // the plain kernel takes this call
-  } else if (only_dirty && (dirty_flag[0] & kFlagDirtyLists) == 0) {
-    return;                                                 // the kernel launched in front of this one took it
-  }
   constexpr int KT = BLK / 32;                       // 32-key tiles per kv block
   __shared__ __attribute__((aligned(16))) char lds_k[C::kTileBytes];
   __shared__ __attribute__((aligned(16))) char lds_v[C::kTileBytes];
   __shared__ int next_item, next_queue;
+  if (kPair) {
+    if (call_is_dirty<C::kThreads>(flags, next_item)) return;   // the plain kernel takes this call
+  } else if (only_dirty) {
+    const bool dirty = call_is_dirty<C::kThreads>(flags, next_item);
+    if (blockIdx.x == 0 && threadIdx.x == 0) plan[kPlanFlags] = dirty ? kFlagDirtyLists : 0;
+    if (!dirty) return;                                     // the kernel launched in front of this one took it
+  }
 
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int l32 = lane & 31, hf = lane >> 5;
@@ -301,10 +352,6 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   int seg_start = plan[kPlanStart + my_queue];
   int seg_len = plan[kPlanLen + my_queue];
   int32_t* counter = plan + kPlanCounter;
-  const int vmax_nc = N - 1;
-  const int tail = L - (N - 1) * BLK;              // tokens in the last block (BLK unless ragged)
-  const uint32_t head_bytes = (uint32_t)L * D * 2;
-  const uint32_t image_head_bytes = (uint32_t)N * C::kTileBytes;
 
   // The queue is pulled when a workgroup is about to become free (at the top of the last
   // step of its row), so neighbouring rows of the queue start close together; the pull and the
@@ -366,7 +413,18 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       __syncthreads();
       continue;
     }
-    const int hq = cur_x;
+    cur_x = __builtin_amdgcn_readfirstlane(cur_x);
+    cur_y = __builtin_amdgcn_readfirstlane(cur_y);
+    cur_z = __builtin_amdgcn_readfirstlane(cur_z);
+    cur_w = __builtin_amdgcn_readfirstlane(cur_w);
+    const int sq = seqs.n > 1 ? cur_x >> kSeqShift : 0;
+    const int hq = seqs.n > 1 ? cur_x & ((1 << kSeqShift) - 1) : cur_x;
+    const int L = seqs.s[sq].L, N = seqs.s[sq].N, tok0 = seqs.s[sq].tok0;
+    const int vmax_nc = N - 1;
+    const int tail = L - (N - 1) * BLK;              // tokens in the last block (BLK unless ragged)
+    const uint32_t head_bytes = (uint32_t)L * D * 2;
+    const uint32_t image_head_bytes = (uint32_t)N * C::kTileBytes;
+    const int32_t* __restrict__ cols = col_idx + seqs.s[sq].col0;
     const int u = cur_y & 0xffff;
     int v = (cur_y >> 16) & 0xffff;
     int it = cur_z;
@@ -381,10 +439,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     if (!has_work) {
       // a row without a valid entry (o = 0, lse = -inf): no tile work; pull the next row right away
       if (kind_cur == kItemRow && qrow < L) {
-        uint16_t* op = out + (size_t)hq * hs.q + (size_t)qrow * D + hf * (D / 2);
+        uint16_t* op = out + (size_t)hq * hs.q + (size_t)(tok0 + qrow) * D + hf * (D / 2);
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
-        if (lse != nullptr && hf == 0) lse[(size_t)hq * hs.lse + qrow] = -INFINITY;
+        if (lse != nullptr && hf == 0) lse[(size_t)hq * hs.lse + tok0 + qrow] = -INFINITY;
       }
       if (t == 0) next_item = atomicAdd(counter + my_queue, 1);
       __syncthreads();
@@ -401,8 +459,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     // K and V^T of this kv head as buffer resources (tile v starts at byte v * kTileBytes).
     // K is the caller's tensor: rows past L in a ragged last block are outside the resource and
     // read as zeros.  The V^T image is padded to whole blocks.
-    const __amdgpu_buffer_rsrc_t krs = make_rsrc(k + (size_t)kvh * hs.kv, head_bytes);
-    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(vt + (size_t)kvh * N * BLK * D, image_head_bytes);
+    const __amdgpu_buffer_rsrc_t krs = make_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
+    const __amdgpu_buffer_rsrc_t vrs =
+        make_rsrc(vt + ((size_t)seqs.s[sq].blk0 * (h / g) + (size_t)kvh * N) * BLK * D, image_head_bytes);
     const int vmax = causal ? u_own : vmax_nc;
 
     // Pair rows: the two lists [it, mid) and [mid, end) are walked together, smallest block first;
@@ -420,22 +479,22 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       const int aa = (ca == vv ? 1 : 0) | (cb == vv ? 2 : 0);
       if (aa & 1) {
         ++ia;
-        if (ia < mid) ca_raw = col_idx[ia];
+        if (ia < mid) ca_raw = cols[ia];
       }
       if (aa & 2) {
         ++ib;
-        if (ib < end) cb_raw = col_idx[ib];
+        if (ib < end) cb_raw = cols[ib];
       }
       *vout = vv;
       *actout = aa;
     };
     if (kPair) {
-      mid = __builtin_amdgcn_readfirstlane(row_ptr[(size_t)hq * N + 2 * u + 1]);
+      mid = __builtin_amdgcn_readfirstlane(row_ptr[seqs.s[sq].row0 + (size_t)hq * N + 2 * u + 1]);
       mid = mid < it ? it : (mid > end ? end : mid);
       ia = it;
       ib = mid;
-      if (ia < mid) ca_raw = col_idx[ia];
-      if (ib < end) cb_raw = col_idx[ib];
+      if (ia < mid) ca_raw = cols[ia];
+      if (ib < end) cb_raw = cols[ib];
       pair_advance(&v, &act);                          // has_work: at least one entry
       active = ((act >> sub) & 1) != 0;
     }
@@ -443,7 +502,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     // Q fragments (B operand of S^T = K Q^T): query row 32*wave + l32, dims 16*ks + 8*hf ..+7
     bf16x8 qf[KS];
     {
-      const uint16_t* qp = q + (size_t)hq * hs.q + (size_t)min(qrow, L - 1) * D + hf * 8;
+      const uint16_t* qp = q + (size_t)hq * hs.q + (size_t)(tok0 + min(qrow, L - 1)) * D + hf * 8;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
     }
@@ -470,6 +529,12 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       async_load_vt_tile<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t);
 
       f32x16 sacc[KT];
+      if (kPair) {
+        // whatever the registers hold: without this the compiler writes zeros for the steps a wave sits out, and does
+        // so in every step (48 moves; 4 % of a 64 x 64 step)
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) asm volatile("" : "=v"(sacc[kt]));
+      }
       if (!kStreamOnly && active) {
       // ---- S^T = K Q^T ----
       // Flat software pipeline over the KT*KS (tile, k-step) pairs: the LDS read of step
@@ -503,27 +568,36 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       if (!kLast) async_load_k_tile<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t);
 
       bf16x8 pf[KT][2];
+      if (kPair) {
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) asm volatile("" : "=v"(pf[kt][s]));
+      }
       if (!kStreamOnly && active) {
       // ---- causal mask inside the diagonal block ----
       if (causal && v == u_own) {
-        const int qloc = (wave % C::kRowWaves) * 32 + l32;
+        int last = (wave % C::kRowWaves) * 32 + l32 - 4 * hf;    // key kloc is kc behind 4 * hf
+        asm volatile("" : "+v"(last));                           // formed here, not kept across the row loop
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int kloc = kt * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-            if (kloc > qloc) sacc[kt][r] = -INFINITY;
+            const int kc = kt * 32 + 8 * (r >> 2) + (r & 3);
+            if (kc > last) sacc[kt][r] = -INFINITY;
           }
       }
 
       // ---- keys past the end of the sequence (ragged last block) ----
       if (v == N - 1 && tail < BLK) {
+        int left = tail - 4 * hf;
+        asm volatile("" : "+v"(left));
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int kloc = kt * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-            if (kloc >= tail) sacc[kt][r] = -INFINITY;
+            const int kc = kt * 32 + 8 * (r >> 2) + (r & 3);
+            if (kc >= left) sacc[kt][r] = -INFINITY;
           }
       }
 
@@ -629,7 +703,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       }
       step(std::true_type{});
     } else {
-    int ahead = it + 1 < end ? col_idx[it + 1] : -1;
+    int ahead = it + 1 < end ? cols[it + 1] : -1;
     for (;;) {
       // next valid entry (v_next <= vmax): normally the entry fetched one block ago; entries
       // that must be skipped (negative or beyond vmax) take the slow path
@@ -638,13 +712,13 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       if (nx < end && !(v_next >= 0 && v_next <= vmax)) {
         ++nx;
         while (nx < end) {
-          v_next = __builtin_amdgcn_readfirstlane(col_idx[nx]);
+          v_next = __builtin_amdgcn_readfirstlane(cols[nx]);
           if (v_next >= 0 && v_next <= vmax) break;
           ++nx;
         }
       }
       if (nx >= end) break;
-      ahead = nx + 1 < end ? col_idx[nx + 1] : -1;
+      ahead = nx + 1 < end ? cols[nx + 1] : -1;
       step(std::false_type{});
       it = nx;
       v = v_next;
@@ -655,7 +729,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     // ---- epilogue: O = O^T / l, bf16, [q][d] ----
     const float l_tot = other_half_sum(l_run);
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    uint16_t* op = out + (size_t)hq * hs.q + (size_t)qrow * D;
+    uint16_t* op = out + (size_t)hq * hs.q + (size_t)(tok0 + qrow) * D;
     if (qrow < L) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -673,7 +747,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
         }
     }
     if (lse != nullptr && hf == 0 && qrow < L)
-      lse[(size_t)hq * hs.lse + qrow] =
+      lse[(size_t)hq * hs.lse + tok0 + qrow] =
           l_tot > 0.f ? (m_run + log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
 
     // ---- the row pulled in the last step becomes the current one ----
@@ -699,12 +773,12 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
     const int32_t* __restrict__ col_idx, const int4* __restrict__ items, int32_t* __restrict__ plan,
-    uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv, int L, int N, HeadStrides hs,
-    int causal) {
+    DirtyFlags flags, uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv, SeqTable seqs,
+    HeadStrides hs, int causal) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) char lds_tiles[65536];
   __shared__ int s_pulled, s_queue;
-  if ((plan[kPlanFlags] & kFlagDirtyLists) != 0) return;    // the general kernel takes this call
+  if (call_is_dirty<128>(flags, s_pulled)) return;          // the general kernel takes this call
 
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -716,11 +790,6 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
   int seg_len = plan[kPlanLen + my_queue];
   int32_t* counter = plan + kPlanCounter;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
-  const uint32_t k_bytes = (uint32_t)L * kHeadDim * 2;
-  const uint32_t vt_bytes = (uint32_t)N * 128u * kHeadDim * 2;
-  const int ragged_block = L < N * 128 ? N - 1 : -1;
-  const int tail1 = causal ? 0 : L - (N - 1) * 128 - 1;       // last token of the last block
-
   int pulled = 0;
   if (t == 0) pulled = atomicAdd(counter + my_queue, 1);
   for (;;) {
@@ -771,7 +840,14 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
       seg_len = plan[kPlanLen + my_queue];
     }
     const int4 it0 = items[seg_start + pos];
-    const int hq = __builtin_amdgcn_readfirstlane(it0.x);
+    const int head_word = __builtin_amdgcn_readfirstlane(it0.x);
+    const int sq = seqs.n > 1 ? head_word >> kSeqShift : 0;
+    const int hq = seqs.n > 1 ? head_word & ((1 << kSeqShift) - 1) : head_word;
+    const int L = seqs.s[sq].L, N = seqs.s[sq].N;
+    const uint32_t k_bytes = (uint32_t)L * kHeadDim * 2;
+    const uint32_t vt_bytes = (uint32_t)N * 128u * kHeadDim * 2;
+    const int ragged_block = L < N * 128 ? N - 1 : -1;
+    const int tail1 = causal ? 0 : L - (N - 1) * 128 - 1;     // last token of the last block
     const int u = __builtin_amdgcn_readfirstlane(it0.y) & 0xffff;
     const int c_first = (__builtin_amdgcn_readfirstlane(it0.y) >> 16) & 0xffff;   // first listed block
     const int it = __builtin_amdgcn_readfirstlane(it0.z);
@@ -780,10 +856,11 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     // the start of its last PV phase) and looked at after it: pulling at the start of a row would
     // reserve a row that its neighbours in the queue have long passed by the time it is started.
 
-    const size_t tok0 = (size_t)u * 128 + (size_t)wave * 64;                    // this wave's first query
+    const int q0 = u * 128 + wave * 64;                                          // this wave's first query
+    const size_t tok0 = (size_t)seqs.s[sq].tok0 + q0;                            // its token in the tensors
     const size_t row0 = (size_t)hq * hs.q + tok0 * kHeadDim;                     // its element offset in Q / O
     // rows of this wave that exist (a ragged last block may end in front of or inside the wave's 64)
-    const int rows_left = L - (int)tok0;
+    const int rows_left = L - q0;
     const int rows_here = __builtin_amdgcn_readfirstlane(rows_left < 0 ? 0 : (rows_left > 64 ? 64 : rows_left));
     if (it >= end) {
       // a row without entries: o = 0, lse = -inf
@@ -801,11 +878,11 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     uint16_t* o_row = out + row0;
     float* lse_row = lse != nullptr ? lse + (size_t)hq * hs.lse + tok0 : nullptr;
     const int kvh = hq / g;
-    const uint16_t* k_head = k + (size_t)kvh * hs.kv;
-    const uint16_t* vt_head = vt + (size_t)kvh * N * 128 * kHeadDim;
-    const int32_t* col_row = col_idx + it;
+    const uint16_t* k_head = k + (size_t)kvh * hs.kv + (size_t)seqs.s[sq].tok0 * kHeadDim;
+    const uint16_t* vt_head = vt + ((size_t)seqs.s[sq].blk0 * h_kv + (size_t)kvh * N) * 128 * kHeadDim;
+    const int32_t* col_row = col_idx + seqs.s[sq].col0 + it;
     const int n_entries = end - it;
-    int32_t* pull_counter = counter + my_queue;
+    int32_t* pull_counter = counter + __builtin_amdgcn_readfirstlane(my_queue);
     // the one block of the row that has hidden keys: the diagonal, or a ragged last block
     const int mask_block = causal ? u : ragged_block;
     int pulled_next;
@@ -1074,6 +1151,281 @@ __global__ __launch_bounds__(256) void queue_fill_kernel(const int32_t* __restri
   if (entry >= 0 && entry < c.h * c.N) items[entry] = make_int4(hq, u | (v << 16), it, end);
 }
 
+// =====================================================================================
+// Everything in front of the attention kernels in one launch, for calls of up to kPrepMaxRows rows whose kv heads
+// form one phase: workgroup 0 (and 1, where the pair kernel may take the call) builds a queue plan, the next
+// `n_check` workgroups look the lists over, the rest write the V image.  The parts do not depend on each other;
+// the attention kernels read what the list check and the image found through DirtyFlags.
+// Such calls are bound by launches: a kernel with next to no work takes 4.5 us, and as four to nine kernels the same
+// work took 34 of 266 us per layer at 8K tokens and 14 of 47 us at 2K tokens and one head (the attention dispatch has
+// the figures of both sides).
+// =====================================================================================
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepMaxRows = 8 * kPrepThreads;
+constexpr int kCheckRows = 64;             // rows per list-check workgroup
+struct PrepArgs {
+  const int32_t *row_ptr, *col_idx;
+  const uint16_t* v;                       // null: the image is there already
+  uint16_t *vt, *vt16;
+  int32_t *range_flags, *check;
+  int4 *items, *pair_items;
+  int32_t *plan, *pair_plan;
+  int32_t h, h_kv, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
+  size_t kv_head_stride;
+};
+
+// The sequence that holds index i of a numbering in which sequence s starts at mult * blk0[s].
+__device__ __forceinline__ int seq_of(const SeqTable& seqs, int i, int mult) {
+  int s = 0;
+  while (s + 1 < seqs.n && i >= mult * seqs.s[s + 1].blk0) ++s;
+  return s;
+}
+
+// One workgroup writes the plan of all rows: the order, parts and entries of queue_count / rank / fill_kernel for one
+// phase.  Wave w owns the rows 64*CH*w .. of the order (q-head, sequence, q-block descending), 64 at a time; rank and
+// work of a row inside its length class come from ballots and prefix sums over the wave, then over the 16 waves.
+struct PlanLds {
+  int rows[16][kClasses], work[16][kClasses];       // per wave: totals, then what lies in front of the wave
+  float scale[kClasses];                            // parts per unit of work
+  int start[kClasses][9];                           // first rank of the class that belongs to part x
+  int before[kClasses][8], qlen[8];
+};
+// stride = 2: rows are pairs of q-blocks (every sequence has an even number of them).
+template <int CH>
+__device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const SeqTable& seqs, int stride,
+                                          int n_queues, int4* __restrict__ items, int32_t* __restrict__ plan) {
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int per_head = seqs.nsum >> (stride - 1);
+  const int R = a.h * per_head;
+  // Row i of the order: its sequence, q-head and number inside the head.
+  struct Row {
+    int s, hq, u;
+  };
+  // (a fp32 product instead of an integer division: i < 2^13, so (i + 1/2) / per_head is at least 2^-14 of itself
+  // away from a whole number and the rounding errors of the product, below 2^-22, cannot cross one)
+  const float per_head_inv = 1.0f / (float)per_head;
+  auto row = [&](int i) {
+    Row r;
+    r.hq = (int)(((float)i + 0.5f) * per_head_inv);
+    const int rem = i - r.hq * per_head;
+    r.s = seq_of(seqs, rem * stride, 1);
+    r.u = (seqs.s[r.s].N >> (stride - 1)) - 1 - (rem - (seqs.s[r.s].blk0 >> (stride - 1)));
+    return r;
+  };
+  // The bounds of all rows are requested at once, and at the end the first entries of all lists: two memory round trips
+  // for the workgroup.  What remains is a few hundred instructions per 64 rows of a wave on one CU, 9.5 us at 2048 rows
+  // (an integer division per row and part and a prefix sum over every class, there or not, took 11.1 us).
+  int beg[CH], len[CH];                               // len = -1 past the last row
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int i = (wave * CH + c) * 64 + lane;
+    beg[c] = 0;
+    len[c] = -1;
+    if (i < R) {
+      const Row r = row(i);
+      const int32_t* rp = a.row_ptr + seqs.s[r.s].row0 +
+                          ((size_t)r.hq * (seqs.s[r.s].N >> (stride - 1)) + r.u) * stride;
+      beg[c] = rp[0];
+      len[c] = rp[stride];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int i = (wave * CH + c) * 64 + lane;
+    if (i < R) {
+      const int s = row(i).s, cap = seqs.s[s].cap;
+      const int b = beg[c] < 0 ? 0 : (beg[c] > cap ? cap : beg[c]), e = len[c];
+      beg[c] = b;
+      len[c] = (e < b ? b : (e > cap ? cap : e)) - b;
+    }
+  }
+  int rank[CH], cum[CH];
+  // Lane k counts the rows and the work of class k that the wave has met.  64 neighbouring rows fall into two or three
+  // classes: one round per class that is there.
+  int crow = 0, cwork = 0;
+  // work of a row: its entries + 1; a list with repeated entries weighs no more than 2 * kMaxBlocks
+  auto weight = [&](int c) { return min(len[c], 2 * kMaxBlocks) + 1; };
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int cls = len[c] < 0 ? -1 : length_class(len[c]);
+    rank[c] = cum[c] = 0;
+    unsigned long long todo = __ballot(cls >= 0);
+    while (todo != 0ull) {                              // uniform
+      const int k = __builtin_amdgcn_readlane(cls, __builtin_ctzll(todo));
+      const unsigned long long mine = __ballot(cls == k);
+      const int incl = wave_scan_inclusive(cls == k ? weight(c) : 0);
+      const int r0 = __builtin_amdgcn_readlane(crow, k), w0 = __builtin_amdgcn_readlane(cwork, k);
+      if (cls == k) {
+        rank[c] = r0 + __popcll(mine & ((1ull << lane) - 1ull));
+        cum[c] = w0 + incl;
+      }
+      const int r1 = r0 + __popcll(mine), w1 = w0 + __builtin_amdgcn_readlane(incl, 63);
+      crow = lane == k ? r1 : crow;
+      cwork = lane == k ? w1 : cwork;
+      todo &= ~mine;
+    }
+  }
+  if (lane < kClasses) {
+    m.rows[wave][lane] = crow;
+    m.work[wave][lane] = cwork;
+  }
+  __syncthreads();
+  if (t < kClasses) {
+    int r = 0, w = 0;
+    for (int i = 0; i < 16; ++i) {
+      const int nr = m.rows[i][t], nw = m.work[i][t];
+      m.rows[i][t] = r;
+      m.work[i][t] = w;
+      r += nr;
+      w += nw;
+    }
+    m.scale[t] = w > 0 ? (float)n_queues / (float)w : 0.f;
+    for (int x = 0; x < 9; ++x) m.start[t][x] = r;
+  }
+  __syncthreads();
+  // part of the row that ends at work `w` of its class: grows with w, 0 .. n_queues - 1
+  auto part = [&](int w, int k) { return min((int)((float)(w - 1) * m.scale[k]), n_queues - 1); };
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    if (len[c] >= 0) {
+      const int k = length_class(len[c]);
+      rank[c] += m.rows[wave][k];
+      cum[c] += m.work[wave][k];
+      const int x1 = part(cum[c], k);
+      const int prev = rank[c] == 0 ? -1 : part(cum[c] - weight(c), k);
+      for (int x = prev + 1; x <= x1; ++x) m.start[k][x] = rank[c];
+    }
+  }
+  __syncthreads();
+  if (t < 8) {
+    int run = 0;
+    for (int k = 0; k < kClasses; ++k) {
+      m.before[k][t] = run;
+      run += m.start[k][t + 1] - m.start[k][t];
+    }
+    m.qlen[t] = run;
+  }
+  __syncthreads();
+  if (t < 8) {
+    int start = 0;
+    for (int x = 0; x < t; ++x) start += m.qlen[x];
+    plan[kPlanStart + t] = start;
+    plan[kPlanLen + t] = m.qlen[t];
+    plan[kPlanCounter + t] = 0;
+    plan[kPlanFlags + t] = 0;
+  }
+  // rank becomes the row's entry, cum its list's first element
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    if (len[c] < 0) continue;
+    const int k = length_class(len[c]), x = part(cum[c], k);
+    int entry = m.before[k][x] + rank[c] - m.start[k][x];
+    for (int y = 0; y < x; ++y) entry += m.qlen[y];
+    rank[c] = entry;
+    cum[c] = 0;
+    if (stride == 1 && len[c] > 0)
+      cum[c] = a.col_idx[seqs.s[row((wave * CH + c) * 64 + lane).s].col0 + beg[c]];
+  }
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    if (len[c] < 0) continue;
+    const Row r = row((wave * CH + c) * 64 + lane);
+    const int end = beg[c] + len[c];
+    int it = beg[c], v = cum[c];
+    if (stride == 1) {
+      const int vmax = a.causal ? r.u : seqs.s[r.s].N - 1;
+      if (len[c] == 0 || v < 0 || v > vmax) {          // rare: look for the first entry that names a valid block
+        const int32_t* cols = a.col_idx + seqs.s[r.s].col0;
+        for (v = 0; it < end; ++it) {
+          const int w = cols[it];
+          if (w >= 0 && w <= vmax) {
+            v = w;
+            break;
+          }
+        }
+      }
+    }                                                  // pair rows: clean lists, the kernel finds its first block
+    items[rank[c]] = make_int4(seqs.n > 1 ? r.hq | (r.s << kSeqShift) : r.hq, r.u | (v << 16), it, end);
+  }
+}
+
+// Does some list of the 64 rows of this workgroup hold an entry to skip (queue_validate_kernel's question)?
+__device__ __forceinline__ void check_rows(const PrepArgs& a, const SeqTable& seqs, int wg, int& s_bad) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int R = a.h * seqs.nsum;
+  bool bad = false;
+  for (int j = 0; j < kCheckRows / 16; ++j) {
+    const int r = wg * kCheckRows + j * 16 + wave;
+    if (r >= R) break;
+    const int s = seq_of(seqs, r, a.h);
+    const int rr = r - a.h * seqs.s[s].blk0, N = seqs.s[s].N, cap = seqs.s[s].cap;
+    int b = a.row_ptr[seqs.s[s].row0 + rr], e = a.row_ptr[seqs.s[s].row0 + rr + 1];
+    bad |= b < 0 || b > cap || e < b || e > cap;
+    b = b < 0 ? 0 : (b > cap ? cap : b);
+    e = e < b ? b : (e > cap ? cap : e);
+    const int vmax = a.causal ? rr % N : N - 1;
+    const int32_t* cols = a.col_idx + seqs.s[s].col0;
+    for (int i = b + lane; i < e; i += 64) {
+      const int v = cols[i];
+      bad |= v < 0 || v > vmax;
+      if (a.need_sorted && i + 1 < e) bad |= cols[i + 1] <= v;
+    }
+  }
+  if (threadIdx.x == 0) s_bad = 0;
+  __syncthreads();
+  if (bad) s_bad = 1;                                // every writer stores 1
+  __syncthreads();
+  if (threadIdx.x == 0) a.check[wg] = s_bad;
+}
+
+template <int BLK, int D>
+union PrepLds {
+  PlanLds plan;
+  uint16_t tile[BLK][D + 2];
+};
+template <int BLK, int D>
+__global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTable table) {
+  __shared__ PrepLds<BLK, D> lds;
+  // The table in LDS: indexed by a lane's own sequence the kernel argument would be copied to scratch memory.
+  __shared__ SeqTable seqs;
+  if (threadIdx.x == 0) {
+    seqs.n = table.n;
+    seqs.nsum = table.nsum;
+  }
+#pragma unroll
+  for (int i = 0; i < kMaxGroupSeqs; ++i)
+    if (i < table.n && threadIdx.x == i) seqs.s[i] = table.s[i];
+  __syncthreads();
+  __shared__ int s_over;
+  int wg = blockIdx.x;
+  if (wg < a.n_plans) {
+    const int stride = 1 + wg;
+    const int R = a.h * seqs.nsum / stride;
+    const int n_queues = wg == 0 ? a.n_queues : a.pair_queues;
+    int4* items = wg == 0 ? a.items : a.pair_items;
+    int32_t* plan = wg == 0 ? a.plan : a.pair_plan;
+    if (R <= kPrepThreads) plan_rows<1>(lds.plan, a, seqs, stride, n_queues, items, plan);
+    else if (R <= 2 * kPrepThreads) plan_rows<2>(lds.plan, a, seqs, stride, n_queues, items, plan);
+    else if (R <= 4 * kPrepThreads) plan_rows<4>(lds.plan, a, seqs, stride, n_queues, items, plan);
+    else plan_rows<8>(lds.plan, a, seqs, stride, n_queues, items, plan);
+    return;
+  }
+  wg -= a.n_plans;
+  if (wg < a.n_check) {
+    check_rows(a, seqs, wg, s_over);
+    return;
+  }
+  wg -= a.n_check;
+  const int s = seq_of(seqs, wg, a.h_kv);
+  const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
+  const int kvh = rr / N, blk = rr - kvh * N;
+  const size_t at = (size_t)wg * D * BLK;
+  vt_image_tile<BLK, D, kPrepThreads>(
+      lds.tile, s_over, a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * BLK) * D,
+      min(BLK, seqs.s[s].L - blk * BLK), a.vt + at, a.vt16 != nullptr ? a.vt16 + at : nullptr,
+      a.vt16 != nullptr ? a.range_flags + wg : nullptr);
+}
+
 }  // namespace prism
 
 using namespace prism;
@@ -1089,8 +1441,8 @@ static bool w64_shape(const prism_params* p) { return p->block == 128 && p->head
 // B = 64 with an even number of blocks: a second plan over pairs of q-blocks for the pair kernel
 static bool pair_shape(const prism_params* p) { return p->block == 64 && n_blocks(p) % 2 == 0; }
 
-static AttnWs attn_ws(const prism_params* p) {
-  const size_t N = n_blocks(p);
+// The layout for `N` blocks (those of one sequence, or of a group of a packed batch).
+static AttnWs attn_layout(const prism_params* p, size_t N, bool pairs) {
   const size_t rows = (size_t)p->n_q_heads * N;
   const size_t image_bytes = (size_t)p->n_kv_heads * N * p->block * p->head_dim * 2;
   AttnWs w;
@@ -1111,7 +1463,7 @@ static AttnWs attn_ws(const prism_params* p) {
   }
   w.pair_items = off;
   w.pair_plan = off;
-  if (pair_shape(p)) {
+  if (pairs) {
     off = align_up(off + rows / 2 * sizeof(int4), 256);
     w.pair_plan = off;
     off = align_up(off + kPlanInts * sizeof(int32_t), 256);
@@ -1121,6 +1473,7 @@ static AttnWs attn_ws(const prism_params* p) {
   w.least = w64_shape(p) && p->seq_len % 128 != 0 ? w.image16 : off;
   return w;
 }
+static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), pair_shape(p)); }
 
 // Does the 64-queries-per-wave kernel take this call?  Decided by the shape and the size of the buffer, in
 // the same way when the V image is written and when it is read.
@@ -1166,6 +1519,14 @@ static int device_facts(DeviceFacts* out) {
 // kept to kCacheBudgetBytes of it.
 constexpr size_t kCacheBudgetBytes = (size_t)160 << 20;
 
+// kv heads whose K and V^T fit that budget together, at least one
+static int heads_in_cache(const prism_params* p, const SeqTable& seqs) {
+  size_t tokens = 0;
+  for (int i = 0; i < seqs.n; ++i) tokens += seqs.s[i].L;
+  const size_t fit = kCacheBudgetBytes / (tokens * p->head_dim * 2 * 2);
+  return fit < 1 ? 1 : (fit > 0x7fffffff ? 0x7fffffff : (int)fit);
+}
+
 static int persistent_grid(int rows, int wgs_per_cu) {
   DeviceFacts f;
   if (device_facts(&f) != PRISM_OK) return -1;
@@ -1189,14 +1550,9 @@ static void launch_vt_image(const prism_params* p, const HeadStrides& hs, const 
                      hs.kv, vt16, range_flags);
 }
 
-static int v_image_core(const prism_params* params, const HeadStrides& hs, const void* v_bf16, char* ws,
-                        size_t ws_bytes, hipStream_t st) {
-  const AttnWs W = attn_ws(params);
-  const bool w64 = w64_call(params, ws_bytes);
-  uint16_t* vt16 = w64 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
-  int32_t* range_flags = w64 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
+static int v_image_core(const prism_params* params, const HeadStrides& hs, const void* v_bf16, uint16_t* vt,
+                        uint16_t* vt16, int32_t* range_flags, hipStream_t st) {
   const uint16_t* v = (const uint16_t*)v_bf16;
-  uint16_t* vt = reinterpret_cast<uint16_t*>(ws + W.image);
   if (params->block == 128) {
     if (params->head_dim == 64) launch_vt_image<128, 64>(params, hs, v, vt, vt16, range_flags, st);
     else if (params->head_dim == 128) launch_vt_image<128, 128>(params, hs, v, vt, vt16, range_flags, st);
@@ -1216,18 +1572,37 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
   if (!v_bf16) return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
-  return v_image_core(params, contiguous_heads(params), v_bf16, static_cast<char*>(v_image),
-                      v_image_bytes, static_cast<hipStream_t>(stream));
+  const AttnWs W = attn_ws(params);
+  char* ws = static_cast<char*>(v_image);
+  const bool w64 = w64_call(params, v_image_bytes);
+  return v_image_core(params, contiguous_heads(params), v_bf16, reinterpret_cast<uint16_t*>(ws + W.image),
+                      w64 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr,
+                      w64 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr, static_cast<hipStream_t>(stream));
 }
 
 template <int BLK, bool kStreamOnly, int D, bool kPair = false>
 static void launch_attn(int grid, hipStream_t st, const uint16_t* q, const uint16_t* k, const uint16_t* vt,
                         const int32_t* row_ptr, const int32_t* col_idx, const int4* items, int32_t* plan,
-                        const int32_t* dirty_flag, uint16_t* out, float* lse, int h, int h_kv, int L, int N,
+                        const DirtyFlags& flags, uint16_t* out, float* lse, int h, int h_kv, const SeqTable& seqs,
                         const HeadStrides& hs, int causal, int only_dirty) {
   hipLaunchKernelGGL((sparse_attn_kernel<BLK, kStreamOnly, D, kPair>), dim3(grid),
                      dim3(AttnCfg<BLK, D, kPair>::kThreads), 0, st, q, k, vt, row_ptr, col_idx, items, plan,
-                     dirty_flag, out, lse, h, h_kv, L, N, hs, causal, only_dirty);
+                     flags, out, lse, h, h_kv, seqs, hs, causal, only_dirty);
+}
+
+template <int BLK, int D>
+static void launch_prep(int grid, const PrepArgs& a, const SeqTable& seqs, hipStream_t st) {
+  hipLaunchKernelGGL((prep_kernel<BLK, D>), dim3(grid), dim3(kPrepThreads), 0, st, a, seqs);
+}
+
+static SeqTable one_sequence(const prism_params* p, int64_t col_count) {
+  SeqTable t = {};
+  t.n = 1;
+  t.nsum = n_blocks(p);
+  t.s[0].L = p->seq_len;
+  t.s[0].N = n_blocks(p);
+  t.s[0].cap = col_count > 0x7fffffff ? 0x7fffffff : (int)col_count;     // CSR offsets are int32
+  return t;
 }
 
 // the three kernels that turn index lists into the queue plan of `pc`
@@ -1242,14 +1617,14 @@ static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t*
                      parts, row_rank, row_part, plan, items);
 }
 
-// Queue build + attention kernels of one sequence (arguments already validated).
-static int attn_core(const prism_params* params, const HeadStrides& hs, const void* q_bf16, const void* k_bf16,
-                     char* ws, size_t ws_bytes, const int32_t* row_ptr, const int32_t* col_idx,
-                     int64_t col_count, void* out_bf16, float* lse, hipStream_t st) {
-  const int N = n_blocks(params);
-  const int h = params->n_q_heads, h_kv = params->n_kv_heads, L = params->seq_len, d = params->head_dim;
+// The whole attention of the sequences in `seqs` (arguments already validated; several sequences only where
+// R <= kPrepMaxRows and one phase).  `v_bf16`: the V image is written first; null: it is there already.
+static int attn_core(const prism_params* params, const HeadStrides& hs, const SeqTable& seqs, const AttnWs& W,
+                     bool w64_takes, const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws,
+                     const int32_t* row_ptr, const int32_t* col_idx, void* out_bf16, float* lse, hipStream_t st) {
+  const int h = params->n_q_heads, h_kv = params->n_kv_heads, d = params->head_dim;
+  const int N = seqs.nsum;
   const int R = h * N;
-  const AttnWs W = attn_ws(params);
   int4* items = reinterpret_cast<int4*>(ws + W.items);
   int32_t* row_rank = reinterpret_cast<int32_t*>(ws + W.row_rank);
   int32_t* row_part = reinterpret_cast<int32_t*>(ws + W.row_part);
@@ -1272,28 +1647,28 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const vo
   pc.g = h / h_kv;
   pc.N = N;
   pc.n_queues = grid < kXcds ? 1 : kXcds;
-  const size_t head_bytes = (size_t)L * d * 2 * 2;                        // K + V^T of one kv head
-  pc.heads_per_phase = (int)(kCacheBudgetBytes / head_bytes) < 1 ? 1 : (int)(kCacheBudgetBytes / head_bytes);
+  pc.heads_per_phase = heads_in_cache(params, seqs);
   pc.n_phases = (h_kv + pc.heads_per_phase - 1) / pc.heads_per_phase;
   if (pc.n_phases * kClasses > kMaxGroups) {                               // very many kv heads: larger phases
     pc.n_phases = kMaxGroups / kClasses;
     pc.heads_per_phase = (h_kv + pc.n_phases - 1) / pc.n_phases;
     pc.n_phases = (h_kv + pc.heads_per_phase - 1) / pc.heads_per_phase;
   }
-  pc.cap = col_count > 0x7fffffff ? 0x7fffffff : (int)col_count;     // CSR offsets are int32
+  pc.cap = seqs.s[0].cap;
   pc.causal = (params->flags & PRISM_FLAG_BIDIRECTIONAL) ? 0 : 1;
   pc.stride = 1;
-  build_plan(pc, row_ptr, col_idx, bins, parts, row_rank, row_part, plan, items, st);
   const int causal = pc.causal;
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
-  const uint16_t* vp = reinterpret_cast<const uint16_t*>(ws + W.image);
+  uint16_t* vp = reinterpret_cast<uint16_t*>(ws + W.image);
+  uint16_t* vp16 = w64_takes ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
+  int32_t* range_flags = w64_takes ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
   uint16_t* op = (uint16_t*)out_bf16;
   // Blocks of 128 tokens go through the 64-queries-per-wave kernel when every list is clean
   // (decided on the device, so the general kernel is queued behind it and returns at once unless
   // the lists turn out to need it).
-  const bool w64 = w64_call(params, ws_bytes) && !stream_only &&
+  const bool w64 = w64_takes && !stream_only &&
                    !(params->flags & PRISM_FLAG_GENERAL_KERNEL);
   // B = 64 with an even number of blocks: the pair kernel (two q-blocks per workgroup sharing the tiles of
   // the union of their lists) takes the call when every list is ascending and clean; decided on the
@@ -1304,41 +1679,87 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const vo
   // even on all-ones lists, where the two lists of a pair coincide (750 -> 712 TFLOP/s at 16K tokens;
   // d = 128: 948 -> 993, d = 256: 438 -> 753).
   constexpr int kPairMinRows = 4096;
-  const bool pair = pair_shape(params) && !stream_only && !(params->flags & PRISM_FLAG_GENERAL_KERNEL) &&
+  const bool pair = W.pair_plan != W.pair_items && !stream_only && !(params->flags & PRISM_FLAG_GENERAL_KERNEL) &&
                     ((R >= kPairMinRows && d >= 128) || (params->flags & PRISM_FLAG_PAIR_KERNEL));
   const int only_dirty = (w64 || pair) ? 1 : 0;
-  const int32_t* dirty_flag = plan + kPlanFlags;
+  int4* pair_items = reinterpret_cast<int4*>(ws + W.pair_items);
+  int32_t* pair_plan = reinterpret_cast<int32_t*>(ws + W.pair_plan);
+  const int pair_grid = pair ? persistent_grid(R / 2, d > 128 ? 1 : 2) : 0;   // 4 waves and 2 * 64 * d * 2 bytes of LDS each
+  if (pair && pair_grid <= 0) return PRISM_ERR_HIP;
+  const int pair_queues = pair_grid < kXcds ? 1 : kXcds;
+  const int n_range_flags = w64 ? h_kv * N : 0;
+
+  // One launch prepares the call up to kPrepMaxRows rows in one phase: 13.6 us instead of 34.4 us at 2048 rows (8K
+  // tokens, 32 heads), 36.8 instead of 46.4 at 5024, 43.7 instead of 62.6 at 8192 (32K tokens; the image alone takes
+  // 13, 22 and 38 us), 4.8 instead of 13.9 at 32 rows.  Beyond, the plan of a single workgroup (33 us at 5024 rows
+  // without an image beside it) would no longer hide behind the image, and the parts run as kernels of their own.
+  DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
+  if (R <= kPrepMaxRows && pc.n_phases == 1) {
+    PrepArgs pa = {};
+    pa.row_ptr = row_ptr;
+    pa.col_idx = col_idx;
+    pa.v = (const uint16_t*)v_bf16;
+    pa.vt = vp;
+    pa.vt16 = vp16;
+    pa.range_flags = range_flags;
+    pa.check = row_rank;
+    pa.items = items;
+    pa.pair_items = pair_items;
+    pa.plan = plan;
+    pa.pair_plan = pair_plan;
+    pa.h = h;
+    pa.h_kv = h_kv;
+    pa.causal = pc.causal;
+    pa.n_queues = pc.n_queues;
+    pa.pair_queues = pair_queues;
+    pa.n_plans = pair ? 2 : 1;
+    pa.n_check = only_dirty ? (R + kCheckRows - 1) / kCheckRows : 0;
+    pa.need_sorted = pair ? 1 : 0;
+    pa.kv_head_stride = hs.kv;
+    const int prep_grid = pa.n_plans + pa.n_check + (v_bf16 != nullptr ? h_kv * N : 0);
+    if (params->block == 128) {
+      if (d == 64) launch_prep<128, 64>(prep_grid, pa, seqs, st);
+      else if (d == 128) launch_prep<128, 128>(prep_grid, pa, seqs, st);
+      else launch_prep<128, 256>(prep_grid, pa, seqs, st);
+    } else {
+      if (d == 64) launch_prep<64, 64>(prep_grid, pa, seqs, st);
+      else if (d == 128) launch_prep<64, 128>(prep_grid, pa, seqs, st);
+      else launch_prep<64, 256>(prep_grid, pa, seqs, st);
+    }
+    flags = DirtyFlags{row_rank, range_flags, pa.n_check, n_range_flags};
+  } else {
+    if (v_bf16 != nullptr) {
+      const int rc = v_image_core(params, hs, v_bf16, vp, vp16, range_flags, st);
+      if (rc != PRISM_OK) return rc;
+    }
+    build_plan(pc, row_ptr, col_idx, bins, parts, row_rank, row_part, plan, items, st);
+    if (pair) {
+      PlanCfg pp = pc;
+      pp.N = N / 2;
+      pp.stride = 2;
+      pp.n_queues = pair_queues;
+      build_plan(pp, row_ptr, col_idx, bins, parts, row_rank, row_part, pair_plan, pair_items, st);
+    }
+    if (only_dirty) {
+      const int by_flags = (n_range_flags + 255) / 256;
+      hipLaunchKernelGGL(queue_validate_kernel, dim3((R + 3) / 4 > by_flags ? (R + 3) / 4 : by_flags), dim3(256), 0, st,
+                         row_ptr, col_idx, h, N, pc.cap, causal, pair ? 1 : 0, range_flags, n_range_flags, plan);
+    }
+  }
   if (pair) {
-    PlanCfg pp = pc;
-    pp.N = N / 2;
-    pp.stride = 2;
-    const int pair_grid = persistent_grid(h * pp.N, d > 128 ? 1 : 2);       // 4 waves and 2 * 64 * d * 2 bytes of LDS each
-    if (pair_grid <= 0) return PRISM_ERR_HIP;
-    pp.n_queues = pair_grid < kXcds ? 1 : kXcds;
-    int4* pair_items = reinterpret_cast<int4*>(ws + W.pair_items);
-    int32_t* pair_plan = reinterpret_cast<int32_t*>(ws + W.pair_plan);
-    build_plan(pp, row_ptr, col_idx, bins, parts, row_rank, row_part, pair_plan, pair_items, st);
-    hipLaunchKernelGGL(queue_validate_kernel, dim3((R + 3) / 4), dim3(256), 0, st, row_ptr, col_idx, h, N,
-                       pc.cap, causal, 1, static_cast<const int32_t*>(nullptr), 0, plan);
 #define PRISM_PAIR(D)                                                                                        \
-  launch_attn<64, false, D, true>(pair_grid, st, qp, kp, vp, row_ptr, col_idx, pair_items, pair_plan, dirty_flag, \
-                                  op, lse, h, h_kv, L, N, hs, causal, 0)
+  launch_attn<64, false, D, true>(pair_grid, st, qp, kp, vp, row_ptr, col_idx, pair_items, pair_plan, flags, \
+                                  op, lse, h, h_kv, seqs, hs, causal, 0)
     if (d == 64) PRISM_PAIR(64);
     else if (d == 128) PRISM_PAIR(128);
     else PRISM_PAIR(256);
 #undef PRISM_PAIR
   }
-  if (w64) {
-    const int n_range_flags = h_kv * N;
-    const int vgrid = ((R + 3) / 4) > ((n_range_flags + 255) / 256) ? (R + 3) / 4 : (n_range_flags + 255) / 256;
-    hipLaunchKernelGGL(queue_validate_kernel, dim3(vgrid), dim3(256), 0, st, row_ptr, col_idx, h, N,
-                       pc.cap, causal, 0, reinterpret_cast<const int32_t*>(ws + W.range_flags), n_range_flags, plan);
-    hipLaunchKernelGGL(sparse_attn_w64_kernel, dim3(grid), dim3(128), 0, st, qp, kp,
-                       reinterpret_cast<const uint16_t*>(ws + W.image16), col_idx, items, plan, op, lse, h, h_kv,
-                       L, N, hs, causal);
-  }
+  if (w64)
+    hipLaunchKernelGGL(sparse_attn_w64_kernel, dim3(grid), dim3(128), 0, st, qp, kp, vp16, col_idx, items, plan, flags,
+                       op, lse, h, h_kv, seqs, hs, causal);
 #define PRISM_ATTN(BLK, SO, D)                                                                                \
-  launch_attn<BLK, SO, D>(grid, st, qp, kp, vp, row_ptr, col_idx, items, plan, dirty_flag, op, lse, h, h_kv, L, N, \
+  launch_attn<BLK, SO, D>(grid, st, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
                           hs, causal, only_dirty)
   if (stream_only) {
     // measurement aid of the d = 128 kernels only
@@ -1368,8 +1789,9 @@ extern "C" int prism_sparse_attn_pre(const prism_params* params, const void* q_b
     return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
-  return attn_core(params, contiguous_heads(params), q_bf16, k_bf16, static_cast<char*>(v_image), v_image_bytes,
-                   row_ptr, col_idx, col_count, out_bf16, lse, static_cast<hipStream_t>(stream));
+  return attn_core(params, contiguous_heads(params), one_sequence(params, col_count), attn_ws(params),
+                   w64_call(params, v_image_bytes), q_bf16, k_bf16, nullptr, static_cast<char*>(v_image),
+                   row_ptr, col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16, const void* k_bf16,
@@ -1382,10 +1804,9 @@ extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16,
     return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, workspace, workspace_bytes);
   if (rc != PRISM_OK) return rc;
-  rc = prism_v_image(params, v_bf16, workspace, workspace_bytes, stream);
-  if (rc != PRISM_OK) return rc;
-  return prism_sparse_attn_pre(params, q_bf16, k_bf16, workspace, workspace_bytes, row_ptr, col_idx,
-                               col_count, out_bf16, lse, stream);
+  return attn_core(params, contiguous_heads(params), one_sequence(params, col_count), attn_ws(params),
+                   w64_call(params, workspace_bytes), q_bf16, k_bf16, v_bf16, static_cast<char*>(workspace), row_ptr,
+                   col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
 // ---- packed variable-length batches: one sequence after the other on the stream ---------
@@ -1432,11 +1853,10 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
     const int64_t N = n_blocks(&ps), h = ps.n_q_heads;
     const int64_t cap = (ps.flags & PRISM_FLAG_BIDIRECTIONAL) ? h * N * N : h * N * (N + 1) / 2;
     const size_t tok = (size_t)cu_seqlens[s];
-    rc = v_image_core(&ps, hs, (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), workspace_bytes, st);
-    if (rc != PRISM_OK) return rc;
-    rc = attn_core(&ps, hs, (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
-                   static_cast<char*>(workspace), workspace_bytes, row_ptr + ro, col_idx + co, cap, (uint16_t*)out_bf16 + tok * d,
-                   lse != nullptr ? lse + tok : nullptr, st);
+    rc = attn_core(&ps, hs, one_sequence(&ps, cap), attn_ws(&ps), w64_call(&ps, workspace_bytes),
+                   (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
+                   (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), row_ptr + ro, col_idx + co,
+                   (uint16_t*)out_bf16 + tok * d, lse != nullptr ? lse + tok : nullptr, st);
     if (rc != PRISM_OK) return rc;
     ro += h * N + 1;
     co += cap;
