@@ -309,9 +309,9 @@ int prism_sparse_attn_pre(const prism_params* params,
  *   col_offsets  : in int32;        sequence s holds room for all its admissible pairs
  *                                   (n_q_heads*N_s*(N_s+1)/2, or n_q_heads*N_s*N_s when bidirectional)
  *   info         : [4 * n_seqs] int32, four per sequence as in prism_estimate (never overflows)
- * The sequences are processed one after the other on `stream` and share the workspace
- * (prism_*_varlen_workspace_bytes: the largest single sequence's need), so a batch of many
- * short sequences costs one set of kernel launches per sequence.
+ * The sequences share the workspace (prism_*_varlen_workspace_bytes: the largest single
+ * sequence's need).  Up to 16 sequences that fit it together also share their kernel launches;
+ * such groups run one after the other on `stream`.  A larger workspace allows larger groups.
  * Errors: PRISM_ERR_INVALID_ARG for malformed offsets, PRISM_ERR_UNSUPPORTED if a sequence
  * exceeds the per-sequence limits; nothing is launched in either case.
  * ---------------------------------------------------------------------------------- */

@@ -94,25 +94,6 @@ __global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restric
                              vt16 != nullptr ? range_flags + kvh * N + blk : nullptr);
 }
 
-// =====================================================================================
-// The sequences of one launch.  A call on one sequence has one entry; a packed variable-length batch is
-// taken in groups of up to kMaxGroupSeqs sequences that share every launch.
-// =====================================================================================
-constexpr int kMaxGroupSeqs = 16;
-struct SeqInfo {
-  int32_t tok0;      // first token inside the packed tensors
-  int32_t L, N;      // tokens, blocks
-  int32_t blk0;      // blocks of the sequences in front of it in the group
-  int32_t cap;       // entries of its col_idx part
-  int32_t pad;
-  int64_t row0;      // its part of row_ptr ...
-  int64_t col0;      // ... and of col_idx starts here
-};
-struct SeqTable {
-  int32_t n;         // sequences
-  int32_t nsum;      // blocks of all of them
-  SeqInfo s[kMaxGroupSeqs];
-};
 // A queue entry names its sequence in the high bits of the head number (only where a group holds several).
 constexpr int kSeqShift = 20;
 
@@ -1174,13 +1155,6 @@ struct PrepArgs {
   size_t kv_head_stride;
 };
 
-// The sequence that holds index i of a numbering in which sequence s starts at mult * blk0[s].
-__device__ __forceinline__ int seq_of(const SeqTable& seqs, int i, int mult) {
-  int s = 0;
-  while (s + 1 < seqs.n && i >= mult * seqs.s[s + 1].blk0) ++s;
-  return s;
-}
-
 // One workgroup writes the plan of all rows: the order, parts and entries of queue_count / rank / fill_kernel for one
 // phase.  Wave w owns the rows 64*CH*w .. of the order (q-head, sequence, q-block descending), 64 at a time; rank and
 // work of a row inside its length class come from ballots and prefix sums over the wave, then over the 16 waves.
@@ -1595,16 +1569,6 @@ static void launch_prep(int grid, const PrepArgs& a, const SeqTable& seqs, hipSt
   hipLaunchKernelGGL((prep_kernel<BLK, D>), dim3(grid), dim3(kPrepThreads), 0, st, a, seqs);
 }
 
-static SeqTable one_sequence(const prism_params* p, int64_t col_count) {
-  SeqTable t = {};
-  t.n = 1;
-  t.nsum = n_blocks(p);
-  t.s[0].L = p->seq_len;
-  t.s[0].N = n_blocks(p);
-  t.s[0].cap = col_count > 0x7fffffff ? 0x7fffffff : (int)col_count;     // CSR offsets are int32
-  return t;
-}
-
 // the three kernels that turn index lists into the queue plan of `pc`
 static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t* col_idx, int32_t* bins,
                        int32_t* parts, int32_t* row_rank, int32_t* row_part, int32_t* plan, int4* items,
@@ -1809,7 +1773,7 @@ extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16,
                    col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
-// ---- packed variable-length batches: one sequence after the other on the stream ---------
+// ---- packed variable-length batches: groups of sequences, one after the other on the stream ---------
 static int varlen_workspace(const prism_params* params, const int32_t* cu_seqlens, int n_seqs, size_t* bytes,
                             size_t* least_bytes) {
   if (bytes == nullptr) return PRISM_ERR_INVALID_ARG;
@@ -1846,20 +1810,29 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
   const size_t d = params->head_dim, T = params->seq_len;
   const HeadStrides hs{T * d, T * d, T};
   hipStream_t st = static_cast<hipStream_t>(stream);
-  int64_t ro = 0, co = 0;
-  for (int s = 0; s < n_seqs; ++s) {
-    prism_params ps = *params;
-    ps.seq_len = cu_seqlens[s + 1] - cu_seqlens[s];
-    const int64_t N = n_blocks(&ps), h = ps.n_q_heads;
-    const int64_t cap = (ps.flags & PRISM_FLAG_BIDIRECTIONAL) ? h * N * N : h * N * (N + 1) / 2;
-    const size_t tok = (size_t)cu_seqlens[s];
-    rc = attn_core(&ps, hs, one_sequence(&ps, cap), attn_ws(&ps), w64_call(&ps, workspace_bytes),
-                   (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
-                   (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), row_ptr + ro, col_idx + co,
-                   (uint16_t*)out_bf16 + tok * d, lse != nullptr ? lse + tok : nullptr, st);
-    if (rc != PRISM_OK) return rc;
-    ro += h * N + 1;
-    co += cap;
-  }
-  return PRISM_OK;
+  // B = 64 in pairs of q-blocks: every sequence of the group has an even number of blocks
+  auto pairs = [&](const SeqTable& t) {
+    bool even = params->block == 64;
+    for (int i = 0; i < t.n; ++i) even = even && t.s[i].N % 2 == 0;
+    return even;
+  };
+  // Sequences share their launches while the one-launch preparation can take them all, their heads form one phase
+  // and the workspace holds them.
+  auto fits = [&](const SeqTable& t) {
+    return (int64_t)params->n_q_heads * t.nsum <= kPrepMaxRows && params->n_q_heads < (1 << kSeqShift) &&
+           heads_in_cache(params, t) >= params->n_kv_heads && attn_layout(params, t.nsum, pairs(t)).total <= workspace_bytes;
+  };
+  auto run = [&](const SeqTable& t, const prism_params& ps) {
+    // the layout of one sequence differs from that of a group only in what a ragged length can do without
+    const AttnWs W = t.n > 1 ? attn_layout(params, t.nsum, pairs(t)) : attn_ws(&ps);
+    const bool w64 = t.n > 1 ? w64_shape(params) : w64_call(&ps, workspace_bytes);
+    const size_t tok = t.n > 1 ? 0 : t.s[0].tok0;
+    SeqTable at = t;
+    if (t.n == 1) at.s[0].tok0 = 0, at.s[0].row0 = 0, at.s[0].col0 = 0;   // one sequence: through the pointers
+    const int64_t ro = t.n > 1 ? 0 : t.s[0].row0, co = t.n > 1 ? 0 : t.s[0].col0;
+    return attn_core(&ps, hs, at, W, w64, (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
+                     (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), row_ptr + ro, col_idx + co,
+                     (uint16_t*)out_bf16 + tok * d, lse != nullptr ? lse + tok : nullptr, st);
+  };
+  return for_each_group(params, cu_seqlens, n_seqs, fits, run);
 }

@@ -63,6 +63,105 @@ inline HeadStrides contiguous_heads(const prism_params* p) {
   return HeadStrides{s, s, (size_t)p->seq_len};
 }
 
+// The sequences of one launch.  A call on one sequence has one entry; a packed variable-length batch is taken in
+// groups of up to kMaxGroupSeqs sequences that share every launch.
+constexpr int kMaxGroupSeqs = 16;
+struct SeqInfo {
+  int32_t tok0;      // first token inside the packed tensors
+  int32_t L, N;      // tokens, blocks
+  int32_t blk0;      // blocks of the sequences in front of it in the group ...
+  int32_t tile0;     // ... and their tiles (strips) of 16 blocks
+  int32_t cap;       // entries of its col_idx part
+  int32_t index;     // its number in the batch
+  int32_t pad;
+  int64_t mask0;     // its part of the mask words, of row_ptr and of col_idx starts here
+  int64_t row0;
+  int64_t col0;
+};
+// kSeqs = 1: a kernel for calls on one sequence.  The table of 16 costs 1 KB of arguments and a search per workgroup,
+// 1 - 2 % of the calls whose kernels take a few microseconds (2K tokens, one head: 38.9 -> 39.7 us).
+template <int kSeqs>
+struct SeqTableOf {
+  int32_t n;         // sequences
+  int32_t nsum;      // blocks of all of them
+  int32_t tiles;     // tiles of 16 blocks of all of them
+  int32_t nmax;      // blocks of the longest
+  SeqInfo s[kSeqs];
+};
+using SeqTable = SeqTableOf<kMaxGroupSeqs>;
+using OneSeq = SeqTableOf<1>;
+inline OneSeq only_sequence(const SeqTable& t) { return OneSeq{t.n, t.nsum, t.tiles, t.nmax, {t.s[0]}}; }
+inline int clamp_capacity(int64_t n) { return n > 0x7fffffff ? 0x7fffffff : (int)n; }   // CSR offsets are int32
+inline void add_sequence(SeqTable* t, const prism_params* p, SeqInfo s) {
+  s.N = n_blocks(p);
+  s.L = p->seq_len;
+  s.blk0 = t->nsum;
+  s.tile0 = t->tiles;
+  t->nsum += s.N;
+  t->tiles += (s.N + 15) / 16;
+  t->nmax = s.N > t->nmax ? s.N : t->nmax;
+  t->s[t->n++] = s;
+}
+inline SeqTable one_sequence(const prism_params* p, int64_t col_capacity) {
+  SeqTable t = {};
+  SeqInfo s = {};
+  s.cap = clamp_capacity(col_capacity);
+  add_sequence(&t, p, s);
+  return t;
+}
+
+// Calls run(table, params of its first sequence) for groups that cover the batch; fits(table) says whether the
+// sequences of a table can share their launches (a table of one always can).  Windows of kVarlenWindow
+// sequences are packed longest first, each group filled with what still fits.  Stops at the first error.
+constexpr int kVarlenWindow = 64;
+template <typename Fits, typename Run>
+inline int for_each_group(const prism_params* params, const int32_t* cu_seqlens, int n_seqs, Fits fits, Run run) {
+  int64_t mo = 0, ro = 0, co = 0;
+  for (int w0 = 0; w0 < n_seqs; w0 += kVarlenWindow) {
+    const int n = n_seqs - w0 < kVarlenWindow ? n_seqs - w0 : kVarlenWindow;
+    prism_params ps[kVarlenWindow];
+    SeqInfo info[kVarlenWindow];
+    int order[kVarlenWindow];
+    bool done[kVarlenWindow];
+    for (int i = 0; i < n; ++i) {
+      ps[i] = *params;
+      ps[i].seq_len = cu_seqlens[w0 + i + 1] - cu_seqlens[w0 + i];
+      const int64_t N = n_blocks(&ps[i]), h = params->n_q_heads;
+      const int64_t cap = (params->flags & PRISM_FLAG_BIDIRECTIONAL) ? h * N * N : h * N * (N + 1) / 2;
+      info[i] = SeqInfo{};
+      info[i].tok0 = cu_seqlens[w0 + i];
+      info[i].cap = clamp_capacity(cap);
+      info[i].index = w0 + i;
+      info[i].mask0 = mo;
+      info[i].row0 = ro;
+      info[i].col0 = co;
+      mo += h * N * ((N + 63) / 64);
+      ro += h * N + 1;
+      co += cap;
+      done[i] = false;
+      int at = i;                                    // insertion sort: longest first, equal ones in batch order
+      for (; at > 0 && ps[order[at - 1]].seq_len < ps[i].seq_len; --at) order[at] = order[at - 1];
+      order[at] = i;
+    }
+    for (int i = 0; i < n; ++i) {
+      if (done[i]) continue;
+      SeqTable t = {};
+      add_sequence(&t, &ps[order[i]], info[order[i]]);
+      for (int j = i + 1; j < n && t.n < kMaxGroupSeqs; ++j) {
+        if (done[j]) continue;
+        SeqTable more = t;
+        add_sequence(&more, &ps[order[j]], info[order[j]]);
+        if (!fits(more)) continue;
+        t = more;
+        done[j] = true;
+      }
+      const int rc = run(t, ps[order[i]]);
+      if (rc != PRISM_OK) return rc;
+    }
+  }
+  return PRISM_OK;
+}
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 inline int launch_status() {
@@ -143,6 +242,15 @@ __device__ __forceinline__ uint32_t float_to_bf16_bits(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return u >> 16;
+}
+
+// The sequence that holds index i of a numbering in which sequence s starts at mult * blk0[s].
+template <int kSeqs>
+__device__ __forceinline__ int seq_of(const SeqTableOf<kSeqs>& seqs, int i, int mult) {
+  int s = 0;
+  if (kSeqs == 1) return s;
+  while (s + 1 < seqs.n && i >= mult * seqs.s[s + 1].blk0) ++s;
+  return s;
 }
 
 }  // namespace prism

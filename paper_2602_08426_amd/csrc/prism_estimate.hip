@@ -25,7 +25,7 @@ struct BandMap {
 };
 
 // Band vectors of all heads and blocks: [z][term], term = hi, mid, lo, each bf16.
-//   q-heads (read once per strip of 16 q-blocks): [h][N][bs], plain rows of bs = max(128, d)
+//   q-heads (read once per strip of 16 q-blocks): per sequence [h][N][bs], plain rows of bs = max(128, d)
 //   elements (band_stride below);
 //   kv heads (read by every strip of the g q-heads): behind them, in the order the score GEMM
 //   reads them: per head ceil(N/16) tiles of 16 blocks; per tile bs/32 k-steps of 32 band dims; per
@@ -39,13 +39,16 @@ struct BandVectors {
 // elements per band vector: room for the widest band a head dim allows, at least four k-steps
 __host__ __device__ inline int band_stride(int head_dim) { return head_dim > 128 ? head_dim : 128; }
 
-// element offset of (kv head, block, band position) behind the q-heads' h*N*bs elements; one tile
+// element offset of (kv head, block, band position) of a sequence whose kv heads start at kv0; one tile
 // of 16 blocks holds 16*bs elements
-__device__ __forceinline__ size_t kv_band_offset(int h, int N, int bs, int kvh, int blk, int pz) {
+__device__ __forceinline__ size_t kv_band_offset(size_t kv0, int N, int bs, int kvh, int blk, int pz) {
   const int n_tiles = (N + 15) >> 4;
   const int tile = blk >> 4, r = blk & 15, ks = pz >> 5, piece = (pz >> 3) & 3, j = pz & 7;
-  return (size_t)h * N * bs + ((size_t)kvh * n_tiles + tile) * 16 * bs + ks * 512 +
-         (piece * 16 + r) * 8 + j;
+  return kv0 + ((size_t)kvh * n_tiles + tile) * 16 * bs + ks * 512 + (piece * 16 + r) * 8 + j;
+}
+// where the kv heads of a sequence start: behind the q-heads of all sequences and the tiles of those in front of it
+__device__ __forceinline__ size_t kv_band_base(int h, int h_kv, int nsum, int tile0, int bs) {
+  return ((size_t)h * nsum + (size_t)h_kv * tile0 * 16) * bs;
 }
 
 // =====================================================================================
@@ -91,9 +94,9 @@ __device__ __forceinline__ void rope_cos_sin(double angle, float* c, float* s) {
   sincosf((float)a, s, c);
 }
 
-template <int BLK, bool kRope, int D>
+template <int BLK, bool kRope, int D, int kSeqs>
 __global__ __launch_bounds__(256) void pool_energy_kernel(
-    const uint16_t* q, const uint16_t* k, int h, int L, int N, size_t q_head_stride, size_t kv_head_stride,
+    const uint16_t* q, const uint16_t* k, int h, SeqTableOf<kSeqs> seqs, size_t q_head_stride, size_t kv_head_stride,
     BandMap map, BandVectors bv, float* __restrict__ energy,
     float* __restrict__ pooled_q_f32, float* __restrict__ pooled_k_f32,
     RopeArgs rope, uint16_t* q_out, uint16_t* k_out) {      // q_out / k_out may alias q / k
@@ -103,8 +106,11 @@ __global__ __launch_bounds__(256) void pool_energy_kernel(
   constexpr int BS = D > 128 ? D : 128;      // band_stride(D)
   __shared__ float part[RG][D + 4];
   __shared__ float esum[4][4];
-  const int blk = blockIdx.x, head = blockIdx.y, t = threadIdx.x;
-  const size_t head_off = (head < h) ? (size_t)head * q_head_stride : (size_t)(head - h) * kv_head_stride;
+  const int sq = seq_of(seqs, blockIdx.x, 1);
+  const int L = seqs.s[sq].L, N = seqs.s[sq].N, heads = gridDim.y;
+  const int blk = blockIdx.x - seqs.s[sq].blk0, head = blockIdx.y, t = threadIdx.x;
+  const size_t head_off = ((head < h) ? (size_t)head * q_head_stride : (size_t)(head - h) * kv_head_stride) +
+                          (size_t)seqs.s[sq].tok0 * D;
   const uint16_t* src = ((head < h) ? q : k) + head_off + (size_t)blk * BLK * D;
   const int c = t % CPR, rg = t / CPR;
 
@@ -181,7 +187,7 @@ __global__ __launch_bounds__(256) void pool_energy_kernel(
     const uint32_t lo = float_to_bf16_bits(rem2);
     const size_t o = ((size_t)head * N + blk) * D + t;
     if (head < h) {
-      const size_t vec = ((size_t)head * N + blk) * BS;
+      const size_t vec = ((size_t)h * seqs.s[sq].blk0 + (size_t)head * N + blk) * BS;
 #pragma unroll
       for (int z = 0; z < 2; ++z) {
         const int pz = map.pos[z][t];
@@ -198,12 +204,13 @@ __global__ __launch_bounds__(256) void pool_energy_kernel(
       }
     } else {
       // the workgroup of a head's last block also clears the blocks that pad the last tile
+      const size_t kv0 = kv_band_base(h, heads - h, seqs.nsum, seqs.s[sq].tile0, BS);
       const int blk_end = blk == N - 1 ? ((N + 15) >> 4) * 16 : blk + 1;
 #pragma unroll
       for (int z = 0; z < 2; ++z) {
         const int pz = map.pos[z][t];
         if (pz >= 0) {
-          const size_t e = kv_band_offset(h, N, BS, head - h, blk, pz);
+          const size_t e = kv_band_offset(kv0, N, BS, head - h, blk, pz);
           bv.v[z][0][e] = (uint16_t)hi;
           bv.v[z][1][e] = (uint16_t)mid;
           bv.v[z][2][e] = (uint16_t)lo;
@@ -211,7 +218,7 @@ __global__ __launch_bounds__(256) void pool_energy_kernel(
         for (int b = blk; b < blk_end; ++b) {
           // zero padding of the last k-step (dims dz .. dpad-1), and whole padding blocks
           if (t < map.dpad[z] && (b > blk || t >= map.dz[z])) {
-            const size_t e = kv_band_offset(h, N, BS, head - h, b, t);
+            const size_t e = kv_band_offset(kv0, N, BS, head - h, b, t);
             bv.v[z][0][e] = 0;
             bv.v[z][1][e] = 0;
             bv.v[z][2][e] = 0;
@@ -239,7 +246,7 @@ __global__ __launch_bounds__(256) void pool_energy_kernel(
     float e = 0.f;
 #pragma unroll
     for (int wv = 0; wv < D / 64; ++wv) e += esum[wv][t];      // fixed order: deterministic
-    energy[((size_t)head * N + blk) * 4 + t] = e;
+    energy[((size_t)heads * seqs.s[sq].blk0 + (size_t)head * N + blk) * 4 + t] = e;
   }
 }
 
@@ -247,14 +254,18 @@ __global__ __launch_bounds__(256) void pool_energy_kernel(
 // Energy-based temperature calibration (Sec. 3.4): per q-head
 //   tau_z = sqrt(d_z/d) * RMS(Qbar_z)/RMS(Qbar) * RMS(Kbar_z)/RMS(Kbar),  scale_z = sqrt(d_z) tau_z.
 // One wave per q-head sums the per-block energies in a fixed order (fp64).
-// inv_scale[hq*2 + z] = 1/scale_z, or 0 when the band is disabled or has no energy.
+// inv_scale[(sequence*h + hq)*2 + z] = 1/scale_z, or 0 when the band is disabled or has no energy.
 // =====================================================================================
+template <int kSeqs>
 __global__ __launch_bounds__(64) void scale_kernel(const float* __restrict__ energy, int h, int h_kv,
-                                                   int N, int head_dim, int d_high, int d_low, int calibrate,
+                                                   SeqTableOf<kSeqs> seqs, int head_dim, int d_high, int d_low, int calibrate,
                                                    float* __restrict__ inv_scale,
                                                    float* __restrict__ scales_out) {
-  const int hq = blockIdx.x, lane = threadIdx.x;
+  const int hq = blockIdx.x, lane = threadIdx.x, sq = kSeqs == 1 ? 0 : blockIdx.y;
   const int kvh = h + hq / (h / h_kv);
+  const int N = seqs.s[sq].N;
+  energy += (size_t)(h + h_kv) * seqs.s[sq].blk0 * 4;
+  inv_scale += (size_t)sq * h * 2;
   double eq[3] = {0, 0, 0}, ek[3] = {0, 0, 0};
   // one 16-byte load per (head, block); several blocks in flight (the sums keep their order)
 #pragma unroll 4
@@ -600,17 +611,25 @@ constexpr int kSelCausal = 1;          // key blocks v > u are excluded (block-c
 constexpr int kSelForceDiagonal = 2;   // block u of every row is switched on after the union
 constexpr int kSelForceSink = 4;       // block 0 of every row is switched on after the union
 
-template <int MAXCH, bool DUMP, int kRowsPerWave>
+template <int MAXCH, bool DUMP, int kRowsPerWave, int kSeqs>
 __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
     BandVectors bv, const float* __restrict__ inv_scale, int h, int h_kv,
-    int N, int bs, int dpad_high, int dpad_low, float top_p, int select_flags,
+    SeqTableOf<kSeqs> seqs, int bs, int dpad_high, int dpad_low, float top_p, int select_flags,
     uint64_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr,
     float* __restrict__ logits_high, float* __restrict__ logits_low) {
   constexpr int kWaves = kStripRows / kRowsPerWave, kThreads = kWaves * 64;
   extern __shared__ float lds_logits[];
   __shared__ uint64_t lds_bits[kStripRows][kMaxBlocks / 64];
-  // heavy strips (large u) first
-  const int strip = gridDim.x - 1 - blockIdx.x, hq = blockIdx.y;
+  // heavy strips (large u) first; the sequences of a group lie longest first
+  int sq = 0;
+  if (kSeqs > 1)
+    while (sq + 1 < seqs.n && (int)blockIdx.x >= seqs.s[sq + 1].tile0) ++sq;
+  const int N = seqs.s[sq].N;
+  const int strip = ((N + 15) >> 4) - 1 - ((int)blockIdx.x - seqs.s[sq].tile0), hq = blockIdx.y;
+  mask_bits += seqs.s[sq].mask0;
+  row_ptr += seqs.s[sq].row0;
+  inv_scale += (size_t)sq * h * 2;
+  const size_t q0 = (size_t)h * seqs.s[sq].blk0 * bs, kv0 = kv_band_base(h, h_kv, seqs.nsum, seqs.s[sq].tile0, bs);
   const int kvh = h + hq / (h / h_kv);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar branches below
@@ -645,8 +664,8 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
       const int kn = min(4, ksteps - k0);
       const bool first = k0 == 0, last = k0 + 4 >= ksteps;
       const int arow = min(u0 + (lane & 15), N - 1);
-      const size_t aoff = ((size_t)hq * N + arow) * bs + k0 * 32 + (lane >> 4) * 8;
-      const size_t tile0 = kv_band_offset(h, N, bs, kvh - h, 0, 0) + k0 * 512 + lane * 8;   // this lane's piece of tile 0
+      const size_t aoff = q0 + ((size_t)hq * N + arow) * bs + k0 * 32 + (lane >> 4) * 8;
+      const size_t tile0 = kv_band_offset(kv0, N, bs, kvh - h, 0, 0) + k0 * 512 + lane * 8;   // this lane's piece of tile 0
       const size_t tile_stride = (size_t)16 * bs;
       // The pass with the number of k-steps and "first pass" as compile-time facts: a fixed number of
       // loads per tile lets the compiler wait for exactly the fragments of the tile whose MFMAs come next
@@ -849,9 +868,16 @@ __device__ __forceinline__ void scan_resident(int32_t* __restrict__ row_ptr, int
   }
 }
 
-__global__ __launch_bounds__(1024) void scan_kernel(int32_t* __restrict__ row_ptr, int R,
-                                                    int64_t capacity, int32_t* __restrict__ info) {
+// One workgroup per sequence.
+template <int kSeqs>
+__global__ __launch_bounds__(1024) void scan_kernel(int32_t* __restrict__ row_ptr, int h, SeqTableOf<kSeqs> seqs,
+                                                    int32_t* __restrict__ info) {
   __shared__ int wave_tot[2][16 * 16];
+  const SeqInfo sq = seqs.s[kSeqs == 1 ? 0 : blockIdx.x];
+  const int R = h * sq.N;
+  const int64_t capacity = sq.cap;
+  row_ptr += sq.row0;
+  info += 4 * (size_t)sq.index;
   const int chunks = (R + 4095) / 4096;              // uniform
   if (chunks <= 16) {
     if (chunks <= 1) scan_resident<1>(row_ptr, R, capacity, info, wave_tot[0], wave_tot[1]);
@@ -909,12 +935,21 @@ __global__ __launch_bounds__(1024) void scan_kernel(int32_t* __restrict__ row_pt
 
 // One wave per row: ascending columns of the set bits.  Lane i fetches word i of the row (one
 // request for the whole row; W <= 32), the words are then taken from registers.
-__global__ __launch_bounds__(256) void fill_kernel(const uint64_t* __restrict__ mask_bits, int R,
-                                                   int W, const int32_t* __restrict__ row_ptr,
-                                                   int32_t* __restrict__ col_idx, int64_t capacity) {
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+template <int kSeqs>
+__global__ __launch_bounds__(256) void fill_kernel(const uint64_t* __restrict__ mask_bits, int h,
+                                                   SeqTableOf<kSeqs> seqs,
+                                                   const int32_t* __restrict__ row_ptr,
+                                                   int32_t* __restrict__ col_idx) {
+  int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (r >= R) return;
+  if (r >= h * seqs.nsum) return;
+  const int sq = seq_of(seqs, r, h);
+  r -= h * seqs.s[sq].blk0;
+  const int W = (seqs.s[sq].N + 63) >> 6;
+  const int64_t capacity = seqs.s[sq].cap;
+  mask_bits += seqs.s[sq].mask0;
+  row_ptr += seqs.s[sq].row0;
+  col_idx += seqs.s[sq].col0;
   int64_t base = row_ptr[r];
   const uint64_t mine = lane < W ? mask_bits[(size_t)r * W + lane] : 0ull;
   const int lo = (int)(uint32_t)mine, hi = (int)(uint32_t)(mine >> 32);
@@ -993,8 +1028,8 @@ static int make_band_map(const prism_params* p, const prism_bands* bands, BandMa
 struct EstimateWs {
   size_t band[2][3], energy, inv_scale, total;
 };
-static EstimateWs estimate_ws(const prism_params* p) {
-  const size_t N = n_blocks(p);
+// The layout for n sequences of together `blocks` blocks and `tiles` tiles of 16 blocks.
+static EstimateWs estimate_layout(const prism_params* p, size_t n, size_t blocks, size_t tiles) {
   const size_t heads = (size_t)p->n_q_heads + p->n_kv_heads;
   EstimateWs w;
   size_t off = 0;
@@ -1002,13 +1037,17 @@ static EstimateWs estimate_ws(const prism_params* p) {
     for (int term = 0; term < 3; ++term) {
       w.band[z][term] = off;
       // q-heads: N rows each; kv heads: whole tiles of 16 blocks
-      off = align_up(off + ((size_t)p->n_q_heads * N + (size_t)p->n_kv_heads * ((N + 15) / 16 * 16)) *
+      off = align_up(off + ((size_t)p->n_q_heads * blocks + (size_t)p->n_kv_heads * tiles * 16) *
                                band_stride(p->head_dim) * 2, 256);
     }
-  w.energy = off;    off = align_up(off + heads * N * 4 * sizeof(float), 256);
-  w.inv_scale = off; off = align_up(off + (size_t)p->n_q_heads * 2 * sizeof(float), 256);
+  w.energy = off;    off = align_up(off + heads * blocks * 4 * sizeof(float), 256);
+  w.inv_scale = off; off = align_up(off + n * p->n_q_heads * 2 * sizeof(float), 256);
   w.total = off;
   return w;
+}
+static EstimateWs estimate_ws(const prism_params* p) {
+  const size_t N = n_blocks(p);
+  return estimate_layout(p, 1, N, (N + 15) / 16);
 }
 
 static BandVectors band_vectors(char* ws, const EstimateWs& L) {
@@ -1019,20 +1058,23 @@ static BandVectors band_vectors(char* ws, const EstimateWs& L) {
 }
 
 template <int BLK, bool kRope, int D>
-static void launch_pool(const prism_params* p, const HeadStrides& hs, const BandMap& map, const BandVectors& bv,
+static void launch_pool(const prism_params* p, const HeadStrides& hs, const SeqTable& seqs, const BandMap& map, const BandVectors& bv,
                         const uint16_t* q, const uint16_t* k, float* energy, float* pooled_q, float* pooled_k,
                         const RopeArgs& rope, uint16_t* q_out, uint16_t* k_out, hipStream_t st) {
-  const int N = n_blocks(p);
-  hipLaunchKernelGGL((pool_energy_kernel<BLK, kRope, D>), dim3(N, p->n_q_heads + p->n_kv_heads), dim3(256), 0,
-                     st, q, k, p->n_q_heads, p->seq_len, N, hs.q, hs.kv, map, bv, energy, pooled_q, pooled_k,
-                     rope, q_out, k_out);
+  const dim3 grid(seqs.nsum, p->n_q_heads + p->n_kv_heads);
+  if (seqs.n == 1)
+    hipLaunchKernelGGL((pool_energy_kernel<BLK, kRope, D, 1>), grid, dim3(256), 0, st, q, k, p->n_q_heads,
+                       only_sequence(seqs), hs.q, hs.kv, map, bv, energy, pooled_q, pooled_k, rope, q_out, k_out);
+  else if constexpr (!kRope)                           // the packed batches come without the rotation
+    hipLaunchKernelGGL((pool_energy_kernel<BLK, kRope, D, kMaxGroupSeqs>), grid, dim3(256), 0, st, q, k, p->n_q_heads,
+                       seqs, hs.q, hs.kv, map, bv, energy, pooled_q, pooled_k, rope, q_out, k_out);
 }
 
-static int run_pool_and_scale(const prism_params* p, const HeadStrides& hs, const BandMap& map, const void* q,
+static int run_pool_and_scale(const prism_params* p, const HeadStrides& hs, const SeqTable& seqs,
+                              const BandMap& map, const void* q,
                               const void* k, char* ws, const EstimateWs& L, float* pooled_q, float* pooled_k,
                               float* scales, hipStream_t st, const RopeArgs* rope = nullptr,
                               void* q_out = nullptr, void* k_out = nullptr) {
-  const int N = n_blocks(p);
   const BandVectors bv = band_vectors(ws, L);
   float* energy = reinterpret_cast<float*>(ws + L.energy);
   float* inv = reinterpret_cast<float*>(ws + L.inv_scale);
@@ -1044,9 +1086,9 @@ static int run_pool_and_scale(const prism_params* p, const HeadStrides& hs, cons
 #define PRISM_POOL(BLK, D)                                                                              \
   do {                                                                                                  \
     if (rope == nullptr)                                                                                \
-      launch_pool<BLK, false, D>(p, hs, map, bv, qp, kp, energy, pooled_q, pooled_k, ra, nullptr, nullptr, st); \
+      launch_pool<BLK, false, D>(p, hs, seqs, map, bv, qp, kp, energy, pooled_q, pooled_k, ra, nullptr, nullptr, st); \
     else                                                                                                \
-      launch_pool<BLK, true, D>(p, hs, map, bv, qp, kp, energy, pooled_q, pooled_k, ra, qo, ko, st);    \
+      launch_pool<BLK, true, D>(p, hs, seqs, map, bv, qp, kp, energy, pooled_q, pooled_k, ra, qo, ko, st);    \
   } while (0)
   if (p->block == 128) {
     if (p->head_dim == 64) PRISM_POOL(128, 64);
@@ -1058,19 +1100,21 @@ static int run_pool_and_scale(const prism_params* p, const HeadStrides& hs, cons
     else PRISM_POOL(64, 256);
   }
 #undef PRISM_POOL
-  hipLaunchKernelGGL(scale_kernel, dim3(p->n_q_heads), dim3(64), 0, st, energy, p->n_q_heads,
-                     p->n_kv_heads, N, p->head_dim, map.dz[0], map.dz[1],
-                     (p->flags & PRISM_FLAG_NO_CALIBRATION) ? 0 : 1, inv, scales);
+  const int calibrate = (p->flags & PRISM_FLAG_NO_CALIBRATION) ? 0 : 1;
+  if (seqs.n == 1)
+    hipLaunchKernelGGL(scale_kernel<1>, dim3(p->n_q_heads), dim3(64), 0, st, energy, p->n_q_heads, p->n_kv_heads,
+                       only_sequence(seqs), p->head_dim, map.dz[0], map.dz[1], calibrate, inv, scales);
+  else
+    hipLaunchKernelGGL(scale_kernel<kMaxGroupSeqs>, dim3(p->n_q_heads, seqs.n), dim3(64), 0, st, energy, p->n_q_heads,
+                       p->n_kv_heads, seqs, p->head_dim, map.dz[0], map.dz[1], calibrate, inv, scales);
   return launch_status();
 }
 
-template <int MAXCH, bool DUMP, int kRowsPerWave = 4>
-static int launch_select(const prism_params* p, const BandMap& map, char* ws, const EstimateWs& L,
-                         uint64_t* mask_bits, int32_t* row_ptr, float* lh, float* ll, hipStream_t st) {
-  const int N = n_blocks(p);
-  const int strips = (N + kStripRows - 1) / kStripRows;
-  const size_t lds = (size_t)kStripRows * (((N + 15) / 16) * 16 + 4) * sizeof(float);
-  auto kern = select_kernel<MAXCH, DUMP, kRowsPerWave>;
+template <int MAXCH, bool DUMP, int kRowsPerWave, int kSeqs>
+static int launch_select_on(const prism_params* p, const SeqTableOf<kSeqs>& seqs, const BandMap& map, char* ws,
+                         const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, float* lh, float* ll, hipStream_t st) {
+  const size_t lds = (size_t)kStripRows * (((seqs.nmax + 15) / 16) * 16 + 4) * sizeof(float);
+  auto kern = select_kernel<MAXCH, DUMP, kRowsPerWave, kSeqs>;
   if (lds > 64 * 1024) {
     // more than 64 KB of dynamic LDS has to be allowed once per kernel and device: what the
     // largest N needs is asked for on the first such call of this instantiation on a device
@@ -1091,25 +1135,37 @@ static int launch_select(const prism_params* p, const BandMap& map, char* ws, co
   if (!(p->flags & PRISM_FLAG_BIDIRECTIONAL)) select_flags |= kSelCausal;
   if (p->flags & PRISM_FLAG_FORCE_DIAGONAL) select_flags |= kSelForceDiagonal;
   if (p->flags & PRISM_FLAG_FORCE_SINK) select_flags |= kSelForceSink;
-  hipLaunchKernelGGL(kern, dim3(strips, p->n_q_heads), dim3(kStripRows / kRowsPerWave * 64), lds, st,
+  hipLaunchKernelGGL(kern, dim3(seqs.tiles, p->n_q_heads), dim3(kStripRows / kRowsPerWave * 64), lds, st,
                      band_vectors(ws, L),
-                     reinterpret_cast<const float*>(ws + L.inv_scale), p->n_q_heads, p->n_kv_heads, N,
+                     reinterpret_cast<const float*>(ws + L.inv_scale), p->n_q_heads, p->n_kv_heads, seqs,
                      band_stride(p->head_dim), map.dpad[0], map.dpad[1], p->top_p, select_flags, mask_bits, row_ptr, lh, ll);
   return launch_status();
 }
 
-static int run_compaction(const prism_params* p, const uint64_t* mask_bits, int32_t* row_ptr,
-                          int32_t* col_idx, int64_t capacity, int32_t* info, bool count_rows,
-                          hipStream_t st) {
-  const int N = n_blocks(p);
-  const int R = p->n_q_heads * N;
-  const int W = (N + 63) / 64;
-  if (count_rows)
-    hipLaunchKernelGGL(row_count_kernel, dim3((R + 255) / 256), dim3(256), 0, st, mask_bits, R, W,
+template <int MAXCH, bool DUMP, int kRowsPerWave = 4>
+static int launch_select(const prism_params* p, const SeqTable& seqs, const BandMap& map, char* ws,
+                         const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, float* lh, float* ll,
+                         hipStream_t st) {
+  if (DUMP || seqs.n == 1)
+    return launch_select_on<MAXCH, DUMP, kRowsPerWave, 1>(p, only_sequence(seqs), map, ws, L, mask_bits, row_ptr, lh, ll, st);
+  return launch_select_on<MAXCH, false, kRowsPerWave, kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, row_ptr, lh, ll, st);
+}
+
+static int run_compaction(const prism_params* p, const SeqTable& seqs, const uint64_t* mask_bits, int32_t* row_ptr,
+                          int32_t* col_idx, int32_t* info, bool count_rows, hipStream_t st) {
+  const int h = p->n_q_heads, R = h * seqs.nsum;
+  if (count_rows)                                      // one sequence
+    hipLaunchKernelGGL(row_count_kernel, dim3((R + 255) / 256), dim3(256), 0, st, mask_bits, R, (seqs.nsum + 63) / 64,
                        row_ptr);
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, row_ptr, R, capacity, info);
-  hipLaunchKernelGGL(fill_kernel, dim3((R + 3) / 4), dim3(256), 0, st, mask_bits, R, W, row_ptr,
-                     col_idx, capacity);
+  if (seqs.n == 1) {
+    const OneSeq one = only_sequence(seqs);
+    hipLaunchKernelGGL(scan_kernel<1>, dim3(1), dim3(1024), 0, st, row_ptr, h, one, info);
+    hipLaunchKernelGGL(fill_kernel<1>, dim3((R + 3) / 4), dim3(256), 0, st, mask_bits, h, one, row_ptr, col_idx);
+  } else {
+    hipLaunchKernelGGL(scan_kernel<kMaxGroupSeqs>, dim3(seqs.n), dim3(1024), 0, st, row_ptr, h, seqs, info);
+    hipLaunchKernelGGL(fill_kernel<kMaxGroupSeqs>, dim3((R + 3) / 4), dim3(256), 0, st, mask_bits, h, seqs, row_ptr,
+                       col_idx);
+  }
   return launch_status();
 }
 
@@ -1145,25 +1201,24 @@ extern "C" int prism_estimate_workspace_bytes(const prism_params* params, size_t
   return PRISM_OK;
 }
 
-// The whole estimate of one sequence (arguments already validated): pooling (+ RoPE when `rope`
+// The whole estimate of the sequences in `seqs` (arguments already validated): pooling (+ RoPE when `rope`
 // is given), calibration, selection, compaction.
-static int estimate_core(const prism_params* params, const HeadStrides& hs, const BandMap& map,
+static int estimate_core(const prism_params* params, const HeadStrides& hs, const SeqTable& seqs, const BandMap& map,
                          const void* q, const void* k, uint64_t* mask_bits, int32_t* row_ptr,
-                         int32_t* col_idx, int64_t col_capacity, int32_t* info, char* ws,
+                         int32_t* col_idx, int32_t* info, char* ws,
                          hipStream_t st, const RopeArgs* rope = nullptr, void* q_out = nullptr,
                          void* k_out = nullptr) {
-  const EstimateWs L = estimate_ws(params);
-  int rc = run_pool_and_scale(params, hs, map, q, k, ws, L, nullptr, nullptr, nullptr, st, rope, q_out, k_out);
+  const EstimateWs L = estimate_layout(params, seqs.n, seqs.nsum, seqs.tiles);
+  int rc = run_pool_and_scale(params, hs, seqs, map, q, k, ws, L, nullptr, nullptr, nullptr, st, rope, q_out, k_out);
   if (rc != PRISM_OK) return rc;
-  const int N = n_blocks(params);
   // up to 1024 blocks: 4 waves of 4 rows, two workgroups per CU; beyond (a 131 KB logit strip, one
   // workgroup per CU, rows of 32 registers): 8 waves of 2 rows (measured 1.89 -> 1.25 ms at N = 2048,
   // while at N = 1024 the 4-wave form is 2 % faster)
-  rc = (N <= 1024)
-           ? launch_select<16, false, 4>(params, map, ws, L, mask_bits, row_ptr, nullptr, nullptr, st)
-           : launch_select<32, false, 2>(params, map, ws, L, mask_bits, row_ptr, nullptr, nullptr, st);
+  rc = (seqs.nmax <= 1024)
+           ? launch_select<16, false, 4>(params, seqs, map, ws, L, mask_bits, row_ptr, nullptr, nullptr, st)
+           : launch_select<32, false, 2>(params, seqs, map, ws, L, mask_bits, row_ptr, nullptr, nullptr, st);
   if (rc != PRISM_OK) return rc;
-  return run_compaction(params, mask_bits, row_ptr, col_idx, col_capacity, info, false, st);
+  return run_compaction(params, seqs, mask_bits, row_ptr, col_idx, info, false, st);
 }
 
 extern "C" int prism_estimate_bands(const prism_params* params, const prism_bands* bands,
@@ -1180,8 +1235,9 @@ extern "C" int prism_estimate_bands(const prism_params* params, const prism_band
     return PRISM_ERR_INVALID_ARG;
   rc = check_ws(workspace, workspace_bytes, estimate_ws(params).total);
   if (rc != PRISM_OK) return rc;
-  return estimate_core(params, contiguous_heads(params), map, q_bf16, k_bf16, mask_bits, row_ptr, col_idx,
-                       col_capacity, info, static_cast<char*>(workspace), static_cast<hipStream_t>(stream));
+  return estimate_core(params, contiguous_heads(params), one_sequence(params, col_capacity), map, q_bf16, k_bf16,
+                       mask_bits, row_ptr, col_idx, info, static_cast<char*>(workspace),
+                       static_cast<hipStream_t>(stream));
 }
 
 // ---- packed variable-length batches ---------------------------------------------------
@@ -1257,22 +1313,16 @@ extern "C" int prism_estimate_varlen(const prism_params* params, const int32_t* 
   if (rc != PRISM_OK) return rc;
   const size_t d = params->head_dim, T = params->seq_len;
   const HeadStrides hs{T * d, T * d, T};
-  int64_t mo = 0, ro = 0, co = 0;
-  for (int s = 0; s < n_seqs; ++s) {
-    const prism_params ps = sequence_params(params, cu_seqlens, s);
-    const int64_t N = n_blocks(&ps), h = ps.n_q_heads;
-    const int64_t cap = (ps.flags & PRISM_FLAG_BIDIRECTIONAL) ? h * N * N : h * N * (N + 1) / 2;
-    const size_t tok = (size_t)cu_seqlens[s] * d;
-    // the sequences share the workspace: they run one after the other on the stream
-    rc = estimate_core(&ps, hs, map, (const uint16_t*)q_bf16 + tok, (const uint16_t*)k_bf16 + tok, mask_bits + mo,
-                       row_ptr + ro, col_idx + co, cap, info + 4 * s, static_cast<char*>(workspace),
-                       static_cast<hipStream_t>(stream));
-    if (rc != PRISM_OK) return rc;
-    mo += h * N * ((N + 63) / 64);
-    ro += h * N + 1;
-    co += cap;
-  }
-  return PRISM_OK;
+  // sequences share their launches while the workspace holds them; groups run one after the other on the stream
+  auto fits = [&](const SeqTable& t) {
+    return estimate_layout(params, t.n, t.nsum, t.tiles).total <= workspace_bytes &&
+           (int64_t)params->n_q_heads * t.nsum < ((int64_t)1 << 31) - 4;
+  };
+  auto run = [&](const SeqTable& t, const prism_params& ps) {
+    return estimate_core(&ps, hs, t, map, q_bf16, k_bf16, mask_bits, row_ptr, col_idx, info,
+                         static_cast<char*>(workspace), static_cast<hipStream_t>(stream));
+  };
+  return for_each_group(params, cu_seqlens, n_seqs, fits, run);
 }
 
 extern "C" int prism_estimate(const prism_params* params, const void* q_bf16, const void* k_bf16,
@@ -1373,9 +1423,9 @@ extern "C" int prism_rope_estimate(const prism_params* params, const prism_rope*
   }
   rc = check_ws(workspace, workspace_bytes, estimate_ws(params).total);
   if (rc != PRISM_OK) return rc;
-  return estimate_core(params, contiguous_heads(params), map, q_in_bf16, k_in_bf16, mask_bits, row_ptr, col_idx,
-                       col_capacity, info, static_cast<char*>(workspace), static_cast<hipStream_t>(stream),
-                       &ra, q_out_bf16, k_out_bf16);
+  return estimate_core(params, contiguous_heads(params), one_sequence(params, col_capacity), map, q_in_bf16, k_in_bf16,
+                       mask_bits, row_ptr, col_idx, info, static_cast<char*>(workspace),
+                       static_cast<hipStream_t>(stream), &ra, q_out_bf16, k_out_bf16);
 }
 
 extern "C" int prism_block_scores_bands(const prism_params* params, const prism_bands* bands,
@@ -1394,11 +1444,12 @@ extern "C" int prism_block_scores_bands(const prism_params* params, const prism_
   if (rc != PRISM_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  rc = run_pool_and_scale(params, contiguous_heads(params), map, q_bf16, k_bf16, ws, L, pooled_q, pooled_k,
+  const SeqTable seqs = one_sequence(params, 0);
+  rc = run_pool_and_scale(params, contiguous_heads(params), seqs, map, q_bf16, k_bf16, ws, L, pooled_q, pooled_k,
                           scales, st);
   if (rc != PRISM_OK) return rc;
   if (logits_high == nullptr && logits_low == nullptr) return PRISM_OK;
-  return launch_select<16, true>(params, map, ws, L, nullptr, nullptr, logits_high, logits_low, st);
+  return launch_select<16, true>(params, seqs, map, ws, L, nullptr, nullptr, logits_high, logits_low, st);
 }
 
 extern "C" int prism_block_scores(const prism_params* params, const void* q_bf16,
@@ -1420,7 +1471,7 @@ extern "C" int prism_mask_to_csr(const prism_params* params, const uint64_t* mas
   int rc = check_params(params);
   if (rc != PRISM_OK) return rc;
   if (!mask_bits || !row_ptr || !col_idx || !info || col_capacity < 0) return PRISM_ERR_INVALID_ARG;
-  return run_compaction(params, mask_bits, row_ptr, col_idx, col_capacity, info, true,
+  return run_compaction(params, one_sequence(params, col_capacity), mask_bits, row_ptr, col_idx, info, true,
                         static_cast<hipStream_t>(stream));
 }
 

@@ -1,0 +1,66 @@
+"""Packed batches whose sequences share launches: the same bits from the estimate and the same attention as one call per
+sequence, for batches of more sequences than a group (16) or a packing window (64) holds, with the workspace the library
+asks for and with a larger one (larger groups), odd and even block counts, lists with an entry to skip."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_08426_amd import binding as pb
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+# two kernels that round P to bf16 and to fp16 in front of the P V product, |o| <= 4: one bf16 step of |o| each (2^-7)
+OUT_TOL, LSE_TOL = 2e-2, 2e-3
+
+
+@pytest.mark.parametrize("lens,h,hkv,B,d,bidir,extra,dirty", [
+    ([1 + 37 * i % 700 for i in range(70)], 4, 2, 128, 128, False, 0, False),
+    ([1 + 37 * i % 700 for i in range(70)], 4, 2, 128, 128, False, 64 << 20, False),
+    ([3000, 129, 5, 1024, 1025, 2000, 640, 1], 8, 2, 128, 128, True, 64 << 20, False),
+    ([3000, 129, 5, 1024, 1025, 2000, 640, 1], 8, 2, 128, 128, False, 64 << 20, True),
+    ([64 * 6, 64 * 2, 64 * 10, 64 * 4], 4, 1, 64, 128, False, 64 << 20, False),      # even numbers of blocks: pairs allowed
+    ([64 * 6 + 1, 64 * 2, 64 * 9, 33], 4, 1, 64, 64, False, 64 << 20, False),
+    ([700, 128, 1400], 2, 2, 128, 256, False, 64 << 20, False),
+])
+def test_groups_equal_single_calls(lens, h, hkv, B, d, bidir, extra, dirty):
+    print(f"case {len(lens)} sequences h={h}/{hkv} B={B} d={d} bidirectional={bidir} extra={extra}", flush=True)
+    flags = pb.PRISM_FLAG_BIDIRECTIONAL if bidir else 0
+    if B == 64 and d == 128:
+        flags |= pb.PRISM_FLAG_PAIR_KERNEL
+    cu = [0] + np.cumsum(lens).tolist()
+    T = cu[-1]
+    g = torch.Generator(device="cuda").manual_seed(sum(lens) + d)
+    q, k, v = (torch.randn((n, T, d), generator=g, device="cuda").bfloat16() for n in (h, hkv, hkv))
+    bands = {64: (32, 48), 128: (64, 96), 256: (128, 192)}[d]
+    params = pb.make_params(h, hkv, T, B, *bands, 0.9, flags, d)
+    mo, ro, co = pb.prism_varlen_layout(params, cu)
+    mask, rp, ci, info = (torch.full((n,), -7, dtype=t, device="cuda") for n, t in (
+        (mo[-1], torch.int64), (ro[-1], torch.int32), (co[-1], torch.int32), (4 * len(lens), torch.int32)))
+    pb.prism_estimate_varlen(params, cu, q, k, mask, rp, ci, info,
+                             pb.alloc_workspace(pb.prism_estimate_varlen_workspace_bytes(params, cu) + extra))
+    if dirty:
+        ci[co[1]] = -1                                    # a list of the second sequence starts with an entry to skip
+    out = torch.full((h, T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((h, T), float("nan"), dtype=torch.float32, device="cuda")
+    pb.prism_sparse_attn_varlen(params, cu, q, k, v, rp, ci, out, lse,
+                                pb.alloc_workspace(pb.prism_sparse_attn_varlen_workspace_bytes(params, cu) + extra))
+    torch.cuda.synchronize()
+    for s, L in enumerate(lens):
+        ps = pb.make_params(h, hkv, L, B, *bands, 0.9, flags, d)
+        qs, ks, vs = (x[:, cu[s]:cu[s + 1]].contiguous() for x in (q, k, v))
+        one = gu.gpu_estimate(ps, qs, ks)
+        _, rp1, ci1, info1 = one["dev"]
+        nnz = int(info1[0])
+        assert torch.equal(mask[mo[s]:mo[s + 1]], one["dev"][0].view(-1)), s
+        assert torch.equal(rp[ro[s]:ro[s + 1]], rp1), s
+        assert torch.equal(info[4 * s:4 * s + 4], info1), s
+        if dirty and s == 1:
+            ci1[0] = -1
+        assert torch.equal(ci[co[s]:co[s] + nnz], ci1[:nnz]), s
+        o1, l1 = gu.gpu_sparse_attn(ps, qs, ks, vs, rp1, ci1, nnz)
+        assert (out[:, cu[s]:cu[s + 1]].float() - o1.float()).abs().max() <= OUT_TOL, s
+        both = torch.isfinite(l1)
+        assert torch.equal(both, torch.isfinite(lse[:, cu[s]:cu[s + 1]])), s
+        if both.any():
+            assert (lse[:, cu[s]:cu[s + 1]] - l1)[both].abs().max() <= LSE_TOL, s
