@@ -264,6 +264,16 @@ constexpr int kPlanStart = 0, kPlanLen = 8, kPlanCounter = 16, kPlanFlags = 24, 
 // 64-queries-per-wave kernel; each of the two kernels returns at once when it is not its turn.
 constexpr int kFlagDirtyLists = 1;
 
+// Pull counters of the queues.  The one-launch preparation spreads them over cache lines of their own and starts
+// them behind the workgroups' first rows, which are dealt out by workgroup number (`first_dealt`): all pulls on one
+// line are served one after the other, 16 ns each, which made 40 us of the 64 us that 2048 rows without any listed
+// block took.  It leaves the counters of the plan to record that a queue was exhausted.
+struct PullCounters {
+  int32_t* at;
+  int32_t stride;        // ints between two queues' counters
+  int32_t first_dealt;
+};
+
 __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len, int* entry) {
   if (pulled >= seg_len) return kItemEnd;
   *entry = seg_start + pulled;
@@ -282,7 +292,7 @@ template <int BLK, bool kStreamOnly, int D, bool kPair>
 __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D, kPair>::kWavesPerSimd)) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const int4* __restrict__ items,
-    int32_t* __restrict__ plan, DirtyFlags flags,
+    int32_t* __restrict__ plan, PullCounters pulls, DirtyFlags flags,
     uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv, SeqTable seqs,
     HeadStrides hs, int causal, int only_dirty) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's signature
@@ -332,14 +342,14 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   int my_queue = blockIdx.x % n_queues;
   int seg_start = plan[kPlanStart + my_queue];
   int seg_len = plan[kPlanLen + my_queue];
-  int32_t* counter = plan + kPlanCounter;
+  int32_t* __restrict__ counter = pulls.at;
 
   // The queue is pulled when a workgroup is about to become free (at the top of the last
   // step of its row), so neighbouring rows of the queue start close together; the pull and the
   // read of the next row's queue entry are hidden behind that last step.
   int lane_zero;                                     // 0, but opaque to the compiler
   asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-  if (t == 0) next_item = atomicAdd(counter + my_queue, 1);
+  if (t == 0) next_item = pulls.first_dealt ? (int)blockIdx.x / n_queues : atomicAdd(counter + my_queue * pulls.stride, 1);
   __syncthreads();
   int cur_x = 0, cur_y = 0, cur_z = 0, cur_w = 0;     // the current row's queue entry, wave-uniform
   int kind_cur;
@@ -363,12 +373,13 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       // queue that still has rows, nearest first round the ring, and pull from it.  A counter
       // only grows, so a queue seen exhausted stays so; the atomic pull decides who gets a row.
       if (wave == 0) {
-        int pulls = 0x7fffffff, len = 0;
+        if (lane == 0 && pulls.first_dealt) plan[kPlanCounter + my_queue] = seg_len + 1;
+        int taken = 0x7fffffff, len = 0;
         if (lane < n_queues) {
-          pulls = __hip_atomic_load(counter + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          taken = __hip_atomic_load(counter + lane * pulls.stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           len = plan[kPlanLen + lane];
         }
-        const unsigned long long open = __ballot(pulls < len);
+        const unsigned long long open = __ballot(taken < len);
         int pick = -1;
         for (int s = 1; s < n_queues && pick < 0; ++s) {
           const int x = my_queue + s < n_queues ? my_queue + s : my_queue + s - n_queues;
@@ -376,7 +387,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
         }
         if (lane == 0) {
           next_queue = pick;
-          if (pick >= 0) next_item = atomicAdd(counter + pick, 1);
+          if (pick >= 0) next_item = atomicAdd(counter + pick * pulls.stride, 1);
         }
       }
       __syncthreads();
@@ -425,7 +436,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
         for (int c = 0; c < D / 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
         if (lse != nullptr && hf == 0) lse[(size_t)hq * hs.lse + tok0 + qrow] = -INFINITY;
       }
-      if (t == 0) next_item = atomicAdd(counter + my_queue, 1);
+      if (t == 0) next_item = atomicAdd(counter + my_queue * pulls.stride, 1);
       __syncthreads();
       int e = 0;
       kind_cur = item_kind(__builtin_amdgcn_readfirstlane(next_item), seg_start, seg_len, &e);
@@ -504,7 +515,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     // step starts the copy of the next K tile after its S^T phase, the last one pulls the queue.
     auto step = [&](auto last_tag) __attribute__((always_inline)) {
       constexpr bool kLast = decltype(last_tag)::value;
-      if (kLast && t == 0) pulled_reg = atomicAdd(counter + my_queue, 1);
+      if (kLast && t == 0) pulled_reg = atomicAdd(counter + my_queue * pulls.stride, 1);
 
       // ---- V(j) -> LDS, in flight during S^T and the softmax ----
       async_load_vt_tile<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t);
@@ -754,8 +765,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
     const int32_t* __restrict__ col_idx, const int4* __restrict__ items, int32_t* __restrict__ plan,
-    DirtyFlags flags, uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv, SeqTable seqs,
-    HeadStrides hs, int causal) {
+    PullCounters pulls, DirtyFlags flags, uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv,
+    SeqTable seqs, HeadStrides hs, int causal) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) char lds_tiles[65536];
   __shared__ int s_pulled, s_queue;
@@ -769,10 +780,10 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
   int my_queue = blockIdx.x % n_queues;
   int seg_start = plan[kPlanStart + my_queue];
   int seg_len = plan[kPlanLen + my_queue];
-  int32_t* counter = plan + kPlanCounter;
+  int32_t* __restrict__ counter = pulls.at;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   int pulled = 0;
-  if (t == 0) pulled = atomicAdd(counter + my_queue, 1);
+  if (t == 0) pulled = pulls.first_dealt ? (int)blockIdx.x / n_queues : atomicAdd(counter + my_queue * pulls.stride, 1);
   for (;;) {
     // hand the pulled queue position to both waves
     __syncthreads();
@@ -784,14 +795,15 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
       // counter only grows, so a queue seen exhausted stays so; the atomic decides who gets a row.
       __syncthreads();
       if (wave == 0) {
+        if (lane == 0 && pulls.first_dealt) plan[kPlanCounter + my_queue] = seg_len + 1;
         int found_pos = -1, found_queue = -1;
         for (;;) {
-          int pulls = 0x7fffffff, len = 0;
+          int taken = 0x7fffffff, len = 0;
           if (lane < n_queues) {
-            pulls = __hip_atomic_load(counter + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            taken = __hip_atomic_load(counter + lane * pulls.stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             len = plan[kPlanLen + lane];
           }
-          const unsigned long long open = __ballot(pulls < len);
+          const unsigned long long open = __ballot(taken < len);
           if (open == 0ull) break;
           int pick = -1;
           for (int s = 1; s <= n_queues && pick < 0; ++s) {
@@ -799,7 +811,7 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
             if ((open >> x) & 1ull) pick = x;
           }
           int got = 0;
-          if (lane == 0) got = atomicAdd(counter + pick, 1);
+          if (lane == 0) got = atomicAdd(counter + pick * pulls.stride, 1);
           got = __builtin_amdgcn_readfirstlane(got);
           if (got < plan[kPlanLen + pick]) {
             found_pos = got;
@@ -852,7 +864,7 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
         for (int c = 0; c < 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
         if (lse != nullptr) lse[(size_t)hq * hs.lse + tok0 + r] = -INFINITY;
       }
-      if (t == 0) pulled = atomicAdd(counter + my_queue, 1);
+      if (t == 0) pulled = atomicAdd(counter + my_queue * pulls.stride, 1);
       continue;
     }
     const uint16_t* q_row = q + row0;
@@ -863,7 +875,7 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     const uint16_t* vt_head = vt + ((size_t)seqs.s[sq].blk0 * h_kv + (size_t)kvh * N) * 128 * kHeadDim;
     const int32_t* col_row = col_idx + seqs.s[sq].col0 + it;
     const int n_entries = end - it;
-    int32_t* pull_counter = counter + __builtin_amdgcn_readfirstlane(my_queue);
+    int32_t* pull_counter = counter + __builtin_amdgcn_readfirstlane(my_queue * pulls.stride);
     // the one block of the row that has hidden keys: the diagonal, or a ragged last block
     const int mask_block = causal ? u : ragged_block;
     int pulled_next;
@@ -1151,6 +1163,9 @@ struct PrepArgs {
   int32_t *range_flags, *check;
   int4 *items, *pair_items;
   int32_t *plan, *pair_plan;
+  int32_t *counters, *pair_counters;
+  int32_t counter_stride;
+  int32_t grid, pair_grid;                 // workgroups of the attention kernels
   int32_t h, h_kv, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
   size_t kv_head_stride;
 };
@@ -1167,7 +1182,8 @@ struct PlanLds {
 // stride = 2: rows are pairs of q-blocks (every sequence has an even number of them).
 template <int CH>
 __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const SeqTable& seqs, int stride,
-                                          int n_queues, int4* __restrict__ items, int32_t* __restrict__ plan) {
+                                          int n_queues, int grid, int32_t* __restrict__ counters,
+                                          int4* __restrict__ items, int32_t* __restrict__ plan) {
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int per_head = seqs.nsum >> (stride - 1);
   const int R = a.h * per_head;
@@ -1287,6 +1303,8 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     plan[kPlanLen + t] = m.qlen[t];
     plan[kPlanCounter + t] = 0;
     plan[kPlanFlags + t] = 0;
+    // the first pulls of queue t belong to the workgroups t, t + n_queues, ...
+    counters[t * a.counter_stride] = t < n_queues ? (grid - t + n_queues - 1) / n_queues : 0;
   }
   // rank becomes the row's entry, cum its list's first element
 #pragma unroll
@@ -1378,10 +1396,12 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
     const int n_queues = wg == 0 ? a.n_queues : a.pair_queues;
     int4* items = wg == 0 ? a.items : a.pair_items;
     int32_t* plan = wg == 0 ? a.plan : a.pair_plan;
-    if (R <= kPrepThreads) plan_rows<1>(lds.plan, a, seqs, stride, n_queues, items, plan);
-    else if (R <= 2 * kPrepThreads) plan_rows<2>(lds.plan, a, seqs, stride, n_queues, items, plan);
-    else if (R <= 4 * kPrepThreads) plan_rows<4>(lds.plan, a, seqs, stride, n_queues, items, plan);
-    else plan_rows<8>(lds.plan, a, seqs, stride, n_queues, items, plan);
+    int32_t* counters = wg == 0 ? a.counters : a.pair_counters;
+    const int grid = wg == 0 ? a.grid : a.pair_grid;
+    if (R <= kPrepThreads) plan_rows<1>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
+    else if (R <= 2 * kPrepThreads) plan_rows<2>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
+    else if (R <= 4 * kPrepThreads) plan_rows<4>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
+    else plan_rows<8>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
     return;
   }
   wg -= a.n_plans;
@@ -1555,13 +1575,13 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
 }
 
 template <int BLK, bool kStreamOnly, int D, bool kPair = false>
-static void launch_attn(int grid, hipStream_t st, const uint16_t* q, const uint16_t* k, const uint16_t* vt,
+static void launch_attn(int grid, hipStream_t st, const PullCounters& pulls, const uint16_t* q, const uint16_t* k, const uint16_t* vt,
                         const int32_t* row_ptr, const int32_t* col_idx, const int4* items, int32_t* plan,
                         const DirtyFlags& flags, uint16_t* out, float* lse, int h, int h_kv, const SeqTable& seqs,
                         const HeadStrides& hs, int causal, int only_dirty) {
   hipLaunchKernelGGL((sparse_attn_kernel<BLK, kStreamOnly, D, kPair>), dim3(grid),
                      dim3(AttnCfg<BLK, D, kPair>::kThreads), 0, st, q, k, vt, row_ptr, col_idx, items, plan,
-                     flags, out, lse, h, h_kv, seqs, hs, causal, only_dirty);
+                     pulls, flags, out, lse, h, h_kv, seqs, hs, causal, only_dirty);
 }
 
 template <int BLK, int D>
@@ -1658,6 +1678,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // 13, 22 and 38 us), 4.8 instead of 13.9 at 32 rows.  Beyond, the plan of a single workgroup (33 us at 5024 rows
   // without an image beside it) would no longer hide behind the image, and the parts run as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
+  PullCounters pulls = {plan + kPlanCounter, 1, 0}, pair_pulls = {pair_plan + kPlanCounter, 1, 0};
   if (R <= kPrepMaxRows && pc.n_phases == 1) {
     PrepArgs pa = {};
     pa.row_ptr = row_ptr;
@@ -1679,6 +1700,15 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.n_plans = pair ? 2 : 1;
     pa.n_check = only_dirty ? (R + kCheckRows - 1) / kCheckRows : 0;
     pa.need_sorted = pair ? 1 : 0;
+    // two sets of 8 counters in row_part, which this path has no other use for, up to a 128-byte line each
+    pulls = PullCounters{row_part, 32, 1};
+    while ((size_t)pulls.stride * 2 * kXcds * sizeof(int32_t) > W.bins - W.row_part) pulls.stride >>= 1;
+    pair_pulls = PullCounters{row_part + pulls.stride * kXcds, pulls.stride, 1};
+    pa.counters = pulls.at;
+    pa.pair_counters = pair_pulls.at;
+    pa.counter_stride = pulls.stride;
+    pa.grid = grid;
+    pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
     const int prep_grid = pa.n_plans + pa.n_check + (v_bf16 != nullptr ? h_kv * N : 0);
     if (params->block == 128) {
@@ -1712,7 +1742,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   }
   if (pair) {
 #define PRISM_PAIR(D)                                                                                        \
-  launch_attn<64, false, D, true>(pair_grid, st, qp, kp, vp, row_ptr, col_idx, pair_items, pair_plan, flags, \
+  launch_attn<64, false, D, true>(pair_grid, st, pair_pulls, qp, kp, vp, row_ptr, col_idx, pair_items, pair_plan, flags, \
                                   op, lse, h, h_kv, seqs, hs, causal, 0)
     if (d == 64) PRISM_PAIR(64);
     else if (d == 128) PRISM_PAIR(128);
@@ -1720,10 +1750,10 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
 #undef PRISM_PAIR
   }
   if (w64)
-    hipLaunchKernelGGL(sparse_attn_w64_kernel, dim3(grid), dim3(128), 0, st, qp, kp, vp16, col_idx, items, plan, flags,
+    hipLaunchKernelGGL(sparse_attn_w64_kernel, dim3(grid), dim3(128), 0, st, qp, kp, vp16, col_idx, items, plan, pulls, flags,
                        op, lse, h, h_kv, seqs, hs, causal);
 #define PRISM_ATTN(BLK, SO, D)                                                                                \
-  launch_attn<BLK, SO, D>(grid, st, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
+  launch_attn<BLK, SO, D>(grid, st, pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
                           hs, causal, only_dirty)
   if (stream_only) {
     // measurement aid of the d = 128 kernels only
