@@ -25,12 +25,17 @@ registers of every 16-register accumulator), which PV(j) reads as its B operand 
 later, before S(j+2) overwrites the bank.
 
 Registers (fixed):
+(with two query tiles; see configure() for one)
     a[0:127]    O^T accumulators  O[dt][qt] at 16*(2*dt+qt)
     a[128:191]  Q fragments       Q[qt][ks] at 128 + 4*(8*qt+ks)
     v[64:191]   S / P banks       bank p, key tile kt, query tile qt at 64 + 64*p + 16*(2*kt+qt)
     v[192:223]  ring of 8 LDS operand fragments
     v[32:63], v[224:255]  per-lane constants, softmax state, temporaries
     v[0:31] and the SGPRs below s40 are left to the compiler.
+
+The same generator also writes prism_attn_w32_body.inc: one query tile per wave and four waves per workgroup
+(QT = 1).  Every fragment then feeds one MFMA, twice as many waves share a row, and 160 VGPRs and 96 AGPRs leave room
+for two waves per SIMD.  Every query sees the same operations in the same order in both: the bits are the same.
 """
 from __future__ import annotations
 
@@ -40,35 +45,63 @@ import sys
 # ----------------------------------------------------------------------------------------------
 # register map
 # ----------------------------------------------------------------------------------------------
+# QT = query tiles of 32 per wave: 2 (sparse_attn_w64_kernel, 2 waves per workgroup) or 1 (the 32-queries-per-wave
+# form, 4 waves per workgroup and 256 registers per lane, so that two workgroups share a CU there too).
+# configure() sets everything that depends on it.
+QT = 2
+
+
 def O(dt, qt):          # AGPR base of O[dt][qt]
-    return 16 * (2 * dt + qt)
+    return 16 * (QT * dt + qt)
 
 
 def Q(qt, ks):          # AGPR base of Q[qt][ks]
-    return 128 + 4 * (8 * qt + ks)
+    return 64 * QT + 4 * (8 * qt + ks)
 
 
 def SB(p, kt, qt):      # VGPR base of S bank p, tile (kt, qt)
-    return 64 + 64 * p + 16 * (2 * kt + qt)
+    return S0 + 32 * QT * p + 16 * (QT * kt + qt)
 
 
-FR0 = 192               # fragment ring: 8 slots of 4 VGPRs
-N_FR = 8
+N_FR = 8                # fragment ring: 8 slots of 4 VGPRs
 
-# per-lane constants / state
-V_KOFF = 32             # 8 regs: LDS offsets of the K fragment of k-step ks
-V_VOFF = 40             # 4 regs: LDS offsets of the V^T fragment of k-step S
-V_CPK = 44              # 8 regs: global offsets of this lane's 8 pieces of a K half-tile copy
-V_CPV = 52              # 8 regs: ... of a V^T half-tile copy
-V_M = 60                # 2 regs: running max (log2 units) per query tile
-V_L = 62                # 2 regs: this lane's share of the running sum
-V_T = 224               # 32 temporaries v[224:255]:
-#   T+0..5 / T+8..13 softmax of query tile 0 / 1;  T+16..25 prologue / epilogue;  T+26,27 mask
-#   thresholds;  T+28 pulled queue position, T+29 its increment (drain .. end of row; the debug dump
-#   borrows both);  T+30 list offset;  T+31 -inf
-V_ALPHA = V_T + 6       # 2 regs: rescale factor decided by the last softmax
-V_IDX = V_T + 14        # 1 reg : list entry loaded two blocks ahead
-V_ZERO = V_T + 15       # 1 reg : 0
+
+def configure(qt):
+    global QT, PIECES, S0, FR0, V_KOFF, V_VOFF, V_CPK, V_CPV, V_M, V_L, V_T, V_ALPHA, V_IDX, V_ZERO, V_LAST, V_FIRST
+    global WAIT_OLDER_COPY, LABEL, V_THR, V_PULL, V_ONE, V_OFF, V_INF
+    QT = qt
+    PIECES = 4 * qt     # 1 KB pieces of a half-tile copy per wave
+    # per-lane constants / state
+    V_FIRST = V_KOFF = 32 if qt == 2 else 16   # 8 regs: LDS offsets of the K fragment of k-step ks
+    after = V_KOFF + 8
+    if qt == 2:
+        V_VOFF = after      # 4 regs: LDS offsets of the V^T fragment of k-step S
+        after += 4
+    V_CPK = after           # PIECES regs: global offsets of this lane's pieces of a K half-tile copy
+    V_CPV = V_CPK + PIECES  # PIECES regs: ... of a V^T half-tile copy
+    after = V_CPV + PIECES
+    if qt == 2:
+        V_M = after         # QT regs: running max (log2 units) per query tile
+        V_L = V_M + qt      # QT regs: this lane's share of the running sum
+        after = V_L + qt
+    S0 = after              # S / P banks (even)
+    assert S0 % 2 == 0
+    FR0 = S0 + 64 * qt      # fragment ring
+    V_T = FR0 + 4 * N_FR    # temporaries:
+    #   T+0..5 / T+8..13 softmax of query tile 0 / 1;  T+16..25 prologue / epilogue;  V_THR mask thresholds (QT regs);
+    #   V_PULL pulled queue position, V_ONE its increment (drain .. end of row; the debug dump borrows both);
+    #   V_OFF list offset;  V_INF -inf.  With one query tile some of them share registers that are never live together.
+    if qt == 1:             # one query tile leaves T+8..13 free
+        V_VOFF, V_M, V_L = V_T + 8, V_T + 12, V_T + 13
+    V_ALPHA = V_T + 6       # QT regs: rescale factor decided by the last softmax
+    V_IDX = V_T + 14        # 1 reg : list entry loaded two blocks ahead
+    V_ZERO = V_T + 15       # 1 reg : 0
+    V_THR, V_PULL, V_ONE, V_OFF, V_INF, V_LAST = (V_T + i for i in ((26, 28, 29, 30, 31, 31) if qt == 2 else
+                                                                    (21, 26, 27, 25, 24, 27)))
+    # two younger copies may stay in flight (see WAIT_OLDER_COPY below)
+    WAIT_OLDER_COPY = f"s_waitcnt vmcnt({2 * PIECES}) lgkmcnt(0)"
+    LABEL = "" if qt == 2 else "q"                 # labels of the two forms must differ
+
 
 # scalars (clobbered; inputs arrive in compiler-chosen SGPRs and are copied in the prologue)
 S_KRS = 40              # 4: buffer resource of K of this kv head
@@ -187,7 +220,7 @@ def pv_ops(p):
         for dt in range(4):
             def make(slot, S=S, dt=dt, kt=kt, sp=sp):
                 fr = FR0 + 4 * slot
-                return [mfma_pv(O(dt, qt), fr, SB(p, kt, qt) + 4 * sp) for qt in range(2)]
+                return [mfma_pv(O(dt, qt), fr, SB(p, kt, qt) + 4 * sp) for qt in range(QT)]
             groups.append((("v", S, dt), make))
     return groups
 
@@ -199,7 +232,7 @@ def s_ops(p):
         for kt in range(2):
             def make(slot, ks=ks, kt=kt):
                 fr = FR0 + 4 * slot
-                return [mfma_s(SB(p, kt, qt), fr, Q(qt, ks), ks == 0) for qt in range(2)]
+                return [mfma_s(SB(p, kt, qt), fr, Q(qt, ks), ks == 0) for qt in range(QT)]
             groups.append((("k", ks, kt), make))
     return groups
 
@@ -223,18 +256,15 @@ def mfma_stream(groups, kbuf, vbuf, depth=6):
     pre = [frag_read(groups[i][0], i % N_FR, kbuf, vbuf) for i in range(min(depth, n))]
     issued = len(pre)
     for i, (desc, make) in enumerate(groups):
-        m0, m1 = make(i % N_FR)
-        slot0 = [m0]
+        slots = [[m] for m in make(i % N_FR)]
         if i % 2 == 0:
             # fragments i and i + 1 must have arrived: reads younger than i + 1 may be outstanding
-            slot0.insert(0, wait_lgkm(issued - (i + 2)))
-        slot1 = [m1]
+            slots[0].insert(0, wait_lgkm(issued - (i + 2)))
         if issued < n:
             # the ring slot being refilled was consumed N_FR - depth groups ago
-            slot1.append(frag_read(groups[issued][0], issued % N_FR, kbuf, vbuf))
+            slots[-1].append(frag_read(groups[issued][0], issued % N_FR, kbuf, vbuf))
             issued += 1
-        out.append(slot0)
-        out.append(slot1)
+        out += slots
     return pre, out
 
 
@@ -324,29 +354,29 @@ def mask_block(p, hh, label):
     T = V_T
     ops = [salu(f"s_cmp_eq_u32 s{S_CV}, s{S_U}"),
            salu(f"s_cbranch_scc0 {label}")]
-    ops.append(valu(f"v_mov_b32 v{T + 31}, 0xff800000", (), vr(T + 31)))
+    ops.append(valu(f"v_mov_b32 v{V_INF}, 0xff800000", (), vr(V_INF)))
     # last visible key relative to this half's keys: limit - 4*hf - 64*hh with
-    # limit = causal * (64*wave + 32*qt + l32) + tail1 (tail1 = 0 for causal rows)
+    # limit = causal * (32*QT*wave + 32*qt + l32) + tail1 (tail1 = 0 for causal rows)
     ops += lane_ids(INP, T + 16)
-    ops.append(valu(f"v_lshl_add_u32 v{T + 19}, v{T + 19}, 6, v{T + 17}", vr(T + 19) + vr(T + 17), vr(T + 19)))
+    ops.append(valu(f"v_lshl_add_u32 v{T + 19}, v{T + 19}, {4 + QT}, v{T + 17}", vr(T + 19) + vr(T + 17), vr(T + 19)))
     ops.append(valu(f"v_lshlrev_b32 v{T + 20}, 2, v{T + 18}", vr(T + 18), vr(T + 20)))
     ops.append(valu(f"v_sub_u32 v{T + 20}, s{S_TAIL}, v{T + 20}", vr(T + 20), vr(T + 20)))
-    for qt in range(2):
+    for qt in range(QT):
         ops.append(valu(f"v_add_u32 v{T + 17}, {lit32(32 * qt)}, v{T + 19}", vr(T + 19), vr(T + 17)))
         ops.append(valu(f"v_mul_u32_u24 v{T + 17}, s{S_CAUSAL}, v{T + 17}", vr(T + 17), vr(T + 17)))
         ops.append(valu(f"v_add_u32 v{T + 17}, {lit32(-64 * hh)}, v{T + 17}", vr(T + 17), vr(T + 17)))
-        ops.append(valu(f"v_add_u32 v{T + 26 + qt}, v{T + 17}, v{T + 20}", vr(T + 17) + vr(T + 20), vr(T + 26 + qt)))
-    todo = [(qt, kt, r) for qt in range(2) for kt in range(2) for r in range(16)]
+        ops.append(valu(f"v_add_u32 v{V_THR + qt}, v{T + 17}, v{T + 20}", vr(T + 17) + vr(T + 20), vr(V_THR + qt)))
+    todo = [(qt, kt, r) for qt in range(QT) for kt in range(2) for r in range(16)]
     def cmp_ins(i):
         qt, kt, r = todo[i]
         c = 32 * kt + 8 * (r // 4) + r % 4
         sp = S_MASK + 2 * (i % 4)
-        return valu(f"v_cmp_gt_i32 s[{sp}:{sp + 1}], {c}, v{T + 26 + qt}", vr(T + 26 + qt), [("s", sp), ("s", sp + 1)])
+        return valu(f"v_cmp_gt_i32 s[{sp}:{sp + 1}], {c}, v{V_THR + qt}", vr(V_THR + qt), [("s", sp), ("s", sp + 1)])
     def sel_ins(i):
         qt, kt, r = todo[i]
         reg = SB(p, kt, qt) + r
         sp = S_MASK + 2 * (i % 4)
-        return valu(f"v_cndmask_b32 v{reg}, v{reg}, v{T + 31}, s[{sp}:{sp + 1}]", vr(reg) + vr(T + 31) + [("s", sp), ("s", sp + 1)], vr(reg))
+        return valu(f"v_cndmask_b32 v{reg}, v{reg}, v{V_INF}, s[{sp}:{sp + 1}]", vr(reg) + vr(V_INF) + [("s", sp), ("s", sp + 1)], vr(reg))
     lead = 3
     for i in range(len(todo) + lead):
         if i < len(todo):
@@ -368,12 +398,13 @@ def lit32(c):
 def rescale_block(label):
     """O *= alpha (per query tile), only when the last softmax moved some lane's max and O holds
     something.  O lives in AGPRs: read, multiply, write back in batches of 16."""
-    ops = [salu(f"s_or_b64 s[{S_TMP}:{S_TMP + 1}], s[{S_FLAG}:{S_FLAG + 1}], s[{S_FLAG + 2}:{S_FLAG + 3}]"),
+    last = S_FLAG + 2 * (QT - 1)
+    ops = [salu(f"s_or_b64 s[{S_TMP}:{S_TMP + 1}], s[{S_FLAG}:{S_FLAG + 1}], s[{last}:{last + 1}]"),
            salu(f"s_cselect_b32 s{S_T2}, s{S_HAVE_O}, 0"),
            salu(f"s_cmp_eq_u32 s{S_T2}, 0"),
            salu(f"s_cbranch_scc1 {label}")]
     tmp = V_T + 16                       # 8 temporaries (fragment reads may be in flight)
-    for qt in range(2):
+    for qt in range(QT):
         for dt in range(4):
             for half in range(2):
                 base = O(dt, qt) + 8 * half
@@ -390,7 +421,7 @@ def rescale_block(label):
 
 def copy_k(buf, half, blk_reg, guard_label=None):
     """Asynchronous copy of a K half-tile (64 keys x 128 dims, 16 KB) of block s[blk_reg] into
-    Kbuf[buf].  Wave w copies rows 32*w .. 32*w + 31 as 8 pieces of 1 KB (4 rows each); the LDS
+    Kbuf[buf].  Wave w copies rows 16*QT*w .. as PIECES pieces of 1 KB (4 rows each); the LDS
     address of piece i is M0 + (i % 4) * 1024 + 16 * lane, so M0 changes twice per tile, and the
     instruction offset that places the piece in LDS is taken out of its global offset V_CPK[i]."""
     ops = []
@@ -400,7 +431,7 @@ def copy_k(buf, half, blk_reg, guard_label=None):
     ops.append(salu(f"s_lshl_b32 s{S_T0}, s{blk_reg}, 15"))                   # block * 32 KB
     if half:
         ops.append(salu(f"s_add_u32 s{S_T0}, s{S_T0}, {16384}"))
-    for i in range(8):
+    for i in range(PIECES):
         if i == 4:
             ops.append(salu(f"s_add_u32 m0, s{S_MK + buf}, 4096"))
             ops.append(nop(0))
@@ -413,14 +444,14 @@ def copy_k(buf, half, blk_reg, guard_label=None):
 
 def copy_v(buf, half, blk_reg):
     """Asynchronous copy of a V^T half-tile (128 dims x 64 keys, 16 KB) of block s[blk_reg] into
-    Vbuf[buf]: wave w copies dims 64*w .. 64*w + 63 as 8 pieces of 1 KB (8 rows of 128 bytes)."""
+    Vbuf[buf]: wave w copies dims 32*QT*w .. as PIECES pieces of 1 KB (8 rows of 128 bytes)."""
     ops = [salu(f"s_mov_b32 m0, s{S_MV + buf}"),
            salu(f"s_lshl_b32 s{S_T1}, s{blk_reg}, 15")]
     if half:
         ops.append(salu(f"s_add_u32 s{S_T1}, s{S_T1}, {128}"))
     else:
         ops.append(nop(0))
-    for i in range(8):
+    for i in range(PIECES):
         if i == 4:
             ops.append(salu(f"s_add_u32 m0, s{S_MV + buf}, 4096"))
             ops.append(nop(0))
@@ -431,9 +462,9 @@ def copy_v(buf, half, blk_reg):
 
 def load_idx():
     """Entry b+2 of the list (reads past its end return 0 and are never used)."""
-    return [valu(f"v_mov_b32 v{V_T + 30}, s{S_COFF}", (), vr(V_T + 30)),
-            Ins(f"buffer_load_dword v{V_IDX}, v{V_T + 30}, s[{S_CRS}:{S_CRS + 3}], 0 offen", "vmem",
-                vr(V_T + 30), vr(V_IDX))]
+    return [valu(f"v_mov_b32 v{V_OFF}, s{S_COFF}", (), vr(V_OFF)),
+            Ins(f"buffer_load_dword v{V_IDX}, v{V_OFF}, s[{S_CRS}:{S_CRS + 3}], 0 offen", "vmem",
+                vr(V_OFF), vr(V_IDX))]
 
 
 def end_of_iteration():
@@ -469,8 +500,7 @@ def zip_streams(a, b):
 
 # Tile copies in flight.  Iteration j issues K(j+2) at its start and V(j+1) at its middle; each is
 # waited for one and a half iterations later (K(j+1) at the middle of j, V(j) at the end of j), with
-# the two younger copies (8 loads each) still in flight.
-WAIT_OLDER_COPY = "s_waitcnt vmcnt(16) lgkmcnt(0)"
+# the two younger copies (PIECES loads each) still in flight.
 LEAD_VALU = 12          # side-stream instructions issued between the up-front LDS reads and the first MFMA
 
 
@@ -507,15 +537,13 @@ def segment(groups, g0, kbuf, vbuf):
     issued = DEPTH
     slots = []
     for i in range(n - HOLD):
-        m0, m1 = groups[i][1]((g0 + i) % N_FR)
-        s0 = [m0]
+        these = [[m] for m in groups[i][1]((g0 + i) % N_FR)]
         if i % 2 == 0:
-            s0.insert(0, wait_lgkm(issued - (i + 2)))
-        s1 = [m1]
+            these[0].insert(0, wait_lgkm(issued - (i + 2)))
         if issued < n:
-            s1.append(frag_read(groups[issued][0], (g0 + issued) % N_FR, kbuf, vbuf))
+            these[-1].append(frag_read(groups[issued][0], (g0 + issued) % N_FR, kbuf, vbuf))
             issued += 1
-        slots += [s0, s1]
+        slots += these
     assert issued == n
     held = []
     for i in range(n - HOLD, n):
@@ -539,7 +567,7 @@ def iteration(p, hh, do_pv, do_s, incoming, uid, sequential=False):
     Past the end of the list the K / V^T resource is given zero records, so those copies touch no
     memory (the number of loads in flight stays a compile-time fact)."""
     q = p ^ 1
-    vops = zip_streams(softmax_ops(p, 0, uid), softmax_ops(p, 1, uid))
+    vops = zip_streams(*(softmax_ops(p, qt, uid) for qt in range(QT))) if QT == 2 else softmax_ops(p, 0, uid)
     if "nosoft" in EXPERIMENT:
         vops = []
     n_a = len(vops) // 2 if (do_pv and do_s) else (len(vops) if do_pv else 0)
@@ -564,14 +592,14 @@ def iteration(p, hh, do_pv, do_s, incoming, uid, sequential=False):
         pre, slots, held1 = segment(pv_ops(q), 0, q, q)
         ops += pre
         ops += interleave([[m] for m in inc], copy_a) if inc else copy_a
-        ops += rescale_block(f"Lnoresc_{uid}")
-        ops += mask_block(p, hh, f"Lnomask_{uid}")
+        ops += rescale_block(f"Lnoresc{LABEL}_{uid}")
+        ops += mask_block(p, hh, f"Lnomask{LABEL}_{uid}")
         ops += interleave(slots, vops[:n_a])
     else:
         assert not inc
         held1 = []
         ops += copy_a
-        ops += mask_block(p, hh, f"Lnomask_{uid}")
+        ops += mask_block(p, hh, f"Lnomask{LABEL}_{uid}")
     ops += sync_point("mid")
     # ---- second phase
     if do_s:
@@ -605,20 +633,20 @@ def pull_next_row():
     neighbouring q-blocks of one head, whose lists share tiles in the L2."""
     T = V_T
     return [salu(f"s_cmp_lg_u32 s{S_WAVE}, 0"),
-            salu("s_cbranch_scc1 Lnopull"),
+            salu(f"s_cbranch_scc1 Lnopull{LABEL}"),
             salu(f"s_mov_b64 s[{S_TMP}:{S_TMP + 1}], exec"),
             salu("s_mov_b64 exec, 1"),
-            valu(f"v_mov_b32 v{T + 29}, 1", (), vr(T + 29)),
-            Ins(f"global_atomic_add v{T + 28}, v{V_ZERO}, v{T + 29}, s[{S_CNT}:{S_CNT + 1}] sc0", "vmem",
-                vr(V_ZERO) + vr(T + 29), vr(T + 28)),
+            valu(f"v_mov_b32 v{V_ONE}, 1", (), vr(V_ONE)),
+            Ins(f"global_atomic_add v{V_PULL}, v{V_ZERO}, v{V_ONE}, s[{S_CNT}:{S_CNT + 1}] sc0", "vmem",
+                vr(V_ZERO) + vr(V_ONE), vr(V_PULL)),
             salu(f"s_mov_b64 exec, s[{S_TMP}:{S_TMP + 1}]"),
-            Ins("Lnopull:", "label")]
+            Ins(f"Lnopull{LABEL}:", "label")]
 
 
 def drain(p_bank):
     """PV of the last half-step (its P is in bank p_bank, its V^T half in Vbuf[p_bank])."""
     pre, slots = mfma_stream(pv_ops(p_bank), p_bank, p_bank)
-    ops = pull_next_row() + rescale_block("Lnoresc_drain") + pre
+    ops = pull_next_row() + rescale_block(f"Lnoresc{LABEL}_drain") + pre
     for s in slots:
         ops += s
     ops += [nop(7), nop(7), nop(7)]
@@ -682,31 +710,32 @@ def prologue(inp):
     a(nop(1))
     a(valu(f"v_readfirstlane_b32 s{S_WAVE}, v{T + 3}", vr(T + 3), [("s", S_WAVE)], "lane"))
     a(valu(f"v_mov_b32 v{V_ZERO}, 0", (), vr(V_ZERO)))
-    # K copy pieces: piece i of this wave = rows 32*wave + 4*i .. + 3 of the half-tile; LDS slot
+    # K copy pieces: piece i of this wave = rows 16*QT*wave + 4*i .. + 3 of the half-tile; LDS slot
     # (row, c') holds global chunk c' ^ (row & 15)
     a(valu(f"v_lshrrev_b32 v{T + 4}, 4, v{T}", vr(T), vr(T + 4)))              # lane >> 4  (0..3)
     a(valu(f"v_and_b32 v{T + 5}, 15, v{T}", vr(T), vr(T + 5)))                 # lane & 15
-    a(valu(f"v_lshlrev_b32 v{T + 6}, 13, v{T + 3}", vr(T + 3), vr(T + 6)))     # wave * 8192
+    a(valu(f"v_lshlrev_b32 v{T + 6}, {11 + QT}, v{T + 3}", vr(T + 3), vr(T + 6)))     # wave * 4096 * QT
     a(valu(f"v_lshl_add_u32 v{T + 6}, v{T + 4}, 8, v{T + 6}", vr(T + 4) + vr(T + 6), vr(T + 6)))
     for i in range(4):
         a(valu(f"v_or_b32 v{T + 7}, {4 * i}, v{T + 4}", vr(T + 4), vr(T + 7)))
         a(valu(f"v_xor_b32 v{T + 7}, v{T + 7}, v{T + 5}", vr(T + 7) + vr(T + 5), vr(T + 7)))
         a(valu(f"v_lshl_add_u32 v{V_CPK + i}, v{T + 7}, 4, v{T + 6}", vr(T + 7) + vr(T + 6), vr(V_CPK + i)))
-        a(valu(f"v_add_u32 v{V_CPK + 4 + i}, 0x1000, v{V_CPK + i}", vr(V_CPK + i), vr(V_CPK + 4 + i)))
-    # V^T copy pieces: piece i = rows 64*wave + 8*i .. + 7 (128 bytes each in LDS, 256 in the
+        if QT == 2:
+            a(valu(f"v_add_u32 v{V_CPK + 4 + i}, 0x1000, v{V_CPK + i}", vr(V_CPK + i), vr(V_CPK + 4 + i)))
+    # V^T copy pieces: piece i = rows 32*QT*wave + 8*i .. + 7 (128 bytes each in LDS, 256 in the
     # image); LDS slot (row, c') holds chunk c' ^ ((row >> 1) & 7) of the row's half
     a(valu(f"v_lshrrev_b32 v{T + 5}, 3, v{T}", vr(T), vr(T + 5)))              # lane >> 3
     a(valu(f"v_and_b32 v{T + 7}, 7, v{T}", vr(T), vr(T + 7)))                  # lane & 7
-    a(valu(f"v_lshlrev_b32 v{T + 6}, 14, v{T + 3}", vr(T + 3), vr(T + 6)))     # wave * 16384
+    a(valu(f"v_lshlrev_b32 v{T + 6}, {12 + QT}, v{T + 3}", vr(T + 3), vr(T + 6)))     # wave * 8192 * QT
     a(valu(f"v_lshl_add_u32 v{T + 6}, v{T + 5}, 8, v{T + 6}", vr(T + 5) + vr(T + 6), vr(T + 6)))
     for e in range(2):
         a(valu(f"v_or_b32 v{T + 16 + e}, {4 * e}, v{T + 4}", vr(T + 4), vr(T + 16 + e)))
         a(valu(f"v_xor_b32 v{T + 16 + e}, v{T + 16 + e}, v{T + 7}", vr(T + 16 + e) + vr(T + 7), vr(T + 16 + e)))
         a(valu(f"v_lshl_add_u32 v{T + 16 + e}, v{T + 16 + e}, 4, v{T + 6}", vr(T + 16 + e) + vr(T + 6), vr(T + 16 + e)))
-    for i in range(8):
+    for i in range(PIECES):
         c = i * 2048 - (i % 4) * 1024
         a(valu(f"v_add_u32 v{V_CPV + i}, {lit(c)}, v{T + 16 + (i & 1)}", vr(T + 16 + (i & 1)), vr(V_CPV + i)))
-    a(salu(f"s_lshl_b32 s{S_MWAVE}, s{S_WAVE}, 13"))
+    a(salu(f"s_lshl_b32 s{S_MWAVE}, s{S_WAVE}, {11 + QT}"))
     a(salu(f"s_add_u32 s{S_MWAVE}, s{S_MWAVE}, s{S_LDS}"))
     for b in range(2):
         a(salu(f"s_add_u32 s{S_MK + b}, s{S_MWAVE}, {LDS_K[b]}" if LDS_K[b] else f"s_mov_b32 s{S_MK + b}, s{S_MWAVE}"))
@@ -724,7 +753,7 @@ def prologue(inp):
     a(valu(f"v_lshlrev_b32 v{T + 5}, 8, v{T + 1}", vr(T + 1), vr(T + 5)))
     a(valu(f"v_lshl_add_u32 v{T + 21}, v{T + 2}, 4, v{T + 5}", vr(T + 2) + vr(T + 5), vr(T + 21)))
     a(valu(f"v_add_u32 v{T + 22}, 0x2000, v{T + 21}", vr(T + 21), vr(T + 22)))
-    for qt in range(2):
+    for qt in range(QT):
         for ks in range(8):
             dst = SB(0, 0, 0) + 4 * (8 * qt + ks)
             a(Ins(f"buffer_load_dwordx4 {vtxt(dst, 4)}, v{T + 21 + qt}, s[{S_QRS}:{S_QRS + 3}], 0 offen offset:{ks * 32}",
@@ -743,15 +772,15 @@ def prologue(inp):
         a(valu(f"v_xor_b32 v{T + 6}, v{T + 6}, v{T + 4}", vr(T + 6) + vr(T + 4), vr(T + 6)))
         a(valu(f"v_lshl_add_u32 v{V_VOFF + S}, v{T + 6}, 4, v{T + 5}", vr(T + 6) + vr(T + 5), vr(V_VOFF + S)))
     # softmax state
-    for qt in range(2):
+    for qt in range(QT):
         a(valu(f"v_mov_b32 v{V_M + qt}, 0xff800000", (), vr(V_M + qt)))
         a(valu(f"v_mov_b32 v{V_L + qt}, 0", (), vr(V_L + qt)))
         a(valu(f"v_mov_b32 v{V_ALPHA + qt}, 1.0", (), vr(V_ALPHA + qt)))
-    for r in range(128):
+    for r in range(64 * QT):
         a(valu(f"v_accvgpr_write_b32 a{r}, 0", (), ar(r)))
     a(Ins("s_waitcnt vmcnt(0)", "wait"))
-    for i in range(64):
-        a(valu(f"v_accvgpr_write_b32 a{128 + i}, v{SB(0, 0, 0) + i}", vr(SB(0, 0, 0) + i), ar(128 + i)))
+    for i in range(32 * QT):
+        a(valu(f"v_accvgpr_write_b32 a{64 * QT + i}, v{SB(0, 0, 0) + i}", vr(SB(0, 0, 0) + i), ar(64 * QT + i)))
     a(valu(f"v_readfirstlane_b32 s{S_CK}, v{V_IDX}", vr(V_IDX), [("s", S_CK)], "lane"))
     a(salu(f"s_mov_b32 s{S_B1}, 1"))
     a(salu(f"s_mov_b32 s{S_COFF}, 8"))
@@ -783,8 +812,9 @@ def epilogue():
     a(valu(f"v_lshl_add_u32 v{T + 21}, v{T + 2}, 3, v{T + 5}", vr(T + 2) + vr(T + 5), vr(T + 21)))
     a(valu(f"v_add_u32 v{T + 22}, 0x2000, v{T + 21}", vr(T + 21), vr(T + 22)))
     a(valu(f"v_lshlrev_b32 v{T + 23}, 2, v{T + 1}", vr(T + 1), vr(T + 23)))
-    a(valu(f"v_add_u32 v{T + 24}, 128, v{T + 23}", vr(T + 23), vr(T + 24)))
-    for qt in range(2):
+    if QT == 2:
+        a(valu(f"v_add_u32 v{T + 24}, 128, v{T + 23}", vr(T + 23), vr(T + 24)))
+    for qt in range(QT):
         lt, inv = T + 16 + qt, T + 18 + qt
         a(valu(f"v_mov_b32 v{T + 20}, v{V_L + qt}", vr(V_L + qt), vr(T + 20)))
         a(valu(f"v_mov_b32 v{lt}, v{V_L + qt}", vr(V_L + qt), vr(lt)))
@@ -794,7 +824,7 @@ def epilogue():
         a(valu(f"v_add_f32 v{lt}, v{lt}, v{T + 20}", vr(lt) + vr(T + 20), vr(lt)))
         a(valu(f"v_rcp_f32 v{inv}, v{lt}", vr(lt), vr(inv), "trans"))
         a(nop(3))
-    for qt in range(2):
+    for qt in range(QT):
         inv = T + 18 + qt
         for dt in range(4):
             base = O(dt, qt)
@@ -810,15 +840,15 @@ def epilogue():
                 a(Ins(f"buffer_store_dwordx2 {vtxt(st + 2 * g4, 2)}, v{T + 21 + qt}, s[{S_KRS}:{S_KRS + 3}], 0 offen offset:{dt * 64 + g4 * 16}",
                       "vmem", vr(T + 21 + qt) + vr(st + 2 * g4, 2)))
     a(salu(f"s_cmp_eq_u64 s[{S_LSE}:{S_LSE + 1}], 0"))
-    a(salu("s_cbranch_scc1 Lnolse"))
-    for qt in range(2):
+    a(salu(f"s_cbranch_scc1 Lnolse{LABEL}"))
+    for qt in range(QT):
         lt = T + 16 + qt
         a(valu(f"v_log_f32 v{lt}, v{lt}", vr(lt), vr(lt), "trans"))
         a(nop(3))
         a(valu(f"v_add_f32 v{lt}, v{lt}, v{V_M + qt}", vr(lt) + vr(V_M + qt), vr(lt)))
         a(valu(f"v_mul_f32 v{lt}, 0x3f317218, v{lt}", vr(lt), vr(lt)))
         a(Ins(f"buffer_store_dword v{lt}, v{T + 23 + qt}, s[{S_VRS}:{S_VRS + 3}], 0 offen", "vmem", vr(T + 23 + qt) + vr(lt)))
-    a(Ins("Lnolse:", "label"))
+    a(Ins(f"Lnolse{LABEL}:", "label"))
     a(Ins("s_waitcnt vmcnt(0)", "wait"))
     return ops
 
@@ -830,20 +860,20 @@ def epilogue():
 def dump_and_exit(regs, inp):
     T = V_T
     ops = [nop(7), nop(7), nop(7),
-           valu(f"v_and_b32 v{T + 29}, 63, {inp['t']}", (), vr(T + 29)),
-           valu(f"v_lshlrev_b32 v{T + 29}, 2, v{T + 29}", vr(T + 29), vr(T + 29))]
+           valu(f"v_and_b32 v{V_ONE}, 63, {inp['t']}", (), vr(V_ONE)),
+           valu(f"v_lshlrev_b32 v{V_ONE}, 2, v{V_ONE}", vr(V_ONE), vr(V_ONE))]
     for kind, r in regs:
         if kind == "a":
-            ops.append(valu(f"v_accvgpr_read_b32 v{T + 28}, a{r}", ar(r), vr(T + 28)))
+            ops.append(valu(f"v_accvgpr_read_b32 v{V_PULL}, a{r}", ar(r), vr(V_PULL)))
             ops.append(nop(1))
-            src = T + 28
+            src = V_PULL
         else:
             src = r
-        ops.append(Ins(f"global_store_dword v{T + 29}, v{src}, s[{S_LSE}:{S_LSE + 1}]", "vmem", vr(T + 29) + vr(src)))
+        ops.append(Ins(f"global_store_dword v{V_ONE}, v{src}, s[{S_LSE}:{S_LSE + 1}]", "vmem", vr(V_ONE) + vr(src)))
         ops.append(salu(f"s_add_u32 s{S_LSE}, s{S_LSE}, 512"))
         ops.append(salu(f"s_addc_u32 s{S_LSE + 1}, s{S_LSE + 1}, 0"))
         ops.append(Ins("s_waitcnt vmcnt(0)", "wait"))
-    ops.append(salu("s_branch Lrow_done"))
+    ops.append(salu(f"s_branch Lrow_done{LABEL}"))
     return ops
 
 
@@ -881,25 +911,25 @@ def row_program(inp, sequential=False):
         ops += dump_and_exit([("v", 64 + i) for i in range(128)] +
                              [("v", V_M), ("v", V_M + 1), ("v", V_L), ("v", V_L + 1), ("v", V_ALPHA), ("v", V_ALPHA + 1)], inp)
     a(salu(f"s_cmp_eq_u32 s{S_N}, 1"))
-    a(salu("s_cbranch_scc1 Lodd_last"))
+    a(salu(f"s_cbranch_scc1 Lodd_last{LABEL}"))
     ops += iteration(1, 1, True, True, True, "o0", sequential)
-    a(Ins("Lloop:", "label"))
+    a(Ins(f"Lloop{LABEL}:", "label"))
     # here S_B1 = (block index b of the coming even iteration) + 1
     a(salu(f"s_cmp_eq_u32 s{S_B1}, s{S_N}"))
-    a(salu("s_cbranch_scc1 Leven_last"))
+    a(salu(f"s_cbranch_scc1 Leven_last{LABEL}"))
     ops += iteration(0, 0, True, True, True, "eL", sequential)
     ops += iteration(1, 1, True, True, True, "oL", sequential)
-    a(salu("s_branch Lloop"))
-    a(Ins("Leven_last:", "label"))
+    a(salu(f"s_branch Lloop{LABEL}"))
+    a(Ins(f"Leven_last{LABEL}:", "label"))
     ops += iteration(0, 0, True, True, True, "eZ", sequential)
-    a(Ins("Lodd_last:", "label"))
+    a(Ins(f"Lodd_last{LABEL}:", "label"))
     ops += iteration(1, 1, True, False, True, "oZ", sequential)
     ops += drain(1)
     if DUMP == "O":
         ops += dump_and_exit([("a", i) for i in range(128)] +
                              [("v", V_M), ("v", V_M + 1), ("v", V_L), ("v", V_L + 1)], inp)
     ops += epilogue()
-    a(Ins("Lrow_done:", "label"))
+    a(Ins(f"Lrow_done{LABEL}:", "label"))
     return ops
 
 
@@ -1035,14 +1065,17 @@ def emit(path, sequential=False):
     INP.update(inp)
     ops = fix_hazards(row_program(inp, sequential))
     # the queue position pulled for the next row (valid in lane 0 of wave 0)
-    ops.append(valu(f"v_mov_b32 %0, v{V_T + 28}", vr(V_T + 28), ()))
+    ops.append(valu(f"v_mov_b32 %0, v{V_PULL}", vr(V_PULL), ()))
     problems = all_hazards(ops)
     if problems:
         for p in problems[:20]:
             print("hazard:", p, file=sys.stderr)
         raise SystemExit(f"{len(problems)} hazard(s) in the generated schedule")
-    clob_v = [f"v{i}" for i in range(32, 256)]
-    clob_a = [f"a{i}" for i in range(0, 256)]
+    clob_v = [f"v{i}" for i in range(V_FIRST, V_LAST + 1)]
+    if QT == 1:             # registers that one query tile leaves untouched stay with the compiler
+        used = {r for ins in ops for kind, r in ins.rd | ins.wr if kind == "v"}
+        clob_v = [f"v{i}" for i in range(V_FIRST, V_LAST + 1) if i in used]
+    clob_a = [f"a{i}" for i in range(0, 256 if QT == 2 else 96)]
     clob_s = [f"s{i}" for i in range(40, 96)]
     with open(path, "w") as f:
         f.write("// generated by gen_attn_w64.py -- do not edit\n")
@@ -1062,4 +1095,7 @@ def emit(path, sequential=False):
 if __name__ == "__main__":
     out = sys.argv[1] if len(sys.argv) > 1 else os.path.join(os.path.dirname(os.path.abspath(__file__)),
                                                               "prism_attn_w64_body.inc")
-    emit(out, sequential="--sequential" in sys.argv)
+    for qt in (2, 1):
+        configure(qt)
+        name = os.path.basename(out) if qt == 2 else os.path.basename(out).replace("w64", "w32")
+        emit(os.path.join(os.path.dirname(out), name), sequential="--sequential" in sys.argv)

@@ -753,16 +753,19 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 }
 
 // =====================================================================================
-// The same computation with 64 queries per wave (B = 128, d = 128, clean lists): workgroup =
-// 2 waves = one (q-head, q-block) row, one wave per SIMD, two workgroups per CU.  Every K / V^T
+// The same computation with kQ = 64 queries per wave (B = 128, d = 128, clean lists): workgroup =
+// 2 waves = one (q-head, q-block) row, one wave per SIMD, two workgroups per CU; or with kQ = 32: 4 waves of
+// 256 registers a lane, still two workgroups per CU, which take a listed block in 1.3 instead of 2.2 us when a row is
+// alone on its CU (the dispatch says which calls want that).  With kQ = 64 every K / V^T
 // fragment read from LDS feeds two MFMAs, K and V^T travel as 64-key half tiles through two LDS
 // buffers each, and the row loop (software-pipelined over half-steps, softmax in the shadow of the
 // neighbouring half-steps' MFMAs, accumulators and Q fragments in AGPRs) is a generated,
-// hand-scheduled instruction sequence: prism_attn_w64_body.inc, written by gen_attn_w64.py, which
+// hand-scheduled instruction sequence: prism_attn_w64_body.inc (and _w32_), written by gen_attn_w64.py, which
 // also documents the register map and the pipeline.  This function supplies the persistent-workgroup
 // loop around it: the same per-XCD queues as the general kernel.
 // =====================================================================================
-__global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
+template <int kQ>
+__global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w64_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
     const int32_t* __restrict__ col_idx, const int4* __restrict__ items, int32_t* __restrict__ plan,
     PullCounters pulls, DirtyFlags flags, uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv,
@@ -770,7 +773,7 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) char lds_tiles[65536];
   __shared__ int s_pulled, s_queue;
-  if (call_is_dirty<128>(flags, s_pulled)) return;          // the general kernel takes this call
+  if (call_is_dirty<128 / kQ * 64>(flags, s_pulled)) return;          // the general kernel takes this call
 
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -795,13 +798,15 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
       // counter only grows, so a queue seen exhausted stays so; the atomic decides who gets a row.
       __syncthreads();
       if (wave == 0) {
-        if (lane == 0 && pulls.first_dealt) plan[kPlanCounter + my_queue] = seg_len + 1;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                        // addresses formed here, not kept across the row loop
+        if (ln == 0 && pulls.first_dealt) plan[kPlanCounter + my_queue] = seg_len + 1;
         int found_pos = -1, found_queue = -1;
         for (;;) {
           int taken = 0x7fffffff, len = 0;
-          if (lane < n_queues) {
-            taken = __hip_atomic_load(counter + lane * pulls.stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            len = plan[kPlanLen + lane];
+          if (ln < n_queues) {
+            taken = __hip_atomic_load(counter + ln * pulls.stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            len = plan[kPlanLen + ln];
           }
           const unsigned long long open = __ballot(taken < len);
           if (open == 0ull) break;
@@ -811,7 +816,7 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
             if ((open >> x) & 1ull) pick = x;
           }
           int got = 0;
-          if (lane == 0) got = atomicAdd(counter + pick * pulls.stride, 1);
+          if (ln == 0) got = atomicAdd(counter + pick * pulls.stride, 1);
           got = __builtin_amdgcn_readfirstlane(got);
           if (got < plan[kPlanLen + pick]) {
             found_pos = got;
@@ -849,15 +854,15 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     // the start of its last PV phase) and looked at after it: pulling at the start of a row would
     // reserve a row that its neighbours in the queue have long passed by the time it is started.
 
-    const int q0 = u * 128 + wave * 64;                                          // this wave's first query
+    const int q0 = u * 128 + wave * kQ;                                          // this wave's first query
     const size_t tok0 = (size_t)seqs.s[sq].tok0 + q0;                            // its token in the tensors
     const size_t row0 = (size_t)hq * hs.q + tok0 * kHeadDim;                     // its element offset in Q / O
     // rows of this wave that exist (a ragged last block may end in front of or inside the wave's 64)
     const int rows_left = L - q0;
-    const int rows_here = __builtin_amdgcn_readfirstlane(rows_left < 0 ? 0 : (rows_left > 64 ? 64 : rows_left));
+    const int rows_here = __builtin_amdgcn_readfirstlane(rows_left < 0 ? 0 : (rows_left > kQ ? kQ : rows_left));
     if (it >= end) {
       // a row without entries: o = 0, lse = -inf
-      const int r = lane;                                   // 64 rows per wave, one per lane
+      const int r = lane;                                   // one row per lane
       if (r < rows_here) {
         uint16_t* op = out + row0 + (size_t)r * kHeadDim;
 #pragma unroll
@@ -879,7 +884,11 @@ __global__ __launch_bounds__(128) void sparse_attn_w64_kernel(
     // the one block of the row that has hidden keys: the diagonal, or a ragged last block
     const int mask_block = causal ? u : ragged_block;
     int pulled_next;
+    if constexpr (kQ == 64) {
 #include "prism_attn_w64_body.inc"
+    } else {
+#include "prism_attn_w32_body.inc"
+    }
     if (t == 0) pulled = pulled_next;
   }
 #endif
@@ -1472,10 +1481,11 @@ static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p)
 // Does the 64-queries-per-wave kernel take this call?  Decided by the shape and the size of the buffer, in
 // the same way when the V image is written and when it is read.
 // A ragged length takes it too (20 011 tokens, 32 / 8 heads: 704 -> 646 us per layer; 19 290 tokens, 16 heads,
-// bidirectional: 695 -> 640 us against the general kernel), except in calls of so few rows that the list check
-// and the second attention launch cost more than it saves (a batch of eight prompts, five of them ragged with
-// 32 to 1280 rows: 1403 -> 1422 us).
-constexpr int kRaggedW64MinRows = 2048;
+// bidirectional: 695 -> 640 us against the general kernel), except in calls of so few rows that the general
+// kernel queued behind it costs more than it saves (attention alone, general -> here: 28 to 93 rows of one head
+// 20.1 -> 22.0 and 22.9 -> 25.5 us, 84 rows 20.3 -> 22.5, 160 rows 38.2 -> 38.5, 232 rows 45.7 -> 41.4,
+// 256 rows 33.4 -> 30.4, 880 rows 135 -> 107).
+constexpr int kRaggedW64MinRows = 160;
 static bool w64_call(const prism_params* p, size_t bytes) {
   if (!w64_shape(p) || bytes < attn_ws(p).total) return false;
   return p->seq_len % 128 == 0 || p->n_q_heads * n_blocks(p) >= kRaggedW64MinRows;
@@ -1749,9 +1759,21 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     else PRISM_PAIR(256);
 #undef PRISM_PAIR
   }
-  if (w64)
-    hipLaunchKernelGGL(sparse_attn_w64_kernel, dim3(grid), dim3(128), 0, st, qp, kp, vp16, col_idx, items, plan, pulls, flags,
-                       op, lse, h, h_kv, seqs, hs, causal);
+  if (w64) {
+    // The same bits from two waves of 64 queries or from four of 32.  Four take 1.3 instead of 2.2 us per block of a
+    // row that has a CU to itself, two need half the LDS reads per block and are 3 % faster where every CU is busy
+    // to the end (2048 rows of 64 blocks: 543 against 558 us).  Up to kW32MaxRows rows, 8 per resident workgroup, the
+    // longest rows decide how long a call takes (us, two waves -> four): 8 heads, 8K tokens (512 rows) 95 -> 70;
+    // 32 heads, 8K (2048) 183 -> 147; 4 heads, 128K (4096) 1204 -> 1018; 32 heads, 16K (4096) 404 -> 409; beyond it the
+    // two are even (20011 tokens, 5024 rows: 516 and 514) and then two waves win (32K, 8192 rows: 1120 and 1126).
+    constexpr int kW32MaxRows = 4096;
+    if (R <= kW32MaxRows)
+      hipLaunchKernelGGL(sparse_attn_w64_kernel<32>, dim3(grid), dim3(256), 0, st, qp, kp, vp16, col_idx, items, plan,
+                         pulls, flags, op, lse, h, h_kv, seqs, hs, causal);
+    else
+      hipLaunchKernelGGL(sparse_attn_w64_kernel<64>, dim3(grid), dim3(128), 0, st, qp, kp, vp16, col_idx, items, plan,
+                         pulls, flags, op, lse, h, h_kv, seqs, hs, causal);
+  }
 #define PRISM_ATTN(BLK, SO, D)                                                                                \
   launch_attn<BLK, SO, D>(grid, st, pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
                           hs, causal, only_dirty)

@@ -1,4 +1,4 @@
-"""Ragged last blocks at B = 128, d = 128 on the 64-queries-per-wave kernel: tails of one token, around the 64
+"""Ragged last blocks at B = 128, d = 128 on the hand-scheduled kernel: tails of one token, around the 32 or 64
 queries of a wave and one short of a block; causal and bidirectional; nothing written past the last row."""
 import numpy as np
 import pytest
@@ -16,12 +16,14 @@ pytestmark = pytest.mark.gpu
 OUT_TOL, LSE_TOL = 2e-2, 2e-3
 
 
-@pytest.mark.parametrize("small_workspace", [False, True])
-@pytest.mark.parametrize("tail,bidir", [(1, False), (63, False), (64, True), (65, False), (65, True), (127, True), (1, True)])
-def test_ragged_last_block(tail, bidir, small_workspace):
-    h, hkv, B, N = 64, 2, 128, 33
+# 64 heads x 33 blocks: four waves of 32 queries (a wave of the last block may start past the end); 128 heads: two of 64
+@pytest.mark.parametrize("h,small_workspace", [(64, False), (64, True), (128, False)])
+@pytest.mark.parametrize("tail,bidir", [(1, False), (32, True), (63, False), (64, True), (65, False), (65, True), (97, False),
+                                        (127, True), (1, True)])
+def test_ragged_last_block(tail, bidir, h, small_workspace):
+    hkv, B, N = 2, 128, 33
     L = (N - 1) * B + tail
-    print(f"case L={L} bidirectional={bidir} small workspace={small_workspace}", flush=True)
+    print(f"case h={h} L={L} bidirectional={bidir} small workspace={small_workspace}", flush=True)
     rng = np.random.default_rng(100 + tail + bidir)
     Qb, Kb, Vb = (wl.f32_to_bf16_bits(rng.standard_normal((n, L, 128)).astype(np.float32) * a)
                   for n, a in ((h, 1.5), (hkv, 1.5), (hkv, 1.0)))
@@ -48,15 +50,15 @@ def test_ragged_last_block(tail, bidir, small_workspace):
     assert (out_g[h * L * 128:] == 7.0).all() and (lse_g[h * L:] == 7.0).all()
     o, s = out.float().cpu().numpy(), lse.cpu().numpy()
     Q, K, V = (orc.bf16_to_f64(x) for x in (Qb, Kb, Vb))
-    for i in (0, 1, 2, 31, 63):
+    for i in (0, 1, 2, 31, h - 1):
         seen = mask[i].repeat(B, 0).repeat(B, 1)[:L, :L]
         if not bidir:
             seen = np.tril(seen)
-        x = np.where(seen, Q[i] @ K[i // 32].T / np.sqrt(128.0), -np.inf)
+        x = np.where(seen, Q[i] @ K[i // (h // 2)].T / np.sqrt(128.0), -np.inf)
         m = x.max(1, keepdims=True)
         e = np.exp(x - np.where(np.isfinite(m), m, 0.0))
         t = e.sum(1)
-        ref = np.where(t[:, None] > 0, e @ V[i // 32] / np.where(t > 0, t, 1.0)[:, None], 0.0)
+        ref = np.where(t[:, None] > 0, e @ V[i // (h // 2)] / np.where(t > 0, t, 1.0)[:, None], 0.0)
         assert np.abs(o[i] - ref).max() <= OUT_TOL
         live = t > 0
         assert np.abs(s[i][live] - (m[live, 0] + np.log(t[live]))).max() <= LSE_TOL
