@@ -127,8 +127,8 @@ __device__ __forceinline__ bool call_is_dirty(const DirtyFlags& f, int& shared_w
 //     online softmax | wait V(j) | barrier | O^T += V^T P^T | wait K(j+1) | barrier
 // and two buffers per tile (AttnCfg::kDouble):
 //     K(j), V(j) in LDS | start K(j+1), V(j+1) copies | S^T | softmax | O^T += V^T P^T | wait both | barrier
-// (one barrier instead of three and no tile latency inside a step; us per layer, one buffer -> two: 12345 tokens,
-// d = 64 248 -> 241; 16K, d = 256, B = 64 801 -> 780; 32K, d = 128, B = 64 in pairs 1791 -> 1730).
+// (one barrier instead of three and no tile latency inside a step; us per layer, one buffer -> two: 16K, d = 256,
+// B = 64 801 -> 780; 32K, d = 128, B = 64 in pairs 1791 -> 1730; 12345 tokens, d = 64 254 -> 252, the mean of five inputs).
 // The workgroups are persistent: a workgroup pulls its next row from its XCD's queue at the top
 // of the last step of the current row and reads that row's queue entry during the last PV, so
 // a row switch exposes only the load of the Q rows and of the first K tile.

@@ -307,6 +307,34 @@ __global__ __launch_bounds__(64) void scale_kernel(const float* __restrict__ ene
   }
 }
 
+// The same 1/scale_z for one band, by one wave that every lane asks: the sums in scale_kernel's order (lane-strided,
+// then across the lanes), the roots side by side in four lanes.
+__device__ __forceinline__ float band_inv_scale(const float* __restrict__ energy, int hq, int kvh, int N, int z,
+                                                int dz, int head_dim, int calibrate, int lane) {
+  if (dz <= 0) return 0.f;
+  double scale = sqrt((double)dz);
+  if (calibrate) {
+    double e[4] = {0, 0, 0, 0};                       // q: all dims, band; k: all dims, band
+#pragma unroll 4
+    for (int i = lane; i < N; i += 64) {
+      const float4 a = *reinterpret_cast<const float4*>(energy + ((size_t)hq * N + i) * 4);
+      const float4 b = *reinterpret_cast<const float4*>(energy + ((size_t)kvh * N + i) * 4);
+      e[0] += (double)a.x;
+      e[1] += (double)(z == 0 ? a.y : a.z);
+      e[2] += (double)b.x;
+      e[3] += (double)(z == 0 ? b.y : b.z);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = wave_sum(e[i]);
+    const double d = head_dim;
+    const double mine = (lane & 3) == 0 ? e[0] : ((lane & 3) == 1 ? e[1] : ((lane & 3) == 2 ? e[2] : e[3]));
+    const double rms = sqrt(mine / (N * ((lane & 1) ? (double)dz : d)));
+    const double rq = __shfl(rms, 0, 64), rqz = __shfl(rms, 1, 64), rk = __shfl(rms, 2, 64), rkz = __shfl(rms, 3, 64);
+    scale *= sqrt(dz / d) * (rqz / rq) * (rkz / rk);
+  }
+  return isfinite(scale) && scale > 0.0 ? (float)(1.0 / scale) : 0.f;
+}
+
 // =====================================================================================
 // Dual-band scoring, softmax, top-p, union (Sec. 3.4 steps 4-5, App. C).
 //
@@ -796,8 +824,199 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
 }
 
 // =====================================================================================
+// The same selection for calls of few strips, whose time is the length of one workgroup's chain: sixteen waves per
+// strip, eight per band, so that the two bands run side by side and a wave owns two rows instead of four; the
+// calibration is done here as well instead of in a launch of its own, and the row counts go to `counts`.
+// N <= 512 (two logit strips of 33 KB).  Logits and masks have the bits of select_kernel: a tile's MFMAs and a row's
+// sums keep their order.  Whole estimate, five launches around
+// select_kernel -> three around this one: 1 head, 2K tokens at B = 64 (2 strips) 29.4 -> 17.7 us; 8 heads, 8K 32.2 -> 20.7;
+// 32 heads, 8K (128 strips) 46.5 -> 32.5, 20011 tokens (320 strips) 79.4 -> 69.8; 16 heads, 19290 tokens,
+// bidirectional 71.8 -> 54.9.  At 512 strips and more (32K tokens) its strips no longer run all at once and the four-wave
+// form wins (107 against 113 us; at 896 strips 174 against 209).
+// =====================================================================================
+constexpr int kSmallBlocks = 512;
+template <int kSeqs>
+__global__ __launch_bounds__(1024) void select_small_kernel(
+    BandVectors bv, const float* __restrict__ energy, int h, int h_kv, SeqTableOf<kSeqs> seqs, int bs, int head_dim,
+    int dz_high, int dz_low, int dpad_high, int dpad_low, int calibrate, float top_p, int select_flags,
+    uint64_t* __restrict__ mask_bits, int32_t* __restrict__ counts) {
+  extern __shared__ float lds_logits[];
+  __shared__ uint64_t lds_bits[2][kStripRows][kSmallBlocks / 64];
+  int sq = 0;
+  if (kSeqs > 1)
+    while (sq + 1 < seqs.n && (int)blockIdx.x >= seqs.s[sq + 1].tile0) ++sq;
+  const int N = seqs.s[sq].N;
+  const int strip = ((N + 15) >> 4) - 1 - ((int)blockIdx.x - seqs.s[sq].tile0), hq = blockIdx.y;
+  mask_bits += seqs.s[sq].mask0;
+  counts += (size_t)h * seqs.s[sq].blk0;
+  energy += (size_t)(h + h_kv) * seqs.s[sq].blk0 * 4;
+  const size_t q0 = (size_t)h * seqs.s[sq].blk0 * bs, kv0 = kv_band_base(h, h_kv, seqs.nsum, seqs.s[sq].tile0, bs);
+  const int kvh = hq / (h / h_kv);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int z = wave >> 3, w8 = wave & 7;              // band, wave of the band
+  const int u0 = strip * kStripRows;
+  const bool causal = (select_flags & kSelCausal) != 0;
+  const int ncols = causal ? min(N, u0 + kStripRows) : N;
+  const int ntiles = (ncols + 15) >> 4;
+  const int ld = ntiles * 16 + 4;
+  const int W = (N + 63) >> 6;
+  float* const strip_lds = lds_logits + (size_t)z * kStripRows * ld;
+  for (int i = threadIdx.x; i < 2 * kStripRows * (kSmallBlocks / 64); i += 1024) (&lds_bits[0][0][0])[i] = 0ull;
+
+  const int dpad = z == 0 ? dpad_high : dpad_low;
+  if (dpad != 0) {                                     // uniform per wave
+    const int ksteps = dpad >> 5;
+    const uint16_t* __restrict__ pooled_hi = bv.v[z][0];
+    const uint16_t* __restrict__ pooled_mid = bv.v[z][1];
+    const uint16_t* __restrict__ pooled_lo = bv.v[z][2];
+    const float inv = band_inv_scale(energy, hq, h + kvh, N, z, z == 0 ? dz_high : dz_low, head_dim, calibrate, lane);
+    const int arow = min(u0 + (lane & 15), N - 1);
+#pragma unroll 1
+    for (int k0 = 0; k0 < ksteps; k0 += 4) {           // four k-steps per pass, as in select_kernel
+      const int kn = min(4, ksteps - k0);
+      const size_t aoff = q0 + ((size_t)hq * N + arow) * bs + k0 * 32 + (lane >> 4) * 8;
+      const size_t tile0 = kv_band_offset(kv0, N, bs, kvh, 0, 0) + k0 * 512 + lane * 8;
+#pragma unroll 1
+      for (int ct = w8; ct < ntiles; ct += 8) {
+        const size_t boff = tile0 + (size_t)ct * 16 * bs;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        auto kstep = [&](int ks) __attribute__((always_inline)) {
+          const bf16x8 ah = *reinterpret_cast<const bf16x8*>(pooled_hi + aoff + ks * 32);
+          const bf16x8 am = *reinterpret_cast<const bf16x8*>(pooled_mid + aoff + ks * 32);
+          const bf16x8 al = *reinterpret_cast<const bf16x8*>(pooled_lo + aoff + ks * 32);
+          const bf16x8 ch = *reinterpret_cast<const bf16x8*>(pooled_hi + boff + ks * 512);
+          const bf16x8 cm = *reinterpret_cast<const bf16x8*>(pooled_mid + boff + ks * 512);
+          const bf16x8 cl = *reinterpret_cast<const bf16x8*>(pooled_lo + boff + ks * 512);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, ch, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, cl, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, cm, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, ch, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, cm, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, ch, acc, 0, 0, 0);
+        };
+        switch (kn) {                                  // uniform
+          case 1: kstep(0); break;
+          case 2: kstep(0); kstep(1); break;
+          case 3: kstep(0); kstep(1); kstep(2); break;
+          default: kstep(0); kstep(1); kstep(2); kstep(3); break;
+        }
+        const int col = ct * 16 + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = (lane >> 4) * 4 + r;
+          float lg = acc[r] * inv;
+          if (k0 > 0) lg += strip_lds[row * ld + col];
+          strip_lds[row * ld + col] = lg;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (dpad != 0) {
+    const int r0 = w8 * 2;
+    const int nrows = min(2, N - (u0 + r0));             // uniform per wave, may be <= 0
+    if (nrows > 0) {
+      const int n0 = causal ? u0 + r0 + 1 : N;
+      const int nstep = causal ? 1 : 0;
+      const int nmax = n0 + (nrows - 1) * nstep;
+      const float* lg = strip_lds + r0 * ld;
+      uint64_t* bits = &lds_bits[z][r0][0];
+      constexpr int bld = kSmallBlocks / 64;
+      if (nmax <= 128) select_rows<2, 2>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
+      else if (nmax <= 256) select_rows<4, 2>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
+      else select_rows<8, 2>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
+    }
+  }
+  __syncthreads();
+  const int u = u0 + wave;                               // one row per wave
+  if (u < N) {
+    const size_t row = (size_t)hq * N + u;
+    uint64_t word = lane < W ? lds_bits[0][wave][lane] | lds_bits[1][wave][lane] : 0ull;
+    if ((select_flags & kSelForceDiagonal) && lane == (u >> 6)) word |= 1ull << (u & 63);
+    if ((select_flags & kSelForceSink) && lane == 0) word |= 1ull;
+    const int cnt = wave_sum((int)__popcll(word));
+    if (lane < W) mask_bits[row * W + lane] = word;
+    if (lane == 0) counts[row] = cnt;
+  }
+}
+
+// =====================================================================================
 // Bit rows -> CSR
 // =====================================================================================
+// Row offsets and column lists in one launch from row counts that lie apart from row_ptr: a workgroup takes 16 rows,
+// adds up all counts in front of them (from the L2, 10 KB on average at the 5120 rows that calls of this form have at
+// most), scans its own and writes their columns, four rows per wave.  For more rows the sums cost more than the launch
+// they save: at 8192 rows 114 instead of 106 us for the whole estimate, at 32768 486 instead of 462 (64 rows per
+// workgroup), so scan_kernel and fill_kernel stay there.
+constexpr int kCompactRows = 16;
+template <int kSeqs>
+__global__ __launch_bounds__(256) void compact_kernel(const uint64_t* __restrict__ mask_bits,
+                                                      const int32_t* __restrict__ counts, int h,
+                                                      SeqTableOf<kSeqs> seqs, int32_t* __restrict__ row_ptr,
+                                                      int32_t* __restrict__ col_idx, int32_t* __restrict__ info) {
+  __shared__ int s_before[4], s_base[kCompactRows];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  int sq = 0, wg = blockIdx.x;
+  if (kSeqs > 1) {
+    while (sq + 1 < seqs.n) {
+      const int n = (h * seqs.s[sq].N + kCompactRows - 1) / kCompactRows;
+      if (wg < n) break;
+      wg -= n;
+      ++sq;
+    }
+  }
+  const int N = seqs.s[sq].N, R = h * N, W = (N + 63) >> 6;
+  const int64_t capacity = seqs.s[sq].cap;
+  mask_bits += seqs.s[sq].mask0;
+  counts += (size_t)h * seqs.s[sq].blk0;
+  row_ptr += seqs.s[sq].row0;
+  col_idx += seqs.s[sq].col0;
+  const int r0 = wg * kCompactRows;
+  int part = 0;
+  // this wave's rows, requested before the sums
+  uint64_t words[kCompactRows / 4];
+#pragma unroll
+  for (int j = 0; j < kCompactRows / 4; ++j) {
+    const int r = r0 + wave * (kCompactRows / 4) + j;
+    words[j] = r < R && lane < W ? mask_bits[(size_t)r * W + lane] : 0ull;
+  }
+#pragma unroll 8
+  for (int i = t; i < r0; i += 256) part += counts[i];
+  part = wave_sum(part);
+  if (lane == 0) s_before[wave] = part;
+  __syncthreads();
+  if (wave == 0) {
+    const bool own = lane < kCompactRows && r0 + lane < R;
+    const int mine = own ? counts[r0 + lane] : 0;
+    const int incl = wave_scan_inclusive(mine) + s_before[0] + s_before[1] + s_before[2] + s_before[3];
+    if (lane < kCompactRows) s_base[lane] = incl - mine;
+    if (own) row_ptr[r0 + lane + 1] = incl;
+    if (lane == 0 && r0 == 0) row_ptr[0] = 0;
+    if (own && r0 + lane == R - 1) {
+      int32_t* out = info + 4 * (size_t)seqs.s[sq].index;
+      out[0] = incl;
+      out[1] = (int64_t)incl > capacity ? 1 : 0;
+      out[2] = 0;
+      out[3] = 0;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kCompactRows / 4; ++j) {           // rows past the end have no bits
+    int64_t base = s_base[wave * (kCompactRows / 4) + j];
+    const int lo = (int)(uint32_t)words[j], hi = (int)(uint32_t)(words[j] >> 32);
+    for (int i = 0; i < W; ++i) {
+      const uint64_t word = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32) |
+                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i);
+      if (word == 0ull) continue;                      // uniform
+      const int rank = __popcll(word & ((1ull << lane) - 1ull));
+      if (((word >> lane) & 1ull) && base + rank < capacity) col_idx[base + rank] = i * 64 + lane;
+      base += __popcll(word);
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void row_count_kernel(const uint64_t* __restrict__ mask_bits,
                                                         int R, int W, int32_t* __restrict__ row_ptr) {
   const int r = blockIdx.x * 256 + threadIdx.x;
@@ -1026,7 +1245,8 @@ static int make_band_map(const prism_params* p, const prism_bands* bands, BandMa
 
 // ---- workspace layout ------------------------------------------------------------
 struct EstimateWs {
-  size_t band[2][3], energy, inv_scale, total;
+  size_t band[2][3], energy, inv_scale, counts, total;
+  size_t least;      // without the row counts: a buffer of this size runs the separate scan and fill kernels
 };
 // The layout for n sequences of together `blocks` blocks and `tiles` tiles of 16 blocks.
 static EstimateWs estimate_layout(const prism_params* p, size_t n, size_t blocks, size_t tiles) {
@@ -1042,6 +1262,8 @@ static EstimateWs estimate_layout(const prism_params* p, size_t n, size_t blocks
     }
   w.energy = off;    off = align_up(off + heads * blocks * 4 * sizeof(float), 256);
   w.inv_scale = off; off = align_up(off + n * p->n_q_heads * 2 * sizeof(float), 256);
+  w.least = off;
+  w.counts = off;    off = align_up(off + (size_t)p->n_q_heads * blocks * sizeof(int32_t), 256);
   w.total = off;
   return w;
 }
@@ -1074,7 +1296,7 @@ static int run_pool_and_scale(const prism_params* p, const HeadStrides& hs, cons
                               const BandMap& map, const void* q,
                               const void* k, char* ws, const EstimateWs& L, float* pooled_q, float* pooled_k,
                               float* scales, hipStream_t st, const RopeArgs* rope = nullptr,
-                              void* q_out = nullptr, void* k_out = nullptr) {
+                              void* q_out = nullptr, void* k_out = nullptr, bool with_scale = true) {
   const BandVectors bv = band_vectors(ws, L);
   float* energy = reinterpret_cast<float*>(ws + L.energy);
   float* inv = reinterpret_cast<float*>(ws + L.inv_scale);
@@ -1100,6 +1322,7 @@ static int run_pool_and_scale(const prism_params* p, const HeadStrides& hs, cons
     else PRISM_POOL(64, 256);
   }
 #undef PRISM_POOL
+  if (!with_scale) return launch_status();
   const int calibrate = (p->flags & PRISM_FLAG_NO_CALIBRATION) ? 0 : 1;
   if (seqs.n == 1)
     hipLaunchKernelGGL(scale_kernel<1>, dim3(p->n_q_heads), dim3(64), 0, st, energy, p->n_q_heads, p->n_kv_heads,
@@ -1110,35 +1333,46 @@ static int run_pool_and_scale(const prism_params* p, const HeadStrides& hs, cons
   return launch_status();
 }
 
+// More than 64 KB of dynamic LDS has to be allowed once per kernel and device: what the largest call needs is asked
+// for on the first such call of a kernel on a device.
+struct LdsGrant {
+  std::mutex mu;
+  bool raised[kMaxDevices] = {};
+  int ask(const void* kernel, size_t bytes) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return PRISM_ERR_HIP;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!raised[dev]) {
+      if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+        return PRISM_ERR_HIP;
+      raised[dev] = true;
+    }
+    return PRISM_OK;
+  }
+};
+
+static int select_flags_of(const prism_params* p) {
+  int f = 0;
+  if (!(p->flags & PRISM_FLAG_BIDIRECTIONAL)) f |= kSelCausal;
+  if (p->flags & PRISM_FLAG_FORCE_DIAGONAL) f |= kSelForceDiagonal;
+  if (p->flags & PRISM_FLAG_FORCE_SINK) f |= kSelForceSink;
+  return f;
+}
+
 template <int MAXCH, bool DUMP, int kRowsPerWave, int kSeqs>
 static int launch_select_on(const prism_params* p, const SeqTableOf<kSeqs>& seqs, const BandMap& map, char* ws,
                          const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, float* lh, float* ll, hipStream_t st) {
   const size_t lds = (size_t)kStripRows * (((seqs.nmax + 15) / 16) * 16 + 4) * sizeof(float);
   auto kern = select_kernel<MAXCH, DUMP, kRowsPerWave, kSeqs>;
   if (lds > 64 * 1024) {
-    // more than 64 KB of dynamic LDS has to be allowed once per kernel and device: what the
-    // largest N needs is asked for on the first such call of this instantiation on a device
-    static std::mutex mu;
-    static bool raised[kMaxDevices];
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return PRISM_ERR_HIP;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!raised[dev]) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)(kStripRows * (kMaxBlocks + 4) * sizeof(float))) != hipSuccess)
-        return PRISM_ERR_HIP;
-      raised[dev] = true;
-    }
+    static LdsGrant grant;
+    const int rc = grant.ask(reinterpret_cast<const void*>(kern), kStripRows * (kMaxBlocks + 4) * sizeof(float));
+    if (rc != PRISM_OK) return rc;
   }
-  int select_flags = 0;
-  if (!(p->flags & PRISM_FLAG_BIDIRECTIONAL)) select_flags |= kSelCausal;
-  if (p->flags & PRISM_FLAG_FORCE_DIAGONAL) select_flags |= kSelForceDiagonal;
-  if (p->flags & PRISM_FLAG_FORCE_SINK) select_flags |= kSelForceSink;
   hipLaunchKernelGGL(kern, dim3(seqs.tiles, p->n_q_heads), dim3(kStripRows / kRowsPerWave * 64), lds, st,
                      band_vectors(ws, L),
                      reinterpret_cast<const float*>(ws + L.inv_scale), p->n_q_heads, p->n_kv_heads, seqs,
-                     band_stride(p->head_dim), map.dpad[0], map.dpad[1], p->top_p, select_flags, mask_bits, row_ptr, lh, ll);
+                     band_stride(p->head_dim), map.dpad[0], map.dpad[1], p->top_p, select_flags_of(p), mask_bits, row_ptr, lh, ll);
   return launch_status();
 }
 
@@ -1149,6 +1383,20 @@ static int launch_select(const prism_params* p, const SeqTable& seqs, const Band
   if (DUMP || seqs.n == 1)
     return launch_select_on<MAXCH, DUMP, kRowsPerWave, 1>(p, only_sequence(seqs), map, ws, L, mask_bits, row_ptr, lh, ll, st);
   return launch_select_on<MAXCH, false, kRowsPerWave, kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, row_ptr, lh, ll, st);
+}
+
+static int run_compact(const prism_params* p, const SeqTable& seqs, const uint64_t* mask_bits, const int32_t* counts,
+                       int32_t* row_ptr, int32_t* col_idx, int32_t* info, hipStream_t st) {
+  const int h = p->n_q_heads;
+  int grid = 0;
+  for (int i = 0; i < seqs.n; ++i) grid += (h * seqs.s[i].N + kCompactRows - 1) / kCompactRows;
+  if (seqs.n == 1)
+    hipLaunchKernelGGL(compact_kernel<1>, dim3(grid), dim3(256), 0, st, mask_bits, counts, h, only_sequence(seqs), row_ptr,
+                       col_idx, info);
+  else
+    hipLaunchKernelGGL(compact_kernel<kMaxGroupSeqs>, dim3(grid), dim3(256), 0, st, mask_bits, counts, h, seqs, row_ptr,
+                       col_idx, info);
+  return launch_status();
 }
 
 static int run_compaction(const prism_params* p, const SeqTable& seqs, const uint64_t* mask_bits, int32_t* row_ptr,
@@ -1201,16 +1449,51 @@ extern "C" int prism_estimate_workspace_bytes(const prism_params* params, size_t
   return PRISM_OK;
 }
 
+template <int kSeqs>
+static int run_small_on(const prism_params* p, const SeqTableOf<kSeqs>& seqs, const BandMap& map, char* ws,
+                        const EstimateWs& L, uint64_t* mask_bits, int32_t* counts, hipStream_t st) {
+  const int h = p->n_q_heads;
+  const size_t lds = (size_t)2 * kStripRows * (((seqs.nmax + 15) / 16) * 16 + 4) * sizeof(float);
+  auto kern = select_small_kernel<kSeqs>;
+  if (lds > 60 * 1024) {
+    static LdsGrant grant;
+    const int rc = grant.ask(reinterpret_cast<const void*>(kern), 2 * kStripRows * (kSmallBlocks + 4) * sizeof(float));
+    if (rc != PRISM_OK) return rc;
+  }
+  hipLaunchKernelGGL(kern, dim3(seqs.tiles, h), dim3(1024), lds, st, band_vectors(ws, L),
+                     reinterpret_cast<const float*>(ws + L.energy), h, p->n_kv_heads, seqs, band_stride(p->head_dim),
+                     p->head_dim, map.dz[0], map.dz[1], map.dpad[0], map.dpad[1],
+                     (p->flags & PRISM_FLAG_NO_CALIBRATION) ? 0 : 1, p->top_p, select_flags_of(p), mask_bits, counts);
+  return launch_status();
+}
+static int run_small(const prism_params* p, const SeqTable& seqs, const BandMap& map, char* ws, const EstimateWs& L,
+                     uint64_t* mask_bits, int32_t* counts, hipStream_t st) {
+  if (seqs.n == 1) return run_small_on<1>(p, only_sequence(seqs), map, ws, L, mask_bits, counts, st);
+  return run_small_on<kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, counts, st);
+}
+
+constexpr int64_t kSmallStrips = 320;         // of the whole call: strips * q-heads
+
 // The whole estimate of the sequences in `seqs` (arguments already validated): pooling (+ RoPE when `rope`
 // is given), calibration, selection, compaction.
 static int estimate_core(const prism_params* params, const HeadStrides& hs, const SeqTable& seqs, const BandMap& map,
                          const void* q, const void* k, uint64_t* mask_bits, int32_t* row_ptr,
-                         int32_t* col_idx, int32_t* info, char* ws,
+                         int32_t* col_idx, int32_t* info, char* ws, size_t ws_bytes,
                          hipStream_t st, const RopeArgs* rope = nullptr, void* q_out = nullptr,
                          void* k_out = nullptr) {
   const EstimateWs L = estimate_layout(params, seqs.n, seqs.nsum, seqs.tiles);
-  int rc = run_pool_and_scale(params, hs, seqs, map, q, k, ws, L, nullptr, nullptr, nullptr, st, rope, q_out, k_out);
+  // Few strips: three launches instead of five, and a shorter chain per strip (both sides of the rule at
+  // select_small_kernel).  A workspace without room for the row counts goes the general way.
+  const bool small = ws_bytes >= L.total && seqs.nmax <= kSmallBlocks &&
+                     (int64_t)seqs.tiles * params->n_q_heads <= kSmallStrips;
+  int rc = run_pool_and_scale(params, hs, seqs, map, q, k, ws, L, nullptr, nullptr, nullptr, st, rope, q_out, k_out, !small);
   if (rc != PRISM_OK) return rc;
+  if (small) {
+    int32_t* counts = reinterpret_cast<int32_t*>(ws + L.counts);
+    rc = run_small(params, seqs, map, ws, L, mask_bits, counts, st);
+    if (rc != PRISM_OK) return rc;
+    return run_compact(params, seqs, mask_bits, counts, row_ptr, col_idx, info, st);
+  }
   // up to 1024 blocks: 4 waves of 4 rows, two workgroups per CU; beyond (a 131 KB logit strip, one
   // workgroup per CU, rows of 32 registers): 8 waves of 2 rows (measured 1.89 -> 1.25 ms at N = 2048,
   // while at N = 1024 the 4-wave form is 2 % faster)
@@ -1233,10 +1516,10 @@ extern "C" int prism_estimate_bands(const prism_params* params, const prism_band
   if (rc != PRISM_OK) return rc;
   if (!q_bf16 || !k_bf16 || !mask_bits || !row_ptr || !col_idx || !info || col_capacity < 0)
     return PRISM_ERR_INVALID_ARG;
-  rc = check_ws(workspace, workspace_bytes, estimate_ws(params).total);
+  rc = check_ws(workspace, workspace_bytes, estimate_ws(params).least);
   if (rc != PRISM_OK) return rc;
   return estimate_core(params, contiguous_heads(params), one_sequence(params, col_capacity), map, q_bf16, k_bf16,
-                       mask_bits, row_ptr, col_idx, info, static_cast<char*>(workspace),
+                       mask_bits, row_ptr, col_idx, info, static_cast<char*>(workspace), workspace_bytes,
                        static_cast<hipStream_t>(stream));
 }
 
@@ -1305,7 +1588,13 @@ extern "C" int prism_estimate_varlen(const prism_params* params, const int32_t* 
   rc = check_bands(params);
   if (rc != PRISM_OK) return rc;
   if (!q_bf16 || !k_bf16 || !mask_bits || !row_ptr || !col_idx || !info) return PRISM_ERR_INVALID_ARG;
-  rc = check_ws(workspace, workspace_bytes, need);
+  size_t least = 0;
+  for (int s = 0; s < n_seqs; ++s) {
+    const prism_params ps = sequence_params(params, cu_seqlens, s);
+    const size_t b = estimate_ws(&ps).least;
+    least = b > least ? b : least;
+  }
+  rc = check_ws(workspace, workspace_bytes, least);
   if (rc != PRISM_OK) return rc;
   const prism_bands bands = default_bands(params);
   BandMap map;
@@ -1320,7 +1609,7 @@ extern "C" int prism_estimate_varlen(const prism_params* params, const int32_t* 
   };
   auto run = [&](const SeqTable& t, const prism_params& ps) {
     return estimate_core(&ps, hs, t, map, q_bf16, k_bf16, mask_bits, row_ptr, col_idx, info,
-                         static_cast<char*>(workspace), static_cast<hipStream_t>(stream));
+                         static_cast<char*>(workspace), workspace_bytes, static_cast<hipStream_t>(stream));
   };
   return for_each_group(params, cu_seqlens, n_seqs, fits, run);
 }
@@ -1373,7 +1662,7 @@ extern "C" int prism_estimate_static(const prism_params* params, const void* q_b
   if (rc != PRISM_OK) return rc;
   rc = check_bands(params);
   if (rc != PRISM_OK) return rc;
-  if (estimate_ws(params).total > kStaticScratchBytes) return PRISM_ERR_TOO_LARGE;
+  if (estimate_ws(params).least > kStaticScratchBytes) return PRISM_ERR_TOO_LARGE;
   void* ws = nullptr;
   rc = static_scratch(&ws);
   if (rc != PRISM_OK) return rc;
@@ -1421,10 +1710,10 @@ extern "C" int prism_rope_estimate(const prism_params* params, const prism_rope*
     ra.yarn_beta = rope->yarn_beta;
     ra.yarn_native_len = (double)rope->yarn_native_len;
   }
-  rc = check_ws(workspace, workspace_bytes, estimate_ws(params).total);
+  rc = check_ws(workspace, workspace_bytes, estimate_ws(params).least);
   if (rc != PRISM_OK) return rc;
   return estimate_core(params, contiguous_heads(params), one_sequence(params, col_capacity), map, q_in_bf16, k_in_bf16,
-                       mask_bits, row_ptr, col_idx, info, static_cast<char*>(workspace),
+                       mask_bits, row_ptr, col_idx, info, static_cast<char*>(workspace), workspace_bytes,
                        static_cast<hipStream_t>(stream), &ra, q_out_bf16, k_out_bf16);
 }
 
@@ -1440,7 +1729,7 @@ extern "C" int prism_block_scores_bands(const prism_params* params, const prism_
   if (rc != PRISM_OK) return rc;
   if (!q_bf16 || !k_bf16) return PRISM_ERR_INVALID_ARG;
   const EstimateWs L = estimate_ws(params);
-  rc = check_ws(workspace, workspace_bytes, L.total);
+  rc = check_ws(workspace, workspace_bytes, L.least);
   if (rc != PRISM_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);

@@ -1,0 +1,67 @@
+"""The short form of the estimate (bands side by side, calibration and compaction without launches of their own) against
+the general one, which a workspace without room for the row counts selects: the same bits, at the edges of a strip (16
+blocks), of a row's registers (128, 256, 512 columns), with every option, with equal elements at the cut and with more
+columns selected than the list has room for."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_08426_amd import binding as pb
+
+pytestmark = pytest.mark.gpu
+
+AXIS = ([(0, 8), (16, 32), (72, 32)], [(0, 16), (36, 36), (92, 36)])
+
+
+@pytest.mark.parametrize("h,hkv,N,tail,B,d,bands,p,flags,kind", [
+    (1, 1, 1, 5, 128, 128, (64, 96), 0.95, 0, "noise"),
+    (2, 1, 16, 64, 64, 128, (64, 96), 0.95, 0, "noise"),
+    (7, 1, 17, 1, 128, 128, (64, 96), 0.9, 0, "noise"),
+    (4, 2, 64, 128, 128, 64, (32, 48), 0.95, 0, "noise"),
+    (4, 2, 65, 100, 128, 256, (128, 192), 0.95, 0, "noise"),
+    (3, 1, 128, 64, 64, 128, (64, 96), 0.95, 0, "topics"),
+    (3, 1, 129, 33, 64, 128, (0, 96), 0.95, 0, "topics"),
+    (3, 3, 257, 64, 64, 128, (64, 0), 0.93, pb.PRISM_FLAG_NO_CALIBRATION, "topics"),
+    (10, 2, 512, 64, 64, 64, (32, 48), 0.95, 0, "topics"),                        # 320 strips
+    (2, 2, 200, 9, 64, 128, AXIS, 0.9, pb.PRISM_FLAG_BIDIRECTIONAL, "topics"),
+    (2, 1, 90, 64, 64, 128, (64, 96), 0.95, pb.PRISM_FLAG_FORCE_DIAGONAL | pb.PRISM_FLAG_FORCE_SINK, "topics"),
+    (2, 1, 90, 64, 64, 128, (64, 96), 1.0, 0, "noise"),
+    (2, 1, 70, 64, 64, 128, (64, 96), 0.5, 0, "equal"),                           # every logit of a row the same: ties
+    (2, 1, 70, 64, 64, 128, (64, 96), 0.95, 0, "zero"),                           # no energy
+])
+def test_same_bits_as_the_general_form(h, hkv, N, tail, B, d, bands, p, flags, kind):
+    L = (N - 1) * B + tail
+    print(f"case h={h}/{hkv} L={L} B={B} d={d} bands={bands} p={p} flags={flags:#x} {kind}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N * d + h)
+    q, k = (torch.randn((n, L, d), generator=g, device="cuda") for n in (h, hkv))
+    if kind == "topics":                                  # blocks that differ from one another
+        for x in (q, k):
+            x += torch.randn((x.shape[0], N, d), generator=g, device="cuda").repeat_interleave(B, 1)[:, :L] * 0.7
+    elif kind == "equal":
+        q, k = torch.ones_like(q), torch.ones_like(k)
+    elif kind == "zero":
+        q, k = torch.zeros_like(q), torch.zeros_like(k)
+    q, k = q.bfloat16(), k.bfloat16()
+    slices = isinstance(bands[0], list)
+    params = pb.make_params(h, hkv, L, B, *((0, 0) if slices else bands), p, flags, d)
+    need = pb.prism_estimate_workspace_bytes(params)
+    outs = []
+    for room in (need, need - (h * N * 4 + 255) // 256 * 256):
+        for cap in (None, 37):
+            mask, rp, ci, info = pb.alloc_estimate_outputs(params)
+            ci.fill_(-7)
+            n = ci.numel() if cap is None else min(cap, ci.numel())
+            ws = pb.alloc_workspace(room)[:max(room, 1)]
+            if slices:
+                pb.prism_estimate_bands(params, pb.make_bands(*bands), q, k, mask, rp, ci, n, info, ws)
+            else:
+                pb.prism_estimate(params, q, k, mask, rp, ci, n, info, ws)
+            outs.append((mask, rp, ci, info))
+    torch.cuda.synchronize()
+    for i in (0, 1):
+        for a, b in zip(outs[i], outs[2 + i]):
+            assert torch.equal(a, b)
+    assert int(outs[0][3][0]) == int(outs[0][1][-1]) and int(outs[0][3][0]) >= h * N
+    with pytest.raises(pb.PrismError):
+        ws = pb.alloc_workspace(need)[:need - (h * N * 4 + 255) // 256 * 256 - 1]
+        pb.prism_estimate(params, q, k, *outs[0][:3], 1, outs[0][3], ws)
