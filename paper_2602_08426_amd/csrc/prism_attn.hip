@@ -1492,7 +1492,8 @@ using namespace prism;
 // ---- workspace layout: [ V image | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
 //                            bins[2*h*kClasses] | parts[h_kv*kClasses*8] | plan[24] ] ----
 struct AttnWs {
-  size_t image, items, row_rank, row_part, bins, parts, plan, image16, range_flags, pair_items, pair_plan, total, least;
+  size_t image, items, row_rank, row_part, bins, parts, plan, image16, range_flags, pair_items, pair_plan, total;
+  bool has16;
 };
 // the fp16 image exists where the 64-queries-per-wave kernel can take the call
 static bool w64_shape(const prism_params* p) { return p->block == 128 && p->head_dim == kHeadDim; }
@@ -1500,26 +1501,32 @@ static bool w64_shape(const prism_params* p) { return p->block == 128 && p->head
 // B = 64 with an even number of blocks: a second plan over pairs of q-blocks for the pair kernel
 static bool pair_shape(const prism_params* p) { return p->block == 64 && n_blocks(p) % 2 == 0; }
 
+// Where the fp16 image lies: behind everything else, or for a ragged length next to the bf16 image, so that neither
+// depends on the number of q-heads (calls with other q-heads of the same kv heads may share one image); nowhere in a
+// buffer of a ragged length that has no room for it.
+enum class Image16 { kNone, kFirst, kLast };
+
 // The layout for `N` blocks (those of one sequence, or of a group of a packed batch).
-static AttnWs attn_layout(const prism_params* p, size_t N, bool pairs) {
+static AttnWs attn_layout(const prism_params* p, size_t N, bool pairs, Image16 where) {
   const size_t rows = (size_t)p->n_q_heads * N;
   const size_t image_bytes = (size_t)p->n_kv_heads * N * p->block * p->head_dim * 2;
   AttnWs w;
   size_t off = 0;
+  auto place_image16 = [&] {
+    w.image16 = off;     off = align_up(off + image_bytes, 256);
+    w.range_flags = off; off = align_up(off + (size_t)p->n_kv_heads * N * sizeof(int32_t), 256);
+  };
+  w.has16 = w64_shape(p) && where != Image16::kNone;
   w.image = off;    off = align_up(off + image_bytes, 256);
+  w.image16 = w.range_flags = off;
+  if (w.has16 && where == Image16::kFirst) place_image16();
   w.items = off;    off = align_up(off + rows * sizeof(int4), 256);
   w.row_rank = off; off = align_up(off + rows * sizeof(int32_t), 256);
   w.row_part = off; off = align_up(off + rows * sizeof(int32_t), 256);
   w.bins = off;     off = align_up(off + (size_t)2 * p->n_q_heads * kClasses * sizeof(int32_t), 256);
   w.parts = off;    off = align_up(off + (size_t)p->n_kv_heads * kClasses * 8 * sizeof(int32_t), 256);
   w.plan = off;     off = align_up(off + kPlanInts * sizeof(int32_t), 256);
-  w.image16 = off;
-  w.range_flags = off;
-  if (w64_shape(p)) {
-    off = align_up(off + image_bytes, 256);
-    w.range_flags = off;
-    off = align_up(off + (size_t)p->n_kv_heads * N * sizeof(int32_t), 256);
-  }
+  if (w.has16 && where == Image16::kLast) place_image16();
   w.pair_items = off;
   w.pair_plan = off;
   if (pairs) {
@@ -1528,28 +1535,36 @@ static AttnWs attn_layout(const prism_params* p, size_t N, bool pairs) {
     off = align_up(off + kPlanInts * sizeof(int32_t), 256);
   }
   w.total = off;
-  // A ragged length can do without the fp16 image: a caller with only this much runs the general kernel.
-  w.least = w64_shape(p) && p->seq_len % 128 != 0 ? w.image16 : off;
   return w;
 }
-static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), pair_shape(p)); }
+static bool ragged(const prism_params* p) { return p->seq_len % p->block != 0; }
+static AttnWs attn_ws(const prism_params* p) {
+  return attn_layout(p, n_blocks(p), pair_shape(p), ragged(p) ? Image16::kFirst : Image16::kLast);
+}
+// the smallest buffer that is taken: a ragged length can do without the fp16 image (through the general kernel)
+static size_t attn_least(const prism_params* p) {
+  return ragged(p) ? attn_layout(p, n_blocks(p), pair_shape(p), Image16::kNone).total : attn_ws(p).total;
+}
+// the layout in a buffer of that size or more
+static AttnWs attn_ws_in(const prism_params* p, size_t bytes) {
+  const AttnWs w = attn_ws(p);
+  return bytes >= w.total ? w : attn_layout(p, n_blocks(p), pair_shape(p), Image16::kNone);
+}
 
-// Does the 64-queries-per-wave kernel take this call?  Decided by the shape and the size of the buffer, in
-// the same way when the V image is written and when it is read.
+// Does the 64-queries-per-wave kernel take the call on one sequence whose buffer holds its image?
 // A ragged length takes it too (20 011 tokens, 32 / 8 heads: 704 -> 646 us per layer; 19 290 tokens, 16 heads,
 // bidirectional: 695 -> 640 us against the general kernel), except in calls of so few rows that the general
 // kernel queued behind it costs more than it saves (attention alone, general -> here: 28 to 93 rows of one head
 // 20.1 -> 22.0 and 22.9 -> 25.5 us, 84 rows 20.3 -> 22.5, 160 rows 38.2 -> 38.5, 232 rows 45.7 -> 41.4,
 // 256 rows 33.4 -> 30.4, 880 rows 135 -> 107).
 constexpr int kRaggedW64MinRows = 160;
-static bool w64_call(const prism_params* p, size_t bytes) {
-  if (!w64_shape(p) || bytes < attn_ws(p).total) return false;
-  return p->seq_len % 128 == 0 || p->n_q_heads * n_blocks(p) >= kRaggedW64MinRows;
+static bool w64_call(const prism_params* p) {
+  return !ragged(p) || p->n_q_heads * n_blocks(p) >= kRaggedW64MinRows;
 }
 
 static int check_image(const prism_params* params, const void* img, size_t bytes) {
   if (img == nullptr || (reinterpret_cast<uintptr_t>(img) & 255u) != 0 ||
-      bytes < attn_ws(params).least)
+      bytes < attn_least(params))
     return PRISM_ERR_WORKSPACE;
   return PRISM_OK;
 }
@@ -1632,12 +1647,11 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
   if (!v_bf16) return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
-  const AttnWs W = attn_ws(params);
+  const AttnWs W = attn_ws_in(params, v_image_bytes);
   char* ws = static_cast<char*>(v_image);
-  const bool w64 = w64_call(params, v_image_bytes);
   return v_image_core(params, contiguous_heads(params), v_bf16, reinterpret_cast<uint16_t*>(ws + W.image),
-                      w64 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr,
-                      w64 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr, static_cast<hipStream_t>(stream));
+                      W.has16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr,
+                      W.has16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr, static_cast<hipStream_t>(stream));
 }
 
 template <int BLK, bool kStreamOnly, int D, bool kPair = false>
@@ -1712,13 +1726,13 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
   uint16_t* vp = reinterpret_cast<uint16_t*>(ws + W.image);
-  uint16_t* vp16 = w64_takes ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
-  int32_t* range_flags = w64_takes ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
+  uint16_t* vp16 = W.has16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
+  int32_t* range_flags = W.has16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
   uint16_t* op = (uint16_t*)out_bf16;
   // Blocks of 128 tokens go through the 64-queries-per-wave kernel when every list is clean
   // (decided on the device, so the general kernel is queued behind it and returns at once unless
   // the lists turn out to need it).
-  const bool w64 = w64_takes && !stream_only &&
+  const bool w64 = W.has16 && w64_takes && !stream_only &&
                    !(params->flags & PRISM_FLAG_GENERAL_KERNEL);
   // B = 64 with an even number of blocks: the pair kernel (two q-blocks per workgroup sharing the tiles of
   // the union of their lists) takes the call when every list is ascending and clean; decided on the
@@ -1861,8 +1875,8 @@ extern "C" int prism_sparse_attn_pre(const prism_params* params, const void* q_b
     return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
-  return attn_core(params, contiguous_heads(params), one_sequence(params, col_count), attn_ws(params),
-                   w64_call(params, v_image_bytes), q_bf16, k_bf16, nullptr, static_cast<char*>(v_image),
+  return attn_core(params, contiguous_heads(params), one_sequence(params, col_count),
+                   attn_ws_in(params, v_image_bytes), w64_call(params), q_bf16, k_bf16, nullptr, static_cast<char*>(v_image),
                    row_ptr, col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
@@ -1876,8 +1890,8 @@ extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16,
     return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, workspace, workspace_bytes);
   if (rc != PRISM_OK) return rc;
-  return attn_core(params, contiguous_heads(params), one_sequence(params, col_count), attn_ws(params),
-                   w64_call(params, workspace_bytes), q_bf16, k_bf16, v_bf16, static_cast<char*>(workspace), row_ptr,
+  return attn_core(params, contiguous_heads(params), one_sequence(params, col_count),
+                   attn_ws_in(params, workspace_bytes), w64_call(params), q_bf16, k_bf16, v_bf16, static_cast<char*>(workspace), row_ptr,
                    col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
@@ -1891,9 +1905,9 @@ static int varlen_workspace(const prism_params* params, const int32_t* cu_seqlen
   for (int s = 0; s < n_seqs; ++s) {
     prism_params ps = *params;
     ps.seq_len = cu_seqlens[s + 1] - cu_seqlens[s];
-    const AttnWs w = attn_ws(&ps);
-    need = w.total > need ? w.total : need;
-    least = w.least > least ? w.least : least;
+    const size_t all = attn_ws(&ps).total, few = attn_least(&ps);
+    need = all > need ? all : need;
+    least = few > least ? few : least;
   }
   if (least_bytes != nullptr) *least_bytes = least;
   *bytes = need;
@@ -1928,12 +1942,11 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
   // and the workspace holds them.
   auto fits = [&](const SeqTable& t) {
     return (int64_t)params->n_q_heads * t.nsum <= kPrepMaxRows && params->n_q_heads < (1 << kSeqShift) &&
-           heads_in_cache(params, t) >= params->n_kv_heads && attn_layout(params, t.nsum, pairs(t)).total <= workspace_bytes;
+           heads_in_cache(params, t) >= params->n_kv_heads && attn_layout(params, t.nsum, pairs(t), Image16::kLast).total <= workspace_bytes;
   };
   auto run = [&](const SeqTable& t, const prism_params& ps) {
-    // the layout of one sequence differs from that of a group only in what a ragged length can do without
-    const AttnWs W = t.n > 1 ? attn_layout(params, t.nsum, pairs(t)) : attn_ws(&ps);
-    const bool w64 = t.n > 1 ? w64_shape(params) : w64_call(&ps, workspace_bytes);
+    const AttnWs W = t.n > 1 ? attn_layout(params, t.nsum, pairs(t), Image16::kLast) : attn_ws_in(&ps, workspace_bytes);
+    const bool w64 = t.n > 1 || w64_call(&ps);
     const size_t tok = t.n > 1 ? 0 : t.s[0].tok0;
     SeqTable at = t;
     if (t.n == 1) at.s[0].tok0 = 0, at.s[0].row0 = 0, at.s[0].col0 = 0;   // one sequence: through the pointers

@@ -63,3 +63,23 @@ def test_ragged_last_block(tail, bidir, h, small_workspace):
         live = t > 0
         assert np.abs(s[i][live] - (m[live, 0] + np.log(t[live]))).max() <= LSE_TOL
         assert (s[i][~live] == -np.inf).all()
+
+
+def test_one_image_for_calls_with_other_query_heads():
+    """A V image of a ragged length serves attention calls on any of the q-heads of its kv heads."""
+    hkv, B, L = 2, 128, 128 * 20 + 17
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn((n, L, 128), generator=g, device="cuda").bfloat16() for n in (16, hkv, hkv))
+    full = pb.make_params(16, hkv, L, B)
+    image = pb.alloc_workspace(pb.prism_sparse_attn_workspace_bytes(full))
+    pb.prism_v_image(full, v, image)
+    for n in (16, 8, 2):                                   # 336 and 168 rows, and 42, which the general kernel takes
+        part = pb.make_params(n, hkv, L, B)
+        _, rp, ci, _ = pb.alloc_estimate_outputs(part)
+        pb.prism_causal_csr(part, rp, ci, ci.numel())
+        qs = q.view(hkv, 16 // hkv, L, 128)[:, :n // hkv].reshape(n, L, 128).contiguous()
+        out, lse = torch.empty_like(qs), torch.empty((n, L), device="cuda")
+        pb.prism_sparse_attn_pre(part, qs, k, image, rp, ci, ci.numel(), out, lse)
+        ref, ref_lse = gu.gpu_sparse_attn(part, qs, k, v, rp, ci, ci.numel())
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and torch.equal(lse, ref_lse), n
