@@ -128,7 +128,7 @@ __device__ __forceinline__ bool call_is_dirty(const DirtyFlags& f, int& shared_w
 // and two buffers per tile (AttnCfg::kDouble):
 //     K(j), V(j) in LDS | start K(j+1), V(j+1) copies | S^T | softmax | O^T += V^T P^T | wait both | barrier
 // (one barrier instead of three and no tile latency inside a step; us per layer, one buffer -> two: 16K, d = 256,
-// B = 64 801 -> 780; 32K, d = 128, B = 64 in pairs 1791 -> 1730; 12345 tokens, d = 64 254 -> 252, the mean of five inputs).
+// B = 64 801 -> 780; 12345 tokens, d = 64 254 -> 252, the mean of five inputs).
 // The workgroups are persistent: a workgroup pulls its next row from its XCD's queue at the top
 // of the last step of the current row and reads that row's queue entry during the last PV, so
 // a row switch exposes only the load of the Q rows and of the first K tile.
@@ -152,7 +152,9 @@ struct AttnCfg {
   static constexpr int kPerCu = D > 128 ? 1 : (BLK == 128 || PAIR ? 2 : 4);
   // Two buffers per tile where the CU's 160 KB hold them for all of them (not at 128 x 128 and 128 x 256, nor for the
   // four small workgroups of 64 x 128): both tiles of the next block are then requested a whole step ahead.
-  static constexpr bool kDouble = 4 * kTileBytes * kPerCu + 4096 <= 160 * 1024;
+  // Not for the pair form of 64 x 128 either, though it fits: us per layer, one buffer -> two, 28/4 heads at 21376
+  // tokens 668 -> 722, 32/8 at 20480 726 -> 779, at 32768 1506 -> 1481, 16/4 at 65536 2636 -> 2615.
+  static constexpr bool kDouble = !(PAIR && D == 128) && 4 * kTileBytes * kPerCu + 4096 <= 160 * 1024;
   static constexpr int kBuffers = kDouble ? 2 : 1;
 };
 
