@@ -104,16 +104,19 @@ struct DirtyFlags {
   const int32_t* b;
   int32_t na, nb;
 };
+// The verdict has a word of its own.  Every wave reads it behind the last barrier here, so a word that the caller goes on
+// to write (the queue position, say) could change under a wave that reads late.
 template <int kThreads>
-__device__ __forceinline__ bool call_is_dirty(const DirtyFlags& f, int& shared_word) {
-  if (threadIdx.x == 0) shared_word = 0;
+__device__ __forceinline__ bool call_is_dirty(const DirtyFlags& f) {
+  __shared__ int verdict;
+  if (threadIdx.x == 0) verdict = 0;
   int bad = 0;
   for (int i = threadIdx.x; i < f.na; i += kThreads) bad |= f.a[i];
   for (int i = threadIdx.x; i < f.nb; i += kThreads) bad |= f.b[i];
   __syncthreads();
-  if (bad != 0) shared_word = 1;                     // every writer stores 1
+  if (bad != 0) verdict = 1;                         // every writer stores 1
   __syncthreads();
-  return __builtin_amdgcn_readfirstlane(shared_word) != 0;
+  return __builtin_amdgcn_readfirstlane(verdict) != 0;
 }
 
 // =====================================================================================
@@ -337,9 +340,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   __shared__ __attribute__((aligned(16))) char lds_v[C::kTileBytes * C::kBuffers];
   __shared__ int next_item, next_queue;
   if (kPair) {
-    if (call_is_dirty<C::kThreads>(flags, next_item)) return;   // the plain kernel takes this call
+    if (call_is_dirty<C::kThreads>(flags)) return;   // the plain kernel takes this call
   } else if (only_dirty) {
-    const bool dirty = call_is_dirty<C::kThreads>(flags, next_item);
+    const bool dirty = call_is_dirty<C::kThreads>(flags);
     if (blockIdx.x == 0 && threadIdx.x == 0) plan[kPlanFlags] = dirty ? kFlagDirtyLists : 0;
     if (!dirty) return;                                     // the kernel launched in front of this one took it
   }
@@ -831,7 +834,7 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) char lds_tiles[65536];
   __shared__ int s_pulled, s_queue;
-  if (call_is_dirty<128 / kQ * 64>(flags, s_pulled)) return;          // the general kernel takes this call
+  if (call_is_dirty<128 / kQ * 64>(flags)) return;          // the general kernel takes this call
 
   const int t = threadIdx.x;
   const int lane = t & 63;

@@ -1,0 +1,69 @@
+"""Properties of the compiled kernels that no run shows reliably, read from the assembly of the library built here (no
+GPU)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2602_08426_amd import binding as pb
+
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """name -> instructions of every kernel of the built library."""
+    if not os.path.exists(os.path.join(LLVM, "llvm-objdump")):
+        pytest.skip("no llvm-objdump")
+    if not os.path.exists(pb.library_path()):
+        from paper_2602_08426_amd.build import build_library
+        build_library()
+    tmp = tmp_path_factory.mktemp("code")
+    os.symlink(pb.library_path(), tmp / "lib.so")
+    objdump = os.path.join(LLVM, "llvm-objdump")
+    subprocess.run([objdump, "--offloading", "lib.so"], cwd=tmp, check=True, capture_output=True)
+    out, name = {}, None
+    for part in sorted(p for p in os.listdir(tmp) if p.endswith("gfx950")):
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", part], cwd=tmp, check=True, capture_output=True,
+                              text=True).stdout
+        for line in text.splitlines():
+            m = re.match(r"[0-9a-f]+ <(_Z\w+)>:", line)
+            if m:
+                name = m.group(1)
+                out[name] = []
+            elif name is not None and line.startswith("\t"):
+                out[name].append(line.split("//")[0].strip())
+    return out
+
+
+def _lds_address(ins, constants):
+    """Byte address of a one-word LDS access, or None if its base register holds no known constant."""
+    m = re.match(r"ds_read_b32 v\d+, v(\d+)|ds_write_b32 v(\d+),", ins)
+    base = constants.get(m.group(1) or m.group(2))
+    off = re.search(r"offset:(\d+)", ins)
+    return None if base is None else base + (int(off.group(1)) if off else 0)
+
+
+def test_verdict_word_is_not_written_while_waves_may_still_read_it(kernels):
+    """The general attention kernel asks first whether the call is its own.  Behind the last barrier of that question
+    every wave reads the verdict; until the next barrier no wave may store to the same word, or a late wave takes
+    something else for the verdict and leaves (or stays) alone."""
+    names = [n for n in kernels if "sparse_attn_kernel" in n]
+    assert len(names) >= 9
+    for name in names:
+        constants, barriers, word = {}, 0, None
+        for ins in kernels[name]:
+            m = re.match(r"v_mov_b32_e32 v(\d+), (0x[0-9a-f]+|\d+)$", ins)
+            if m:
+                constants[m.group(1)] = int(m.group(2), 0)
+            elif ins.startswith("s_barrier"):
+                barriers += 1
+                if barriers == 3:
+                    break
+            elif barriers == 2 and word is None and ins.startswith("ds_read_b32"):
+                word = _lds_address(ins, constants)
+                assert word is not None, (name, ins)
+            elif word is not None and ins.startswith("ds_write_b32"):
+                assert _lds_address(ins, constants) != word, (name, ins)
+        assert barriers == 3 and word is not None, name
