@@ -259,8 +259,6 @@ int prism_dense_csr(const prism_params* params, int32_t* row_ptr, int32_t* col_i
  * workspace: prism_sparse_attn_workspace_bytes() bytes (a transposed copy of V plus the
  *            kernel's work queues: one entry per row, ordered by list-length class and
  *            q-head and dealt to the eight XCDs in parts of equal work).
- *            At B = 128, d = 128 a ragged length runs without the second (fp16) copy of V when the
- *            buffer has no room for it, through a kernel of 32 instead of 64 queries per wave.
  * top_p, d_high, d_low and the other flags of `params` are ignored here.
  * ---------------------------------------------------------------------------------- */
 int prism_sparse_attn_workspace_bytes(const prism_params* params, size_t* bytes /* host, out */);

@@ -113,8 +113,8 @@ S_B1 = 54               # b + 1
 S_N = 55                # entries in the list
 S_T0 = 56
 S_T1 = 57
-S_U = 58                # the block of this row that has hidden keys (none: 0xffffffff)
-S_CAUSAL = 59           # 1 = causal row, 0 = bidirectional
+S_U = 58
+S_CAUSAL = 59
 S_HAVE_O = 60
 S_WAVE = 61
 S_FLAG = 62             # 2+2: per query tile "some lane's max moved past the threshold"
@@ -129,7 +129,6 @@ S_LSE = 74              # 2: lse row base (0 = not requested)
 S_QB = 76               # 2
 S_OB = 78               # 2
 S_VBYTES = 92           # bytes of the V^T image of one kv head (records of the V^T resource)
-S_TAIL = 93             # last token of the ragged last block of bidirectional rows, 0 for causal rows
 S_CNT = 94              # 2: address of the pull counter of this workgroup's queue
 S_MK = 88               # 2: LDS address of this wave's part of Kbuf[0], Kbuf[1]
 S_MV = 90               # 2: ... of Vbuf[0], Vbuf[1]
@@ -339,33 +338,27 @@ def f32_bits(x):
     return struct.unpack("<I", struct.pack("<f", x))[0]
 
 
-S_QRS = 80               # 4: buffer resource of the Q rows (prologue; the mask compares use the registers later)
 S_MASK = 80              # 4 x 2: compare results of the causal mask, used two instructions later
 
 
 def mask_block(p, hh, label):
-    """Hidden keys of the one block of a row that has some, applied to bank p before its softmax.
-    Causal rows: the diagonal block, key 64*hh + 32*kt + 8*(r/4) + 4*hf + r%4 is hidden from query
-    64*wave + 32*qt + l32 when it is larger (in a ragged last block that hides the keys past the end
-    from every query that exists as well).  Bidirectional rows: the ragged last block, keys past its
-    last token are hidden from every query; s[S_U] names no block when there is none.
-    A compare result is read by its select no
+    """Causal mask of the diagonal block, applied to bank p before its softmax: key
+    64*hh + 32*kt + 8*(r/4) + 4*hf + r%4 is hidden from query 32*QT*wave + 32*qt + l32 when it is
+    larger.  A compare result is read by its select no
     sooner than two instructions later (VALU-written SGPR read by a VALU)."""
     T = V_T
     ops = [salu(f"s_cmp_eq_u32 s{S_CV}, s{S_U}"),
-           salu(f"s_cbranch_scc0 {label}")]
+           salu(f"s_cselect_b32 s{S_T2}, s{S_CAUSAL}, 0"),
+           salu(f"s_cmp_eq_u32 s{S_T2}, 0"),
+           salu(f"s_cbranch_scc1 {label}")]
     ops.append(valu(f"v_mov_b32 v{V_INF}, 0xff800000", (), vr(V_INF)))
-    # last visible key relative to this half's keys: limit - 4*hf - 64*hh with
-    # limit = causal * (32*QT*wave + 32*qt + l32) + tail1 (tail1 = 0 for causal rows)
+    # thresholds relative to this half's keys: 32*QT*wave + 32*qt + l32 - 4*hf - 64*hh
     ops += lane_ids(INP, T + 16)
-    ops.append(valu(f"v_lshl_add_u32 v{T + 19}, v{T + 19}, {4 + QT}, v{T + 17}", vr(T + 19) + vr(T + 17), vr(T + 19)))
     ops.append(valu(f"v_lshlrev_b32 v{T + 20}, 2, v{T + 18}", vr(T + 18), vr(T + 20)))
-    ops.append(valu(f"v_sub_u32 v{T + 20}, s{S_TAIL}, v{T + 20}", vr(T + 20), vr(T + 20)))
+    ops.append(valu(f"v_sub_u32 v{T + 20}, v{T + 17}, v{T + 20}", vr(T + 17) + vr(T + 20), vr(T + 20)))
+    ops.append(valu(f"v_lshl_add_u32 v{T + 20}, v{T + 19}, {4 + QT}, v{T + 20}", vr(T + 19) + vr(T + 20), vr(T + 20)))
     for qt in range(QT):
-        ops.append(valu(f"v_add_u32 v{T + 17}, {lit32(32 * qt)}, v{T + 19}", vr(T + 19), vr(T + 17)))
-        ops.append(valu(f"v_mul_u32_u24 v{T + 17}, s{S_CAUSAL}, v{T + 17}", vr(T + 17), vr(T + 17)))
-        ops.append(valu(f"v_add_u32 v{T + 17}, {lit32(-64 * hh)}, v{T + 17}", vr(T + 17), vr(T + 17)))
-        ops.append(valu(f"v_add_u32 v{V_THR + qt}, v{T + 17}, v{T + 20}", vr(T + 17) + vr(T + 20), vr(V_THR + qt)))
+        ops.append(valu(f"v_add_u32 v{V_THR + qt}, {lit32(32 * qt - 64 * hh)}, v{T + 20}", vr(T + 20), vr(V_THR + qt)))
     todo = [(qt, kt, r) for qt in range(QT) for kt in range(2) for r in range(16)]
     def cmp_ins(i):
         qt, kt, r = todo[i]
@@ -665,14 +658,6 @@ def lane_ids(inp, T):
             valu(f"v_lshrrev_b32 v{T + 3}, 6, {t}", (), vr(T + 3))]
 
 
-def row_rsrc(rs, ptr, rows, log2_bytes):
-    """Buffer resource s[rs:rs+3] over `rows` rows of 2^log2_bytes bytes at s[ptr:ptr+1]."""
-    return [salu(f"s_mov_b64 s[{rs}:{rs + 1}], s[{ptr}:{ptr + 1}]"),
-            salu(f"s_and_b32 s{rs + 1}, s{rs + 1}, 0xffff"),
-            salu(f"s_lshl_b32 s{rs + 2}, {rows}, {log2_bytes}"),
-            salu(f"s_mov_b32 s{rs + 3}, 0x00020000")]
-
-
 def prologue(inp):
     """inp: dict name -> inline-asm operand text ("%3", ...)."""
     T = V_T
@@ -680,8 +665,7 @@ def prologue(inp):
     a = ops.append
     # scalars
     a(salu(f"s_mov_b32 s{S_N}, {inp['n']}"))
-    a(salu(f"s_mov_b32 s{S_U}, {inp['mblk']}"))
-    a(salu(f"s_mov_b32 s{S_TAIL}, {inp['tail1']}"))
+    a(salu(f"s_mov_b32 s{S_U}, {inp['u']}"))
     a(salu(f"s_mov_b32 s{S_CAUSAL}, {inp['causal']}"))
     a(salu(f"s_mov_b32 s{S_LDS}, {inp['lds']}"))
     a(salu(f"s_mov_b64 s[{S_LSE}:{S_LSE + 1}], {inp['lse']}"))
@@ -703,8 +687,6 @@ def prologue(inp):
     a(salu(f"s_and_b32 s{S_CRS + 1}, s{S_CRS + 1}, 0xffff"))
     a(salu(f"s_lshl_b32 s{S_CRS + 2}, s{S_N}, 2"))
     a(salu(f"s_mov_b32 s{S_CRS + 3}, 0x00020000"))
-    # Q rows of this wave: rows past the end of the sequence are outside the resource and read as zeros
-    ops += row_rsrc(S_QRS, S_QB, inp["rows"], 8)
     # per-lane constants from the thread index
     ops += lane_ids(inp, T)
     a(nop(1))
@@ -756,7 +738,7 @@ def prologue(inp):
     for qt in range(QT):
         for ks in range(8):
             dst = SB(0, 0, 0) + 4 * (8 * qt + ks)
-            a(Ins(f"buffer_load_dwordx4 {vtxt(dst, 4)}, v{T + 21 + qt}, s[{S_QRS}:{S_QRS + 3}], 0 offen offset:{ks * 32}",
+            a(Ins(f"global_load_dwordx4 {vtxt(dst, 4)}, v{T + 21 + qt}, s[{S_QB}:{S_QB + 1}] offset:{ks * 32}",
                   "vmem", vr(T + 21 + qt), vr(dst, 4)))
     # LDS read offsets of the MFMA operand fragments
     a(valu(f"v_and_b32 v{T + 4}, 15, v{T + 1}", vr(T + 1), vr(T + 4)))   # l32 & 15
@@ -802,10 +784,6 @@ def epilogue():
     T = V_T
     ops = []
     a = ops.append
-    # the copies are done: their resources now describe this wave's rows of O and lse; rows past the end
-    # of the sequence are outside them and are not written
-    ops += row_rsrc(S_KRS, S_OB, INP["rows"], 8)
-    ops += row_rsrc(S_VRS, S_LSE, INP["rows"], 2)
     # row offsets of this lane: O row (32*qt + l32) * 256 + hf * 8 bytes, lse (32*qt + l32) * 4
     ops += lane_ids(INP, T)
     a(valu(f"v_lshlrev_b32 v{T + 5}, 8, v{T + 1}", vr(T + 1), vr(T + 5)))
@@ -837,7 +815,7 @@ def epilogue():
                 a(valu(f"v_cvt_pk_bf16_f32 v{st + r // 2}, v{FR0 + r}, v{FR0 + r + 1}",
                        vr(FR0 + r) + vr(FR0 + r + 1), vr(st + r // 2)))
             for g4 in range(4):
-                a(Ins(f"buffer_store_dwordx2 {vtxt(st + 2 * g4, 2)}, v{T + 21 + qt}, s[{S_KRS}:{S_KRS + 3}], 0 offen offset:{dt * 64 + g4 * 16}",
+                a(Ins(f"global_store_dwordx2 v{T + 21 + qt}, {vtxt(st + 2 * g4, 2)}, s[{S_OB}:{S_OB + 1}] offset:{dt * 64 + g4 * 16}",
                       "vmem", vr(T + 21 + qt) + vr(st + 2 * g4, 2)))
     a(salu(f"s_cmp_eq_u64 s[{S_LSE}:{S_LSE + 1}], 0"))
     a(salu(f"s_cbranch_scc1 Lnolse{LABEL}"))
@@ -847,7 +825,7 @@ def epilogue():
         a(nop(3))
         a(valu(f"v_add_f32 v{lt}, v{lt}, v{V_M + qt}", vr(lt) + vr(V_M + qt), vr(lt)))
         a(valu(f"v_mul_f32 v{lt}, 0x3f317218, v{lt}", vr(lt), vr(lt)))
-        a(Ins(f"buffer_store_dword v{lt}, v{T + 23 + qt}, s[{S_VRS}:{S_VRS + 3}], 0 offen", "vmem", vr(T + 23 + qt) + vr(lt)))
+        a(Ins(f"global_store_dword v{T + 23 + qt}, v{lt}, s[{S_LSE}:{S_LSE + 1}]", "vmem", vr(T + 23 + qt) + vr(lt)))
     a(Ins(f"Lnolse{LABEL}:", "label"))
     a(Ins("s_waitcnt vmcnt(0)", "wait"))
     return ops
@@ -1056,8 +1034,7 @@ def fix_hazards(ops):
 INP = {}          # operand names of the inline-asm inputs, filled by emit()
 
 
-INPUTS = ["t", "q", "o", "lse", "k", "vt", "col", "n", "mblk", "causal", "lds", "kbytes", "vbytes", "c0", "cnt",
-          "rows", "tail1"]
+INPUTS = ["t", "q", "o", "lse", "k", "vt", "col", "n", "u", "causal", "lds", "kbytes", "vbytes", "c0", "cnt"]
 
 
 def emit(path, sequential=False):
@@ -1084,8 +1061,8 @@ def emit(path, sequential=False):
             f.write(f'    "{ins.text}\\n\\t"\n')
         f.write('    : "=&v"(pulled_next)\n')
         f.write('    : "v"(t), "s"(q_row), "s"(o_row), "s"(lse_row), "s"(k_head), "s"(vt_head), "s"(col_row),\n')
-        f.write('      "s"(n_entries), "s"(mask_block), "s"(causal), "s"(lds_base), "s"(k_bytes), "s"(vt_bytes), "s"(c_first),\n')
-        f.write('      "s"(pull_counter), "s"(rows_here), "s"(tail1)\n')
+        f.write('      "s"(n_entries), "s"(u), "s"(causal), "s"(lds_base), "s"(k_bytes), "s"(vt_bytes), "s"(c_first),\n')
+        f.write('      "s"(pull_counter)\n')
         clob = ", ".join(f'"{c}"' for c in clob_v + clob_a + clob_s + ["vcc", "scc", "memory"])
         f.write(f"    : {clob});\n")
     n_mfma = sum(1 for i in ops if i.kind == "mfma")

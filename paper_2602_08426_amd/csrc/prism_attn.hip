@@ -814,7 +814,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 }
 
 // =====================================================================================
-// The same computation with kQ = 64 queries per wave (B = 128, d = 128, clean lists): workgroup =
+// The same computation with kQ = 64 queries per wave (B = 128, d = 128, whole blocks, clean lists): workgroup =
 // 2 waves = one (q-head, q-block) row, one wave per SIMD, two workgroups per CU; or with kQ = 32: 4 waves of
 // 256 registers a lane, still two workgroups per CU, which take a listed block in 1.3 instead of 2.2 us when a row is
 // alone on its CU (the dispatch says which calls want that).  With kQ = 64 every K / V^T
@@ -905,8 +905,6 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
     const int L = seqs.s[sq].L, N = seqs.s[sq].N;
     const uint32_t k_bytes = (uint32_t)L * kHeadDim * 2;
     const uint32_t vt_bytes = (uint32_t)N * 128u * kHeadDim * 2;
-    const int ragged_block = L < N * 128 ? N - 1 : -1;
-    const int tail1 = causal ? 0 : L - (N - 1) * 128 - 1;     // last token of the last block
     const int u = __builtin_amdgcn_readfirstlane(it0.y) & 0xffff;
     const int c_first = (__builtin_amdgcn_readfirstlane(it0.y) >> 16) & 0xffff;   // first listed block
     const int it = __builtin_amdgcn_readfirstlane(it0.z);
@@ -918,13 +916,10 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
     const int q0 = u * 128 + wave * kQ;                                          // this wave's first query
     const size_t tok0 = (size_t)seqs.s[sq].tok0 + q0;                            // its token in the tensors
     const size_t row0 = (size_t)hq * hs.q + tok0 * kHeadDim;                     // its element offset in Q / O
-    // rows of this wave that exist (a ragged last block may end in front of or inside the wave's 64)
-    const int rows_left = L - q0;
-    const int rows_here = __builtin_amdgcn_readfirstlane(rows_left < 0 ? 0 : (rows_left > kQ ? kQ : rows_left));
     if (it >= end) {
       // a row without entries: o = 0, lse = -inf
       const int r = lane;                                   // one row per lane
-      if (r < rows_here) {
+      if (r < kQ) {
         uint16_t* op = out + row0 + (size_t)r * kHeadDim;
 #pragma unroll
         for (int c = 0; c < 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
@@ -942,8 +937,6 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
     const int32_t* col_row = col_idx + seqs.s[sq].col0 + it;
     const int n_entries = end - it;
     int32_t* pull_counter = counter + __builtin_amdgcn_readfirstlane(my_queue * pulls.stride);
-    // the one block of the row that has hidden keys: the diagonal, or a ragged last block
-    const int mask_block = causal ? u : ragged_block;
     int pulled_next;
     if constexpr (kQ == 64) {
 #include "prism_attn_w64_body.inc"
@@ -1495,43 +1488,44 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
 using namespace prism;
 
 // ---- workspace layout: [ V image | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
-//                            bins[2*h*kClasses] | parts[h_kv*kClasses*8] | plan[24] ] ----
+//                            bins[2*h*kClasses] | parts[h_kv*kClasses*8] | plan[kPlanInts] |
+//                            fp16 V image | range_flags[h_kv*N]        where the fp16 image is read |
+//                            pair_items[h*N/2] | pair_plan[kPlanInts]  where the pair kernel may run ] ----
 struct AttnWs {
   size_t image, items, row_rank, row_part, bins, parts, plan, image16, range_flags, pair_items, pair_plan, total;
-  bool has16;
 };
-// the fp16 image exists where the 64-queries-per-wave kernel can take the call
-static bool w64_shape(const prism_params* p) { return p->block == 128 && p->head_dim == kHeadDim; }
+// The fp16 image exists where the 64-queries-per-wave kernel can take the call: whole blocks only.  Ragged lengths stay
+// with the general kernel, which reads V as it is given: fp16 loses bits of values below 2^-17 and has nothing left of
+// them at 2^-25.  (Attention alone, us, general kernel against this one with fp16: 8 heads, 8100 tokens 91 and 77;
+// 32 heads, 8100 183 and 165; 20011 539 and 541; 32001 1052 and 1025.  With bf16 P and V in this kernel the error
+// of a lagging maximum, 0.0020 instead of the general kernel's 0.0017, or the rescaling without the lag, 570 at 20011.)
+static bool w64_shape(const prism_params* p) {
+  return p->block == 128 && p->head_dim == kHeadDim && p->seq_len % 128 == 0;
+}
 
 // B = 64 with an even number of blocks: a second plan over pairs of q-blocks for the pair kernel
 static bool pair_shape(const prism_params* p) { return p->block == 64 && n_blocks(p) % 2 == 0; }
 
-// Where the fp16 image lies: behind everything else, or for a ragged length next to the bf16 image, so that neither
-// depends on the number of q-heads (calls with other q-heads of the same kv heads may share one image); nowhere in a
-// buffer of a ragged length that has no room for it.
-enum class Image16 { kNone, kFirst, kLast };
-
 // The layout for `N` blocks (those of one sequence, or of a group of a packed batch).
-static AttnWs attn_layout(const prism_params* p, size_t N, bool pairs, Image16 where) {
+static AttnWs attn_layout(const prism_params* p, size_t N, bool with16, bool pairs) {
   const size_t rows = (size_t)p->n_q_heads * N;
   const size_t image_bytes = (size_t)p->n_kv_heads * N * p->block * p->head_dim * 2;
   AttnWs w;
   size_t off = 0;
-  auto place_image16 = [&] {
-    w.image16 = off;     off = align_up(off + image_bytes, 256);
-    w.range_flags = off; off = align_up(off + (size_t)p->n_kv_heads * N * sizeof(int32_t), 256);
-  };
-  w.has16 = w64_shape(p) && where != Image16::kNone;
   w.image = off;    off = align_up(off + image_bytes, 256);
-  w.image16 = w.range_flags = off;
-  if (w.has16 && where == Image16::kFirst) place_image16();
   w.items = off;    off = align_up(off + rows * sizeof(int4), 256);
   w.row_rank = off; off = align_up(off + rows * sizeof(int32_t), 256);
   w.row_part = off; off = align_up(off + rows * sizeof(int32_t), 256);
   w.bins = off;     off = align_up(off + (size_t)2 * p->n_q_heads * kClasses * sizeof(int32_t), 256);
   w.parts = off;    off = align_up(off + (size_t)p->n_kv_heads * kClasses * 8 * sizeof(int32_t), 256);
   w.plan = off;     off = align_up(off + kPlanInts * sizeof(int32_t), 256);
-  if (w.has16 && where == Image16::kLast) place_image16();
+  w.image16 = off;
+  w.range_flags = off;
+  if (with16) {
+    off = align_up(off + image_bytes, 256);
+    w.range_flags = off;
+    off = align_up(off + (size_t)p->n_kv_heads * N * sizeof(int32_t), 256);
+  }
   w.pair_items = off;
   w.pair_plan = off;
   if (pairs) {
@@ -1542,34 +1536,11 @@ static AttnWs attn_layout(const prism_params* p, size_t N, bool pairs, Image16 w
   w.total = off;
   return w;
 }
-static bool ragged(const prism_params* p) { return p->seq_len % p->block != 0; }
-static AttnWs attn_ws(const prism_params* p) {
-  return attn_layout(p, n_blocks(p), pair_shape(p), ragged(p) ? Image16::kFirst : Image16::kLast);
-}
-// the smallest buffer that is taken: a ragged length can do without the fp16 image (through the general kernel)
-static size_t attn_least(const prism_params* p) {
-  return ragged(p) ? attn_layout(p, n_blocks(p), pair_shape(p), Image16::kNone).total : attn_ws(p).total;
-}
-// the layout in a buffer of that size or more
-static AttnWs attn_ws_in(const prism_params* p, size_t bytes) {
-  const AttnWs w = attn_ws(p);
-  return bytes >= w.total ? w : attn_layout(p, n_blocks(p), pair_shape(p), Image16::kNone);
-}
-
-// Does the 64-queries-per-wave kernel take the call on one sequence whose buffer holds its image?
-// A ragged length takes it too (20 011 tokens, 32 / 8 heads: 704 -> 646 us per layer; 19 290 tokens, 16 heads,
-// bidirectional: 695 -> 640 us against the general kernel), except in calls of so few rows that the general
-// kernel queued behind it costs more than it saves (attention alone, general -> here: 28 to 93 rows of one head
-// 20.1 -> 22.0 and 22.9 -> 25.5 us, 84 rows 20.3 -> 22.5, 160 rows 38.2 -> 38.5, 232 rows 45.7 -> 41.4,
-// 256 rows 33.4 -> 30.4, 880 rows 135 -> 107).
-constexpr int kRaggedW64MinRows = 160;
-static bool w64_call(const prism_params* p) {
-  return !ragged(p) || p->n_q_heads * n_blocks(p) >= kRaggedW64MinRows;
-}
+static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), w64_shape(p), pair_shape(p)); }
 
 static int check_image(const prism_params* params, const void* img, size_t bytes) {
   if (img == nullptr || (reinterpret_cast<uintptr_t>(img) & 255u) != 0 ||
-      bytes < attn_least(params))
+      bytes < attn_ws(params).total)
     return PRISM_ERR_WORKSPACE;
   return PRISM_OK;
 }
@@ -1652,11 +1623,12 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
   if (!v_bf16) return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
-  const AttnWs W = attn_ws_in(params, v_image_bytes);
+  const AttnWs W = attn_ws(params);
   char* ws = static_cast<char*>(v_image);
+  const bool with16 = w64_shape(params);
   return v_image_core(params, contiguous_heads(params), v_bf16, reinterpret_cast<uint16_t*>(ws + W.image),
-                      W.has16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr,
-                      W.has16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr, static_cast<hipStream_t>(stream));
+                      with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr,
+                      with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr, static_cast<hipStream_t>(stream));
 }
 
 template <int BLK, bool kStreamOnly, int D, bool kPair = false>
@@ -1687,9 +1659,10 @@ static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t*
 }
 
 // The whole attention of the sequences in `seqs` (arguments already validated; several sequences only where
-// R <= kPrepMaxRows and one phase).  `v_bf16`: the V image is written first; null: it is there already.
+// R <= kPrepMaxRows and one phase, and where w64_shape says the same of all).  `v_bf16`: the V image is written first;
+// null: it is there already.
 static int attn_core(const prism_params* params, const HeadStrides& hs, const SeqTable& seqs, const AttnWs& W,
-                     bool w64_takes, const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws,
+                     const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws,
                      const int32_t* row_ptr, const int32_t* col_idx, void* out_bf16, float* lse, hipStream_t st) {
   const int h = params->n_q_heads, h_kv = params->n_kv_heads, d = params->head_dim;
   const int N = seqs.nsum;
@@ -1731,14 +1704,14 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
   uint16_t* vp = reinterpret_cast<uint16_t*>(ws + W.image);
-  uint16_t* vp16 = W.has16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
-  int32_t* range_flags = W.has16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
+  const bool with16 = w64_shape(params);
+  uint16_t* vp16 = with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
+  int32_t* range_flags = with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
   uint16_t* op = (uint16_t*)out_bf16;
-  // Blocks of 128 tokens go through the 64-queries-per-wave kernel when every list is clean
+  // Whole blocks of 128 tokens go through the 64-queries-per-wave kernel when every list is clean
   // (decided on the device, so the general kernel is queued behind it and returns at once unless
   // the lists turn out to need it).
-  const bool w64 = W.has16 && w64_takes && !stream_only &&
-                   !(params->flags & PRISM_FLAG_GENERAL_KERNEL);
+  const bool w64 = with16 && !stream_only && !(params->flags & PRISM_FLAG_GENERAL_KERNEL);
   // B = 64 with an even number of blocks: the pair kernel (two q-blocks per workgroup sharing the tiles of
   // the union of their lists) takes the call when every list is ascending and clean; decided on the
   // device in the same way.
@@ -1881,7 +1854,7 @@ extern "C" int prism_sparse_attn_pre(const prism_params* params, const void* q_b
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
   return attn_core(params, contiguous_heads(params), one_sequence(params, col_count),
-                   attn_ws_in(params, v_image_bytes), w64_call(params), q_bf16, k_bf16, nullptr, static_cast<char*>(v_image),
+                   attn_ws(params), q_bf16, k_bf16, nullptr, static_cast<char*>(v_image),
                    row_ptr, col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
@@ -1896,43 +1869,36 @@ extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16,
   rc = check_image(params, workspace, workspace_bytes);
   if (rc != PRISM_OK) return rc;
   return attn_core(params, contiguous_heads(params), one_sequence(params, col_count),
-                   attn_ws_in(params, workspace_bytes), w64_call(params), q_bf16, k_bf16, v_bf16, static_cast<char*>(workspace), row_ptr,
+                   attn_ws(params), q_bf16, k_bf16, v_bf16, static_cast<char*>(workspace), row_ptr,
                    col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
 // ---- packed variable-length batches: groups of sequences, one after the other on the stream ---------
-static int varlen_workspace(const prism_params* params, const int32_t* cu_seqlens, int n_seqs, size_t* bytes,
-                            size_t* least_bytes) {
+extern "C" int prism_sparse_attn_varlen_workspace_bytes(const prism_params* params, const int32_t* cu_seqlens,
+                                                        int n_seqs, size_t* bytes) {
   if (bytes == nullptr) return PRISM_ERR_INVALID_ARG;
   int rc = prism_varlen_layout(params, cu_seqlens, n_seqs, nullptr, nullptr, nullptr);
   if (rc != PRISM_OK) return rc;
-  size_t need = 0, least = 0;
+  size_t need = 0;
   for (int s = 0; s < n_seqs; ++s) {
     prism_params ps = *params;
     ps.seq_len = cu_seqlens[s + 1] - cu_seqlens[s];
-    const size_t all = attn_ws(&ps).total, few = attn_least(&ps);
-    need = all > need ? all : need;
-    least = few > least ? few : least;
+    const size_t b = attn_ws(&ps).total;
+    need = b > need ? b : need;
   }
-  if (least_bytes != nullptr) *least_bytes = least;
   *bytes = need;
   return PRISM_OK;
-}
-
-extern "C" int prism_sparse_attn_varlen_workspace_bytes(const prism_params* params, const int32_t* cu_seqlens,
-                                                        int n_seqs, size_t* bytes) {
-  return varlen_workspace(params, cu_seqlens, n_seqs, bytes, nullptr);
 }
 
 extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_t* cu_seqlens, int n_seqs,
                                         const void* q_bf16, const void* k_bf16, const void* v_bf16,
                                         const int32_t* row_ptr, const int32_t* col_idx, void* out_bf16,
                                         float* lse, void* workspace, size_t workspace_bytes, void* stream) {
-  size_t need = 0, least = 0;
-  int rc = varlen_workspace(params, cu_seqlens, n_seqs, &need, &least);
+  size_t need = 0;
+  int rc = prism_sparse_attn_varlen_workspace_bytes(params, cu_seqlens, n_seqs, &need);
   if (rc != PRISM_OK) return rc;
   if (!q_bf16 || !k_bf16 || !v_bf16 || !row_ptr || !col_idx || !out_bf16) return PRISM_ERR_INVALID_ARG;
-  if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < least)
+  if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return PRISM_ERR_WORKSPACE;
   const size_t d = params->head_dim, T = params->seq_len;
   const HeadStrides hs{T * d, T * d, T};
@@ -1943,20 +1909,27 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
     for (int i = 0; i < t.n; ++i) even = even && t.s[i].N % 2 == 0;
     return even;
   };
+  // Whole blocks of 128 and ragged lengths have kernels of their own (w64_shape), here as in calls on one sequence:
+  // a group is of one kind.
+  auto kind = [&](const SeqInfo& q) {
+    prism_params ps = *params;
+    ps.seq_len = q.L;
+    return w64_shape(&ps);
+  };
+  auto layout = [&](const SeqTable& t) { return attn_layout(params, t.nsum, kind(t.s[0]), pairs(t)); };
   // Sequences share their launches while the one-launch preparation can take them all, their heads form one phase
   // and the workspace holds them.
   auto fits = [&](const SeqTable& t) {
     return (int64_t)params->n_q_heads * t.nsum <= kPrepMaxRows && params->n_q_heads < (1 << kSeqShift) &&
-           heads_in_cache(params, t) >= params->n_kv_heads && attn_layout(params, t.nsum, pairs(t), Image16::kLast).total <= workspace_bytes;
+           kind(t.s[t.n - 1]) == kind(t.s[0]) && heads_in_cache(params, t) >= params->n_kv_heads &&
+           layout(t).total <= workspace_bytes;
   };
   auto run = [&](const SeqTable& t, const prism_params& ps) {
-    const AttnWs W = t.n > 1 ? attn_layout(params, t.nsum, pairs(t), Image16::kLast) : attn_ws_in(&ps, workspace_bytes);
-    const bool w64 = t.n > 1 || w64_call(&ps);
     const size_t tok = t.n > 1 ? 0 : t.s[0].tok0;
     SeqTable at = t;
     if (t.n == 1) at.s[0].tok0 = 0, at.s[0].row0 = 0, at.s[0].col0 = 0;   // one sequence: through the pointers
     const int64_t ro = t.n > 1 ? 0 : t.s[0].row0, co = t.n > 1 ? 0 : t.s[0].col0;
-    return attn_core(&ps, hs, at, W, w64, (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
+    return attn_core(&ps, hs, at, layout(t), (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
                      (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), row_ptr + ro, col_idx + co,
                      (uint16_t*)out_bf16 + tok * d, lse != nullptr ? lse + tok : nullptr, st);
   };

@@ -1,5 +1,5 @@
-"""Ragged last blocks at B = 128, d = 128 on the hand-scheduled kernel: tails of one token, around the 32 or 64
-queries of a wave and one short of a block; causal and bidirectional; nothing written past the last row."""
+"""Ragged last blocks at B = 128, d = 128: tails of one token, around the 32 queries of a wave and one short of a block;
+causal and bidirectional; nothing written past the last row; V of any magnitude; one V image for several calls."""
 import numpy as np
 import pytest
 import torch
@@ -16,14 +16,13 @@ pytestmark = pytest.mark.gpu
 OUT_TOL, LSE_TOL = 2e-2, 2e-3
 
 
-# 64 heads x 33 blocks: four waves of 32 queries (a wave of the last block may start past the end); 128 heads: two of 64
-@pytest.mark.parametrize("h,small_workspace", [(64, False), (64, True), (128, False)])
+@pytest.mark.parametrize("h", [64, 128])
 @pytest.mark.parametrize("tail,bidir", [(1, False), (32, True), (63, False), (64, True), (65, False), (65, True), (97, False),
                                         (127, True), (1, True)])
-def test_ragged_last_block(tail, bidir, h, small_workspace):
+def test_ragged_last_block(tail, bidir, h):
     hkv, B, N = 2, 128, 33
     L = (N - 1) * B + tail
-    print(f"case h={h} L={L} bidirectional={bidir} small workspace={small_workspace}", flush=True)
+    print(f"case h={h} L={L} bidirectional={bidir}", flush=True)
     rng = np.random.default_rng(100 + tail + bidir)
     Qb, Kb, Vb = (wl.f32_to_bf16_bits(rng.standard_normal((n, L, 128)).astype(np.float32) * a)
                   for n, a in ((h, 1.5), (hkv, 1.5), (hkv, 1.0)))
@@ -39,8 +38,6 @@ def test_ragged_last_block(tail, bidir, h, small_workspace):
     rp_d, ci_d, cnt = gu.csr_to_device(*orc.mask_to_csr(mask))
     qd, kd, vd = (pb.bf16_bits_to_device(x) for x in (Qb, Kb, Vb))
     need = pb.prism_sparse_attn_workspace_bytes(params)
-    if small_workspace:                                     # without room for the second V image: the general kernel
-        need -= hkv * N * B * 128 * 2
     # guard elements behind the outputs
     out_g = torch.full((h * L * 128 + 4096,), 7.0, dtype=torch.bfloat16, device="cuda")
     lse_g = torch.full((h * L + 128,), 7.0, dtype=torch.float32, device="cuda")
@@ -73,7 +70,7 @@ def test_one_image_for_calls_with_other_query_heads():
     full = pb.make_params(16, hkv, L, B)
     image = pb.alloc_workspace(pb.prism_sparse_attn_workspace_bytes(full))
     pb.prism_v_image(full, v, image)
-    for n in (16, 8, 2):                                   # 336 and 168 rows, and 42, which the general kernel takes
+    for n in (16, 8, 2):
         part = pb.make_params(n, hkv, L, B)
         _, rp, ci, _ = pb.alloc_estimate_outputs(part)
         pb.prism_causal_csr(part, rp, ci, ci.numel())
@@ -83,3 +80,95 @@ def test_one_image_for_calls_with_other_query_heads():
         ref, ref_lse = gu.gpu_sparse_attn(part, qs, k, v, rp, ci, ci.numel())
         torch.cuda.synchronize()
         assert torch.equal(out, ref) and torch.equal(lse, ref_lse), n
+
+
+def test_image_calls_are_right_whatever_the_buffer_holds():
+    """An image written for some number of q-heads, then attention with others, in buffers of several sizes: every call that
+    is accepted gives what one call with a workspace of its own gives, before and after calls with other q-heads."""
+    hkv, L = 2, 128 * 20 + 17
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((n, L, 128), generator=g, device="cuda").bfloat16() for n in (16, hkv, hkv))
+    calls = {}
+    for n in (2, 8, 16):
+        p = pb.make_params(n, hkv, L, 128)
+        _, rp, ci, _ = pb.alloc_estimate_outputs(p)
+        pb.prism_causal_csr(p, rp, ci, ci.numel())
+        qs = q[:n].contiguous()
+        calls[n] = (p, qs, rp, ci, gu.gpu_sparse_attn(p, qs, k, v, rp, ci, ci.numel()))
+    need = {n: pb.prism_sparse_attn_workspace_bytes(calls[n][0]) for n in calls}
+    image = hkv * 21 * 128 * 128 * 2
+    accepted = 0
+    for size in (need[2], need[8], need[16] - 256, need[16], need[8] + image, need[16] + image):
+        buf = pb.alloc_workspace(size)[:size]
+        for writer in calls:
+            buf.fill_(0x3c)                                # 1.06 as fp16, a set flag as a word
+            try:
+                pb.prism_v_image(calls[writer][0], v, buf)
+            except pb.PrismError:
+                continue
+            for reader in (16, 8, 2, 8, 16):
+                p, qs, rp, ci, (ref, ref_lse) = calls[reader]
+                out, lse = torch.zeros_like(qs), torch.zeros_like(ref_lse)
+                try:
+                    pb.prism_sparse_attn_pre(p, qs, k, buf, rp, ci, ci.numel(), out, lse)
+                except pb.PrismError:
+                    continue
+                torch.cuda.synchronize()
+                assert torch.equal(out, ref) and torch.equal(lse, ref_lse), (size, writer, reader)
+                accepted += 1
+    assert accepted >= 40
+
+
+def _check_small_values(q, k, v, out):
+    """One head of causal attention in 64 bits; every output within one bf16 rounding (2^-8) of P and one of itself."""
+    L = q.shape[0]
+    x = (q.double() @ k.double().T) / np.sqrt(128.0)
+    p = torch.softmax(x.masked_fill(torch.ones(L, L, dtype=torch.bool, device="cuda").triu(1), -np.inf), -1)
+    ref, size = p @ v.double(), p @ v.double().abs()
+    assert ((out.double() - ref).abs() <= 1.02 * 2.0 ** -8 * (size + ref.abs())).all()
+
+
+@pytest.mark.parametrize("h,hkv,L", [(2, 2, 128 * 5 + 100), (8, 2, 128 * 21 - 1), (65, 1, 128 * 63 + 77)])
+def test_values_of_any_magnitude(h, hkv, L):
+    """V is used as it is given: dims of 1 down to 2^-30 (below 2^-24 fp16 has nothing left), and a token of tiny values."""
+    print(f"case h={h} L={L}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(L)
+    q, k, v = (torch.randn((n, L, 128), generator=g, device="cuda") for n in (h, hkv, hkv))
+    v = v * 2.0 ** -(torch.arange(128, device="cuda") % 31).float()
+    v[:, 7] *= 2.0 ** -20
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    params = pb.make_params(h, hkv, L, 128)
+    _, rp, ci, _ = pb.alloc_estimate_outputs(params)
+    pb.prism_causal_csr(params, rp, ci, ci.numel())
+    out, _ = gu.gpu_sparse_attn(params, q, k, v, rp, ci, ci.numel())
+    for i in {0, h - 1}:
+        _check_small_values(q[i], k[i // (h // hkv)], v[i // (h // hkv)], out[i])
+
+
+@pytest.mark.parametrize("h,hkv,lens", [(8, 2, [128 * 20 + 5, 256, 77, 128 * 9 + 64]), (48, 2, [128 * 60 + 5, 128 * 25, 777])])
+def test_values_of_any_magnitude_in_a_packed_batch(h, hkv, lens):
+    """The same for the ragged sequences of a batch that holds others too."""
+    print(f"case h={h} lens={lens}", flush=True)
+    cu = [0] + np.cumsum(lens).tolist()
+    g = torch.Generator(device="cuda").manual_seed(cu[-1])
+    q, k, v = (torch.randn((n, cu[-1], 128), generator=g, device="cuda") for n in (h, hkv, hkv))
+    small = v * 2.0 ** -(torch.arange(128, device="cuda") % 31).float()
+    for s, L in enumerate(lens):
+        if L % 128:
+            v[:, cu[s]:cu[s + 1]] = small[:, cu[s]:cu[s + 1]]
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    params = pb.make_params(h, hkv, cu[-1], 128)
+    _, ro, co = pb.prism_varlen_layout(params, cu)
+    rp = torch.zeros(ro[-1], dtype=torch.int32, device="cuda")
+    ci = torch.zeros(co[-1], dtype=torch.int32, device="cuda")
+    for s, L in enumerate(lens):
+        one = pb.make_params(h, hkv, L, 128)
+        pb.prism_causal_csr(one, rp[ro[s]:], ci[co[s]:], co[s + 1] - co[s])
+    out = torch.full((h, cu[-1], 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = pb.alloc_workspace(pb.prism_sparse_attn_varlen_workspace_bytes(params, cu) + (64 << 20))
+    pb.prism_sparse_attn_varlen(params, cu, q, k, v, rp, ci, out, None, ws)
+    torch.cuda.synchronize()
+    for s in range(len(lens)):
+        at = slice(cu[s], cu[s + 1])
+        for i in (0, h - 1):
+            _check_small_values(q[i, at], k[i // (h // hkv), at], v[i // (h // hkv), at], out[i, at])
