@@ -36,7 +36,7 @@ template <int BLK, int D, int kThreads>
 __device__ __forceinline__ void vt_image_tile(uint16_t (&tile)[BLK][D + 2], int& s_over,
                                               const uint16_t* __restrict__ src, int cnt,
                                               uint16_t* __restrict__ dstb, uint16_t* __restrict__ dst16,
-                                              int32_t* __restrict__ range_flag) {
+                                              int32_t* __restrict__ range_flag, int flag_value) {
   const int t = threadIdx.x;
   if (t == 0) s_over = 0;
   constexpr int RCH = D / 8;                         // 16-byte chunks per token row
@@ -75,7 +75,7 @@ __device__ __forceinline__ void vt_image_tile(uint16_t (&tile)[BLK][D + 2], int&
   if (dst16 != nullptr) {
     if (over) s_over = 1;                            // benign race: every writer stores 1
     __syncthreads();
-    if (t == 0) *range_flag = s_over;
+    if (t == 0) *range_flag = s_over != 0 ? flag_value : 0;
   }
 }
 
@@ -91,32 +91,32 @@ __global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restric
   const size_t at = ((size_t)kvh * N + blk) * (size_t)D * BLK;
   vt_image_tile<BLK, D, 256>(tile, s_over, v + (size_t)kvh * kv_head_stride + (size_t)blk * BLK * D,
                              min(BLK, L - blk * BLK), vt + at, vt16 != nullptr ? vt16 + at : nullptr,
-                             vt16 != nullptr ? range_flags + kvh * N + blk : nullptr);
+                             vt16 != nullptr ? range_flags + kvh * N + blk : nullptr, 1);
 }
 
 // A queue entry names its sequence in the high bits of the head number (only where a group holds several).
 constexpr int kSeqShift = 20;
 
-// What decides, on the device, whether the lists and values of a call suit the specialised attention kernels:
-// the call is "dirty" when any word of the two arrays is not zero.
+// What decides, on the device, whether the lists and values of a sequence suit the specialised attention kernels: sequence
+// s of the call is "dirty" when bit s of any word of the two arrays is set.
 struct DirtyFlags {
   const int32_t* a;
   const int32_t* b;
   int32_t na, nb;
 };
-// The verdict has a word of its own.  Every wave reads it behind the last barrier here, so a word that the caller goes on
-// to write (the queue position, say) could change under a wave that reads late.
+// The dirty sequences, one bit each.  The answer has a word of its own: every wave reads it behind the last barrier here,
+// so a word that the caller goes on to write (the queue position, say) could change under a wave that reads late.
 template <int kThreads>
-__device__ __forceinline__ bool call_is_dirty(const DirtyFlags& f) {
+__device__ __forceinline__ int dirty_sequences(const DirtyFlags& f) {
   __shared__ int verdict;
   if (threadIdx.x == 0) verdict = 0;
   int bad = 0;
   for (int i = threadIdx.x; i < f.na; i += kThreads) bad |= f.a[i];
   for (int i = threadIdx.x; i < f.nb; i += kThreads) bad |= f.b[i];
   __syncthreads();
-  if (bad != 0) verdict = 1;                         // every writer stores 1
+  if (bad != 0) atomicOr(&verdict, bad);
   __syncthreads();
-  return __builtin_amdgcn_readfirstlane(verdict) != 0;
+  return __builtin_amdgcn_readfirstlane(verdict);
 }
 
 // =====================================================================================
@@ -298,7 +298,8 @@ constexpr int kXcds = 8;
 constexpr int kPlanStart = 0, kPlanLen = 8, kPlanCounter = 16, kPlanFlags = 24, kPlanInts = 32;
 // plan[kPlanFlags]: bit 0 = some list holds an entry that must be skipped (negative, beyond the
 // row's last admissible block): such lists go through the general kernel, clean lists through the
-// 64-queries-per-wave kernel; each of the two kernels returns at once when it is not its turn.
+// 64-queries-per-wave kernel, each sequence of a packed batch for itself; each of the two kernels returns at once when
+// it is not its turn.
 constexpr int kFlagDirtyLists = 1;
 
 // Pull counters of the queues.  The one-launch preparation spreads them over cache lines of their own and starts
@@ -323,8 +324,10 @@ __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len,
 // rows (q-blocks 2u' and 2u' + 1 of a head, whose two lists lie one behind the other in col_idx); the
 // workgroup walks the union of the two lists in ascending order, copies every tile of the union once,
 // and the waves of a q-block compute only in the steps whose block their own list names.  `flags` is what
-// the list check found: the pair kernel returns at once on a dirty call, the plain
-// kernel launched behind it (only_dirty) returns at once on a clean one.
+// the list check found.  A kernel launched behind another one takes what that one left (only_dirty): behind the pair
+// kernel, which returns at once if any sequence is dirty, the whole call then (kDirtyCall; both give the same bits); behind
+// the 64-queries-per-wave kernel the dirty sequences (kDirtySequences), so that no sequence's bits follow from the others'.
+enum { kEverything, kDirtyCall, kDirtySequences };
 template <int BLK, bool kStreamOnly, int D, bool kPair>
 __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D, kPair>::kWavesPerSimd)) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
@@ -339,12 +342,14 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   __shared__ __attribute__((aligned(16))) char lds_k[C::kTileBytes * C::kBuffers];
   __shared__ __attribute__((aligned(16))) char lds_v[C::kTileBytes * C::kBuffers];
   __shared__ int next_item, next_queue;
+  int take = ~0;                                            // the sequences that are this launch's to do
   if (kPair) {
-    if (call_is_dirty<C::kThreads>(flags)) return;   // the plain kernel takes this call
-  } else if (only_dirty) {
-    const bool dirty = call_is_dirty<C::kThreads>(flags);
-    if (blockIdx.x == 0 && threadIdx.x == 0) plan[kPlanFlags] = dirty ? kFlagDirtyLists : 0;
-    if (!dirty) return;                                     // the kernel launched in front of this one took it
+    if (dirty_sequences<C::kThreads>(flags) != 0) return;   // the plain kernel takes this call
+  } else if (only_dirty != kEverything) {
+    const int dirty = dirty_sequences<C::kThreads>(flags);
+    if (blockIdx.x == 0 && threadIdx.x == 0) plan[kPlanFlags] = dirty != 0 ? kFlagDirtyLists : 0;
+    if (dirty == 0) return;                                 // the kernel launched in front of this one took it
+    if (only_dirty == kDirtySequences) take = dirty;
   }
 
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -460,7 +465,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     int v = (cur_y >> 16) & 0xffff;
     int it = cur_z;
     const int end = cur_w;
-    const bool has_work = kind_cur == kItemRow && it < end;
+    const bool mine = ((take >> sq) & 1) != 0;
+    const bool has_work = kind_cur == kItemRow && it < end && mine;
     const int kvh = hq / g;
     // `u` is the index of the row among the head's rows: a q-block, or a pair of them
     const int qrow = u * (C::kWaves * 32) + wave * 32 + l32;   // >= L for the padding rows of a ragged last block
@@ -468,8 +474,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     int kind_nxt = kItemEnd;
 
     if (!has_work) {
-      // a row without a valid entry (o = 0, lse = -inf): no tile work; pull the next row right away
-      if (kind_cur == kItemRow && qrow < L) {
+      // a row without a valid entry (o = 0, lse = -inf), or another kernel's: no tile work; pull the next row right away
+      if (kind_cur == kItemRow && mine && qrow < L) {
         uint16_t* op = out + (size_t)hq * hs.q + (size_t)(tok0 + qrow) * D + hf * (D / 2);
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
@@ -834,7 +840,8 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) char lds_tiles[65536];
   __shared__ int s_pulled, s_queue;
-  if (call_is_dirty<128 / kQ * 64>(flags)) return;          // the general kernel takes this call
+  const int dirty = dirty_sequences<128 / kQ * 64>(flags);  // the general kernel takes these
+  if (dirty == (1 << seqs.n) - 1) return;
 
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -916,10 +923,11 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
     const int q0 = u * 128 + wave * kQ;                                          // this wave's first query
     const size_t tok0 = (size_t)seqs.s[sq].tok0 + q0;                            // its token in the tensors
     const size_t row0 = (size_t)hq * hs.q + tok0 * kHeadDim;                     // its element offset in Q / O
-    if (it >= end) {
-      // a row without entries: o = 0, lse = -inf
+    const bool mine = ((dirty >> sq) & 1) == 0;
+    if (it >= end || !mine) {
+      // a row without entries (o = 0, lse = -inf), or the general kernel's
       const int r = lane;                                   // one row per lane
-      if (r < kQ) {
+      if (mine && r < kQ) {
         uint16_t* op = out + row0 + (size_t)r * kHeadDim;
 #pragma unroll
         for (int c = 0; c < 16; ++c) *reinterpret_cast<uint4*>(op + c * 8) = make_uint4(0u, 0u, 0u, 0u);
@@ -1226,7 +1234,7 @@ struct PrepArgs {
   int32_t *range_flags, *check;
   int4 *items, *pair_items;
   int32_t *plan, *pair_plan;
-  int32_t *counters, *pair_counters;
+  int32_t *counters, *pair_counters;       // without a second plan: counters of the first one for a second kernel
   int32_t counter_stride;
   int32_t grid, pair_grid;                 // workgroups of the attention kernels
   int32_t h, h_kv, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
@@ -1246,7 +1254,7 @@ struct PlanLds {
 template <int CH>
 __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const SeqTable& seqs, int stride,
                                           int n_queues, int grid, int32_t* __restrict__ counters,
-                                          int4* __restrict__ items, int32_t* __restrict__ plan) {
+                                          int32_t* __restrict__ more_counters, int4* __restrict__ items, int32_t* __restrict__ plan) {
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int per_head = seqs.nsum >> (stride - 1);
   const int R = a.h * per_head;
@@ -1367,7 +1375,9 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     plan[kPlanCounter + t] = 0;
     plan[kPlanFlags + t] = 0;
     // the first pulls of queue t belong to the workgroups t, t + n_queues, ...
-    counters[t * a.counter_stride] = t < n_queues ? (grid - t + n_queues - 1) / n_queues : 0;
+    const int dealt = t < n_queues ? (grid - t + n_queues - 1) / n_queues : 0;
+    counters[t * a.counter_stride] = dealt;
+    if (more_counters != nullptr) more_counters[t * a.counter_stride] = dealt;
   }
   // rank becomes the row's entry, cum its list's first element
 #pragma unroll
@@ -1404,18 +1414,19 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   }
 }
 
-// Does some list of the 64 rows of this workgroup hold an entry to skip (queue_validate_kernel's question)?
+// Which sequences have, among the 64 rows of this workgroup, a list with an entry to skip (queue_validate_kernel's
+// question)?
 __device__ __forceinline__ void check_rows(const PrepArgs& a, const SeqTable& seqs, int wg, int& s_bad) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int R = a.h * seqs.nsum;
-  bool bad = false;
+  int bad_seqs = 0;
   for (int j = 0; j < kCheckRows / 16; ++j) {
     const int r = wg * kCheckRows + j * 16 + wave;
     if (r >= R) break;
     const int s = seq_of(seqs, r, a.h);
     const int rr = r - a.h * seqs.s[s].blk0, N = seqs.s[s].N, cap = seqs.s[s].cap;
     int b = a.row_ptr[seqs.s[s].row0 + rr], e = a.row_ptr[seqs.s[s].row0 + rr + 1];
-    bad |= b < 0 || b > cap || e < b || e > cap;
+    bool bad = b < 0 || b > cap || e < b || e > cap;
     b = b < 0 ? 0 : (b > cap ? cap : b);
     e = e < b ? b : (e > cap ? cap : e);
     const int vmax = a.causal ? rr % N : N - 1;
@@ -1425,10 +1436,11 @@ __device__ __forceinline__ void check_rows(const PrepArgs& a, const SeqTable& se
       bad |= v < 0 || v > vmax;
       if (a.need_sorted && i + 1 < e) bad |= cols[i + 1] <= v;
     }
+    if (bad) bad_seqs |= 1 << s;
   }
   if (threadIdx.x == 0) s_bad = 0;
   __syncthreads();
-  if (bad) s_bad = 1;                                // every writer stores 1
+  if (bad_seqs != 0) atomicOr(&s_bad, bad_seqs);
   __syncthreads();
   if (threadIdx.x == 0) a.check[wg] = s_bad;
 }
@@ -1460,11 +1472,12 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
     int4* items = wg == 0 ? a.items : a.pair_items;
     int32_t* plan = wg == 0 ? a.plan : a.pair_plan;
     int32_t* counters = wg == 0 ? a.counters : a.pair_counters;
+    int32_t* more = a.n_plans == 1 ? a.pair_counters : nullptr;
     const int grid = wg == 0 ? a.grid : a.pair_grid;
-    if (R <= kPrepThreads) plan_rows<1>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
-    else if (R <= 2 * kPrepThreads) plan_rows<2>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
-    else if (R <= 4 * kPrepThreads) plan_rows<4>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
-    else plan_rows<8>(lds.plan, a, seqs, stride, n_queues, grid, counters, items, plan);
+    if (R <= kPrepThreads) plan_rows<1>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 2 * kPrepThreads) plan_rows<2>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 4 * kPrepThreads) plan_rows<4>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else plan_rows<8>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
     return;
   }
   wg -= a.n_plans;
@@ -1480,7 +1493,7 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
   vt_image_tile<BLK, D, kPrepThreads>(
       lds.tile, s_over, a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * BLK) * D,
       min(BLK, seqs.s[s].L - blk * BLK), a.vt + at, a.vt16 != nullptr ? a.vt16 + at : nullptr,
-      a.vt16 != nullptr ? a.range_flags + wg : nullptr);
+      a.vt16 != nullptr ? a.range_flags + wg : nullptr, 1 << s);
 }
 
 }  // namespace prism
@@ -1708,9 +1721,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   uint16_t* vp16 = with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
   int32_t* range_flags = with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
   uint16_t* op = (uint16_t*)out_bf16;
-  // Whole blocks of 128 tokens go through the 64-queries-per-wave kernel when every list is clean
-  // (decided on the device, so the general kernel is queued behind it and returns at once unless
-  // the lists turn out to need it).
+  // Whole blocks of 128 tokens go through the 64-queries-per-wave kernel when every list of a sequence is clean
+  // (decided on the device, so the general kernel is queued behind it, takes the sequences whose lists or values turn
+  // out to need it and returns at once where none do).
   const bool w64 = with16 && !stream_only && !(params->flags & PRISM_FLAG_GENERAL_KERNEL);
   // B = 64 with an even number of blocks: the pair kernel (two q-blocks per workgroup sharing the tiles of
   // the union of their lists) takes the call when every list is ascending and clean; decided on the
@@ -1723,7 +1736,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   constexpr int kPairMinRows = 4096;
   const bool pair = W.pair_plan != W.pair_items && !stream_only && !(params->flags & PRISM_FLAG_GENERAL_KERNEL) &&
                     ((R >= kPairMinRows && d >= 128) || (params->flags & PRISM_FLAG_PAIR_KERNEL));
-  const int only_dirty = (w64 || pair) ? 1 : 0;
+  const int only_dirty = w64 ? kDirtySequences : (pair ? kDirtyCall : kEverything);
   int4* pair_items = reinterpret_cast<int4*>(ws + W.pair_items);
   int32_t* pair_plan = reinterpret_cast<int32_t*>(ws + W.pair_plan);
   const int pair_grid = pair ? persistent_grid(R / 2, d > 128 ? 1 : 2) : 0;   // 4 waves and 2 * 64 * d * 2 bytes of LDS each
@@ -1737,6 +1750,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // without an image beside it) would no longer hide behind the image, and the parts run as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   PullCounters pulls = {plan + kPlanCounter, 1, 0}, pair_pulls = {pair_plan + kPlanCounter, 1, 0};
+  PullCounters later_pulls = pulls;        // of the kernel behind the 64-queries-per-wave one, which may have used its own
   if (R <= kPrepMaxRows && pc.n_phases == 1) {
     PrepArgs pa = {};
     pa.row_ptr = row_ptr;
@@ -1756,12 +1770,12 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.n_queues = pc.n_queues;
     pa.pair_queues = pair_queues;
     pa.n_plans = pair ? 2 : 1;
-    pa.n_check = only_dirty ? (R + kCheckRows - 1) / kCheckRows : 0;
+    pa.n_check = only_dirty != kEverything ? (R + kCheckRows - 1) / kCheckRows : 0;
     pa.need_sorted = pair ? 1 : 0;
     // two sets of 8 counters in row_part, which this path has no other use for, up to a 128-byte line each
     pulls = PullCounters{row_part, 32, 1};
     while ((size_t)pulls.stride * 2 * kXcds * sizeof(int32_t) > W.bins - W.row_part) pulls.stride >>= 1;
-    pair_pulls = PullCounters{row_part + pulls.stride * kXcds, pulls.stride, 1};
+    pair_pulls = later_pulls = PullCounters{row_part + pulls.stride * kXcds, pulls.stride, 1};
     pa.counters = pulls.at;
     pa.pair_counters = pair_pulls.at;
     pa.counter_stride = pulls.stride;
@@ -1792,7 +1806,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
       pp.n_queues = pair_queues;
       build_plan(pp, row_ptr, col_idx, bins, parts, row_rank, row_part, pair_plan, pair_items, st);
     }
-    if (only_dirty) {
+    if (only_dirty != kEverything) {
       const int by_flags = (n_range_flags + 255) / 256;
       hipLaunchKernelGGL(queue_validate_kernel, dim3((R + 3) / 4 > by_flags ? (R + 3) / 4 : by_flags), dim3(256), 0, st,
                          row_ptr, col_idx, h, N, pc.cap, causal, pair ? 1 : 0, range_flags, n_range_flags, plan);
@@ -1823,7 +1837,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
                          pulls, flags, op, lse, h, h_kv, seqs, hs, causal);
   }
 #define PRISM_ATTN(BLK, SO, D)                                                                                \
-  launch_attn<BLK, SO, D>(grid, st, pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
+  launch_attn<BLK, SO, D>(grid, st, w64 ? later_pulls : pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
                           hs, causal, only_dirty)
   if (stream_only) {
     // measurement aid of the d = 128 kernels only
