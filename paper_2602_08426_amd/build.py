@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
@@ -21,6 +22,8 @@ HIPCC_FLAGS = [
     "-Wno-unused-command-line-argument",
     # queue pulls stay plain returning atomics whose result is waited for where it is used
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
+    # the registers of every kernel, for check_registers
+    "-Rpass-analysis=kernel-resource-usage",
 ]
 
 
@@ -31,13 +34,43 @@ def _compile(sources: list[str], out_path: str, verbose: bool, extra_flags: list
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
-    noise = "is not a recognized feature for this target"
-    err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
+    noise = ("is not a recognized feature for this target", "kernel-resource-usage")
+    err = "\n".join(l for l in res.stderr.splitlines() if not any(n in l for n in noise))
     if res.returncode != 0:
         raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
     if verbose and err.strip():
         print(err, file=sys.stderr)
+    if SOURCES[-1] in sources:
+        try:
+            check_registers(res.stderr)
+        except RuntimeError:
+            os.remove(out_path)
+            raise
     return out_path
+
+
+def check_registers(remarks: str, bodies: dict[int, tuple[int, int]] | None = None) -> None:
+    """The generated row loops name their registers themselves.  A kernel around one is right only if the compiler set
+    aside as many VGPRs and AGPRs as the loop goes up to (the first AGPR lies behind the last VGPR it counted) and
+    spilled none, and the four-wave form shares a CU with another workgroup only within 256 registers together.  The
+    compiler warns that the four-wave loop clobbers registers it has reserved and gives no word on what that means for
+    the count, so every build holds the counts it reports (`remarks`) against the loops' own (`bodies`)."""
+    if bodies is None:
+        bodies = {}
+        for q, name in ((64, "prism_attn_w64_body.inc"), (32, "prism_attn_w32_body.inc")):
+            with open(os.path.join(CSRC, name)) as f:
+                m = re.search(r"registers: (\d+) VGPRs, (\d+) AGPRs", f.read(400))
+            bodies[q] = (int(m.group(1)), int(m.group(2)))
+    for q, (vgprs, agprs) in bodies.items():
+        m = re.search(rf"Function Name: \S*sparse_attn_w64_kernelILi{q}E(.*?)LDS Size", remarks, re.S)
+        if m is None:
+            raise RuntimeError(f"the compiler reports no registers of sparse_attn_w64_kernel<{q}>")
+        got = {k: int(v) for k, v in re.findall(r"(VGPRs|AGPRs|VGPRs Spill|ScratchSize \[bytes/lane\]): (\d+)", m.group(1))}
+        together = -(-got["VGPRs"] // 4) * 4 + got["AGPRs"]
+        if (got["VGPRs"] < vgprs or got["AGPRs"] < agprs or got["VGPRs Spill"] or got["ScratchSize [bytes/lane]"] or
+                together > (512 if q == 64 else 256)):
+            raise RuntimeError(f"sparse_attn_w64_kernel<{q}>: its row loop needs {vgprs} VGPRs and {agprs} AGPRs, "
+                               f"the compiler counted {got}")
 
 
 def build_library(verbose: bool = False, extra_flags: list[str] | None = None) -> str:
@@ -85,6 +118,7 @@ def build_ablation(experiment: str, out_path: str, verbose: bool = False) -> str
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError(f"hipcc failed ({res.returncode}):\n{res.stderr}")
+        check_registers(res.stderr)
     return out_path
 
 

@@ -1056,6 +1056,8 @@ def emit(path, sequential=False):
     clob_s = [f"s{i}" for i in range(40, 96)]
     with open(path, "w") as f:
         f.write("// generated by gen_attn_w64.py -- do not edit\n")
+        # build.py holds the compiled kernel against these
+        f.write(f"// registers: {V_LAST + 1} VGPRs, {len(clob_a)} AGPRs\n")
         f.write("asm volatile(\n")
         for ins in ops:
             f.write(f'    "{ins.text}\\n\\t"\n')

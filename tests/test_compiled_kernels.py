@@ -67,3 +67,32 @@ def test_verdict_word_is_not_written_while_waves_may_still_read_it(kernels):
             elif word is not None and ins.startswith("ds_write_b32"):
                 assert _lds_address(ins, constants) != word, (name, ins)
         assert barriers == 3 and word is not None, name
+
+
+REMARKS = """
+remark: Function Name: _ZN5prism22sparse_attn_w64_kernelILi32EEEvPKt
+remark:     VGPRs: {v} [-Rpass-analysis=kernel-resource-usage]
+remark:     AGPRs: {a}
+remark:     ScratchSize [bytes/lane]: {scratch}
+remark:     VGPRs Spill: {spill}
+remark:     LDS Size [bytes/block]: 65548
+"""
+
+
+@pytest.mark.parametrize("v,a,scratch,spill,good", [
+    (156, 100, 0, 0, True), (156, 96, 0, 0, True),
+    (152, 100, 0, 0, False),                               # the loop's last VGPRs would be the first AGPRs
+    (156, 92, 0, 0, False),
+    (158, 97, 0, 0, False),                                # counted as 160 and 97: one workgroup per CU
+    (156, 100, 16, 0, False), (156, 100, 0, 3, False),
+])
+def test_build_refuses_a_kernel_without_the_registers_of_its_row_loop(v, a, scratch, spill, good):
+    from paper_2602_08426_amd.build import check_registers
+    text = REMARKS.format(v=v, a=a, scratch=scratch, spill=spill)
+    if good:
+        check_registers(text, {32: (156, 96)})
+    else:
+        with pytest.raises(RuntimeError):
+            check_registers(text, {32: (156, 96)})
+    with pytest.raises(RuntimeError):
+        check_registers(text, {64: (256, 256)})            # no such kernel in the report
