@@ -1065,7 +1065,7 @@ def emit(path, sequential=False):
         f.write('    : "v"(t), "s"(q_row), "s"(o_row), "s"(lse_row), "s"(k_head), "s"(vt_head), "s"(col_row),\n')
         f.write('      "s"(n_entries), "s"(u), "s"(causal), "s"(lds_base), "s"(k_bytes), "s"(vt_bytes), "s"(c_first),\n')
         f.write('      "s"(pull_counter)\n')
-        clob = ", ".join(f'"{c}"' for c in clob_v + clob_a + clob_s + ["vcc", "scc", "memory"])
+        clob = ", ".join(f'"{c}"' for c in clob_v + clob_a + clob_s + ["m0", "vcc", "scc", "memory"])
         f.write(f"    : {clob});\n")
     n_mfma = sum(1 for i in ops if i.kind == "mfma")
     print(f"{path}: {len(ops)} instructions, {n_mfma} MFMAs", file=sys.stderr)

@@ -239,7 +239,7 @@ __device__ __forceinline__ void async_load_buffered(u32x4 rs, int tile_off, uint
     asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :
                  : "s"(base), "v"(off), "s"(rs), "s"(tile_off), "n"(i * C::kThreads * 16)
-                 : "memory", "scc");
+                 : "m0", "scc", "memory");
   }
 }
 

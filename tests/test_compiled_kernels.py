@@ -3,10 +3,12 @@ GPU)."""
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 
 from paper_2602_08426_amd import binding as pb
+from paper_2602_08426_amd import build
 
 LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
 
@@ -17,8 +19,7 @@ def kernels(tmp_path_factory):
     if not os.path.exists(os.path.join(LLVM, "llvm-objdump")):
         pytest.skip("no llvm-objdump")
     if not os.path.exists(pb.library_path()):
-        from paper_2602_08426_amd.build import build_library
-        build_library()
+        build.build_library()
     tmp = tmp_path_factory.mktemp("code")
     os.symlink(pb.library_path(), tmp / "lib.so")
     objdump = os.path.join(LLVM, "llvm-objdump")
@@ -87,7 +88,7 @@ remark:     LDS Size [bytes/block]: 65548
     (156, 100, 16, 0, False), (156, 100, 0, 3, False),
 ])
 def test_build_refuses_a_kernel_without_the_registers_of_its_row_loop(v, a, scratch, spill, good):
-    from paper_2602_08426_amd.build import check_registers
+    check_registers = build.check_registers
     text = REMARKS.format(v=v, a=a, scratch=scratch, spill=spill)
     if good:
         check_registers(text, {32: (156, 96)})
@@ -96,3 +97,26 @@ def test_build_refuses_a_kernel_without_the_registers_of_its_row_loop(v, a, scra
             check_registers(text, {32: (156, 96)})
     with pytest.raises(RuntimeError):
         check_registers(text, {64: (256, 256)})            # no such kernel in the report
+
+
+def test_asm_blocks_list_every_scalar_register_they_write(tmp_path):
+    """s40 and up, vcc and M0 in the generated row loops; M0 in the tile copies of the general kernel."""
+    subprocess.run([sys.executable, os.path.join(build.CSRC, "gen_attn_w64.py"), str(tmp_path / "x_w64_body.inc")],
+                   check=True, capture_output=True)
+    blocks = [(tmp_path / n).read_text() for n in ("x_w64_body.inc", "x_w32_body.inc")]
+    with open(os.path.join(build.CSRC, "prism_attn.hip")) as f:
+        blocks += [b for b in re.findall(r"asm volatile\(.*?\);", f.read(), re.S)]
+    seen = 0
+    for text in blocks:
+        code, clobbers = text, set(re.findall(r'"(\w+)"', text.rsplit(":", 1)[1]))
+        written = set()
+        for ins in re.findall(r'(?:"|\\n\\t)([a-z]\w+ [^"\\]+)', code):
+            m = re.match(r"(s_(?!cmp|cbranch|branch|waitcnt|nop|barrier|endpgm|setprio)\w+|v_cmp\w+|v_readfirstlane_b32)"
+                         r" (m0|vcc|exec|s\d+|s\[\d+:\d+\])", ins)
+            if m is None or m.group(2) == "exec":          # saved and restored inside the block
+                continue
+            regs = re.match(r"s\[(\d+):(\d+)\]", m.group(2))
+            written |= ({f"s{i}" for i in range(int(regs.group(1)), int(regs.group(2)) + 1)} if regs else {m.group(2)})
+        seen += "m0" in written
+        assert written <= clobbers, sorted(written - clobbers)
+    assert seen >= 3
