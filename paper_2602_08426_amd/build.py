@@ -42,25 +42,29 @@ def _compile(sources: list[str], out_path: str, verbose: bool, extra_flags: list
         print(err, file=sys.stderr)
     if SOURCES[-1] in sources:
         try:
-            check_registers(res.stderr)
+            check_registers(res.stderr, row_loop_registers(CSRC))
         except RuntimeError:
             os.remove(out_path)
             raise
     return out_path
 
 
-def check_registers(remarks: str, bodies: dict[int, tuple[int, int]] | None = None) -> None:
+def row_loop_registers(folder: str) -> dict[int, tuple[int, int]]:
+    """VGPRs and AGPRs of the generated row loops in `folder`, by queries per wave."""
+    bodies = {}
+    for q, name in ((64, "prism_attn_w64_body.inc"), (32, "prism_attn_w32_body.inc")):
+        with open(os.path.join(folder, name)) as f:
+            m = re.search(r"registers: (\d+) VGPRs, (\d+) AGPRs", f.read(400))
+        bodies[q] = (int(m.group(1)), int(m.group(2)))
+    return bodies
+
+
+def check_registers(remarks: str, bodies: dict[int, tuple[int, int]]) -> None:
     """The generated row loops name their registers themselves.  A kernel around one is right only if the compiler set
     aside as many VGPRs and AGPRs as the loop goes up to (the first AGPR lies behind the last VGPR it counted) and
     spilled none, and the four-wave form shares a CU with another workgroup only within 256 registers together.  The
     compiler warns that the four-wave loop clobbers registers it has reserved and gives no word on what that means for
     the count, so every build holds the counts it reports (`remarks`) against the loops' own (`bodies`)."""
-    if bodies is None:
-        bodies = {}
-        for q, name in ((64, "prism_attn_w64_body.inc"), (32, "prism_attn_w32_body.inc")):
-            with open(os.path.join(CSRC, name)) as f:
-                m = re.search(r"registers: (\d+) VGPRs, (\d+) AGPRs", f.read(400))
-            bodies[q] = (int(m.group(1)), int(m.group(2)))
     for q, (vgprs, agprs) in bodies.items():
         m = re.search(rf"Function Name: \S*sparse_attn_w64_kernelILi{q}E(.*?)LDS Size", remarks, re.S)
         if m is None:
@@ -118,7 +122,7 @@ def build_ablation(experiment: str, out_path: str, verbose: bool = False) -> str
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError(f"hipcc failed ({res.returncode}):\n{res.stderr}")
-        check_registers(res.stderr)
+        check_registers(res.stderr, row_loop_registers(tmp))
     return out_path
 
 
