@@ -89,7 +89,7 @@ def configure(qt):
     FR0 = S0 + 64 * qt      # fragment ring
     V_T = FR0 + 4 * N_FR    # temporaries:
     #   T+0..5 / T+8..13 softmax of query tile 0 / 1;  T+16..25 prologue / epilogue;  V_THR mask thresholds (QT regs);
-    #   V_PULL pulled queue position, V_ONE its increment (drain .. end of row; the debug dump borrows both);
+    #   V_PULL pulled queue position, V_ONE its increment (drain .. end of row);
     #   V_OFF list offset;  V_INF -inf.  With one query tile some of them share registers that are never live together.
     if qt == 1:             # one query tile leaves T+8..13 free
         V_VOFF, V_M, V_L = V_T + 8, V_T + 12, V_T + 13
@@ -831,31 +831,6 @@ def epilogue():
     return ops
 
 
-# ----------------------------------------------------------------------------------------------
-# debugging aid (never part of a product build): dump registers to the buffer whose address came in
-# as the lse pointer, as dbg[i][t] (i = position in `regs`, t = thread 0..127), then leave the row
-# ----------------------------------------------------------------------------------------------
-def dump_and_exit(regs, inp):
-    T = V_T
-    ops = [nop(7), nop(7), nop(7),
-           valu(f"v_and_b32 v{V_ONE}, 63, {inp['t']}", (), vr(V_ONE)),
-           valu(f"v_lshlrev_b32 v{V_ONE}, 2, v{V_ONE}", vr(V_ONE), vr(V_ONE))]
-    for kind, r in regs:
-        if kind == "a":
-            ops.append(valu(f"v_accvgpr_read_b32 v{V_PULL}, a{r}", ar(r), vr(V_PULL)))
-            ops.append(nop(1))
-            src = V_PULL
-        else:
-            src = r
-        ops.append(Ins(f"global_store_dword v{V_ONE}, v{src}, s[{S_LSE}:{S_LSE + 1}]", "vmem", vr(V_ONE) + vr(src)))
-        ops.append(salu(f"s_add_u32 s{S_LSE}, s{S_LSE}, 512"))
-        ops.append(salu(f"s_addc_u32 s{S_LSE + 1}, s{S_LSE + 1}, 0"))
-        ops.append(Ins("s_waitcnt vmcnt(0)", "wait"))
-    ops.append(salu(f"s_branch Lrow_done{LABEL}"))
-    return ops
-
-
-DUMP = os.environ.get("PRISM_W64_DUMP", "")
 # timing experiments (wrong results, same control flow): leave out the tile copies of the steady-state
 # iterations / the softmax arithmetic
 EXPERIMENT = os.environ.get("PRISM_W64_EXPERIMENT", "")
@@ -867,27 +842,8 @@ EXPERIMENT = os.environ.get("PRISM_W64_EXPERIMENT", "")
 def row_program(inp, sequential=False):
     ops = prologue(inp)
     a = ops.append
-    if DUMP == "LDS":
-        ops.append(valu(f"v_and_b32 v{V_T + 27}, 63, {inp['t']}", (), vr(V_T + 27)))
-        ops.append(valu(f"v_lshlrev_b32 v{V_T + 27}, 4, v{V_T + 27}", vr(V_T + 27), vr(V_T + 27)))
-        for kk in range(64):
-            ops.append(Ins(f"ds_read_b32 v{64 + kk}, v{V_T + 27} offset:{kk * 1024}", "lds", vr(V_T + 27), vr(64 + kk)))
-        ops.append(Ins("s_waitcnt lgkmcnt(0)", "wait"))
-        for i, sreg in enumerate((S_WAVE, S_MWAVE, S_LDS, S_T1, S_CV, S_N, S_U)):
-            ops.append(valu(f"v_mov_b32 v{128 + i}, s{sreg}", (), vr(128 + i)))
-        ops.append(valu(f"v_mov_b32 v{128 + 8}, {inp['t']}", (), vr(128 + 8)))
-        ops += dump_and_exit([("v", 64 + i) for i in range(64 + 9)], inp)
-    if DUMP == "S0":
-        ops += [ds_read(FR0, V_KOFF, LDS_K[0]), ds_read(FR0 + 4, V_KOFF + 1, LDS_K[0] + 8192),
-                Ins("s_waitcnt lgkmcnt(0)", "wait")]
-        ops += dump_and_exit([("v", 64 + i) for i in range(64)] + [("a", 128 + i) for i in range(64)] +
-                             [("v", FR0 + i) for i in range(8)] + [("v", V_KOFF + i) for i in range(16)] +
-                             [("v", V_QOFF), ("v", V_QOFF + 1)], inp)
     # block 0, even iteration: no PV yet
     ops += iteration(0, 0, False, True, False, "e0", sequential)
-    if DUMP == "I0":
-        ops += dump_and_exit([("v", 64 + i) for i in range(128)] +
-                             [("v", V_M), ("v", V_M + 1), ("v", V_L), ("v", V_L + 1), ("v", V_ALPHA), ("v", V_ALPHA + 1)], inp)
     a(salu(f"s_cmp_eq_u32 s{S_N}, 1"))
     a(salu(f"s_cbranch_scc1 Lodd_last{LABEL}"))
     ops += iteration(1, 1, True, True, True, "o0", sequential)
@@ -903,11 +859,7 @@ def row_program(inp, sequential=False):
     a(Ins(f"Lodd_last{LABEL}:", "label"))
     ops += iteration(1, 1, True, False, True, "oZ", sequential)
     ops += drain(1)
-    if DUMP == "O":
-        ops += dump_and_exit([("a", i) for i in range(128)] +
-                             [("v", V_M), ("v", V_M + 1), ("v", V_L), ("v", V_L + 1)], inp)
     ops += epilogue()
-    a(Ins(f"Lrow_done{LABEL}:", "label"))
     return ops
 
 
