@@ -125,13 +125,13 @@ __device__ __forceinline__ int dirty_sequences(const DirtyFlags& f) {
 // LDS: K tile [BLK][d] bf16 and V^T tile [d][BLK] bf16 (d = 64, 128, 256), 16-byte chunks XOR-swizzled by
 // row so that the 16-lane column reads are conflict-free.  Tiles are copied global -> LDS
 // asynchronously, without passing through registers.
-// Step per listed kv block, one buffer per tile (each refilled as soon as its last reader is done):
+// Step per listed kv block (each tile buffer is refilled as soon as its last reader is done):
 //     K(j) in LDS | start V(j) copy | S^T = K Q^T | barrier | start K(j+1) copy
 //     online softmax | wait V(j) | barrier | O^T += V^T P^T | wait K(j+1) | barrier
-// and two buffers per tile (AttnCfg::kDouble):
-//     K(j), V(j) in LDS | start K(j+1), V(j+1) copies | S^T | softmax | O^T += V^T P^T | wait both | barrier
-// (one barrier instead of three and no tile latency inside a step; us per layer, one buffer -> two: 16K, d = 256,
-// B = 64 801 -> 780; 12345 tokens, d = 64 254 -> 252, the mean of five inputs).
+// Two buffers per tile (one barrier per step instead of three, both tiles of the next block requested a whole step ahead)
+// fit at 64 x 64, 128 x 64 and 64 x 256 and are no gain over the range: us of attention, one buffer -> two, 32/8 heads: 128 x 64
+// at 8192 tokens 127 -> 123, at 20000 331 -> 345, at 32768 755 -> 790; 64 x 256 at 16320 1374 -> 1432, at 32768 3159 -> 3257;
+// 64 x 64 at 16384 298 -> 303, at 40000 1060 -> 1007.
 // The workgroups are persistent: a workgroup pulls its next row from its XCD's queue at the top
 // of the last step of the current row and reads that row's queue entry during the last PV, so
 // a row switch exposes only the load of the Q rows and of the first K tile.
@@ -151,14 +151,6 @@ struct AttnCfg {
   static constexpr int kDTiles = D / 32;                   // 32-dim tiles of the output
   static constexpr int kKSteps = D / 16;                   // MFMA k-steps of S^T = K Q^T
   static constexpr int kWavesPerSimd = D > 128 ? 1 : 2;    // register budget: 512 or 256 per lane
-  // workgroups that share a CU, by the LDS of their two tiles and their waves
-  static constexpr int kPerCu = D > 128 ? 1 : (BLK == 128 || PAIR ? 2 : 4);
-  // Two buffers per tile where the CU's 160 KB hold them for all of them (not at 128 x 128 and 128 x 256, nor for the
-  // four small workgroups of 64 x 128): both tiles of the next block are then requested a whole step ahead.
-  // Not for the pair form of 64 x 128 either, though it fits: us per layer, one buffer -> two, 28/4 heads at 21376
-  // tokens 668 -> 722, 32/8 at 20480 726 -> 779, at 32768 1506 -> 1481, 16/4 at 65536 2636 -> 2615.
-  static constexpr bool kDouble = !(PAIR && D == 128) && 4 * kTileBytes * kPerCu + 4096 <= 160 * 1024;
-  static constexpr int kBuffers = kDouble ? 2 : 1;
 };
 
 // Asynchronous global -> LDS tile copies (buffer_load_dwordx4 ... lds: every lane fetches 16
@@ -223,26 +215,6 @@ __device__ __forceinline__ void async_load_vt_tile(__amdgpu_buffer_rsrc_t rs, in
                                              vt_piece_offset<BLK, D>(i * C::kThreads + t), tile_off, 0, 0);
 }
 
-// The same copies where both buffers of a tile are in use: a K tile (kIsK) or a V^T tile into the LDS object at byte
-// address lds_addr.  Written in asm because of what the compiler does with the builtin: it takes a copy into one buffer
-// for a write to the whole LDS object and waits for it in front of every read of the other buffer.  There is no
-// result register, M0 is set in the same block, and the waits in front of the reads are explicit (wait_async_loads);
-// copies the compiler does not know of can only make its own waits for other loads longer.
-template <int BLK, int D, bool PAIR, bool kIsK>
-__device__ __forceinline__ void async_load_buffered(u32x4 rs, int tile_off, uint32_t lds_addr, int t) {
-  using C = AttnCfg<BLK, D, PAIR>;
-  const uint32_t base = lds_addr + (uint32_t)__builtin_amdgcn_readfirstlane(t & ~63) * 16u;
-#pragma unroll
-  for (int i = 0; i < C::kPerThread; ++i) {
-    const int p = i * C::kThreads + t;
-    const int off = kIsK ? k_piece_offset<BLK, D>(p) : vt_piece_offset<BLK, D>(p);
-    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(base), "v"(off), "s"(rs), "s"(tile_off), "n"(i * C::kThreads * 16)
-                 : "m0", "scc", "memory");
-  }
-}
-
 // Waits on the vector-memory counter, written with the builtin (immediate: vmcnt in bits 3:0,
 // expcnt = 7 and lgkmcnt = 15 meaning "no wait") rather than inline asm, so that the compiler's
 // own wait-count bookkeeping sees them: it then knows which tile copies have landed and adds no
@@ -252,8 +224,6 @@ __device__ __forceinline__ void wait_async_loads() {
   __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
   asm volatile("" ::: "memory");
 }
-// The wait for copies issued in asm: the compiler does not know that there is anything to wait for.
-__device__ __forceinline__ void wait_buffered_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // all but the youngest tile copy (kPerThread = d/16 vector-memory operations per thread) are complete
 template <int kPerThread>
 __device__ __forceinline__ void wait_async_loads_but_last_tile() {
@@ -339,8 +309,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   using C = AttnCfg<BLK, D, kPair>;
   constexpr int KS = C::kKSteps, DT = C::kDTiles;
   constexpr int KT = BLK / 32;                       // 32-key tiles per kv block
-  __shared__ __attribute__((aligned(16))) char lds_k[C::kTileBytes * C::kBuffers];
-  __shared__ __attribute__((aligned(16))) char lds_v[C::kTileBytes * C::kBuffers];
+  __shared__ __attribute__((aligned(16))) char lds_k[C::kTileBytes];
+  __shared__ __attribute__((aligned(16))) char lds_v[C::kTileBytes];
   __shared__ int next_item, next_queue;
   int take = ~0;                                            // the sequences that are this launch's to do
   if (kPair) {
@@ -359,8 +329,6 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   const int sub = kPair ? __builtin_amdgcn_readfirstlane(wave / C::kRowWaves) : 0;
   // log2(e) / sqrt(d)
   const float sm_scale = 1.4426950408889634f * (D == 64 ? 0.125f : (D == 128 ? 0.08838834764831845f : 0.0625f));
-
-  const uint32_t lds_k_addr = (uint32_t)(size_t)lds_k, lds_v_addr = (uint32_t)(size_t)lds_v;
 
   // LDS read offsets of this lane inside a 32-row slab: row l32, swizzled chunk
   // (2*step + hf) ^ swizzle(row).  The K tile has d/8 chunks per row; the V^T tile has BLK/8
@@ -497,12 +465,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     // K is the caller's tensor: rows past L in a ragged last block are outside the resource and
     // read as zeros.  The V^T image is padded to whole blocks.
     const __amdgpu_buffer_rsrc_t krs = make_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
-    const uint16_t* vt_head = vt + ((size_t)seqs.s[sq].blk0 * (h / g) + (size_t)kvh * N) * BLK * D;
-    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(vt_head, image_head_bytes);
-    // the same resources as words, for the copies into two buffers
-    const size_t ka = (size_t)(k + (size_t)kvh * hs.kv + (size_t)tok0 * D), va = (size_t)vt_head;
-    const u32x4 krw = {(uint32_t)ka, (uint32_t)(ka >> 32) & 0xffffu, head_bytes, 0x00020000u};
-    const u32x4 vrw = {(uint32_t)va, (uint32_t)(va >> 32) & 0xffffu, image_head_bytes, 0x00020000u};
+    const __amdgpu_buffer_rsrc_t vrs =
+        make_rsrc(vt + ((size_t)seqs.s[sq].blk0 * (h / g) + (size_t)kvh * N) * BLK * D, image_head_bytes);
     const int vmax = causal ? u_own : vmax_nc;
 
     // Pair rows: the two lists [it, mid) and [mid, end) are walked together, smallest block first;
@@ -547,14 +511,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
     }
-    if (C::kDouble) {
-      async_load_buffered<BLK, D, kPair, true>(krw, v * C::kTileBytes, lds_k_addr, t);
-      async_load_buffered<BLK, D, kPair, false>(vrw, v * C::kTileBytes, lds_v_addr, t);
-    } else {
-      async_load_k_tile<BLK, D, kPair>(krs, v * C::kTileBytes, lds_k, t);
-    }
-    int cur = 0;                      // byte offset of the buffers that hold K(j) and V(j)
-    if (C::kDouble) wait_buffered_loads();
+    async_load_k_tile<BLK, D, kPair>(krs, v * C::kTileBytes, lds_k, t);
     wait_async_loads();
     tile_barrier();
 
@@ -573,17 +530,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       constexpr bool kLast = decltype(last_tag)::value;
       if (kLast && t == 0) pulled_reg = atomicAdd(counter + my_queue * pulls.stride, 1);
 
-      const char* kb = lds_k + cur;
-      const char* vb = lds_v + cur;
-      if (!C::kDouble) {
-        // ---- V(j) -> LDS, in flight during S^T and the softmax ----
-        async_load_vt_tile<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t);
-      } else if (!kLast) {
-        // ---- K(j+1), V(j+1) -> the other buffers, in flight during the whole step ----
-        const int other = C::kTileBytes - cur;
-        async_load_buffered<BLK, D, kPair, true>(krw, v_next * C::kTileBytes, lds_k_addr + other, t);
-        async_load_buffered<BLK, D, kPair, false>(vrw, v_next * C::kTileBytes, lds_v_addr + other, t);
-      }
+      // ---- V(j) -> LDS, in flight during S^T and the softmax ----
+      async_load_vt_tile<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t);
 
       f32x16 sacc[KT];
       if (kPair) {
@@ -604,7 +552,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
         bf16x8 fr[kDepth];
 #pragma unroll
         for (int i = 0; i < kDepth; ++i)
-          fr[i] = *reinterpret_cast<const bf16x8*>(kb + (i % KT) * kSlab + koff[i / KT]);
+          fr[i] = *reinterpret_cast<const bf16x8*>(lds_k + (i % KT) * kSlab + koff[i / KT]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < kSteps; ++i) {
@@ -612,7 +560,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
           sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % kDepth], qf[ks], ks == 0 ? zero16 : sacc[kt], 0, 0, 0);
           if (i + kDepth < kSteps) {
             const int j = i + kDepth;
-            fr[i % kDepth] = *reinterpret_cast<const bf16x8*>(kb + (j % KT) * kSlab + koff[j / KT]);
+            fr[i % kDepth] = *reinterpret_cast<const bf16x8*>(lds_k + (j % KT) * kSlab + koff[j / KT]);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -621,8 +569,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       }
 
       // every wave is done reading K(j): K(j+1) can start now and land during softmax + PV
-      if (!C::kDouble) tile_barrier();
-      if (!C::kDouble && !kLast) async_load_k_tile<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t);
+      tile_barrier();
+      if (!kLast) async_load_k_tile<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t);
 
       bf16x8 pf[KT][2];
       if (kPair) {
@@ -703,10 +651,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       if (kLast) {
         if (t == 0) next_item = pulled_reg;         // the queue position pulled at the top of the step
         wait_async_loads();                          // this wave's share of V(j) has landed
-      } else if (!C::kDouble) {
+      } else {
         wait_async_loads_but_last_tile<C::kPerThread>();   // ... while the younger loads of K(j+1) may still be in flight
       }
-      if (kLast || !C::kDouble) tile_barrier();      // V(j) complete
+      tile_barrier();                                // V(j) complete
 
       if (kLast) {
         // the next row's queue entry, read through a per-lane (vector) address so that it arrives
@@ -726,7 +674,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
         bf16x8 fr[kDepth];
 #pragma unroll
         for (int i = 0; i < kDepth; ++i)
-          fr[i] = *reinterpret_cast<const bf16x8*>(vb + (i % DT) * (32 * BLK * 2) + voff[i / DT]);
+          fr[i] = *reinterpret_cast<const bf16x8*>(lds_v + (i % DT) * (32 * BLK * 2) + voff[i / DT]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < kSteps; ++i) {
@@ -734,7 +682,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
           oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % kDepth], pf[st >> 1][st & 1], oacc[dt], 0, 0, 0);
           if (i + kDepth < kSteps) {
             const int j = i + kDepth;
-            fr[i % kDepth] = *reinterpret_cast<const bf16x8*>(vb + (j % DT) * (32 * BLK * 2) + voff[j / DT]);
+            fr[i % kDepth] = *reinterpret_cast<const bf16x8*>(lds_v + (j % DT) * (32 * BLK * 2) + voff[j / DT]);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -742,10 +690,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 
       }
 
-      if (C::kDouble) wait_buffered_loads();
       wait_async_loads();              // this wave's share of K(j+1) (or the next row's entry) has landed
       tile_barrier();                  // K(j+1) complete; everyone is done reading V(j)
-      if (C::kDouble) cur = C::kTileBytes - cur;
     };
 
     // The list is walked one entry ahead of its use: col_idx[it + 1] is requested here and

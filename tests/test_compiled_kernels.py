@@ -100,7 +100,7 @@ def test_build_refuses_a_kernel_without_the_registers_of_its_row_loop(v, a, scra
 
 
 def test_asm_blocks_list_every_scalar_register_they_write(tmp_path):
-    """s40 and up, vcc and M0 in the generated row loops; M0 in the tile copies of the general kernel."""
+    """s40 and up, vcc and M0 in the generated row loops, and whatever the blocks of prism_attn.hip set."""
     subprocess.run([sys.executable, os.path.join(build.CSRC, "gen_attn_w64.py"), str(tmp_path / "x_w64_body.inc")],
                    check=True, capture_output=True)
     blocks = [(tmp_path / n).read_text() for n in ("x_w64_body.inc", "x_w32_body.inc")]
@@ -119,4 +119,4 @@ def test_asm_blocks_list_every_scalar_register_they_write(tmp_path):
             written |= ({f"s{i}" for i in range(int(regs.group(1)), int(regs.group(2)) + 1)} if regs else {m.group(2)})
         seen += "m0" in written
         assert written <= clobbers, sorted(written - clobbers)
-    assert seen >= 3
+    assert seen >= 2
