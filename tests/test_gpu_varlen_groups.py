@@ -23,6 +23,10 @@ pytestmark = pytest.mark.gpu
     ([1024, 640, 2048, 384, 500, 128 * 9], 8, 2, 128, 128, True, 64 << 20, "value"),
     ([4096, 640, 2048, 384, 500, 128 * 90], 32, 8, 128, 128, False, 256 << 20, "list"),   # more than 4096 rows
     ([64 * 6, 64 * 2, 64 * 10, 64 * 4], 4, 1, 64, 128, False, 64 << 20, "list"),
+    # the general form of the estimate over several sequences: 384 strips, 624 strips and bidirectional, N > 1024
+    ([8192, 2048, 4096, 3000, 5000], 32, 8, 128, 128, False, 256 << 20, False),
+    ([64 * 300, 64 * 299 + 1, 64 * 5], 16, 4, 64, 64, True, 128 << 20, False),
+    ([64 * 1030, 64 * 20 + 3, 64 * 100, 64 * 513], 2, 1, 64, 128, False, 128 << 20, False),
 ])
 def test_groups_equal_single_calls(lens, h, hkv, B, d, bidir, extra, dirty):
     print(f"case {len(lens)} sequences h={h}/{hkv} B={B} d={d} bidirectional={bidir} extra={extra}", flush=True)
@@ -64,3 +68,28 @@ def test_groups_equal_single_calls(lens, h, hkv, B, d, bidir, extra, dirty):
         o1, l1 = gu.gpu_sparse_attn(ps, qs, ks, vs, rp1, ci1, nnz)
         assert torch.equal(out[:, cu[s]:cu[s + 1]].view(torch.int16), o1.view(torch.int16)), s
         assert torch.equal(lse[:, cu[s]:cu[s + 1]], l1), s
+
+
+@pytest.mark.parametrize("room", [-1, 0, 1 << 20])
+def test_estimate_of_a_batch_is_the_same_in_any_workspace(room):
+    """In the least workspace that is taken (one without room for the row counts of the longest sequence, which goes the
+    general way), in the one the library asks for and in a larger one."""
+    lens, h, hkv, B = [5000, 300, 2048, 4999], 8, 2, 128
+    cu = [0] + np.cumsum(lens).tolist()
+    g = torch.Generator(device="cuda").manual_seed(12)
+    q, k = (torch.randn((n, cu[-1], 128), generator=g, device="cuda").bfloat16() for n in (h, hkv))
+    params = pb.make_params(h, hkv, cu[-1], B)
+    need = pb.prism_estimate_varlen_workspace_bytes(params, cu)
+    least = need - (h * 40 * 4 + 255) // 256 * 256           # ceil(5000 / 128) = 40 blocks
+    mo, ro, co = pb.prism_varlen_layout(params, cu)
+
+    def run(size):
+        mask, rp, ci, info = (torch.full((n,), -7, dtype=t, device="cuda") for n, t in (
+            (mo[-1], torch.int64), (ro[-1], torch.int32), (co[-1], torch.int32), (4 * len(lens), torch.int32)))
+        pb.prism_estimate_varlen(params, cu, q, k, mask, rp, ci, info, pb.alloc_workspace(size)[:size])
+        return mask, rp, ci, info
+
+    for a, b in zip(run(least if room < 0 else need + room), run(need + (64 << 20))):
+        assert torch.equal(a, b)
+    with pytest.raises(pb.PrismError):
+        run(least - 256)
