@@ -1690,9 +1690,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const int pair_queues = pair_grid < kXcds ? 1 : kXcds;
   const int n_range_flags = w64 ? h_kv * N : 0;
 
-  // One launch prepares the call up to kPrepMaxRows rows in one phase: 13.6 us instead of 34.4 us at 2048 rows (8K
-  // tokens, 32 heads), 36.8 instead of 46.4 at 5024, 43.7 instead of 62.6 at 8192 (32K tokens; the image alone takes
-  // 13, 22 and 38 us), 4.8 instead of 13.9 at 32 rows.  Beyond, the plan of a single workgroup (33 us at 5024 rows
+  // One launch prepares the call up to kPrepMaxRows rows in one phase: 14.4 us instead of 34.7 us at 2048 rows (8K
+  // tokens, 32 heads), 38.0 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 45.3 instead of 63.1 at 8192
+  // (32K tokens; the images alone take 13, 22 and 39 us), 5.3 instead of 13.9 at 32 rows.  Beyond, the plan of a single workgroup (33 us at 5024 rows
   // without an image beside it) would no longer hide behind the image, and the parts run as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   PullCounters pulls = {plan + kPlanCounter, 1, 0}, pair_pulls = {pair_plan + kPlanCounter, 1, 0};
@@ -1771,9 +1771,10 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     // The same bits from two waves of 64 queries or from four of 32.  Four take 1.3 instead of 2.2 us per block of a
     // row that has a CU to itself, two need half the LDS reads per block and are 3 % faster where every CU is busy
     // to the end (2048 rows of 64 blocks: 543 against 558 us).  Up to kW32MaxRows rows, 8 per resident workgroup, the
-    // longest rows decide how long a call takes (us, two waves -> four): 8 heads, 8K tokens (512 rows) 95 -> 70;
-    // 32 heads, 8K (2048) 183 -> 147; 4 heads, 128K (4096) 1204 -> 1018; 32 heads, 16K (4096) 404 -> 409; beyond it the
-    // two are even (20011 tokens, 5024 rows: 516 and 514) and then two waves win (32K, 8192 rows: 1120 and 1126).
+    // longest rows decide how long a call takes (us, two waves -> four): 8 heads, 8K tokens (512 rows) 93 -> 71;
+    // 32 heads, 8K (2048) 184 -> 152; 4 heads, 128K (4096) 1010 -> 836; 32 heads, 16K (4096) 396 -> 392; beyond it, with
+    // as many heads, two waves win: 17K (4352 rows) 457 and 460, 20096 tokens (5024) 515 and 530, 32K (8192) 1056 and 1068.
+    // (Few heads with long rows would still want four: 5 heads, 128K, 5120 rows 888 -> 703.)
     constexpr int kW32MaxRows = 4096;
     if (R <= kW32MaxRows)
       hipLaunchKernelGGL(sparse_attn_w64_kernel<32>, dim3(grid), dim3(256), 0, st, qp, kp, vp16, col_idx, items, plan,

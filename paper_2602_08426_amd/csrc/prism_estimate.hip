@@ -828,11 +828,12 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
 // strip, eight per band, so that the two bands run side by side and a wave owns two rows instead of four; the
 // calibration is done here as well instead of in a launch of its own, and the row counts go to `counts`.
 // N <= 512 (two logit strips of 33 KB).  Logits and masks have the bits of select_kernel: a tile's MFMAs and a row's
-// sums keep their order.  Whole estimate, five launches around
-// select_kernel -> three around this one: 1 head, 2K tokens at B = 64 (2 strips) 29.4 -> 17.7 us; 8 heads, 8K 32.2 -> 20.7;
-// 32 heads, 8K (128 strips) 46.5 -> 32.5, 20011 tokens (320 strips) 79.4 -> 69.8; 16 heads, 19290 tokens,
-// bidirectional 71.8 -> 54.9.  At 512 strips and more (32K tokens) its strips no longer run all at once and the four-wave
-// form wins (107 against 113 us; at 896 strips 174 against 209).
+// sums keep their order.  A workgroup of 16 waves with 90 registers a lane has a CU to itself, so up to 256 strips run
+// at once and the strips beyond start a second round; of select_kernel two workgroups share a CU.  Whole estimate, us, five
+// launches around select_kernel -> three around this one: 1 head, 2K tokens at B = 64 (2 strips) 29.4 -> 17.7; 32/8 heads,
+// B = 128: 128 strips 47.6 -> 32.8, 256 64.6 -> 50.6, 288 76.2 -> 64.9, 320 79.0 -> 71.7, 384 88.4 -> 82.3, 448 95.9 -> 92.6,
+// 512 even (105); 28/4 heads, 448 even (88); d = 64: 320 59.1 -> 52.2; d = 256 (16/4 heads, B = 64): 256 79.2 -> 68.2,
+// 320 99.9 -> 95.4, 352 104.2 -> 106.5, 448 120.2 -> 134.5.
 // =====================================================================================
 constexpr int kSmallBlocks = 512;
 template <int kSeqs>
@@ -1472,7 +1473,10 @@ static int run_small(const prism_params* p, const SeqTable& seqs, const BandMap&
   return run_small_on<kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, counts, st);
 }
 
-constexpr int64_t kSmallStrips = 320;         // of the whole call: strips * q-heads
+// Strips * q-heads of the whole call up to which the short form is taken: the second round of its workgroups (see
+// select_small_kernel) may be a quarter full.  All head dims still gain there (5 - 13 % at 320 strips); with d = 256, whose
+// strips take longest, it loses 2 % from 352 on, d <= 128 would gain up to some 450.
+constexpr int64_t kSmallStrips = 320;
 
 // The whole estimate of the sequences in `seqs` (arguments already validated): pooling (+ RoPE when `rope`
 // is given), calibration, selection, compaction.
