@@ -1692,8 +1692,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
 
   // One launch prepares the call up to kPrepMaxRows rows in one phase: 14.4 us instead of 34.7 us at 2048 rows (8K
   // tokens, 32 heads), 38.0 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 45.3 instead of 63.1 at 8192
-  // (32K tokens; the images alone take 13, 22 and 39 us), 5.3 instead of 13.9 at 32 rows.  Beyond, the plan of a single workgroup (33 us at 5024 rows
-  // without an image beside it) would no longer hide behind the image, and the parts run as kernels of their own.
+  // (32K tokens; the images alone take 13, 22 and 39 us), 5.3 instead of 13.9 at 32 rows.  Beyond, the plan of a single
+  // workgroup (33 us at 5024 rows without an image beside it) would no longer hide behind the image, and the parts run
+  // as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   PullCounters pulls = {plan + kPlanCounter, 1, 0}, pair_pulls = {pair_plan + kPlanCounter, 1, 0};
   PullCounters later_pulls = pulls;        // of the kernel behind the 64-queries-per-wave one, which may have used its own
