@@ -298,7 +298,7 @@ __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len,
 // kernel, which returns at once if any sequence is dirty, the whole call then (kDirtyCall; both give the same bits); behind
 // the 64-queries-per-wave kernel the dirty sequences (kDirtySequences), so that no sequence's bits follow from the others'.
 enum { kEverything, kDirtyCall, kDirtySequences };
-template <int BLK, bool kStreamOnly, int D, bool kPair>
+template <int BLK, bool kStreamOnly, int D, bool kPair, bool kKeepMask>
 __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D, kPair>::kWavesPerSimd)) void sparse_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const int4* __restrict__ items,
@@ -583,7 +583,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       // ---- causal mask inside the diagonal block ----
       if (causal && v == u_own) {
         int last = (wave % C::kRowWaves) * 32 + l32 - 4 * hf;    // key kloc is kc behind 4 * hf
-        asm volatile("" : "+v"(last));                           // formed here, not kept across the row loop
+        // kKeepMask leaves the compares to the compiler, which forms them once in front of the row loop and keeps the
+        // results in spilled scalar registers; otherwise they are formed here (the dispatch has both sides)
+        if (!kKeepMask) asm volatile("" : "+v"(last));
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -596,7 +598,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       // ---- keys past the end of the sequence (ragged last block) ----
       if (v == N - 1 && tail < BLK) {
         int left = tail - 4 * hf;
-        asm volatile("" : "+v"(left));
+        if (!kKeepMask) asm volatile("" : "+v"(left));
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -1590,12 +1592,12 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
                       with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr, static_cast<hipStream_t>(stream));
 }
 
-template <int BLK, bool kStreamOnly, int D, bool kPair = false>
+template <int BLK, bool kStreamOnly, int D, bool kPair = false, bool kKeepMask = false>
 static void launch_attn(int grid, hipStream_t st, const PullCounters& pulls, const uint16_t* q, const uint16_t* k, const uint16_t* vt,
                         const int32_t* row_ptr, const int32_t* col_idx, const int4* items, int32_t* plan,
                         const DirtyFlags& flags, uint16_t* out, float* lse, int h, int h_kv, const SeqTable& seqs,
                         const HeadStrides& hs, int causal, int only_dirty) {
-  hipLaunchKernelGGL((sparse_attn_kernel<BLK, kStreamOnly, D, kPair>), dim3(grid),
+  hipLaunchKernelGGL((sparse_attn_kernel<BLK, kStreamOnly, D, kPair, kKeepMask>), dim3(grid),
                      dim3(AttnCfg<BLK, D, kPair>::kThreads), 0, st, q, k, vt, row_ptr, col_idx, items, plan,
                      pulls, flags, out, lse, h, h_kv, seqs, hs, causal, only_dirty);
 }
@@ -1784,22 +1786,28 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
       hipLaunchKernelGGL(sparse_attn_w64_kernel<64>, dim3(grid), dim3(128), 0, st, qp, kp, vp16, col_idx, items, plan,
                          pulls, flags, op, lse, h, h_kv, seqs, hs, causal);
   }
-#define PRISM_ATTN(BLK, SO, D)                                                                                \
-  launch_attn<BLK, SO, D>(grid, st, w64 ? later_pulls : pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
+  // Plain 64 x 128 beyond kPrepMaxRows rows keeps its mask compares across the row loop.  us of attention before they were
+  // formed in place / formed / kept: 32/8 heads, 16448 tokens (8224 rows) 546 / 558 / 549, 30016 1086 / 1115 / 1091, 28/4 heads,
+  // 33328 1121 / 1148 / 1130.  Forming them once costs a workgroup about 1 us, which short calls notice (32 rows 15 -> 16,
+  // 7968 rows 433 -> 436), and the other shapes are faster without: 64 x 64 at 16448 tokens 413 -> 401, 64 x 256 at 16320
+  // 1406 -> 1375, 128 x 64 at 32768 804 -> 795, 128 x 128 at 40001 1669 -> 1662.
+#define PRISM_ATTN(BLK, SO, D, KEEP)                                                                          \
+  launch_attn<BLK, SO, D, false, KEEP>(grid, st, w64 ? later_pulls : pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
                           hs, causal, only_dirty)
   if (stream_only) {
     // measurement aid of the d = 128 kernels only
     if (d != 128) return PRISM_ERR_UNSUPPORTED;
-    if (params->block == 128) PRISM_ATTN(128, true, 128);
-    else PRISM_ATTN(64, true, 128);
+    if (params->block == 128) PRISM_ATTN(128, true, 128, false);
+    else PRISM_ATTN(64, true, 128, false);
   } else if (params->block == 128) {
-    if (d == 64) PRISM_ATTN(128, false, 64);
-    else if (d == 128) PRISM_ATTN(128, false, 128);
-    else PRISM_ATTN(128, false, 256);
+    if (d == 64) PRISM_ATTN(128, false, 64, false);
+    else if (d == 128) PRISM_ATTN(128, false, 128, false);
+    else PRISM_ATTN(128, false, 256, false);
   } else {
-    if (d == 64) PRISM_ATTN(64, false, 64);
-    else if (d == 128) PRISM_ATTN(64, false, 128);
-    else PRISM_ATTN(64, false, 256);
+    if (d == 64) PRISM_ATTN(64, false, 64, false);
+    else if (d == 128 && R > kPrepMaxRows) PRISM_ATTN(64, false, 128, true);
+    else if (d == 128) PRISM_ATTN(64, false, 128, false);
+    else PRISM_ATTN(64, false, 256, false);
   }
 #undef PRISM_ATTN
   return launch_status();

@@ -1,7 +1,12 @@
 """The one-launch preparation of the attention (queue plan by a single workgroup, list check, V image): numbers of rows
 at the edges of its steps (1024, 2048, 4096, 8192 rows) and just past them, up to where the separate kernels take over."""
+import numpy as np
 import pytest
+import torch
 
+from oracle import prism_oracle as orc
+from paper_2602_08426_amd import binding as pb
+from tests import gpu_util as gu
 from tests.test_gpu_queues import test_every_row_is_queued_once_and_the_queues_are_balanced as check_queues
 from tests.test_gpu_queues import test_pair_plan_at_block_64 as check_pair_plan
 
@@ -24,3 +29,35 @@ def test_queues_at_the_edges(h, hkv, L, B, bidir):
 @pytest.mark.parametrize("h,hkv,N,dirty", [(16, 4, 256, False), (17, 1, 242, True), (32, 8, 256, False)])
 def test_pair_queues_at_the_edges(h, hkv, N, dirty):
     check_pair_plan(h, hkv, N, dirty)    # 4096, 4114 and 8192 rows
+
+
+@pytest.mark.parametrize("tail,bidir", [(64, False), (1, False), (33, True), (63, True)])
+def test_rows_beyond_one_launch_have_the_bits_of_fewer(tail, bidir):
+    """B = 64, an odd number of blocks: a call of 8385 rows has the bits of calls on its halves, whose masks another
+    instance of the kernel forms, and agrees with the oracle."""
+    h, N, B = 129, 65, 64
+    L = (N - 1) * B + tail
+    rng = np.random.default_rng(tail)
+    g = torch.Generator(device="cuda").manual_seed(tail)
+    q, k, v = (torch.randn((n, L, 128), generator=g, device="cuda").bfloat16() for n in (h, 1, 1))
+    mask = rng.random((h, N, N)) < 0.3
+    mask[:, np.arange(N), np.arange(N)] = True
+    mask[:, N // 2, N - 1] = True                          # the ragged block (bidirectional rows)
+    if not bidir:
+        mask = np.tril(mask)
+    flags = pb.PRISM_FLAG_BIDIRECTIONAL if bidir else 0
+
+    def run(heads):
+        params = pb.make_params(len(heads), 1, L, B, flags=flags)
+        rp, ci, cnt = gu.csr_to_device(*orc.mask_to_csr(mask[heads]))
+        return gu.gpu_sparse_attn(params, q[heads].contiguous(), k, v, rp, ci, cnt)
+
+    out, lse = run(range(h))
+    for part in (range(64), range(64, h)):
+        o, s = run(part)
+        assert torch.equal(out[part].view(torch.int16), o.view(torch.int16)) and torch.equal(lse[part], s)
+    Q, K, V = (t.float().cpu().numpy().astype(np.float64) for t in (q, k, v))
+    rows = {(i, u) for i in (0, h - 1) for u in (0, N // 2, N - 1)}
+    ref = orc.block_sparse_attention(Q, K, V, mask, B, rows, causal=not bidir)
+    for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
+        assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
