@@ -126,8 +126,8 @@ __device__ __forceinline__ int dirty_sequences(const DirtyFlags& f) {
 // row so that the 16-lane column reads are conflict-free.  Tiles are copied global -> LDS
 // asynchronously, without passing through registers.
 // Step per listed kv block (each tile buffer is refilled as soon as its last reader is done):
-//     K(j) in LDS | start V(j) copy | S^T = K Q^T | barrier | start K(j+1) copy
-//     online softmax | wait V(j) | barrier | O^T += V^T P^T | wait K(j+1) | barrier
+//     K(j) in LDS | S^T = K Q^T, requests of V(j) between the MFMAs | barrier
+//     online softmax, requests of K(j+1) at its start or in it | wait V(j) | barrier | O^T += V^T P^T | wait K(j+1) | barrier
 // Two buffers per tile (one barrier per step instead of three, both tiles of the next block requested a whole step ahead)
 // fit at 64 x 64, 128 x 64 and 64 x 256 and are no gain over the range: us of attention, one buffer -> two, 32/8 heads: 128 x 64
 // at 8192 tokens 127 -> 123, at 20000 331 -> 345, at 32768 755 -> 790; 64 x 256 at 16320 1374 -> 1432, at 32768 3159 -> 3257;
@@ -151,6 +151,16 @@ struct AttnCfg {
   static constexpr int kDTiles = D / 32;                   // 32-dim tiles of the output
   static constexpr int kKSteps = D / 16;                   // MFMA k-steps of S^T = K Q^T
   static constexpr int kWavesPerSimd = D > 128 ? 1 : 2;    // register budget: 512 or 256 per lane
+  // Where the requests of the next K tile go.  A wave that issues all its pieces of a tile in a row stands still until the
+  // texture path has taken them, 500 - 1000 cycles of a step (S phase 2770 cycles, PV phase with as many MFMAs 1640).  The
+  // V^T pieces are spread over the S MFMAs in every form; the K pieces over the maximum at B = 128, over the exponentials
+  // at d = 256, where no second wave of the SIMD fills the gap; at B = 64 the softmax is too short to hide a later request.
+  // us of attention, all in a row / V^T spread / K over the maximum too / K over the exponentials instead:
+  // 128 x 128, 32/8 heads, 12345 tokens 281 / 274 / 271 / 270, 40001 1822 / 1752 / 1755 / 1754; 128 x 64, 12345
+  // 195 / 189 / 186 / 183, 28001 591 / 592 / 590 / 605; 128 x 256, 4/4 heads, 16384 216 / 201 / 192 / 187; pair 64 x 256, 16/4,
+  // 16384 714 / 701 / 697 / 682; pair 64 x 128, 8/2, 60000 605 / 584 / 591 / 592; 64 x 64, 32/8, 16384 305 / 298 / 298 / 316.
+  static constexpr int kPiecesInMax = BLK == 128 && D <= 128 ? kPerThread : 0;
+  static constexpr int kPiecesInExp = D > 128 ? kPerThread : 0;
 };
 
 // Asynchronous global -> LDS tile copies (buffer_load_dwordx4 ... lds: every lane fetches 16
@@ -189,28 +199,31 @@ __device__ __forceinline__ int vt_piece_offset(int p) {
   return row * (BLK * 2) + (((p % C::kVtCpr) ^ (row & (C::kVtCpr - 1))) << 4);
 }
 
-template <int BLK, int D, bool PAIR>
-__device__ __forceinline__ void async_load_k_tile(__amdgpu_buffer_rsrc_t rs, int tile_off, char* lds,
-                                                  int t) {
-  using C = AttnCfg<BLK, D, PAIR>;
-  // wave-uniform LDS base, re-materialised here so that the per-piece M0 values are formed
-  // with scalar adds instead of being kept live (and spilled) across the whole loop
+// this wave's first LDS slot of a tile's piece 0, wave-uniform and re-materialised per step so that the per-piece M0
+// values are formed with scalar adds instead of being kept live (and spilled) across the whole loop
+__device__ __forceinline__ int first_slot(int t) {
   int wave_base = __builtin_amdgcn_readfirstlane(t & ~63);
   asm volatile("" : "+s"(wave_base));
+  return wave_base;
+}
+
+// the pieces [i0, i1) of the kPerThread 16-byte pieces that a thread copies of a tile
+template <int BLK, int D, bool PAIR>
+__device__ __forceinline__ void async_load_k_pieces(__amdgpu_buffer_rsrc_t rs, int tile_off, char* lds, int t,
+                                                    int wave_base, int i0, int i1) {
+  using C = AttnCfg<BLK, D, PAIR>;
 #pragma unroll
-  for (int i = 0; i < C::kPerThread; ++i)
+  for (int i = i0; i < i1; ++i)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(lds + (i * C::kThreads + wave_base) * 16), 16,
                                              k_piece_offset<BLK, D>(i * C::kThreads + t), tile_off, 0, 0);
 }
 
 template <int BLK, int D, bool PAIR>
-__device__ __forceinline__ void async_load_vt_tile(__amdgpu_buffer_rsrc_t rs, int tile_off, char* lds,
-                                                   int t) {
+__device__ __forceinline__ void async_load_vt_pieces(__amdgpu_buffer_rsrc_t rs, int tile_off, char* lds, int t,
+                                                     int wave_base, int i0, int i1) {
   using C = AttnCfg<BLK, D, PAIR>;
-  int wave_base = __builtin_amdgcn_readfirstlane(t & ~63);
-  asm volatile("" : "+s"(wave_base));
 #pragma unroll
-  for (int i = 0; i < C::kPerThread; ++i)
+  for (int i = i0; i < i1; ++i)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(lds + (i * C::kThreads + wave_base) * 16), 16,
                                              vt_piece_offset<BLK, D>(i * C::kThreads + t), tile_off, 0, 0);
 }
@@ -511,7 +524,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
     }
-    async_load_k_tile<BLK, D, kPair>(krs, v * C::kTileBytes, lds_k, t);
+    async_load_k_pieces<BLK, D, kPair>(krs, v * C::kTileBytes, lds_k, t, first_slot(t), 0, C::kPerThread);
     wait_async_loads();
     tile_barrier();
 
@@ -530,8 +543,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       constexpr bool kLast = decltype(last_tag)::value;
       if (kLast && t == 0) pulled_reg = atomicAdd(counter + my_queue * pulls.stride, 1);
 
-      // ---- V(j) -> LDS, in flight during S^T and the softmax ----
-      async_load_vt_tile<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t);
+      // ---- V(j) -> LDS, requested piece by piece between the MFMAs of S^T, in flight during the softmax ----
+      const int wave_base = first_slot(t);
+      const bool computes = !kStreamOnly && active;
+      if (!computes) async_load_vt_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, 0, C::kPerThread);
 
       f32x16 sacc[KT];
       if (kPair) {
@@ -540,7 +555,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) asm volatile("" : "=v"(sacc[kt]));
       }
-      if (!kStreamOnly && active) {
+      if (computes) {
       // ---- S^T = K Q^T ----
       // Flat software pipeline over the KT*KS (tile, k-step) pairs: the LDS read of step
       // i + kDepth is issued right after the MFMA of step i, in source order.
@@ -562,6 +577,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
             const int j = i + kDepth;
             fr[i % kDepth] = *reinterpret_cast<const bf16x8*>(lds_k + (j % KT) * kSlab + koff[j / KT]);
           }
+          constexpr int kEvery = kSteps / C::kPerThread;
+          static_assert(kSteps % C::kPerThread == 0, "a piece per kEvery MFMAs");
+          if (i % kEvery == 0)
+            async_load_vt_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, i / kEvery, i / kEvery + 1);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -570,7 +589,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 
       // every wave is done reading K(j): K(j+1) can start now and land during softmax + PV
       tile_barrier();
-      if (!kLast) async_load_k_tile<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t);
+      constexpr int kNow = C::kPerThread - C::kPiecesInMax - C::kPiecesInExp;
+      if (!kLast)
+        async_load_k_pieces<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t, wave_base, 0, computes ? kNow : C::kPerThread);
 
       bf16x8 pf[KT][2];
       if (kPair) {
@@ -579,7 +600,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 #pragma unroll
           for (int s = 0; s < 2; ++s) asm volatile("" : "=v"(pf[kt][s]));
       }
-      if (!kStreamOnly && active) {
+      if (computes) {
       // ---- causal mask inside the diagonal block ----
       if (causal && v == u_own) {
         int last = (wave % C::kRowWaves) * 32 + l32 - 4 * hf;    // key kloc is kc behind 4 * hf
@@ -611,9 +632,16 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       // ---- online softmax (per query = per lane pair l, l^32) ----
       float mx = -INFINITY;
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt)
+      for (int kt = 0; kt < KT; ++kt) {
+        if (!kLast && C::kPiecesInMax > 0) {
+          constexpr int kEach = C::kPiecesInMax / KT;
+          static_assert(kEach * KT == C::kPiecesInMax, "pieces per 32 keys");
+          async_load_k_pieces<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t, wave_base, kNow + kt * kEach, kNow + (kt + 1) * kEach);
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[kt][r]);
+      }
       mx = other_half_max(mx);
       const float m_new = fmaxf(m_run, mx * sm_scale);       // finite: every query sees a key
       if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) { // some query's max moved: rescale
@@ -633,6 +661,13 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       for (int kt = 0; kt < KT; ++kt) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
+          if (!kLast && C::kPiecesInExp > 0) {
+            constexpr int kEach = C::kPiecesInExp / (2 * KT), kFirst = kNow + C::kPiecesInMax;
+            static_assert(kEach * 2 * KT == C::kPiecesInExp, "pieces per 16 keys");
+            async_load_k_pieces<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t, wave_base,
+                                               kFirst + (2 * kt + s) * kEach, kFirst + (2 * kt + s + 1) * kEach);
+            __builtin_amdgcn_sched_barrier(0);
+          }
 #pragma unroll
           for (int j = 0; j < 8; j += 2) {
             const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[kt][8 * s + j], sm_scale, -m_new));
@@ -667,7 +702,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
         if (kind_nxt == kItemRow) item_nxt = items[e_nxt + lane_zero];
       }
 
-      if (!kStreamOnly && active) {
+      if (computes) {
       // ---- O^T += V^T P^T ----  (same flat pipeline over the DT*KT*2 (d-tile, k-step) pairs)
       {
         constexpr int kPer = KT * 2;                   // k-steps per d-tile
