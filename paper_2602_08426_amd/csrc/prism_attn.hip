@@ -1670,11 +1670,14 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   int32_t* parts = reinterpret_cast<int32_t*>(ws + W.parts);
   int32_t* plan = reinterpret_cast<int32_t*>(ws + W.plan);
   // resident workgroups per CU, by the LDS the two tiles of a workgroup take (2 * B * d * 2 bytes of the
-  // CU's 160 KB) and its waves: 2 at B = 128, d = 128 (64 KB, 4 waves); one when d = 256
-  const int tile_pair = 2 * params->block * d * 2;
-  int per_cu = (160 * 1024) / tile_pair;
-  per_cu = per_cu > 4 ? 4 : per_cu;
-  if (d > 128) per_cu = 1;
+  // CU's 160 KB) and its waves: 2 at B = 128, d = 128 (64 KB, 4 waves).  At d = 256 a wave has a SIMD to itself: one
+  // workgroup of four waves, or two of two at B = 64.  Two of these share the LDS and the copies of the CU, which a call
+  // of few rows, bound by its longest ones, feels and a longer one does not; around 2600 rows it depends on the lists.  us of
+  // attention, one -> two: 16/4 heads, 8100 tokens (2032 rows) 313 -> 326, 10001 (2512) 368 -> 388, 12001 (3008) 524 -> 462,
+  // 30016 (7504) 2605 -> 1630; 32/8, 2000 (1024) 90 -> 97, 5050 (2528) 247 -> 219, 8100 (4064) 489 -> 350, 16300 (8160)
+  // 1354 -> 858; 28/4, 4001 (1764) 169 -> 178, 6050 (2660) 249 -> 259; 7/1, 24001 (2632) 252 -> 268.
+  constexpr int kTwoWideRows = 2816;     // 11 per CU
+  if (d > 128) per_cu = params->block == 64 && R > kTwoWideRows ? 2 : 1;
   else if (params->block == 128 && per_cu > 2) per_cu = 2;
   const int grid = persistent_grid(R, per_cu);
   if (grid <= 0) return PRISM_ERR_HIP;

@@ -61,3 +61,34 @@ def test_rows_beyond_one_launch_have_the_bits_of_fewer(tail, bidir):
     ref = orc.block_sparse_attention(Q, K, V, mask, B, rows, causal=not bidir)
     for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
         assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
+
+
+@pytest.mark.parametrize("h,bidir", [(43, False), (44, False), (44, True)])
+def test_wide_rows_beyond_one_workgroup_per_cu(h, bidir):
+    """d = 256, B = 64, an odd number of blocks, 2795 and 2860 rows: the first call has a workgroup per CU, the others two.
+    Every head has the bits of a call on a few heads, and agrees with the oracle."""
+    N, B, d = 65, 64, 256
+    L = (N - 1) * B + 7
+    rng = np.random.default_rng(h)
+    g = torch.Generator(device="cuda").manual_seed(h)
+    q, k, v = (torch.randn((n, L, d), generator=g, device="cuda").bfloat16() for n in (h, 1, 1))
+    mask = rng.random((h, N, N)) < 0.2
+    mask[:, np.arange(N), np.arange(N)] = True
+    if not bidir:
+        mask = np.tril(mask)
+    flags = pb.PRISM_FLAG_BIDIRECTIONAL if bidir else 0
+
+    def run(heads):
+        params = pb.make_params(len(heads), 1, L, B, 128, 192, 0.9, flags, d)
+        rp, ci, cnt = gu.csr_to_device(*orc.mask_to_csr(mask[heads]))
+        return gu.gpu_sparse_attn(params, q[heads].contiguous(), k, v, rp, ci, cnt)
+
+    out, lse = run(range(h))
+    for part in (range(8), range(h - 5, h)):
+        o, s = run(part)
+        assert torch.equal(out[part].view(torch.int16), o.view(torch.int16)) and torch.equal(lse[part], s)
+    Q, K, V = (t.float().cpu().numpy().astype(np.float64) for t in (q, k, v))
+    rows = {(i, u) for i in (0, h - 1) for u in (0, N // 2, N - 1)}
+    ref = orc.block_sparse_attention(Q, K, V, mask, B, rows, causal=not bidir)
+    for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
+        assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
