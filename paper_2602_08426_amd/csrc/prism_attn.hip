@@ -1676,6 +1676,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // attention, one -> two: 16/4 heads, 8100 tokens (2032 rows) 313 -> 326, 10001 (2512) 368 -> 388, 12001 (3008) 524 -> 462,
   // 30016 (7504) 2605 -> 1630; 32/8, 2000 (1024) 90 -> 97, 5050 (2528) 247 -> 219, 8100 (4064) 489 -> 350, 16300 (8160)
   // 1354 -> 858; 28/4, 4001 (1764) 169 -> 178, 6050 (2660) 249 -> 259; 7/1, 24001 (2632) 252 -> 268.
+  const int tile_pair = 2 * params->block * d * 2;
+  int per_cu = (160 * 1024) / tile_pair;
+  per_cu = per_cu > 4 ? 4 : per_cu;
   constexpr int kTwoWideRows = 2816;     // 11 per CU
   if (d > 128) per_cu = params->block == 64 && R > kTwoWideRows ? 2 : 1;
   else if (params->block == 128 && per_cu > 2) per_cu = 2;
