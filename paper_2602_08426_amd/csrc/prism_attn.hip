@@ -285,15 +285,19 @@ constexpr int kPlanStart = 0, kPlanLen = 8, kPlanCounter = 16, kPlanFlags = 24, 
 // it is not its turn.
 constexpr int kFlagDirtyLists = 1;
 
-// Pull counters of the queues.  The one-launch preparation spreads them over cache lines of their own and starts
-// them behind the workgroups' first rows, which are dealt out by workgroup number (`first_dealt`): all pulls on one
-// line are served one after the other, 16 ns each, which made 40 us of the 64 us that 2048 rows without any listed
-// block took.  It leaves the counters of the plan to record that a queue was exhausted.
+// Pull counters of the queues, on cache lines of their own: all pulls on one line are served one after the other, 16 ns
+// each, which made 40 us of the 64 us that 2048 rows without any listed block took, and held the short rows at the end of
+// a longer call back (us of attention, 8512 rows of 32/8 heads, 17024 tokens, B = 64 521 -> 449; 10016 of d = 64, 20001
+// tokens 478 -> 377; 14336 of 28/4, 64K, B = 128 2514 -> 2483).  They start behind the workgroups' first rows, which are
+// dealt out by workgroup number.  The counters of the plan are left to record that a queue was exhausted.
 struct PullCounters {
   int32_t* at;
   int32_t stride;        // ints between two queues' counters
-  int32_t first_dealt;
 };
+// the rows of queue x that are dealt to the first pulls of the workgroups x, x + n_queues, ...
+__device__ __forceinline__ int dealt_rows(int x, int n_queues, int grid) {
+  return x < n_queues ? (grid - x + n_queues - 1) / n_queues : 0;
+}
 
 __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len, int* entry) {
   if (pulled >= seg_len) return kItemEnd;
@@ -374,7 +378,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // read of the next row's queue entry are hidden behind that last step.
   int lane_zero;                                     // 0, but opaque to the compiler
   asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-  if (t == 0) next_item = pulls.first_dealt ? (int)blockIdx.x / n_queues : atomicAdd(counter + my_queue * pulls.stride, 1);
+  if (t == 0) next_item = (int)blockIdx.x / n_queues;
   __syncthreads();
   int cur_x = 0, cur_y = 0, cur_z = 0, cur_w = 0;     // the current row's queue entry, wave-uniform
   int kind_cur;
@@ -398,7 +402,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       // queue that still has rows, nearest first round the ring, and pull from it.  A counter
       // only grows, so a queue seen exhausted stays so; the atomic pull decides who gets a row.
       if (wave == 0) {
-        if (lane == 0 && pulls.first_dealt) plan[kPlanCounter + my_queue] = seg_len + 1;
+        if (lane == 0) plan[kPlanCounter + my_queue] = seg_len + 1;
         int taken = 0x7fffffff, len = 0;
         if (lane < n_queues) {
           taken = __hip_atomic_load(counter + lane * pulls.stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -837,7 +841,7 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
   int32_t* __restrict__ counter = pulls.at;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   int pulled = 0;
-  if (t == 0) pulled = pulls.first_dealt ? (int)blockIdx.x / n_queues : atomicAdd(counter + my_queue * pulls.stride, 1);
+  if (t == 0) pulled = (int)blockIdx.x / n_queues;
   for (;;) {
     // hand the pulled queue position to both waves
     __syncthreads();
@@ -851,7 +855,7 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
       if (wave == 0) {
         int ln = lane;
         asm volatile("" : "+v"(ln));                        // addresses formed here, not kept across the row loop
-        if (ln == 0 && pulls.first_dealt) plan[kPlanCounter + my_queue] = seg_len + 1;
+        if (ln == 0) plan[kPlanCounter + my_queue] = seg_len + 1;
         int found_pos = -1, found_queue = -1;
         for (;;) {
           int taken = 0x7fffffff, len = 0;
@@ -988,6 +992,13 @@ __global__ __launch_bounds__(256) void queue_validate_kernel(const int32_t* __re
 struct PlanCfg {
   int h, g, N, heads_per_phase, n_phases, n_queues, cap, causal, stride;
 };
+// Two sets of kXcds pull counters, `stride` ints apart, in row_part (stride 0: not in this launch), and the queues and
+// workgroups of the kernels that pull from them.
+struct CounterInit {
+  int stride;
+  int n_queues[2], grid[2];
+};
+constexpr int kCounterStride = 32;        // ints: a 128-byte line
 constexpr int kClasses = 11;
 constexpr int kMaxGroups = 512;           // (phase, class) groups held in LDS by queue_fill_kernel
 
@@ -1137,14 +1148,16 @@ __global__ __launch_bounds__(256) void queue_rank_kernel(const int32_t* __restri
 // The thread of a row writes the row's queue entry: list bounds clamped to [0, cap], and the
 // first entry that names a valid key block (0 <= v <= u for causal attention, 0 <= v < N
 // otherwise).  Queue x holds, group after group, the rows of its part of the group; workgroup 0
-// also writes the plan (segment starts and lengths, cleared pull counters).
+// also writes the plan (segment starts and lengths, cleared pull counters).  The call's last launch
+// of it turns the first entries of row_part into the pull counters of the two attention kernels: the
+// thread that has read an entry, the last to do so, writes the counter that takes its place.
 __global__ __launch_bounds__(256) void queue_fill_kernel(const int32_t* __restrict__ row_ptr,
                                                          const int32_t* __restrict__ col_idx, PlanCfg c,
                                                          const int32_t* __restrict__ parts,
                                                          const int32_t* __restrict__ row_rank,
-                                                         const int32_t* __restrict__ row_part,
+                                                         int32_t* __restrict__ row_part,
                                                          int32_t* __restrict__ plan,
-                                                         int4* __restrict__ items) {
+                                                         int4* __restrict__ items, CounterInit ci) {
   __shared__ int s_parts[kMaxGroups * 8];            // rows of (group, part)
   __shared__ int s_before[kMaxGroups * 8];           // rows of the same part in earlier groups
   __shared__ int s_start[8];
@@ -1180,6 +1193,10 @@ __global__ __launch_bounds__(256) void queue_fill_kernel(const int32_t* __restri
   if (r >= c.h * c.N) return;
   const int hq = r / c.N, u = r - hq * c.N;
   const int gp = row_part[r], x = gp & 7;
+  if (ci.stride > 0 && r % ci.stride == 0 && r < 2 * kXcds * ci.stride) {
+    const int k = r / ci.stride, set = k / kXcds;
+    row_part[r] = dealt_rows(k % kXcds, ci.n_queues[set], ci.grid[set]);
+  }
   int in_earlier_parts = 0;
   for (int y = 0; y < x; ++y) in_earlier_parts += s_parts[(gp & ~7) + y];
   const int entry = s_start[x] + s_before[gp] + row_rank[r] - in_earlier_parts;
@@ -1358,7 +1375,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     plan[kPlanCounter + t] = 0;
     plan[kPlanFlags + t] = 0;
     // the first pulls of queue t belong to the workgroups t, t + n_queues, ...
-    const int dealt = t < n_queues ? (grid - t + n_queues - 1) / n_queues : 0;
+    const int dealt = dealt_rows(t, n_queues, grid);
     counters[t * a.counter_stride] = dealt;
     if (more_counters != nullptr) more_counters[t * a.counter_stride] = dealt;
   }
@@ -1645,13 +1662,13 @@ static void launch_prep(int grid, const PrepArgs& a, const SeqTable& seqs, hipSt
 // the three kernels that turn index lists into the queue plan of `pc`
 static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t* col_idx, int32_t* bins,
                        int32_t* parts, int32_t* row_rank, int32_t* row_part, int32_t* plan, int4* items,
-                       hipStream_t st) {
+                       const CounterInit& ci, hipStream_t st) {
   const int R = pc.h * pc.N;
   hipLaunchKernelGGL(queue_count_kernel, dim3(pc.h), dim3(256), 0, st, row_ptr, pc, bins, parts, plan);
   hipLaunchKernelGGL(queue_rank_kernel, dim3(pc.h), dim3(256), 0, st, row_ptr, pc, bins, parts, row_rank,
                      row_part);
   hipLaunchKernelGGL(queue_fill_kernel, dim3((R + 255) / 256), dim3(256), 0, st, row_ptr, col_idx, pc,
-                     parts, row_rank, row_part, plan, items);
+                     parts, row_rank, row_part, plan, items, ci);
 }
 
 // The whole attention of the sequences in `seqs` (arguments already validated; several sequences only where
@@ -1739,9 +1756,16 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // workgroup (33 us at 5024 rows without an image beside it) would no longer hide behind the image, and the parts run
   // as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
-  PullCounters pulls = {plan + kPlanCounter, 1, 0}, pair_pulls = {pair_plan + kPlanCounter, 1, 0};
-  PullCounters later_pulls = pulls;        // of the kernel behind the 64-queries-per-wave one, which may have used its own
-  if (R <= kPrepMaxRows && pc.n_phases == 1) {
+  // Two sets of pull counters in row_part, which the preparation is done with: of the pair kernel and the one behind it, or
+  // of the 64-queries-per-wave kernel and the one behind it.  A short table holds them closer together.
+  const bool one_launch = R <= kPrepMaxRows && pc.n_phases == 1;
+  const int last_fill_rows = pair ? R / 2 : R;             // of queue_fill_kernel, whose threads write the counters
+  int counter_stride = kCounterStride;
+  while ((size_t)counter_stride * 2 * kXcds * sizeof(int32_t) > W.bins - W.row_part ||
+         (!one_launch && counter_stride * 2 * kXcds > last_fill_rows))
+    counter_stride >>= 1;
+  const PullCounters pulls = {row_part, counter_stride}, second_pulls = {row_part + counter_stride * kXcds, counter_stride};
+  if (one_launch) {
     PrepArgs pa = {};
     pa.row_ptr = row_ptr;
     pa.col_idx = col_idx;
@@ -1762,12 +1786,8 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.n_plans = pair ? 2 : 1;
     pa.n_check = only_dirty != kEverything ? (R + kCheckRows - 1) / kCheckRows : 0;
     pa.need_sorted = pair ? 1 : 0;
-    // two sets of 8 counters in row_part, which this path has no other use for, up to a 128-byte line each
-    pulls = PullCounters{row_part, 32, 1};
-    while ((size_t)pulls.stride * 2 * kXcds * sizeof(int32_t) > W.bins - W.row_part) pulls.stride >>= 1;
-    pair_pulls = later_pulls = PullCounters{row_part + pulls.stride * kXcds, pulls.stride, 1};
     pa.counters = pulls.at;
-    pa.pair_counters = pair_pulls.at;
+    pa.pair_counters = second_pulls.at;
     pa.counter_stride = pulls.stride;
     pa.grid = grid;
     pa.pair_grid = pair_grid;
@@ -1788,13 +1808,16 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
       const int rc = v_image_core(params, hs, v_bf16, vp, vp16, range_flags, st);
       if (rc != PRISM_OK) return rc;
     }
-    build_plan(pc, row_ptr, col_idx, bins, parts, row_rank, row_part, plan, items, st);
+    // (over a thousand rows here: more than kPrepMaxRows, or kv heads that do not fit the memory-side cache together)
+    const CounterInit later = {};
+    const CounterInit ci = {counter_stride, {pc.n_queues, pair ? pair_queues : pc.n_queues}, {grid, pair ? pair_grid : grid}};
+    build_plan(pc, row_ptr, col_idx, bins, parts, row_rank, row_part, plan, items, pair ? later : ci, st);
     if (pair) {
       PlanCfg pp = pc;
       pp.N = N / 2;
       pp.stride = 2;
       pp.n_queues = pair_queues;
-      build_plan(pp, row_ptr, col_idx, bins, parts, row_rank, row_part, pair_plan, pair_items, st);
+      build_plan(pp, row_ptr, col_idx, bins, parts, row_rank, row_part, pair_plan, pair_items, ci, st);
     }
     if (only_dirty != kEverything) {
       const int by_flags = (n_range_flags + 255) / 256;
@@ -1804,7 +1827,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   }
   if (pair) {
 #define PRISM_PAIR(D)                                                                                        \
-  launch_attn<64, false, D, true>(pair_grid, st, pair_pulls, qp, kp, vp, row_ptr, col_idx, pair_items, pair_plan, flags, \
+  launch_attn<64, false, D, true>(pair_grid, st, second_pulls, qp, kp, vp, row_ptr, col_idx, pair_items, pair_plan, flags, \
                                   op, lse, h, h_kv, seqs, hs, causal, 0)
     if (d == 64) PRISM_PAIR(64);
     else if (d == 128) PRISM_PAIR(128);
@@ -1833,7 +1856,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // 7968 rows 433 -> 436), and the other shapes are faster without: 64 x 64 at 16448 tokens 413 -> 401, 64 x 256 at 16320
   // 1406 -> 1375, 128 x 64 at 32768 804 -> 795, 128 x 128 at 40001 1669 -> 1662.
 #define PRISM_ATTN(BLK, SO, D, KEEP)                                                                          \
-  launch_attn<BLK, SO, D, false, KEEP>(grid, st, w64 ? later_pulls : pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
+  launch_attn<BLK, SO, D, false, KEEP>(grid, st, w64 ? second_pulls : pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
                           hs, causal, only_dirty)
   if (stream_only) {
     // measurement aid of the d = 128 kernels only

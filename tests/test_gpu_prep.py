@@ -92,3 +92,8 @@ def test_wide_rows_beyond_one_workgroup_per_cu(h, bidir):
     ref = orc.block_sparse_attention(Q, K, V, mask, B, rows, causal=not bidir)
     for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
         assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
+
+
+@pytest.mark.parametrize("dirty", [False, True])
+def test_pair_queues_of_the_separate_kernels(dirty):
+    check_pair_plan(33, 11, 250, dirty)  # 8250 rows: the counters of both plans are written by the last launch that fills one
