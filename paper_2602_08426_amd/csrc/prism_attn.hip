@@ -305,6 +305,31 @@ __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len,
   return kItemRow;
 }
 
+// 64 entries of one of a pair's lists, one a lane.  Loaded one by one, two steps ahead, the entries came through the scalar
+// cache, whose answers arrive in no order: the first LDS read of a step then waited for them, 300 - 1000 cycles of a
+// step.  us of attention, entry by entry -> from here: 64 x 128, 8/2 heads, 60000 tokens 583 -> 550, 32/8, 12288 304 -> 292,
+// 20480 557 -> 546, 32768 1329 -> 1314; 64 x 256, 16/4, 16384 680 -> 662.  The other forms, one list and one entry a step, gain
+// nothing (128 x 128, 32/8, 20011 516 -> 524; 128 x 64, 32768 825 -> 839).
+struct ListWindow {
+  const int32_t* cols;
+  int first, end, lane, held;
+  __device__ __forceinline__ void fetch(int i) {
+    first = i;
+    held = cols[min(i + lane, end - 1)];
+  }
+  __device__ __forceinline__ void start(const int32_t* c, int i, int e, int l) {
+    cols = c;
+    end = e;
+    lane = l;
+    if (i < e) fetch(i);
+  }
+  // entry i, first <= i < end; i never goes back
+  __device__ __forceinline__ int at(int i) {
+    if (i - first >= 64) fetch(i);
+    return __builtin_amdgcn_readlane(held, i - first);
+  }
+};
+
 // kStreamOnly (PRISM_FLAG_STREAM_ONLY): the same tile copies, waits, barriers and queue traffic
 // with the arithmetic left out; it measures how long the memory side of a call takes alone.
 // kPair (B = 64, an even number of blocks, every list ascending and clean): items and plan describe PAIR
@@ -487,26 +512,19 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     const int vmax = causal ? u_own : vmax_nc;
 
     // Pair rows: the two lists [it, mid) and [mid, end) are walked together, smallest block first;
-    // `act` says whose list names the block (bit 0: q-block 2u, bit 1: q-block 2u + 1).  The heads of
-    // both lists are fetched one step before they are looked at.
+    // `act` says whose list names the block (bit 0: q-block 2u, bit 1: q-block 2u + 1).
     constexpr int kNoEntry = 0x7fffffff;
     int mid = 0, ia = 0, ib = 0, act = 0, act_next = 0;
-    int ca_raw = 0, cb_raw = 0;                       // heads of the two lists as loaded (looked at a step later)
+    ListWindow list_a, list_b;
     bool active = true;                               // this wave computes in the current step
     auto pair_advance = [&](int* vout, int* actout) __attribute__((always_inline)) {
       // precondition: ia < mid or ib < end
-      const int ca = ia < mid ? __builtin_amdgcn_readfirstlane(ca_raw) : kNoEntry;
-      const int cb = ib < end ? __builtin_amdgcn_readfirstlane(cb_raw) : kNoEntry;
+      const int ca = ia < mid ? list_a.at(ia) : kNoEntry;
+      const int cb = ib < end ? list_b.at(ib) : kNoEntry;
       const int vv = ca < cb ? ca : cb;
       const int aa = (ca == vv ? 1 : 0) | (cb == vv ? 2 : 0);
-      if (aa & 1) {
-        ++ia;
-        if (ia < mid) ca_raw = cols[ia];
-      }
-      if (aa & 2) {
-        ++ib;
-        if (ib < end) cb_raw = cols[ib];
-      }
+      ia += aa & 1;
+      ib += aa >> 1;
       *vout = vv;
       *actout = aa;
     };
@@ -515,8 +533,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       mid = mid < it ? it : (mid > end ? end : mid);
       ia = it;
       ib = mid;
-      if (ia < mid) ca_raw = cols[ia];
-      if (ib < end) cb_raw = cols[ib];
+      list_a.start(cols, ia, mid, lane);
+      list_b.start(cols, ib, end, lane);
       pair_advance(&v, &act);                          // has_work: at least one entry
       active = ((act >> sub) & 1) != 0;
     }
