@@ -278,7 +278,7 @@ enum { kItemEnd = 0, kItemRow = 2 };
 // MI355X: 8 accelerator dies (XCDs), each with its own L2; workgroups are dealt to them round-robin,
 // so the attention kernels keep one work queue per XCD (the plan below has room for exactly kXcds).
 constexpr int kXcds = 8;
-constexpr int kPlanStart = 0, kPlanLen = 8, kPlanCounter = 16, kPlanFlags = 24, kPlanInts = 32;
+constexpr int kPlanStart = 0, kPlanLen = 8, kPlanCounter = 16, kPlanFlags = 24, kPlanAlone = 32, kPlanInts = 40;
 // plan[kPlanFlags]: bit 0 = some list holds an entry that must be skipped (negative, beyond the
 // row's last admissible block): such lists go through the general kernel, clean lists through the
 // 64-queries-per-wave kernel, each sequence of a packed batch for itself; each of the two kernels returns at once when
@@ -297,6 +297,20 @@ struct PullCounters {
 // the rows of queue x that are dealt to the first pulls of the workgroups x, x + n_queues, ...
 __device__ __forceinline__ int dealt_rows(int x, int n_queues, int grid) {
   return x < n_queues ? (grid - x + n_queues - 1) / n_queues : 0;
+}
+
+// The longest rows of a short call have a CU to themselves.  With two workgroups on every CU a row among them advances a
+// block in 2.25 us and alone in 1.3 (128 x 128, four waves): at 8K tokens its 62 blocks ended at 142 us, the other
+// workgroups, out of rows, at 105 - 115.  plan[kPlanAlone + x] has bit p for the p-th row of queue x if it is such a
+// row; it is dealt to workgroup x + 8 p, which shares its CU with workgroup x + 8 p + gridDim.x / 2 (in the order that
+// the hardware places a grid of two workgroups per CU; otherwise only the gain is lost).  That one ends at once, and the
+// workgroups behind it move up to its row.  Returns the workgroup's first row in its queue, or -1: it ends.
+__device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, int queue, int n_queues) {
+  const int p = (int)blockIdx.x / n_queues, half = (int)gridDim.x / 2 / n_queues;
+  const unsigned alone = plan[kPlanAlone + queue];
+  if (alone == 0 || p < half) return p;                     // bits are set only where half <= 32
+  const int mate = p - half;
+  return (alone >> mate) & 1u ? -1 : p - __popc(alone & ((1u << mate) - 1u));
 }
 
 __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len, int* entry) {
@@ -403,7 +417,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // read of the next row's queue entry are hidden behind that last step.
   int lane_zero;                                     // 0, but opaque to the compiler
   asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-  if (t == 0) next_item = (int)blockIdx.x / n_queues;
+  const int first = first_row(plan, my_queue, n_queues);
+  if (first < 0) return;
+  if (t == 0) next_item = first;
   __syncthreads();
   int cur_x = 0, cur_y = 0, cur_z = 0, cur_w = 0;     // the current row's queue entry, wave-uniform
   int kind_cur;
@@ -859,7 +875,9 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
   int32_t* __restrict__ counter = pulls.at;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   int pulled = 0;
-  if (t == 0) pulled = (int)blockIdx.x / n_queues;
+  const int first = first_row(plan, my_queue, n_queues);
+  if (first < 0) return;
+  if (t == 0) pulled = first;
   for (;;) {
     // hand the pulled queue position to both waves
     __syncthreads();
@@ -1255,6 +1273,7 @@ struct PrepArgs {
   int32_t *counters, *pair_counters;       // without a second plan: counters of the first one for a second kernel
   int32_t counter_stride;
   int32_t grid, pair_grid;                 // workgroups of the attention kernels
+  float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
   int32_t h, h_kv, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
   size_t kv_head_stride;
 };
@@ -1267,6 +1286,8 @@ struct PlanLds {
   float scale[kClasses];                            // parts per unit of work
   int start[kClasses][9];                           // first rank of the class that belongs to part x
   int before[kClasses][8], qlen[8];
+  int total;                                        // entries + 3 per row (a row costs about three blocks beside its own)
+  unsigned alone[8];
 };
 // stride = 2: rows are pairs of q-blocks (every sequence has an even number of them).
 template <int CH>
@@ -1348,6 +1369,8 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     m.rows[wave][lane] = crow;
     m.work[wave][lane] = cwork;
   }
+  if (t < 8) m.alone[t] = 0;
+  if (t == 8) m.total = 0;
   __syncthreads();
   if (t < kClasses) {
     int r = 0, w = 0;
@@ -1358,6 +1381,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
       r += nr;
       w += nw;
     }
+    atomicAdd(&m.total, w + 2 * r);
     m.scale[t] = w > 0 ? (float)n_queues / (float)w : 0.f;
     for (int x = 0; x < 9; ++x) m.start[t][x] = r;
   }
@@ -1392,17 +1416,16 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     plan[kPlanLen + t] = m.qlen[t];
     plan[kPlanCounter + t] = 0;
     plan[kPlanFlags + t] = 0;
-    // the first pulls of queue t belong to the workgroups t, t + n_queues, ...
-    const int dealt = dealt_rows(t, n_queues, grid);
-    counters[t * a.counter_stride] = dealt;
-    if (more_counters != nullptr) more_counters[t * a.counter_stride] = dealt;
   }
+  const float alone_from = stride == 1 && a.alone > 0.f ? a.alone * (float)m.total / (float)grid : INFINITY;
+  const int half = grid / 2 / n_queues;
   // rank becomes the row's entry, cum its list's first element
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
     if (len[c] < 0) continue;
     const int k = length_class(len[c]), x = part(cum[c], k);
     int entry = m.before[k][x] + rank[c] - m.start[k][x];
+    if ((float)len[c] > alone_from && entry < half) atomicOr(&m.alone[x], 1u << entry);
     for (int y = 0; y < x; ++y) entry += m.qlen[y];
     rank[c] = entry;
     cum[c] = 0;
@@ -1429,6 +1452,15 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
       }
     }                                                  // pair rows: clean lists, the kernel finds its first block
     items[rank[c]] = make_int4(seqs.n > 1 ? r.hq | (r.s << kSeqShift) : r.hq, r.u | (v << 16), it, end);
+  }
+  __syncthreads();
+  if (t < 8) {
+    const unsigned alone = m.alone[t];
+    plan[kPlanAlone + t] = (int)alone;
+    // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
+    const int dealt = dealt_rows(t, n_queues, grid) - __popc(alone);
+    counters[t * a.counter_stride] = dealt;
+    if (more_counters != nullptr) more_counters[t * a.counter_stride] = dealt;
   }
 }
 
@@ -1737,6 +1769,16 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   pc.causal = (params->flags & PRISM_FLAG_BIDIRECTIONAL) ? 0 : 1;
   pc.stride = 1;
   const int causal = pc.causal;
+  // Which rows have a CU to themselves (first_row), where the grid fills the chip with two workgroups per CU.  A row that
+  // shares its CU advances a block in 2.25 us where the average workgroup, over all of a call, takes 3 (four waves of
+  // 32 queries; the general kernel 3.3 and 4), so from 1.4 times the average work on it would be the last to end.  us of
+  // preparation and attention, without / 1.0 / 1.1 / 1.25 / 1.4: 32/8 heads, 8192 tokens 155.2 / 141.4 / 140.8 / 140.5 / 140.8,
+  // 8100 177.8 / 165.4 / 164.5 / 164.6 / 165.2, 8/2 heads, 8192 78.6 / 76.3 / 75.9 / 76.6 / 76.2; below 1.4 other calls lose:
+  // 16 heads, 19290, bidirectional 459 / 480 / 462 / 461 / 461, 4 heads, 128K 1640 / 1691 / 1646 / 1640 / 1638, the eight packed
+  // prompts of perf/cases.py 656 / 663 / 659 / 659 / 657.
+  constexpr float kAlone = 1.4f;
+  const bool full = grid == persistent_grid(0x7fffffff, 2) && grid % (2 * kXcds) == 0 && grid / (2 * kXcds) <= 32;
+  const float alone = params->block == 128 && per_cu == 2 && full ? kAlone : 0.f;
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
@@ -1808,6 +1850,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.pair_counters = second_pulls.at;
     pa.counter_stride = pulls.stride;
     pa.grid = grid;
+    pa.alone = alone;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
     const int prep_grid = pa.n_plans + pa.n_check + (v_bf16 != nullptr ? h_kv * N : 0);

@@ -8,6 +8,7 @@ from oracle import prism_oracle as orc
 from paper_2602_08426_amd import binding as pb
 from tests import gpu_util as gu
 from tests.test_gpu_queues import test_every_row_is_queued_once_and_the_queues_are_balanced as check_queues
+from tests.test_gpu_queues import _layout as queue_layout
 from tests.test_gpu_queues import test_pair_plan_at_block_64 as check_pair_plan
 
 pytestmark = pytest.mark.gpu
@@ -97,3 +98,46 @@ def test_wide_rows_beyond_one_workgroup_per_cu(h, bidir):
 @pytest.mark.parametrize("dirty", [False, True])
 def test_pair_queues_of_the_separate_kernels(dirty):
     check_pair_plan(33, 11, 250, dirty)  # 8250 rows: the counters of both plans are written by the last launch that fills one
+
+
+@pytest.mark.parametrize("tail,longest", [(128, 4), (128, None), (5, 4)])
+def test_rows_that_have_a_cu_to_themselves(tail, longest):
+    """576 rows at B = 128, whole blocks (four waves of 32 queries) and ragged (general kernel).  With one head of full
+    lists its longest rows are marked and the workgroups that would share their CUs end at once: every row is still done
+    once, with the bits of calls on single heads, which mark none, and the oracle's values.  Without it no row is marked."""
+    h, N, B = 9, 64, 128
+    L = (N - 1) * B + tail
+    rng = np.random.default_rng(3)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn((n, L, 128), generator=g, device="cuda").bfloat16() for n in (h, 1, 1))
+    mask = rng.random((h, N, N)) < 0.03
+    mask[:, np.arange(N), np.arange(N)] = True
+    if longest is not None:
+        mask[longest] = True
+    mask = np.tril(mask)
+
+    def run(heads):
+        params = pb.make_params(len(heads), 1, L, B)
+        rp, ci, cnt = gu.csr_to_device(*orc.mask_to_csr(mask[heads]))
+        out = torch.full_like(q[heads], float("nan"))
+        lse = torch.full((len(heads), L), float("nan"), device="cuda")
+        ws = pb.alloc_workspace(pb.prism_sparse_attn_workspace_bytes(params))
+        pb.prism_sparse_attn(params, q[heads].contiguous(), k, v, rp, ci, cnt, out, lse, ws)
+        torch.cuda.synchronize()
+        at = queue_layout(len(heads), 1, N, B, L)["plan"]
+        return out, lse, ws[at:at + 160].cpu().numpy().view(np.uint32)
+
+    out, lse, plan = run(list(range(h)))
+    marked = sum(bin(int(w)).count("1") for w in plan[32:40])
+    lens = mask.sum(-1)
+    line = 1.4 * (lens.sum() + 3 * h * N) / 512
+    assert marked == (lens > line).sum() and (marked >= 32 if longest is not None else marked == 0)
+    for i in range(h):
+        o, s, alone = run([i])
+        assert (alone[32:40] == 0).all()                   # 64 rows: one workgroup each
+        assert torch.equal(out[i].view(torch.int16), o[0].view(torch.int16)) and torch.equal(lse[i], s[0]), i
+    Q, K, V = (t.float().cpu().numpy().astype(np.float64) for t in (q, k, v))
+    rows = {(i, u) for i in (0, 4) for u in (0, N // 2, N - 1)}
+    ref = orc.block_sparse_attention(Q, K, V, mask, B, rows)
+    for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
+        assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
