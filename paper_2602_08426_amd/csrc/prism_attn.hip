@@ -1289,14 +1289,27 @@ struct PlanLds {
   int total;                                        // entries + 3 per row (a row costs about three blocks beside its own)
   unsigned alone[8];
 };
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = __builtin_amdgcn_readfirstlane((int)(x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 // stride = 2: rows are pairs of q-blocks (every sequence has an even number of them).
-template <int CH>
+template <int CH, bool kOne>
 __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const SeqTable& seqs, int stride,
                                           int n_queues, int grid, int32_t* __restrict__ counters,
                                           int32_t* __restrict__ more_counters, int4* __restrict__ items, int32_t* __restrict__ plan) {
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int per_head = seqs.nsum >> (stride - 1);
   const int R = a.h * per_head;
+  // What the rows need to know of their sequence: a call of one sequence (kOne) holds it in scalar registers.  Looked up in
+  // LDS for every row and use it was 40 % of the instructions, which bind this workgroup: 38.1 -> 33.1 us at 5024 rows,
+  // 17.1 -> 14.6 at 3104 (d = 64), 43.8 -> 41.1 at 8192.
+  const int n0 = __builtin_amdgcn_readfirstlane(seqs.s[0].N), cap0 = __builtin_amdgcn_readfirstlane(seqs.s[0].cap);
+  const int64_t row_at0 = uniform64(seqs.s[0].row0), col_at0 = uniform64(seqs.s[0].col0);
+  auto n_of = [&](int s) { return kOne ? n0 : seqs.s[s].N; };
+  auto cap_of = [&](int s) { return kOne ? cap0 : seqs.s[s].cap; };
+  auto row0_of = [&](int s) { return kOne ? row_at0 : (int64_t)seqs.s[s].row0; };
+  auto col0_of = [&](int s) { return kOne ? col_at0 : (int64_t)seqs.s[s].col0; };
   // Row i of the order: its sequence, q-head and number inside the head.
   struct Row {
     int s, hq, u;
@@ -1308,8 +1321,8 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     Row r;
     r.hq = (int)(((float)i + 0.5f) * per_head_inv);
     const int rem = i - r.hq * per_head;
-    r.s = seq_of(seqs, rem * stride, 1);
-    r.u = (seqs.s[r.s].N >> (stride - 1)) - 1 - (rem - (seqs.s[r.s].blk0 >> (stride - 1)));
+    r.s = kOne ? 0 : seq_of(seqs, rem * stride, 1);
+    r.u = (n_of(r.s) >> (stride - 1)) - 1 - (kOne ? rem : rem - (seqs.s[r.s].blk0 >> (stride - 1)));
     return r;
   };
   // The bounds of all rows are requested at once, and at the end the first entries of all lists: two memory round trips
@@ -1323,8 +1336,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     len[c] = -1;
     if (i < R) {
       const Row r = row(i);
-      const int32_t* rp = a.row_ptr + seqs.s[r.s].row0 +
-                          ((size_t)r.hq * (seqs.s[r.s].N >> (stride - 1)) + r.u) * stride;
+      const int32_t* rp = a.row_ptr + row0_of(r.s) + ((size_t)r.hq * (n_of(r.s) >> (stride - 1)) + r.u) * stride;
       beg[c] = rp[0];
       len[c] = rp[stride];
     }
@@ -1333,7 +1345,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   for (int c = 0; c < CH; ++c) {
     const int i = (wave * CH + c) * 64 + lane;
     if (i < R) {
-      const int s = row(i).s, cap = seqs.s[s].cap;
+      const int cap = cap_of(kOne ? 0 : row(i).s);
       const int b = beg[c] < 0 ? 0 : (beg[c] > cap ? cap : beg[c]), e = len[c];
       beg[c] = b;
       len[c] = (e < b ? b : (e > cap ? cap : e)) - b;
@@ -1430,7 +1442,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     rank[c] = entry;
     cum[c] = 0;
     if (stride == 1 && len[c] > 0)
-      cum[c] = a.col_idx[seqs.s[row((wave * CH + c) * 64 + lane).s].col0 + beg[c]];
+      cum[c] = a.col_idx[col0_of(kOne ? 0 : row((wave * CH + c) * 64 + lane).s) + beg[c]];
   }
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
@@ -1439,9 +1451,9 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     const int end = beg[c] + len[c];
     int it = beg[c], v = cum[c];
     if (stride == 1) {
-      const int vmax = a.causal ? r.u : seqs.s[r.s].N - 1;
+      const int vmax = a.causal ? r.u : n_of(r.s) - 1;
       if (len[c] == 0 || v < 0 || v > vmax) {          // rare: look for the first entry that names a valid block
-        const int32_t* cols = a.col_idx + seqs.s[r.s].col0;
+        const int32_t* cols = a.col_idx + col0_of(r.s);
         for (v = 0; it < end; ++it) {
           const int w = cols[it];
           if (w >= 0 && w <= vmax) {
@@ -1451,7 +1463,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
         }
       }
     }                                                  // pair rows: clean lists, the kernel finds its first block
-    items[rank[c]] = make_int4(seqs.n > 1 ? r.hq | (r.s << kSeqShift) : r.hq, r.u | (v << 16), it, end);
+    items[rank[c]] = make_int4(kOne ? r.hq : r.hq | (r.s << kSeqShift), r.u | (v << 16), it, end);
   }
   __syncthreads();
   if (t < 8) {
@@ -1524,10 +1536,15 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
     int32_t* counters = wg == 0 ? a.counters : a.pair_counters;
     int32_t* more = a.n_plans == 1 ? a.pair_counters : nullptr;
     const int grid = wg == 0 ? a.grid : a.pair_grid;
-    if (R <= kPrepThreads) plan_rows<1>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-    else if (R <= 2 * kPrepThreads) plan_rows<2>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-    else if (R <= 4 * kPrepThreads) plan_rows<4>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-    else plan_rows<8>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    auto run = [&](auto one) __attribute__((always_inline)) {
+      constexpr bool kOne = decltype(one)::value;
+      if (R <= kPrepThreads) plan_rows<1, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+      else if (R <= 2 * kPrepThreads) plan_rows<2, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+      else if (R <= 4 * kPrepThreads) plan_rows<4, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+      else plan_rows<8, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    };
+    if (seqs.n == 1) run(std::true_type{});
+    else run(std::false_type{});
     return;
   }
   wg -= a.n_plans;
@@ -1811,9 +1828,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const int n_range_flags = w64 ? h_kv * N : 0;
 
   // One launch prepares the call up to kPrepMaxRows rows in one phase: 14.4 us instead of 34.7 us at 2048 rows (8K
-  // tokens, 32 heads), 38.0 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 45.3 instead of 63.1 at 8192
+  // tokens, 32 heads), 33.1 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 41.1 instead of 63.1 at 8192
   // (32K tokens; the images alone take 13, 22 and 39 us), 5.3 instead of 13.9 at 32 rows.  Beyond, the plan of a single
-  // workgroup (33 us at 5024 rows without an image beside it) would no longer hide behind the image, and the parts run
+  // workgroup (about 30 us at 5024 rows) would no longer hide behind the image, and the parts run
   // as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   // Two sets of pull counters in row_part, which the preparation is done with: of the pair kernel and the one behind it, or
