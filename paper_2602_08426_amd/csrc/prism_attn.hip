@@ -1536,11 +1536,15 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
     int32_t* counters = wg == 0 ? a.counters : a.pair_counters;
     int32_t* more = a.n_plans == 1 ? a.pair_counters : nullptr;
     const int grid = wg == 0 ? a.grid : a.pair_grid;
+    // The waves take 64 * CH rows each in turn, so a CH too large leaves the last waves idle: 5024 rows at 8 instead of 5 are
+    // ten waves' work, and the preparation of 20011 tokens took 32.8 us instead of 25.4.
     auto run = [&](auto one) __attribute__((always_inline)) {
       constexpr bool kOne = decltype(one)::value;
       if (R <= kPrepThreads) plan_rows<1, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
       else if (R <= 2 * kPrepThreads) plan_rows<2, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
       else if (R <= 4 * kPrepThreads) plan_rows<4, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+      else if (kOne && R <= 5 * kPrepThreads) plan_rows<5, true>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+      else if (kOne && R <= 6 * kPrepThreads) plan_rows<6, true>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
       else plan_rows<8, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
     };
     if (seqs.n == 1) run(std::true_type{});
@@ -1828,9 +1832,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const int n_range_flags = w64 ? h_kv * N : 0;
 
   // One launch prepares the call up to kPrepMaxRows rows in one phase: 14.4 us instead of 34.7 us at 2048 rows (8K
-  // tokens, 32 heads), 33.1 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 41.1 instead of 63.1 at 8192
+  // tokens, 32 heads), 25.4 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 41.1 instead of 63.1 at 8192
   // (32K tokens; the images alone take 13, 22 and 39 us), 5.3 instead of 13.9 at 32 rows.  Beyond, the plan of a single
-  // workgroup (about 30 us at 5024 rows) would no longer hide behind the image, and the parts run
+  // workgroup (about 24 us at 5024 rows) would no longer hide behind the image, and the parts run
   // as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   // Two sets of pull counters in row_part, which the preparation is done with: of the pair kernel and the one behind it, or
