@@ -27,6 +27,11 @@ def test_queues_at_the_edges(h, hkv, L, B, bidir):
     check_queues(h, hkv, L, B, bidir, 7)
 
 
+@pytest.mark.parametrize("h,hkv,N", [(12, 4, 256), (7, 1, 439), (20, 4, 256), (3, 1, 1707), (24, 8, 256), (5, 1, 1229)])
+def test_queues_at_the_edges_of_the_rows_per_wave(h, hkv, N):
+    check_queues(h, hkv, 128 * N, 128, False, 11)   # 3072, 3073, 5120, 5121, 6144 and 6145 rows
+
+
 @pytest.mark.parametrize("h,hkv,N,dirty", [(16, 4, 256, False), (17, 1, 242, True), (32, 8, 256, False)])
 def test_pair_queues_at_the_edges(h, hkv, N, dirty):
     check_pair_plan(h, hkv, N, dirty)    # 4096, 4114 and 8192 rows
