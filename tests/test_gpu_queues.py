@@ -8,7 +8,7 @@ list and its first valid entry; the segments tile the table; every queue was pul
 inside a queue the (phase, length class) groups come in order; the queues hold about equal work.
 
 The offsets below restate the workspace layout of prism_attn.hip (V^T image, then the int4
-entries, two int32 tables of h*N, class counts, part counts, the 32-int plan, and for whole
+entries, two int32 tables of h*N, class counts, part counts, the 40-int plan, and for whole
 blocks of 128 tokens an fp16 copy of the image with one range flag per kv block; every piece
 aligned to 256 bytes).  They are not part of the C ABI: this file changes with that layout.
 """
@@ -27,12 +27,12 @@ def _align(x, a=256):
     return (x + a - 1) // a * a
 
 
-def _layout(h, hkv, N, B, L=None):
+def _layout(h, hkv, N, B, L=None, d=128):
     rows = h * N
     off = {}
     o = 0
     off["image"] = o
-    o = _align(o + hkv * N * B * 128 * 2)
+    o = _align(o + hkv * N * B * d * 2)
     off["items"] = o
     o = _align(o + rows * 16)
     off["row_rank"] = o
@@ -44,11 +44,11 @@ def _layout(h, hkv, N, B, L=None):
     off["parts"] = o
     o = _align(o + hkv * N_CLASSES * 8 * 4)
     off["plan"] = o
-    o = _align(o + 32 * 4)
-    if B == 128 and (L is None or L % 128 == 0):
+    o = _align(o + 40 * 4)
+    if B == 128 and d == 128 and (L is None or L % 128 == 0):
         # whole blocks of 128 tokens: a second V^T image in fp16 and one range flag per kv block
         off["image16"] = o
-        o = _align(o + hkv * N * B * 128 * 2)
+        o = _align(o + hkv * N * B * d * 2)
         off["range_flags"] = o
         o = _align(o + hkv * N * 4)
     if B == 64 and N % 2 == 0:
@@ -56,7 +56,7 @@ def _layout(h, hkv, N, B, L=None):
         off["pair_items"] = o
         o = _align(o + rows // 2 * 16)
         off["pair_plan"] = o
-        o = _align(o + 32 * 4)
+        o = _align(o + 40 * 4)
     off["total"] = o
     return off
 
