@@ -1274,6 +1274,7 @@ struct PrepArgs {
   int32_t counter_stride;
   int32_t grid, pair_grid;                 // workgroups of the attention kernels
   float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
+  int32_t alone_max;                       // ... in the queues that hold no more such rows than this
   int32_t h, h_kv, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
   size_t kv_head_stride;
 };
@@ -1287,6 +1288,7 @@ struct PlanLds {
   int start[kClasses][9];                           // first rank of the class that belongs to part x
   int before[kClasses][8], qlen[8];
   int total;                                        // entries + 3 per row (a row costs about three blocks beside its own)
+  int above[8];                                     // rows of queue x with that much work
   unsigned alone[8];
 };
 __device__ __forceinline__ int64_t uniform64(int64_t x) {
@@ -1381,7 +1383,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     m.rows[wave][lane] = crow;
     m.work[wave][lane] = cwork;
   }
-  if (t < 8) m.alone[t] = 0;
+  if (t < 8) m.alone[t] = m.above[t] = 0;
   if (t == 8) m.total = 0;
   __syncthreads();
   if (t < kClasses) {
@@ -1437,7 +1439,10 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     if (len[c] < 0) continue;
     const int k = length_class(len[c]), x = part(cum[c], k);
     int entry = m.before[k][x] + rank[c] - m.start[k][x];
-    if ((float)len[c] > alone_from && entry < half) atomicOr(&m.alone[x], 1u << entry);
+    if ((float)len[c] > alone_from) {
+      atomicAdd(&m.above[x], 1);
+      if (entry < half) atomicOr(&m.alone[x], 1u << entry);
+    }
     for (int y = 0; y < x; ++y) entry += m.qlen[y];
     rank[c] = entry;
     cum[c] = 0;
@@ -1467,7 +1472,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   }
   __syncthreads();
   if (t < 8) {
-    const unsigned alone = m.alone[t];
+    const unsigned alone = m.above[t] <= a.alone_max ? m.alone[t] : 0;
     plan[kPlanAlone + t] = (int)alone;
     // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
     const int dealt = dealt_rows(t, n_queues, grid) - __popc(alone);
@@ -1799,9 +1804,16 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // 8100 177.8 / 165.4 / 164.5 / 164.6 / 165.2, 8/2 heads, 8192 78.6 / 76.3 / 75.9 / 76.6 / 76.2; below 1.4 other calls lose:
   // 16 heads, 19290, bidirectional 459 / 480 / 462 / 461 / 461, 4 heads, 128K 1640 / 1691 / 1646 / 1640 / 1638, the eight packed
   // prompts of perf/cases.py 656 / 663 / 659 / 659 / 657.
+  // A CU with one workgroup does less than one with two, and the workgroup that ended does not come back: a queue (an XCD)
+  // with more such rows than 5/8 of its CUs has none alone.  us without / with / only up to 5/8, M rows of N blocks among h * N
+  // with one block (h x N, M): four waves 32 x 124, 128 278 / 253 / 252, 8 x 100, 288 332 / 382 / 333; two waves (beyond kW32MaxRows
+  // rows) 14 x 300, 128 737 / 705 / 703, 288 859 / 1425 / 862; general kernel 32 x 124, 128 305 / 281 / 281, 8 x 100, 288 329 / 452 / 329;
+  // d = 64 32 x 124, 128 205 / 200 / 199, 8 x 100, 288 217 / 310 / 217.  Causal, one of 8 heads with full lists, N = 512, whose 73
+  // longest rows lie in three queues: four waves 1276 / 1333 / 1276, general kernel 1361 / 1286 / 1362.
   constexpr float kAlone = 1.4f;
   const bool full = grid == persistent_grid(0x7fffffff, 2) && grid % (2 * kXcds) == 0 && grid / (2 * kXcds) <= 32;
   const float alone = params->block == 128 && per_cu == 2 && full ? kAlone : 0.f;
+  const int alone_max = grid / (2 * kXcds) * 5 / 8;
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
@@ -1874,6 +1886,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.counter_stride = pulls.stride;
     pa.grid = grid;
     pa.alone = alone;
+    pa.alone_max = alone_max;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
     const int prep_grid = pa.n_plans + pa.n_check + (v_bf16 != nullptr ? h_kv * N : 0);

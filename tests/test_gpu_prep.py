@@ -146,3 +146,55 @@ def test_rows_that_have_a_cu_to_themselves(tail, longest):
     ref = orc.block_sparse_attention(Q, K, V, mask, B, rows)
     for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
         assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
+
+
+def _marks(raw, lay, row_ptr, h, N, cus):
+    """The marks of a plan, and those it should have by its queues and lists: bit p of queue x where its p-th row is longer
+    than 1.4 times the work of an average workgroup, in queues with no more such rows than 5/8 of the CUs of an XCD."""
+    plan = raw[lay["plan"]:lay["plan"] + 160].view(np.int32)
+    items = raw[lay["items"]:lay["items"] + h * N * 16].view(np.int32).reshape(-1, 4)
+    lens = np.diff(row_ptr)
+    line = np.float32(1.4) * np.float32(lens.sum() + 3 * h * N) / np.float32(2 * cus)
+    want = []
+    for x in range(8):
+        rows = items[plan[x]:plan[x] + plan[8 + x]]
+        long = lens[rows[:, 0] * N + (rows[:, 1] & 0xffff)] > line
+        want.append(sum(1 << p for p in np.nonzero(long[:cus // 8])[0]) if long.sum() <= cus // 8 * 5 // 8 else 0)
+    return plan[32:40].view(np.uint32).tolist(), want
+
+
+@pytest.mark.parametrize("h,N,tail,d,n_long,some", [
+    (8, 100, 128, 128, 300, False),      # three heads of full lists: more long rows than CUs; four waves of 32 queries
+    (8, 100, 128, 128, 96, True),
+    (8, 100, 9, 128, 300, False),        # the general kernel
+    (14, 300, 128, 128, 264, False),     # two waves of 64 queries
+    (14, 300, 128, 128, 160, True),      # 20 a queue
+    (8, 100, 9, 64, 300, False),
+])
+def test_long_rows_share_their_cus_where_they_are_many(h, N, tail, d, n_long, some):
+    B, L = 128, (N - 1) * 128 + tail
+    rng = np.random.default_rng(h + n_long)
+    lens = np.ones(h * N, np.int64)
+    lens[rng.choice(h * N, n_long, replace=False) if some else np.arange(n_long)] = N
+    row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col_idx = np.concatenate([np.arange(N) if n > 1 else [r % N] for r, n in enumerate(lens)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    q, k, v = (torch.randn((n, L, d), generator=g, device="cuda").bfloat16() for n in (h, 1, 1))
+    bands = {64: (32, 48), 128: (64, 96)}[d]
+
+    def run(heads):
+        params = pb.make_params(len(heads), 1, L, B, *bands, 0.9, pb.PRISM_FLAG_BIDIRECTIONAL, d)
+        at = row_ptr[heads[0] * N]
+        rp, ci = row_ptr[heads[0] * N:(heads[-1] + 1) * N + 1] - at, col_idx[at:row_ptr[(heads[-1] + 1) * N]]
+        out = torch.full_like(q[heads], float("nan"))
+        ws = pb.alloc_workspace(pb.prism_sparse_attn_workspace_bytes(params))
+        pb.prism_sparse_attn(params, q[heads].contiguous(), k, v, *gu.csr_to_device(rp, ci), out, None, ws)
+        torch.cuda.synchronize()
+        return out, ws.cpu().numpy()
+
+    out, raw = run(list(range(h)))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    got, want = _marks(raw, queue_layout(h, 1, N, B, L, d), row_ptr, h, N, cus)
+    assert got == want and any(want) == some, (got, want)
+    for i in range(h):                                     # each row once: the bits of calls on single heads, which mark none
+        assert torch.equal(out[i].view(torch.int16), run([i])[0][0].view(torch.int16)), i
