@@ -1275,6 +1275,7 @@ struct PrepArgs {
   int32_t grid, pair_grid;                 // workgroups of the attention kernels
   float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
   int32_t alone_max;                       // ... in the queues that hold no more such rows than this
+  float halve;                             // every row has, where the longest is a CU's average work over this or more (0: no)
   int32_t h, h_kv, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
   size_t kv_head_stride;
 };
@@ -1290,6 +1291,7 @@ struct PlanLds {
   int total;                                        // entries + 3 per row (a row costs about three blocks beside its own)
   int above[8];                                     // rows of queue x with that much work
   unsigned alone[8];
+  int longest;
 };
 __device__ __forceinline__ int64_t uniform64(int64_t x) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = __builtin_amdgcn_readfirstlane((int)(x >> 32));
@@ -1384,7 +1386,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     m.work[wave][lane] = cwork;
   }
   if (t < 8) m.alone[t] = m.above[t] = 0;
-  if (t == 8) m.total = 0;
+  if (t == 8) m.total = m.longest = 0;
   __syncthreads();
   if (t < kClasses) {
     int r = 0, w = 0;
@@ -1398,6 +1400,14 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     atomicAdd(&m.total, w + 2 * r);
     m.scale[t] = w > 0 ? (float)n_queues / (float)w : 0.f;
     for (int x = 0; x < 9; ++x) m.start[t][x] = r;
+  }
+  if (a.halve > 0.f) {
+    int longest = 0;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) longest = max(longest, len[c]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off, 64));
+    if (lane == 0) atomicMax(&m.longest, longest);
   }
   __syncthreads();
   // part of the row that ends at work `w` of its class: grows with w, 0 .. n_queues - 1
@@ -1472,7 +1482,8 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   }
   __syncthreads();
   if (t < 8) {
-    const unsigned alone = m.above[t] <= a.alone_max ? m.alone[t] : 0;
+    const bool halve = stride == 1 && (float)m.total < a.halve * (float)m.longest * (float)(grid / 2);
+    const unsigned alone = halve ? ~0u >> (32 - half) : m.above[t] <= a.alone_max ? m.alone[t] : 0;
     plan[kPlanAlone + t] = (int)alone;
     // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
     const int dealt = dealt_rows(t, n_queues, grid) - __popc(alone);
@@ -1767,15 +1778,16 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // resident workgroups per CU, by the LDS the two tiles of a workgroup take (2 * B * d * 2 bytes of the
   // CU's 160 KB) and its waves: 2 at B = 128, d = 128 (64 KB, 4 waves).  At d = 256 a wave has a SIMD to itself: one
   // workgroup of four waves, or two of two at B = 64.  Two of these share the LDS and the copies of the CU, which a call
-  // of few rows, bound by its longest ones, feels and a longer one does not; around 2600 rows it depends on the lists.  us of
+  // of few rows, bound by its longest ones, feels and a longer one does not; beyond 11 rows per CU the lists decide (halve, below;
+  // before it they mostly speak for one, though not always: 32/8 at 5050 tokens).  us of
   // attention, one -> two: 16/4 heads, 8100 tokens (2032 rows) 313 -> 326, 10001 (2512) 368 -> 388, 12001 (3008) 524 -> 462,
   // 30016 (7504) 2605 -> 1630; 32/8, 2000 (1024) 90 -> 97, 5050 (2528) 247 -> 219, 8100 (4064) 489 -> 350, 16300 (8160)
   // 1354 -> 858; 28/4, 4001 (1764) 169 -> 178, 6050 (2660) 249 -> 259; 7/1, 24001 (2632) 252 -> 268.
   const int tile_pair = 2 * params->block * d * 2;
   int per_cu = (160 * 1024) / tile_pair;
   per_cu = per_cu > 4 ? 4 : per_cu;
-  constexpr int kTwoWideRows = 2816;     // 11 per CU
-  if (d > 128) per_cu = params->block == 64 && R > kTwoWideRows ? 2 : 1;
+  const int two_wide_rows = 11 * persistent_grid(0x7fffffff, 1);
+  if (d > 128) per_cu = params->block == 64 && R > two_wide_rows ? 2 : 1;
   else if (params->block == 128 && per_cu > 2) per_cu = 2;
   const int grid = persistent_grid(R, per_cu);
   if (grid <= 0) return PRISM_ERR_HIP;
@@ -1814,6 +1826,13 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const bool full = grid == persistent_grid(0x7fffffff, 2) && grid % (2 * kXcds) == 0 && grid / (2 * kXcds) <= 32;
   const float alone = params->block == 128 && per_cu == 2 && full ? kAlone : 0.f;
   const int alone_max = grid / (2 * kXcds) * 5 / 8;
+  // Wide rows (d = 256, two workgroups per CU): all have a CU to themselves, so half of the workgroups end, where the longest row
+  // bounds the call, a CU's average work (entries + 3 a row) being less than 1.2 times the longest row.  us of preparation
+  // and attention, one / two per CU, at that ratio: 16/2 heads, 11305 tokens (0.90) 408 / 432, 16/8, 11309 (0.94) 385 / 412, 16/4, 11294 (1.02)
+  // 413 / 438, 28/4, 7568 (1.14) 304 / 325, 8/1, 24071 (1.17) 218 / 233; 4/2, 45368 (1.21) 639 / 605, 3/1, 64020 (1.23) 279 / 260,
+  // 16/4, 12066 (1.25) 530 / 482.  Calls of several phases or more than kPrepMaxRows rows have two, whose preparation does
+  // not look for the longest row (16/16, 11298 (0.95) 632 / 562, 15288 (1.12) 771 / 714).
+  const float halve = d > 128 && per_cu == 2 && full ? 1.2f : 0.f;
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
@@ -1887,6 +1906,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.grid = grid;
     pa.alone = alone;
     pa.alone_max = alone_max;
+    pa.halve = halve;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
     const int prep_grid = pa.n_plans + pa.n_check + (v_bf16 != nullptr ? h_kv * N : 0);

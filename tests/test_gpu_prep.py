@@ -198,3 +198,61 @@ def test_long_rows_share_their_cus_where_they_are_many(h, N, tail, d, n_long, so
     assert got == want and any(want) == some, (got, want)
     for i in range(h):                                     # each row once: the bits of calls on single heads, which mark none
         assert torch.equal(out[i].view(torch.int16), run([i])[0][0].view(torch.int16)), i
+
+
+@pytest.mark.parametrize("h,hkv,N,tail,bidir,ratio,halved", [
+    (16, 8, 177, 7, False, 1.19, True), (16, 8, 177, 7, False, 1.21, False),
+    (16, 2, 177, 33, True, 1.19, True), (16, 2, 177, 64, True, 1.21, False),
+])
+def test_wide_rows_bound_by_the_longest_have_a_cu_to_themselves(h, hkv, N, tail, bidir, ratio, halved):
+    """d = 256, B = 64, 2832 rows: two workgroups per CU, the second of which end at once where the longest row bounds the
+    call.  Every row is done once, with the bits of calls on a few heads, and of the oracle in value."""
+    B, d, L = 64, 256, (N - 1) * 64 + tail
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(h)
+    # one list of N blocks, the others up to 40, until a CU's average work is `ratio` times N
+    lens = np.ones((h, N), np.int64)
+    most = np.minimum(40, np.full(N, N) if bidir else np.arange(N) + 1)
+    lens[3, N - 1] = N
+    spare = int(ratio * N * cus) - 3 * h * N - int(lens.sum())
+    for r in rng.permutation(h * N):
+        i, u = divmod(int(r), N)
+        if lens[i, u] == 1:
+            more = min(int(most[u]) - 1, spare)
+            lens[i, u] += more
+            spare -= more
+    assert spare == 0
+    lens = lens.reshape(-1)
+    row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    mask = np.zeros((h, N, N), bool)
+    for r, n in enumerate(lens):
+        i, u = divmod(r, N)
+        top = N if bidir else u + 1
+        mask[i, u, (u - np.arange(n)) % top] = True        # the row's own block among them
+    row_ptr, col_idx = orc.mask_to_csr(mask)
+    assert (np.diff(row_ptr) == lens).all()
+    g = torch.Generator(device="cuda").manual_seed(h)
+    q, k, v = (torch.randn((n, L, d), generator=g, device="cuda").bfloat16() for n in (h, hkv, hkv))
+    flags = pb.PRISM_FLAG_BIDIRECTIONAL if bidir else 0
+
+    def run(heads, kv):
+        params = pb.make_params(len(heads), len(kv), L, B, 128, 192, 0.9, flags, d)
+        out = torch.full_like(q[heads], float("nan"))
+        ws = pb.alloc_workspace(pb.prism_sparse_attn_workspace_bytes(params))
+        pb.prism_sparse_attn(params, q[heads].contiguous(), k[kv].contiguous(), v[kv].contiguous(),
+                             *gu.csr_to_device(*orc.mask_to_csr(mask[heads])), out, None, ws)
+        torch.cuda.synchronize()
+        at = queue_layout(len(heads), len(kv), N, B, L, d)["plan"]
+        return out, ws[at:at + 160].cpu().numpy().view(np.uint32)[32:40]
+
+    out, alone = run(list(range(h)), list(range(hkv)))
+    assert (alone == (0xffffffff >> (32 - cus // 8) if halved else 0)).all(), alone
+    for i in (0, 3, h - 1):
+        o, few = run([i], [i // (h // hkv)])
+        assert (few == 0).all() and torch.equal(out[i].view(torch.int16), o[0].view(torch.int16)), i
+    assert not torch.isnan(out).any()
+    Q, K, V = (t.float().cpu().numpy().astype(np.float64) for t in (q, k, v))
+    rows = {(3, N - 1), (0, 0), (h - 1, N // 2)}
+    ref = orc.block_sparse_attention(Q, K, V, mask, B, rows, causal=not bidir)
+    for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
+        assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
