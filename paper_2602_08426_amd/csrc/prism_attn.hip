@@ -304,13 +304,19 @@ __device__ __forceinline__ int dealt_rows(int x, int n_queues, int grid) {
 // workgroups, out of rows, at 105 - 115.  plan[kPlanAlone + x] has bit p for the p-th row of queue x if it is such a
 // row; it is dealt to workgroup x + 8 p, which shares its CU with workgroup x + 8 p + gridDim.x / 2 (in the order that
 // the hardware places a grid of two workgroups per CU; otherwise only the gain is lost).  That one ends at once, and the
-// workgroups behind it move up to its row.  Returns the workgroup's first row in its queue, or -1: it ends.
-__device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, int queue, int n_queues) {
+// workgroups behind it move up to its row.  Of a packed batch a launch may leave the row to another kernel (`take`: the
+// sequences that are its own): the workgroup then goes on, with a row that nobody starts with.
+// Returns the workgroup's first row in its queue, or what it does without one.
+enum { kFirstEnds = -1, kFirstPulls = -2 };
+__device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, const int4* __restrict__ items, int queue, int n_queues,
+                                         int n_seqs, int take) {
   const int p = (int)blockIdx.x / n_queues, half = (int)gridDim.x / 2 / n_queues;
   const unsigned alone = plan[kPlanAlone + queue];
   if (alone == 0 || p < half) return p;                     // bits are set only where half <= 32
   const int mate = p - half;
-  return (alone >> mate) & 1u ? -1 : p - __popc(alone & ((1u << mate) - 1u));
+  if (((alone >> mate) & 1u) == 0) return p - __popc(alone & ((1u << mate) - 1u));
+  if (n_seqs == 1 || mate >= plan[kPlanLen + queue]) return kFirstEnds;
+  return (take >> (items[plan[kPlanStart + queue] + mate].x >> kSeqShift)) & 1 ? kFirstEnds : kFirstPulls;
 }
 
 __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len, int* entry) {
@@ -417,9 +423,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // read of the next row's queue entry are hidden behind that last step.
   int lane_zero;                                     // 0, but opaque to the compiler
   asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-  const int first = first_row(plan, my_queue, n_queues);
-  if (first < 0) return;
-  if (t == 0) next_item = first;
+  const int first = first_row(plan, items, my_queue, n_queues, seqs.n, take);
+  if (first == kFirstEnds) return;
+  if (t == 0) next_item = first == kFirstPulls ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
   __syncthreads();
   int cur_x = 0, cur_y = 0, cur_z = 0, cur_w = 0;     // the current row's queue entry, wave-uniform
   int kind_cur;
@@ -875,9 +881,9 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
   int32_t* __restrict__ counter = pulls.at;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   int pulled = 0;
-  const int first = first_row(plan, my_queue, n_queues);
-  if (first < 0) return;
-  if (t == 0) pulled = first;
+  const int first = first_row(plan, items, my_queue, n_queues, seqs.n, ~dirty);
+  if (first == kFirstEnds) return;
+  if (t == 0) pulled = first == kFirstPulls ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
   for (;;) {
     // hand the pulled queue position to both waves
     __syncthreads();

@@ -256,3 +256,56 @@ def test_wide_rows_bound_by_the_longest_have_a_cu_to_themselves(h, hkv, N, tail,
     ref = orc.block_sparse_attention(Q, K, V, mask, B, rows, causal=not bidir)
     for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
         assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
+
+
+def _counters(raw, lay, h, N):
+    """The two sets of pull counters that the preparation leaves in row_part, 8 each."""
+    stride = 32
+    while stride * 16 * 4 > lay["bins"] - lay["row_part"]:
+        stride //= 2
+    part = raw[lay["row_part"]:lay["bins"]].view(np.int32)
+    return part[:8 * stride:stride].tolist(), part[8 * stride:16 * stride:stride].tolist()
+
+
+@pytest.mark.parametrize("dirty", [0, 1])
+def test_rows_that_another_kernel_takes_hold_no_cu(dirty):
+    """A packed batch of two, 752 rows: the first holds the long rows, and one of the two has a list with an entry to skip.
+    Where the launch does not take the long rows, the workgroups on their CUs go on: every workgroup pulls its queue to the end."""
+    h, B, Ns = 8, 128, [64, 30]
+    flat = [np.arange(u + 1) if i == 5 else np.array([u]) for i in range(h) for u in range(Ns[0])]
+    short = [np.arange(max(0, u - 2), u + 1) for i in range(h) for u in range(Ns[1])]
+    cu = [0, 128 * Ns[0], 128 * sum(Ns)]
+    g = torch.Generator(device="cuda").manual_seed(8)
+    q, k, v = (torch.randn((n, cu[-1], 128), generator=g, device="cuda").bfloat16() for n in (h, 2, 2))
+    params = pb.make_params(h, 2, cu[-1], B)
+    mo, ro, co = pb.prism_varlen_layout(params, cu)
+    rp, ci = np.zeros(ro[-1], np.int32), np.zeros(co[-1], np.int32)
+    csr = []
+    for s, lists in enumerate((flat, short)):
+        lists = [c.astype(np.int32) for c in lists]
+        if s == dirty:
+            lists[7] = np.concatenate([[-1], lists[7]]).astype(np.int32)
+        row_ptr = np.concatenate([[0], np.cumsum([len(c) for c in lists])]).astype(np.int32)
+        csr.append((row_ptr, np.concatenate(lists)))
+        rp[ro[s]:ro[s] + len(row_ptr)] = row_ptr
+        ci[co[s]:co[s] + row_ptr[-1]] = csr[s][1]
+    out = torch.full_like(q, float("nan"))
+    lse = torch.full(q.shape[:2], float("nan"), device="cuda")
+    ws = pb.alloc_workspace(pb.prism_sparse_attn_varlen_workspace_bytes(params, cu) + (64 << 20))
+    pb.prism_sparse_attn_varlen(params, cu, q, k, v, torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), out, lse, ws)
+    torch.cuda.synchronize()
+    for s in range(2):
+        ps = pb.make_params(h, 2, cu[s + 1] - cu[s], B)
+        o, l = gu.gpu_sparse_attn(ps, *(x[:, cu[s]:cu[s + 1]].contiguous() for x in (q, k, v)), *gu.csr_to_device(*csr[s]))
+        assert torch.equal(out[:, cu[s]:cu[s + 1]].view(torch.int16), o.view(torch.int16)), s
+        assert torch.equal(lse[:, cu[s]:cu[s + 1]], l), s
+    lay, raw = queue_layout(h, 2, sum(Ns), B), ws.cpu().numpy()
+    plan = raw[lay["plan"]:lay["plan"] + 160].view(np.uint32)
+    length, marks = plan[8:16].astype(int), [bin(int(w)).count("1") for w in plan[32:40]]
+    assert sum(marks) >= 32 and plan[24] == 1
+    each = 2 * torch.cuda.get_device_properties(0).multi_processor_count // 8
+    assert (length >= each).all()
+    # a workgroup that goes on meets the end of its queue once, by a pull; the others end without one
+    for n, (took, done) in enumerate(zip([dirty != 0, dirty == 0], _counters(raw, lay, h, sum(Ns)))):
+        for x in range(8):
+            assert done[x] >= length[x] + each - (marks[x] if took else 0), (n, x, done, length, marks)
