@@ -308,6 +308,7 @@ __device__ __forceinline__ int dealt_rows(int x, int n_queues, int grid) {
 // sequences that are its own): the workgroup then goes on, with a row that nobody starts with.
 // Returns the workgroup's first row in its queue, or what it does without one.
 enum { kFirstEnds = -1, kFirstPulls = -2 };
+template <bool kMayLeave>
 __device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, const int4* __restrict__ items, int queue, int n_queues,
                                          int n_seqs, int take) {
   const int p = (int)blockIdx.x / n_queues, half = (int)gridDim.x / 2 / n_queues;
@@ -315,7 +316,7 @@ __device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, const
   if (alone == 0 || p < half) return p;                     // bits are set only where half <= 32
   const int mate = p - half;
   if (((alone >> mate) & 1u) == 0) return p - __popc(alone & ((1u << mate) - 1u));
-  if (n_seqs == 1 || mate >= plan[kPlanLen + queue]) return kFirstEnds;
+  if (!kMayLeave || n_seqs == 1) return kFirstEnds;
   return (take >> (items[plan[kPlanStart + queue] + mate].x >> kSeqShift)) & 1 ? kFirstEnds : kFirstPulls;
 }
 
@@ -423,9 +424,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // read of the next row's queue entry are hidden behind that last step.
   int lane_zero;                                     // 0, but opaque to the compiler
   asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-  const int first = first_row(plan, items, my_queue, n_queues, seqs.n, take);
+  constexpr bool kMayLeave = BLK == 128 && D == kHeadDim;    // the form that stands behind the 64-queries-per-wave kernel
+  const int first = first_row<kMayLeave>(plan, items, my_queue, n_queues, seqs.n, take);
   if (first == kFirstEnds) return;
-  if (t == 0) next_item = first == kFirstPulls ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
+  if (t == 0) next_item = kMayLeave && first == kFirstPulls ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
   __syncthreads();
   int cur_x = 0, cur_y = 0, cur_z = 0, cur_w = 0;     // the current row's queue entry, wave-uniform
   int kind_cur;
@@ -881,7 +883,7 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
   int32_t* __restrict__ counter = pulls.at;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   int pulled = 0;
-  const int first = first_row(plan, items, my_queue, n_queues, seqs.n, ~dirty);
+  const int first = first_row<true>(plan, items, my_queue, n_queues, seqs.n, ~dirty);
   if (first == kFirstEnds) return;
   if (t == 0) pulled = first == kFirstPulls ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
   for (;;) {
