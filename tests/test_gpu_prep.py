@@ -8,6 +8,7 @@ from oracle import prism_oracle as orc
 from paper_2602_08426_amd import binding as pb
 from tests import gpu_util as gu
 from tests.test_gpu_queues import test_every_row_is_queued_once_and_the_queues_are_balanced as check_queues
+from tests.test_gpu_queues import _counters as queue_counters
 from tests.test_gpu_queues import _layout as queue_layout
 from tests.test_gpu_queues import test_pair_plan_at_block_64 as check_pair_plan
 
@@ -163,27 +164,38 @@ def _marks(raw, lay, row_ptr, h, N, cus):
     return plan[32:40].view(np.uint32).tolist(), want
 
 
-@pytest.mark.parametrize("h,N,tail,d,n_long,some", [
-    (8, 100, 128, 128, 300, False),      # three heads of full lists: more long rows than CUs; four waves of 32 queries
-    (8, 100, 128, 128, 96, True),
-    (8, 100, 9, 128, 300, False),        # the general kernel
-    (14, 300, 128, 128, 264, False),     # two waves of 64 queries
-    (14, 300, 128, 128, 160, True),      # 20 a queue
-    (8, 100, 9, 64, 300, False),
+@pytest.mark.parametrize("h,N,tail,d,n_long,some,dirty", [
+    (8, 100, 128, 128, 300, False, False),      # three heads of full lists: more long rows than CUs; four waves of 32 queries
+    (8, 100, 128, 128, 96, True, False),
+    (8, 100, 128, 128, 96, True, True),         # the general kernel with the second set of counters
+    (8, 100, 9, 128, 300, False, False),        # the general kernel alone
+    (8, 100, 9, 128, 96, True, False),
+    (14, 300, 128, 128, 264, False, False),     # two waves of 64 queries
+    (14, 300, 128, 128, 160, True, False),      # 20 a queue
+    (14, 300, 128, 128, 40, True, True),
+    (8, 100, 9, 64, 300, False, False),
+    (8, 100, 9, 64, 96, True, True),
+    (32, 40, 128, 64, 8, True, False),
 ])
-def test_long_rows_share_their_cus_where_they_are_many(h, N, tail, d, n_long, some):
+def test_long_rows_share_their_cus_where_they_are_many(h, N, tail, d, n_long, some, dirty):
+    """Bidirectional calls of n_long lists of N blocks among lists of one: the plan marks the long rows that it should, and
+    every row has the bits of calls on single heads, which mark none."""
     B, L = 128, (N - 1) * 128 + tail
     rng = np.random.default_rng(h + n_long)
     lens = np.ones(h * N, np.int64)
     lens[rng.choice(h * N, n_long, replace=False) if some else np.arange(n_long)] = N
     row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     col_idx = np.concatenate([np.arange(N) if n > 1 else [r % N] for r, n in enumerate(lens)]).astype(np.int32)
+    if dirty:
+        col_idx[row_ptr[np.nonzero(lens == N)[0][3]]] = -1
     g = torch.Generator(device="cuda").manual_seed(4)
     q, k, v = (torch.randn((n, L, d), generator=g, device="cuda").bfloat16() for n in (h, 1, 1))
     bands = {64: (32, 48), 128: (64, 96)}[d]
 
     def run(heads):
-        params = pb.make_params(len(heads), 1, L, B, *bands, 0.9, pb.PRISM_FLAG_BIDIRECTIONAL, d)
+        # one head's lists may be clean where the call's are not: then the same kernel by the flag
+        flags = pb.PRISM_FLAG_BIDIRECTIONAL | (pb.PRISM_FLAG_GENERAL_KERNEL if dirty and len(heads) < h else 0)
+        params = pb.make_params(len(heads), 1, L, B, *bands, 0.9, flags, d)
         at = row_ptr[heads[0] * N]
         rp, ci = row_ptr[heads[0] * N:(heads[-1] + 1) * N + 1] - at, col_idx[at:row_ptr[(heads[-1] + 1) * N]]
         out = torch.full_like(q[heads], float("nan"))
@@ -196,7 +208,7 @@ def test_long_rows_share_their_cus_where_they_are_many(h, N, tail, d, n_long, so
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     got, want = _marks(raw, queue_layout(h, 1, N, B, L, d), row_ptr, h, N, cus)
     assert got == want and any(want) == some, (got, want)
-    for i in range(h):                                     # each row once: the bits of calls on single heads, which mark none
+    for i in range(h):
         assert torch.equal(out[i].view(torch.int16), run([i])[0][0].view(torch.int16)), i
 
 
@@ -258,15 +270,6 @@ def test_wide_rows_bound_by_the_longest_have_a_cu_to_themselves(h, hkv, N, tail,
         assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
 
 
-def _counters(raw, lay, h, N):
-    """The two sets of pull counters that the preparation leaves in row_part, 8 each."""
-    stride = 32
-    while stride * 16 * 4 > lay["bins"] - lay["row_part"]:
-        stride //= 2
-    part = raw[lay["row_part"]:lay["bins"]].view(np.int32)
-    return part[:8 * stride:stride].tolist(), part[8 * stride:16 * stride:stride].tolist()
-
-
 @pytest.mark.parametrize("dirty", [0, 1])
 def test_rows_that_another_kernel_takes_hold_no_cu(dirty):
     """A packed batch of two, 752 rows: the first holds the long rows, and one of the two has a list with an entry to skip.
@@ -306,6 +309,6 @@ def test_rows_that_another_kernel_takes_hold_no_cu(dirty):
     each = 2 * torch.cuda.get_device_properties(0).multi_processor_count // 8
     assert (length >= each).all()
     # a workgroup that goes on meets the end of its queue once, by a pull; the others end without one
-    for n, (took, done) in enumerate(zip([dirty != 0, dirty == 0], _counters(raw, lay, h, sum(Ns)))):
+    for n, (took, done) in enumerate(zip([dirty != 0, dirty == 0], queue_counters(raw, lay))):
         for x in range(8):
             assert done[x] >= length[x] + each - (marks[x] if took else 0), (n, x, done, length, marks)

@@ -4,7 +4,8 @@
 (q-head, q-block) row and a plan of eight queue segments.  The parity tests see a broken queue
 only through the rows they sample, so this test reads the tables back after a call and checks
 what must hold for every row: each row is listed exactly once, with the clamped bounds of its
-list and its first valid entry; the segments tile the table; every queue was pulled to its end;
+list and its first valid entry; the segments tile the table; the pull counters start behind the rows
+that are dealt out by workgroup number, and every queue was pulled to its end; every row was written;
 inside a queue the (phase, length class) groups come in order; the queues hold about equal work.
 
 The offsets below restate the workspace layout of prism_attn.hip (V^T image, then the int4
@@ -61,6 +62,33 @@ def _layout(h, hkv, N, B, L=None, d=128):
     return off
 
 
+def _counters(raw, lay):
+    """The two sets of eight pull counters in row_part: of the first and of the second attention kernel of the call."""
+    stride = 32
+    while stride * 16 * 4 > lay["bins"] - lay["row_part"]:
+        stride //= 2
+    part = raw[lay["row_part"]:lay["bins"]].view(np.int32)
+    return part[:8 * stride:stride], part[8 * stride:16 * stride:stride]
+
+
+def _check_counters(pulled, untouched, length, other_length, workgroups, other_workgroups, marks=(0,) * 8):
+    """`untouched` is the set of a kernel that returned at once: the rows of every queue that its workgroups start with.
+    The other set went on from there: every workgroup that started with a row meets the end of its queue by one pull, and
+    at most all of them that of another queue."""
+    def dealt(grid, x):
+        n = 8 if grid >= 8 else 1
+        return (grid - x + n - 1) // n - marks[x] if x < n else 0
+    for x in range(8):
+        assert untouched[x] == dealt(other_workgroups, x), (x, untouched)
+        mine = dealt(workgroups, x)
+        assert length[x] + mine <= pulled[x] <= max(length[x], mine) + workgroups, (x, pulled, length)
+    assert sum(length) and sum(other_length)
+
+
+def _workgroups(rows, per_cu):
+    return min(rows, per_cu * torch.cuda.get_device_properties(0).multi_processor_count)
+
+
 def _length_class(n):
     if n <= 1:
         return N_CLASSES - 1
@@ -106,11 +134,12 @@ def test_every_row_is_queued_once_and_the_queues_are_balanced(h, hkv, L, B, bidi
     q = torch.zeros((h, L, 128), dtype=torch.bfloat16, device="cuda")
     k = torch.zeros((hkv, L, 128), dtype=torch.bfloat16, device="cuda")
     v = torch.zeros((hkv, L, 128), dtype=torch.bfloat16, device="cuda")
-    out = torch.empty_like(q)
+    out = torch.full_like(q, float("nan"))
     ws = pb.alloc_workspace(lay["total"])
     rp_d, ci_d = torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col_idx).cuda()
     pb.prism_sparse_attn(params, q, k, v, rp_d, ci_d, nnz, out, None, ws)
     torch.cuda.synchronize()
+    assert not torch.isnan(out).any()                         # every row was written
     raw = ws.cpu().numpy()
 
     rows = h * N
@@ -121,9 +150,16 @@ def test_every_row_is_queued_once_and_the_queues_are_balanced(h, hkv, L, B, bidi
     # the segments tile the table, and every queue was pulled past its end
     assert length.sum() == rows
     np.testing.assert_array_equal(start, np.cumsum(length) - length)
-    assert (pulled >= length).all()
-    n_queues = 8 if min(rows, 512 if B == 128 else 1024) >= 8 else 1
+    assert (pulled >= length).all()                          # the plan's own words: every queue was seen exhausted
+    grid = _workgroups(rows, 2 if B == 128 else 4)
+    n_queues = 8 if grid >= 8 else 1
     assert (length[n_queues:] == 0).all()
+    marks = [bin(int(w)).count("1") for w in raw[lay["plan"] + 128:lay["plan"] + 160].view(np.uint32)]
+    first, second = _counters(raw, lay)
+    if "image16" in lay and bool((col_idx[:nnz] < 0).any()):   # a list with garbage: the second kernel takes the call
+        first, second = second, first
+    if B == 128 or N % 2:                                      # (where the pair kernel may run, test_pair_plan_at_block_64)
+        _check_counters(first, second, length, length, grid, grid, marks)
 
     # every row exactly once, with its own list bounds and first valid entry
     hq, u = items[:, 0], items[:, 1] & 0xFFFF
@@ -191,11 +227,12 @@ def test_pair_plan_at_block_64(h, hkv, N, dirty):
     q = torch.zeros((h, L, 128), dtype=torch.bfloat16, device="cuda")
     k = torch.zeros((hkv, L, 128), dtype=torch.bfloat16, device="cuda")
     v = torch.zeros((hkv, L, 128), dtype=torch.bfloat16, device="cuda")
-    out = torch.empty_like(q)
+    out = torch.full_like(q, float("nan"))
     ws = pb.alloc_workspace(lay["total"])
     pb.prism_sparse_attn(params, q, k, v, torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col_idx).cuda(),
                          int(row_ptr[-1]), out, None, ws)
     torch.cuda.synchronize()
+    assert not torch.isnan(out).any()
     raw = ws.cpu().numpy()
     rows = h * N // 2
     items = raw[lay["pair_items"]:lay["pair_items"] + rows * 16].view(np.int32).reshape(rows, 4)
@@ -210,6 +247,12 @@ def test_pair_plan_at_block_64(h, hkv, N, dirty):
     np.testing.assert_array_equal(items[:, 2], row_ptr[r0])
     np.testing.assert_array_equal(items[:, 3], row_ptr[r0 + 2])
     assert plan[24] == (1 if dirty else 0)
+    of_plain, of_pairs = _counters(raw, lay)
+    grids = _workgroups(h * N, 4), _workgroups(rows, 2)
+    if dirty:
+        _check_counters(of_plain, of_pairs, plan[8:16], length, *grids)
+    else:
+        _check_counters(of_pairs, of_plain, length, plan[8:16], *grids[::-1])
     if dirty:
         assert (pulled == 0).all() and (plan[16:24] >= plan[8:16]).all()
     else:
