@@ -1314,8 +1314,8 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   const int per_head = seqs.nsum >> (stride - 1);
   const int R = a.h * per_head;
   // What the rows need to know of their sequence: a call of one sequence (kOne) holds it in scalar registers.  Looked up in
-  // LDS for every row and use it was 40 % of the instructions, which bind this workgroup: 38.1 -> 33.1 us at 5024 rows,
-  // 17.1 -> 14.6 at 3104 (d = 64), 43.8 -> 41.1 at 8192.
+  // LDS for every row and use it was 40 % of the instructions, which bind this workgroup: 32.0 -> 29.0 us at 5024 rows,
+  // 16.1 -> 14.4 at 3104 (d = 64), 20.4 -> 19.0 at 4096, 41.1 -> 40.4 at 8192.
   const int n0 = __builtin_amdgcn_readfirstlane(seqs.s[0].N), cap0 = __builtin_amdgcn_readfirstlane(seqs.s[0].cap);
   const int64_t row_at0 = uniform64(seqs.s[0].row0), col_at0 = uniform64(seqs.s[0].col0);
   auto n_of = [&](int s) { return kOne ? n0 : seqs.s[s].N; };
@@ -1467,6 +1467,18 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     if (stride == 1 && len[c] > 0)
       cum[c] = a.col_idx[col0_of(kOne ? 0 : row((wave * CH + c) * 64 + lane).s) + beg[c]];
   }
+  // (in front of the entries, whose stores the workgroup would wait for at a barrier behind them: 42.8 -> 39.8 us in a packed
+  // batch of 4640 rows)
+  __syncthreads();
+  if (t < 8) {
+    const bool halve = stride == 1 && (float)m.total < a.halve * (float)m.longest * (float)(grid / 2);
+    const unsigned alone = halve ? ~0u >> (32 - half) : m.above[t] <= a.alone_max ? m.alone[t] : 0;
+    plan[kPlanAlone + t] = (int)alone;
+    // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
+    const int dealt = dealt_rows(t, n_queues, grid) - __popc(alone);
+    counters[t * a.counter_stride] = dealt;
+    if (more_counters != nullptr) more_counters[t * a.counter_stride] = dealt;
+  }
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
     if (len[c] < 0) continue;
@@ -1487,16 +1499,6 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
       }
     }                                                  // pair rows: clean lists, the kernel finds its first block
     items[rank[c]] = make_int4(kOne ? r.hq : r.hq | (r.s << kSeqShift), r.u | (v << 16), it, end);
-  }
-  __syncthreads();
-  if (t < 8) {
-    const bool halve = stride == 1 && (float)m.total < a.halve * (float)m.longest * (float)(grid / 2);
-    const unsigned alone = halve ? ~0u >> (32 - half) : m.above[t] <= a.alone_max ? m.alone[t] : 0;
-    plan[kPlanAlone + t] = (int)alone;
-    // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
-    const int dealt = dealt_rows(t, n_queues, grid) - __popc(alone);
-    counters[t * a.counter_stride] = dealt;
-    if (more_counters != nullptr) more_counters[t * a.counter_stride] = dealt;
   }
 }
 
@@ -1560,18 +1562,25 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
     int32_t* counters = wg == 0 ? a.counters : a.pair_counters;
     int32_t* more = a.n_plans == 1 ? a.pair_counters : nullptr;
     const int grid = wg == 0 ? a.grid : a.pair_grid;
-    // The waves take 64 * CH rows each in turn, so a CH too large leaves the last waves idle: 5024 rows at 8 instead of 5 are
-    // ten waves' work, and the preparation of 20011 tokens took 32.8 us instead of 25.4; the four of a packed batch, two of them
-    // of 3072 rows, 79.6 instead of 70.4 without CH = 3.
+    // The waves take 64 * CH rows each in turn, so a CH too large leaves the last waves idle (5024 rows at 8 instead of 5 are
+    // ten waves' work): an instance for every 1024 rows.  us of the launch, with 1, 2, 4 and 8 only -> now: 20011 tokens 30.6 -> 24.4,
+    // 32/8 heads, 28000 (7008 rows) 37.0 -> 33.6; packed batches of 2900 rows 20.6 -> 17.5, 4640 37.8 -> 29.1, 7000 43.1 -> 38.3.
+    // At 64 registers a lane, for two workgroups to a CU, the largest instances spill 11 or 12 of them.
     auto run = [&](auto one) __attribute__((always_inline)) {
       constexpr bool kOne = decltype(one)::value;
-      if (R <= kPrepThreads) plan_rows<1, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-      else if (R <= 2 * kPrepThreads) plan_rows<2, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-      else if (R <= 3 * kPrepThreads) plan_rows<3, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-      else if (R <= 4 * kPrepThreads) plan_rows<4, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-      else if (kOne && R <= 5 * kPrepThreads) plan_rows<5, true>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-      else if (kOne && R <= 6 * kPrepThreads) plan_rows<6, true>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
-      else plan_rows<8, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+      switch ((R - 1) / kPrepThreads) {
+#define PRISM_PLAN(CH) \
+  case CH - 1: plan_rows<CH, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan); break
+        PRISM_PLAN(1);
+        PRISM_PLAN(2);
+        PRISM_PLAN(3);
+        PRISM_PLAN(4);
+        PRISM_PLAN(5);
+        PRISM_PLAN(6);
+        PRISM_PLAN(7);
+        PRISM_PLAN(8);
+#undef PRISM_PLAN
+      }
     };
     if (seqs.n == 1) run(std::true_type{});
     else run(std::false_type{});

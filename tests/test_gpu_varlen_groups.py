@@ -23,6 +23,11 @@ pytestmark = pytest.mark.gpu
     ([1024, 640, 2048, 384, 500, 128 * 9], 8, 2, 128, 128, True, 64 << 20, "value"),
     ([4096, 640, 2048, 384, 500, 128 * 90], 32, 8, 128, 128, False, 256 << 20, "list"),   # more than 4096 rows
     ([64 * 6, 64 * 2, 64 * 10, 64 * 4], 4, 1, 64, 128, False, 64 << 20, "list"),
+    # 2976, 5024, 6016 and 6976 rows in one launch
+    ([3000, 3500, 3001, 2049], 32, 8, 128, 128, False, 256 << 20, False),
+    ([6000, 4500, 5000, 4299], 32, 8, 128, 64, False, 256 << 20, False),
+    ([7000, 6500, 6000, 4400], 32, 8, 128, 64, True, 256 << 20, False),
+    ([7000, 7900, 7000, 5801], 32, 8, 128, 64, False, 256 << 20, False),
     # the general form of the estimate over several sequences: 384 strips, 624 strips and bidirectional, N > 1024
     ([8192, 2048, 4096, 3000, 5000], 32, 8, 128, 128, False, 256 << 20, False),
     ([64 * 300, 64 * 299 + 1, 64 * 5], 16, 4, 64, 64, True, 128 << 20, False),
