@@ -1284,7 +1284,7 @@ struct PrepArgs {
   float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
   int32_t alone_max;                       // ... in the queues that hold no more such rows than this
   float halve;                             // every row has, where the longest is a CU's average work over this or more (0: no)
-  int32_t h, h_kv, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
+  int32_t h, h_kv, block, head_dim, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
   size_t kv_head_stride;
 };
 
@@ -1533,14 +1533,25 @@ __device__ __forceinline__ void check_rows(const PrepArgs& a, const SeqTable& se
   if (threadIdx.x == 0) a.check[wg] = s_bad;
 }
 
-template <int BLK, int D>
 union PrepLds {
   PlanLds plan;
-  uint16_t tile[BLK][D + 2];
+  uint16_t tile[128][256 + 2];             // 66 KB: of the largest block, two workgroups to a CU all the same
 };
+// The part of the V image that belongs to workgroup `wg` of the launch's image workgroups.
 template <int BLK, int D>
+__device__ __forceinline__ void prep_image(PrepLds& lds, int& s_over, const PrepArgs& a, const SeqTable& seqs, int wg) {
+  const int s = seq_of(seqs, wg, a.h_kv);
+  const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
+  const int kvh = rr / N, blk = rr - kvh * N;
+  const size_t at = (size_t)wg * D * BLK;
+  vt_image_tile<BLK, D, kPrepThreads>(
+      *reinterpret_cast<uint16_t(*)[BLK][D + 2]>(&lds), s_over,
+      a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * BLK) * D, min(BLK, seqs.s[s].L - blk * BLK),
+      a.vt + at, a.vt16 != nullptr ? a.vt16 + at : nullptr, a.vt16 != nullptr ? a.range_flags + wg : nullptr, 1 << s);
+}
+// One kernel for all shapes: the plan does not depend on them, and six kernels with its sixteen instances each are 1.1 MB.
 __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTable table) {
-  __shared__ PrepLds<BLK, D> lds;
+  __shared__ PrepLds lds;
   // The table in LDS: indexed by a lane's own sequence the kernel argument would be copied to scratch memory.
   __shared__ SeqTable seqs;
   if (threadIdx.x == 0) {
@@ -1592,14 +1603,13 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
     return;
   }
   wg -= a.n_check;
-  const int s = seq_of(seqs, wg, a.h_kv);
-  const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
-  const int kvh = rr / N, blk = rr - kvh * N;
-  const size_t at = (size_t)wg * D * BLK;
-  vt_image_tile<BLK, D, kPrepThreads>(
-      lds.tile, s_over, a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * BLK) * D,
-      min(BLK, seqs.s[s].L - blk * BLK), a.vt + at, a.vt16 != nullptr ? a.vt16 + at : nullptr,
-      a.vt16 != nullptr ? a.range_flags + wg : nullptr, 1 << s);
+  switch (a.block + a.head_dim) {
+    case 128 + 64: a.block == 128 ? prep_image<128, 64>(lds, s_over, a, seqs, wg) : prep_image<64, 128>(lds, s_over, a, seqs, wg); break;
+    case 128 + 128: prep_image<128, 128>(lds, s_over, a, seqs, wg); break;
+    case 128 + 256: prep_image<128, 256>(lds, s_over, a, seqs, wg); break;
+    case 64 + 64: prep_image<64, 64>(lds, s_over, a, seqs, wg); break;
+    case 64 + 256: prep_image<64, 256>(lds, s_over, a, seqs, wg); break;
+  }
 }
 
 }  // namespace prism
@@ -1760,11 +1770,6 @@ static void launch_attn(int grid, hipStream_t st, const PullCounters& pulls, con
                      pulls, flags, out, lse, h, h_kv, seqs, hs, causal, only_dirty);
 }
 
-template <int BLK, int D>
-static void launch_prep(int grid, const PrepArgs& a, const SeqTable& seqs, hipStream_t st) {
-  hipLaunchKernelGGL((prep_kernel<BLK, D>), dim3(grid), dim3(kPrepThreads), 0, st, a, seqs);
-}
-
 // the three kernels that turn index lists into the queue plan of `pc`
 static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t* col_idx, int32_t* bins,
                        int32_t* parts, int32_t* row_rank, int32_t* row_part, int32_t* plan, int4* items,
@@ -1911,6 +1916,8 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.pair_plan = pair_plan;
     pa.h = h;
     pa.h_kv = h_kv;
+    pa.block = params->block;
+    pa.head_dim = d;
     pa.causal = pc.causal;
     pa.n_queues = pc.n_queues;
     pa.pair_queues = pair_queues;
@@ -1927,15 +1934,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
     const int prep_grid = pa.n_plans + pa.n_check + (v_bf16 != nullptr ? h_kv * N : 0);
-    if (params->block == 128) {
-      if (d == 64) launch_prep<128, 64>(prep_grid, pa, seqs, st);
-      else if (d == 128) launch_prep<128, 128>(prep_grid, pa, seqs, st);
-      else launch_prep<128, 256>(prep_grid, pa, seqs, st);
-    } else {
-      if (d == 64) launch_prep<64, 64>(prep_grid, pa, seqs, st);
-      else if (d == 128) launch_prep<64, 128>(prep_grid, pa, seqs, st);
-      else launch_prep<64, 256>(prep_grid, pa, seqs, st);
-    }
+    hipLaunchKernelGGL(prep_kernel, dim3(prep_grid), dim3(kPrepThreads), 0, st, pa, seqs);
     flags = DirtyFlags{row_rank, range_flags, pa.n_check, n_range_flags};
   } else {
     if (v_bf16 != nullptr) {
