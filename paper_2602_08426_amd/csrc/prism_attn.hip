@@ -271,9 +271,9 @@ __device__ __forceinline__ void tile_barrier() {
 // Queue entry of one row, written by queue_fill_kernel:
 //   x = q-head, y = q-block u | (first valid key block << 16), z = index of that entry in
 //   col_idx, w = end of the row's list (z == w: the row has no valid entry).
-// Every queue (one per XCD) owns a contiguous segment of the table: `plan` = { start[8], len[8],
-// pull counters[8] }; a workgroup's pulls p = 0, 1, 2, ... from queue x are the entries
-// start[x] + p while p < len[x].
+// Every queue (one per XCD) owns a contiguous segment of the table: `plan` = { start[8], len[8], len + 1 of the queues
+// that were seen exhausted[8], flags[8], rows with a CU to themselves[8] }; a workgroup's pulls p = 0, 1, 2, ... from
+// queue x are the entries start[x] + p while p < len[x].
 enum { kItemEnd = 0, kItemRow = 2 };
 // MI355X: 8 accelerator dies (XCDs), each with its own L2; workgroups are dealt to them round-robin,
 // so the attention kernels keep one work queue per XCD (the plan below has room for exactly kXcds).
@@ -1192,7 +1192,7 @@ __global__ __launch_bounds__(256) void queue_rank_kernel(const int32_t* __restri
 // The thread of a row writes the row's queue entry: list bounds clamped to [0, cap], and the
 // first entry that names a valid key block (0 <= v <= u for causal attention, 0 <= v < N
 // otherwise).  Queue x holds, group after group, the rows of its part of the group; workgroup 0
-// also writes the plan (segment starts and lengths, cleared pull counters).  The call's last launch
+// also writes the plan (segment starts and lengths, no queue exhausted).  The call's last launch
 // of it turns the first entries of row_part into the pull counters of the two attention kernels: the
 // thread that has read an entry, the last to do so, writes the counter that takes its place.
 __global__ __launch_bounds__(256) void queue_fill_kernel(const int32_t* __restrict__ row_ptr,
@@ -1886,11 +1886,10 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const int pair_queues = pair_grid < kXcds ? 1 : kXcds;
   const int n_range_flags = w64 ? h_kv * N : 0;
 
-  // One launch prepares the call up to kPrepMaxRows rows in one phase: 14.4 us instead of 34.7 us at 2048 rows (8K
-  // tokens, 32 heads), 25.4 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 41.1 instead of 63.1 at 8192
-  // (32K tokens; the images alone take 13, 22 and 39 us), 5.3 instead of 13.9 at 32 rows.  Beyond, the plan of a single
-  // workgroup (about 24 us at 5024 rows) would no longer hide behind the image, and the parts run
-  // as kernels of their own.
+  // One launch prepares the call up to kPrepMaxRows rows in one phase: 13.4 us instead of 34.7 us at 2048 rows (8K
+  // tokens, 32 heads), 24.4 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 39.2 instead of 63.1 at 8192
+  // (32K tokens; the images alone take 13, 22 and 39 us), 5.0 instead of 13.9 at 32 rows.  Beyond, the plan of a single
+  // workgroup would no longer hide behind the image, and the parts run as kernels of their own.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   // Two sets of pull counters in row_part, which the preparation is done with: of the pair kernel and the one behind it, or
   // of the 64-queries-per-wave kernel and the one behind it.  A short table holds them closer together.
