@@ -304,20 +304,15 @@ __device__ __forceinline__ int dealt_rows(int x, int n_queues, int grid) {
 // workgroups, out of rows, at 105 - 115.  plan[kPlanAlone + x] has bit p for the p-th row of queue x if it is such a
 // row; it is dealt to workgroup x + 8 p, which shares its CU with workgroup x + 8 p + gridDim.x / 2 (in the order that
 // the hardware places a grid of two workgroups per CU; otherwise only the gain is lost).  That one ends at once, and the
-// workgroups behind it move up to its row.  Of a packed batch a launch may leave the row to another kernel (`take`: the
-// sequences that are its own): the workgroup then goes on, with a row that nobody starts with.
-// Returns the workgroup's first row in its queue, or what it does without one.
-enum { kFirstEnds = -1, kFirstPulls = -2 };
-template <bool kMayLeave>
-__device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, const int4* __restrict__ items, int queue, int n_queues,
-                                         int n_seqs, int take) {
+// workgroups behind it move up to its row.  Returns the workgroup's first row in its queue, or -1: it ends.  Of a packed batch a
+// launch may leave the long rows to another kernel: the general kernel behind the 64-queries-per-wave kernel then heeds no
+// mark (its counters start accordingly), and there the workgroup beside a row that is left goes on.
+__device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, int queue, int n_queues, bool heed) {
   const int p = (int)blockIdx.x / n_queues, half = (int)gridDim.x / 2 / n_queues;
-  const unsigned alone = plan[kPlanAlone + queue];
+  const unsigned alone = heed ? plan[kPlanAlone + queue] : 0;
   if (alone == 0 || p < half) return p;                     // bits are set only where half <= 32
   const int mate = p - half;
-  if (((alone >> mate) & 1u) == 0) return p - __popc(alone & ((1u << mate) - 1u));
-  if (!kMayLeave || n_seqs == 1) return kFirstEnds;
-  return (take >> (items[plan[kPlanStart + queue] + mate].x >> kSeqShift)) & 1 ? kFirstEnds : kFirstPulls;
+  return (alone >> mate) & 1u ? -1 : p - __popc(alone & ((1u << mate) - 1u));
 }
 
 __device__ __forceinline__ int item_kind(int pulled, int seg_start, int seg_len, int* entry) {
@@ -359,7 +354,8 @@ struct ListWindow {
 // and the waves of a q-block compute only in the steps whose block their own list names.  `flags` is what
 // the list check found.  A kernel launched behind another one takes what that one left (only_dirty): behind the pair
 // kernel, which returns at once if any sequence is dirty, the whole call then (kDirtyCall; both give the same bits); behind
-// the 64-queries-per-wave kernel the dirty sequences (kDirtySequences), so that no sequence's bits follow from the others'.
+// the 64-queries-per-wave kernel the one sequence of the call (kDirtyCall) or the dirty ones of a packed batch
+// (kDirtySequences), so that no sequence's bits follow from the others'.
 enum { kEverything, kDirtyCall, kDirtySequences };
 template <int BLK, bool kStreamOnly, int D, bool kPair, bool kKeepMask>
 __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D, kPair>::kWavesPerSimd)) void sparse_attn_kernel(
@@ -424,10 +420,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // read of the next row's queue entry are hidden behind that last step.
   int lane_zero;                                     // 0, but opaque to the compiler
   asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-  constexpr bool kMayLeave = BLK == 128 && D == kHeadDim;    // the form that stands behind the 64-queries-per-wave kernel
-  const int first = first_row<kMayLeave>(plan, items, my_queue, n_queues, seqs.n, take);
-  if (first == kFirstEnds) return;
-  if (t == 0) next_item = kMayLeave && first == kFirstPulls ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
+  constexpr bool kBehind = BLK == 128 && D == kHeadDim;      // this form stands behind the 64-queries-per-wave kernel
+  const int first = first_row(plan, my_queue, n_queues, !kBehind || only_dirty != kDirtySequences);
+  if (first < 0) return;
+  if (t == 0) next_item = first;
   __syncthreads();
   int cur_x = 0, cur_y = 0, cur_z = 0, cur_w = 0;     // the current row's queue entry, wave-uniform
   int kind_cur;
@@ -883,9 +879,13 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
   int32_t* __restrict__ counter = pulls.at;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   int pulled = 0;
-  const int first = first_row<true>(plan, items, my_queue, n_queues, seqs.n, ~dirty);
-  if (first == kFirstEnds) return;
-  if (t == 0) pulled = first == kFirstPulls ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
+  const int first = first_row(plan, my_queue, n_queues, true);
+  if (first < 0) {
+    // the row on this CU may be one of those that the general kernel takes
+    const int mate = (int)blockIdx.x / n_queues - (int)gridDim.x / 2 / n_queues;
+    if (seqs.n == 1 || ((dirty >> (items[seg_start + mate].x >> kSeqShift)) & 1) == 0) return;
+  }
+  if (t == 0) pulled = first < 0 ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
   for (;;) {
     // hand the pulled queue position to both waves
     __syncthreads();
@@ -1477,7 +1477,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
     const int dealt = dealt_rows(t, n_queues, grid) - __popc(alone);
     counters[t * a.counter_stride] = dealt;
-    if (more_counters != nullptr) more_counters[t * a.counter_stride] = dealt;
+    if (more_counters != nullptr) more_counters[t * a.counter_stride] = kOne ? dealt : dealt_rows(t, n_queues, grid);
   }
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
@@ -1878,7 +1878,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   constexpr int kPairMinRows = 4096;
   const bool pair = W.pair_plan != W.pair_items && !stream_only && !(params->flags & PRISM_FLAG_GENERAL_KERNEL) &&
                     ((R >= kPairMinRows && d >= 128) || (params->flags & PRISM_FLAG_PAIR_KERNEL));
-  const int only_dirty = w64 ? kDirtySequences : (pair ? kDirtyCall : kEverything);
+  const int only_dirty = w64 && seqs.n > 1 ? kDirtySequences : (w64 || pair ? kDirtyCall : kEverything);
   int4* pair_items = reinterpret_cast<int4*>(ws + W.pair_items);
   int32_t* pair_plan = reinterpret_cast<int32_t*>(ws + W.pair_plan);
   const int pair_grid = pair ? persistent_grid(R / 2, d > 128 ? 1 : 2) : 0;   // 4 waves and 2 * 64 * d * 2 bytes of LDS each
