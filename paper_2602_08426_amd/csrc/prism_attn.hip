@@ -307,10 +307,10 @@ __device__ __forceinline__ int dealt_rows(int x, int n_queues, int grid) {
 // workgroups behind it move up to its row.  Returns the workgroup's first row in its queue, or -1: it ends.  Of a packed batch a
 // launch may leave the long rows to another kernel: the general kernel behind the 64-queries-per-wave kernel then heeds no
 // mark (its counters start accordingly), and there the workgroup beside a row that is left goes on.
-__device__ __forceinline__ int first_row(const int32_t* __restrict__ plan, int queue, int n_queues, bool heed) {
-  const int p = (int)blockIdx.x / n_queues, half = (int)gridDim.x / 2 / n_queues;
-  const unsigned alone = heed ? plan[kPlanAlone + queue] : 0;
-  if (alone == 0 || p < half) return p;                     // bits are set only where half <= 32
+__device__ __forceinline__ int first_row(unsigned alone, int n_queues, bool heed) {
+  const unsigned shift = n_queues == 1 ? 0 : 3;             // kXcds or one; divisions are 40 instructions each
+  const int p = blockIdx.x >> shift, half = gridDim.x >> 1 >> shift;
+  if (!heed || alone == 0 || p < half) return p;            // bits are set only where half <= 32
   const int mate = p - half;
   return (alone >> mate) & 1u ? -1 : p - __popc(alone & ((1u << mate) - 1u));
 }
@@ -413,6 +413,8 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   int my_queue = blockIdx.x % n_queues;
   int seg_start = plan[kPlanStart + my_queue];
   int seg_len = plan[kPlanLen + my_queue];
+  const unsigned alone = plan[kPlanAlone + my_queue];
+  asm volatile("" ::"s"(seg_start), "s"(seg_len), "s"(alone));   // three requests, one wait (8/2 heads, 4096 tokens 37.2 -> 36.4 us)
   int32_t* __restrict__ counter = pulls.at;
 
   // The queue is pulled when a workgroup is about to become free (at the top of the last
@@ -421,7 +423,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   int lane_zero;                                     // 0, but opaque to the compiler
   asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
   constexpr bool kBehind = BLK == 128 && D == kHeadDim;      // this form stands behind the 64-queries-per-wave kernel
-  const int first = first_row(plan, my_queue, n_queues, !kBehind || only_dirty != kDirtySequences);
+  const int first = first_row(alone, n_queues, !kBehind || only_dirty != kDirtySequences);
   if (first < 0) return;
   if (t == 0) next_item = first;
   __syncthreads();
@@ -876,13 +878,15 @@ __global__ __launch_bounds__(128 / kQ * 64, kQ == 64 ? 1 : 2) void sparse_attn_w
   int my_queue = blockIdx.x % n_queues;
   int seg_start = plan[kPlanStart + my_queue];
   int seg_len = plan[kPlanLen + my_queue];
+  const unsigned alone = plan[kPlanAlone + my_queue];
+  asm volatile("" ::"s"(seg_start), "s"(seg_len), "s"(alone));   // three requests, one wait (8/2 heads, 4096 tokens 37.2 -> 36.4 us)
   int32_t* __restrict__ counter = pulls.at;
   const uint32_t lds_base = (uint32_t)(size_t)lds_tiles;
   int pulled = 0;
-  const int first = first_row(plan, my_queue, n_queues, true);
+  const int first = first_row(alone, n_queues, true);
   if (first < 0) {
     // the row on this CU may be one of those that the general kernel takes
-    const int mate = (int)blockIdx.x / n_queues - (int)gridDim.x / 2 / n_queues;
+    const int mate = (int)(blockIdx.x - gridDim.x / 2) / kXcds;
     if (seqs.n == 1 || ((dirty >> (items[seg_start + mate].x >> kSeqShift)) & 1) == 0) return;
   }
   if (t == 0) pulled = first < 0 ? atomicAdd(counter + my_queue * pulls.stride, 1) : first;
@@ -1282,9 +1286,9 @@ struct PrepArgs {
   int32_t counter_stride;
   int32_t grid, pair_grid;                 // workgroups of the attention kernels
   float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
-  int32_t alone_max;                       // ... in the queues that hold no more such rows than this
   float halve;                             // every row has, where the longest is a CU's average work over this or more (0: no)
-  int32_t h, h_kv, block, head_dim, causal, n_queues, pair_queues, n_plans, n_check, need_sorted;
+  int32_t h, h_kv, n_queues, pair_queues, n_check;
+  uint8_t n_plans, causal, need_sorted, shape;      // shape: block / 64 * 8 + head_dim / 64
   size_t kv_head_stride;
 };
 
@@ -1441,6 +1445,14 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     m.qlen[t] = run;
   }
   __syncthreads();
+  const bool marks = stride == 1 && (a.alone > 0.f || a.halve > 0.f);     // some row may have a CU to itself
+  auto count = [&](unsigned alone) __attribute__((always_inline)) {
+    plan[kPlanAlone + t] = (int)alone;
+    // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
+    const int all = dealt_rows(t, n_queues, grid), dealt = all - __popc(alone);
+    counters[t * a.counter_stride] = dealt;
+    if (more_counters != nullptr) more_counters[t * a.counter_stride] = kOne ? dealt : all;
+  };
   if (t < 8) {
     int start = 0;
     for (int x = 0; x < t; ++x) start += m.qlen[x];
@@ -1448,6 +1460,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     plan[kPlanLen + t] = m.qlen[t];
     plan[kPlanCounter + t] = 0;
     plan[kPlanFlags + t] = 0;
+    if (!marks) count(0);
   }
   const float alone_from = stride == 1 && a.alone > 0.f ? a.alone * (float)m.total / (float)grid : INFINITY;
   const int half = grid / 2 / n_queues;
@@ -1467,17 +1480,14 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     if (stride == 1 && len[c] > 0)
       cum[c] = a.col_idx[col0_of(kOne ? 0 : row((wave * CH + c) * 64 + lane).s) + beg[c]];
   }
-  // (in front of the entries, whose stores the workgroup would wait for at a barrier behind them: 42.8 -> 39.8 us in a packed
-  // batch of 4640 rows)
-  __syncthreads();
-  if (t < 8) {
-    const bool halve = stride == 1 && (float)m.total < a.halve * (float)m.longest * (float)(grid / 2);
-    const unsigned alone = halve ? ~0u >> (32 - half) : m.above[t] <= a.alone_max ? m.alone[t] : 0;
-    plan[kPlanAlone + t] = (int)alone;
-    // the first pulls of queue t belong to the workgroups t, t + n_queues, ... that first_row leaves
-    const int dealt = dealt_rows(t, n_queues, grid) - __popc(alone);
-    counters[t * a.counter_stride] = dealt;
-    if (more_counters != nullptr) more_counters[t * a.counter_stride] = kOne ? dealt : dealt_rows(t, n_queues, grid);
+  if (marks) {
+    // (in front of the entries, whose stores the workgroup would wait for at a barrier behind them: 42.8 -> 39.8 us in a
+    // packed batch of 4640 rows)
+    __syncthreads();
+    if (t < 8) {
+      const bool halve = (float)m.total < a.halve * (float)m.longest * (float)(grid / 2);
+      count(halve ? ~0u >> (32 - half) : m.above[t] <= half * 5 / 8 ? m.alone[t] : 0);
+    }
   }
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
@@ -1549,7 +1559,9 @@ __device__ __forceinline__ void prep_image(PrepLds& lds, int& s_over, const Prep
       a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * BLK) * D, min(BLK, seqs.s[s].L - blk * BLK),
       a.vt + at, a.vt16 != nullptr ? a.vt16 + at : nullptr, a.vt16 != nullptr ? a.range_flags + wg : nullptr, 1 << s);
 }
-// One kernel for all shapes: the plan does not depend on them, and six kernels with its sixteen instances each are 1.1 MB.
+// One kernel for all shapes: the plan does not depend on them, and six kernels with its sixteen instances each are 1.1 MB more.
+// The smallest calls feel what lies in front of their work: with the image and the shortest plans first, and without a look
+// at each of sixteen sequences where there is one, 32 rows of one head take 4.3 us instead of 4.9.
 __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTable table) {
   __shared__ PrepLds lds;
   // The table in LDS: indexed by a lane's own sequence the kernel argument would be copied to scratch memory.
@@ -1557,59 +1569,61 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
   if (threadIdx.x == 0) {
     seqs.n = table.n;
     seqs.nsum = table.nsum;
+    seqs.s[0] = table.s[0];
   }
+  if (table.n > 1) {
 #pragma unroll
-  for (int i = 0; i < kMaxGroupSeqs; ++i)
-    if (i < table.n && threadIdx.x == i) seqs.s[i] = table.s[i];
+    for (int i = 1; i < kMaxGroupSeqs; ++i)
+      if (i < table.n && threadIdx.x == i) seqs.s[i] = table.s[i];
+  }
   __syncthreads();
   __shared__ int s_over;
   int wg = blockIdx.x;
-  if (wg < a.n_plans) {
-    const int stride = 1 + wg;
-    const int R = a.h * seqs.nsum / stride;
-    const int n_queues = wg == 0 ? a.n_queues : a.pair_queues;
-    int4* items = wg == 0 ? a.items : a.pair_items;
-    int32_t* plan = wg == 0 ? a.plan : a.pair_plan;
-    int32_t* counters = wg == 0 ? a.counters : a.pair_counters;
-    int32_t* more = a.n_plans == 1 ? a.pair_counters : nullptr;
-    const int grid = wg == 0 ? a.grid : a.pair_grid;
-    // The waves take 64 * CH rows each in turn, so a CH too large leaves the last waves idle (5024 rows at 8 instead of 5 are
-    // ten waves' work): an instance for every 1024 rows.  us of the launch, with 1, 2, 4 and 8 only -> now: 20011 tokens 30.6 -> 24.4,
-    // 32/8 heads, 28000 (7008 rows) 37.0 -> 33.6; packed batches of 2900 rows 20.6 -> 17.5, 4640 37.8 -> 29.1, 7000 43.1 -> 38.3.
-    // At 64 registers a lane, for two workgroups to a CU, the largest instances spill 11 or 12 of them.
-    auto run = [&](auto one) __attribute__((always_inline)) {
-      constexpr bool kOne = decltype(one)::value;
-      switch ((R - 1) / kPrepThreads) {
-#define PRISM_PLAN(CH) \
-  case CH - 1: plan_rows<CH, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan); break
-        PRISM_PLAN(1);
-        PRISM_PLAN(2);
-        PRISM_PLAN(3);
-        PRISM_PLAN(4);
-        PRISM_PLAN(5);
-        PRISM_PLAN(6);
-        PRISM_PLAN(7);
-        PRISM_PLAN(8);
-#undef PRISM_PLAN
-      }
-    };
-    if (seqs.n == 1) run(std::true_type{});
-    else run(std::false_type{});
+  if (wg >= a.n_plans) {
+    wg -= a.n_plans;
+    if (wg < a.n_check) {
+      check_rows(a, seqs, wg, s_over);
+      return;
+    }
+    wg -= a.n_check;
+    switch (a.shape) {
+#define PRISM_IMAGE(BLK, D) \
+    case BLK / 64 * 8 + D / 64: prep_image<BLK, D>(lds, s_over, a, seqs, wg); break
+      PRISM_IMAGE(64, 64);
+      PRISM_IMAGE(64, 128);
+      PRISM_IMAGE(64, 256);
+      PRISM_IMAGE(128, 64);
+      PRISM_IMAGE(128, 128);
+      PRISM_IMAGE(128, 256);
+#undef PRISM_IMAGE
+    }
     return;
   }
-  wg -= a.n_plans;
-  if (wg < a.n_check) {
-    check_rows(a, seqs, wg, s_over);
-    return;
-  }
-  wg -= a.n_check;
-  switch (a.block + a.head_dim) {
-    case 128 + 64: a.block == 128 ? prep_image<128, 64>(lds, s_over, a, seqs, wg) : prep_image<64, 128>(lds, s_over, a, seqs, wg); break;
-    case 128 + 128: prep_image<128, 128>(lds, s_over, a, seqs, wg); break;
-    case 128 + 256: prep_image<128, 256>(lds, s_over, a, seqs, wg); break;
-    case 64 + 64: prep_image<64, 64>(lds, s_over, a, seqs, wg); break;
-    case 64 + 256: prep_image<64, 256>(lds, s_over, a, seqs, wg); break;
-  }
+  const int stride = 1 + wg;
+  const int R = a.h * seqs.nsum / stride;
+  const int n_queues = wg == 0 ? a.n_queues : a.pair_queues;
+  int4* items = wg == 0 ? a.items : a.pair_items;
+  int32_t* plan = wg == 0 ? a.plan : a.pair_plan;
+  int32_t* counters = wg == 0 ? a.counters : a.pair_counters;
+  int32_t* more = a.n_plans == 1 ? a.pair_counters : nullptr;
+  const int grid = wg == 0 ? a.grid : a.pair_grid;
+  // The waves take 64 * CH rows each in turn, so a CH too large leaves the last waves idle (5024 rows at 8 instead of 5 are
+  // ten waves' work): an instance for every 1024 rows.  us of the launch, with 1, 2, 4 and 8 only -> now: 20011 tokens 30.6 -> 24.4,
+  // 32/8 heads, 28000 (7008 rows) 37.0 -> 33.6; packed batches of 2900 rows 20.6 -> 17.5, 4640 37.8 -> 29.1, 7000 43.1 -> 38.3.
+  // At 64 registers a lane, for two workgroups to a CU, the largest instances spill 11 or 12 of them.
+  auto run = [&](auto one) __attribute__((always_inline)) {
+    constexpr bool kOne = decltype(one)::value;
+    if (R <= kPrepThreads) plan_rows<1, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 2 * kPrepThreads) plan_rows<2, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 3 * kPrepThreads) plan_rows<3, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 4 * kPrepThreads) plan_rows<4, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 5 * kPrepThreads) plan_rows<5, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 6 * kPrepThreads) plan_rows<6, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else if (R <= 7 * kPrepThreads) plan_rows<7, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+    else plan_rows<8, kOne>(lds.plan, a, seqs, stride, n_queues, grid, counters, more, items, plan);
+  };
+  if (seqs.n == 1) run(std::true_type{});
+  else run(std::false_type{});
 }
 
 }  // namespace prism
@@ -1847,7 +1861,6 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   constexpr float kAlone = 1.4f;
   const bool full = grid == persistent_grid(0x7fffffff, 2) && grid % (2 * kXcds) == 0 && grid / (2 * kXcds) <= 32;
   const float alone = params->block == 128 && per_cu == 2 && full ? kAlone : 0.f;
-  const int alone_max = grid / (2 * kXcds) * 5 / 8;
   // Wide rows (d = 256, two workgroups per CU): all have a CU to themselves, so half of the workgroups end, where the longest row
   // bounds the call, a CU's average work (entries + 3 a row) being less than 1.2 times the longest row.  us of preparation
   // and attention, one / two per CU, at that ratio: 16/2 heads, 11305 tokens (0.90) 408 / 432, 16/8, 11309 (0.94) 385 / 412, 16/4, 11294 (1.02)
@@ -1915,9 +1928,8 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.pair_plan = pair_plan;
     pa.h = h;
     pa.h_kv = h_kv;
-    pa.block = params->block;
-    pa.head_dim = d;
-    pa.causal = pc.causal;
+    pa.shape = (uint8_t)(params->block / 64 * 8 + d / 64);
+    pa.causal = (uint8_t)pc.causal;
     pa.n_queues = pc.n_queues;
     pa.pair_queues = pair_queues;
     pa.n_plans = pair ? 2 : 1;
@@ -1928,7 +1940,6 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.counter_stride = pulls.stride;
     pa.grid = grid;
     pa.alone = alone;
-    pa.alone_max = alone_max;
     pa.halve = halve;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
