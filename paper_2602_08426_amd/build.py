@@ -22,6 +22,10 @@ HIPCC_FLAGS = [
     "-Wno-unused-command-line-argument",
     # queue pulls stay plain returning atomics whose result is waited for where it is used
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
+    # accumulators of the compiler's MFMAs stay in VGPRs; at head dim 256, the only kernels with more than 256 registers a
+    # lane, it otherwise puts them in AGPRs and moves each in and out for every rescale (330 of the 746 vector instructions
+    # of a 64 x 256 step, now none)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     # the registers of every kernel, for check_registers
     "-Rpass-analysis=kernel-resource-usage",
 ]

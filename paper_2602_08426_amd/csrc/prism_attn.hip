@@ -570,6 +570,15 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     }
     async_load_k_pieces<BLK, D, kPair>(krs, v * C::kTileBytes, lds_k, t, first_slot(t), 0, C::kPerThread);
     wait_async_loads();
+    // At d = 256 a lane holds 128 accumulators, 64 registers of Q and 32 scores beside the operands.  What the maximum moves
+    // in nearly every step, the accumulators, has to be in VGPRs (build.py), and the Q fragments, which only the MFMAs read,
+    // in AGPRs, from where they are read in place.  A 64 x 256 step of the pair form then is 417 vector instructions instead of
+    // 746.  us of attention, accumulators in AGPRs / in VGPRs / and Q pinned here: pair 64 x 256, 16/4 heads, 16384 tokens
+    // 665 / 535 / 522, 28/4, 32768 2297 / 1917 / 1889; plain 64 x 256, 16/4, 16330 659 / 533 / 519; 128 x 256, 16384 529 / 450 / 438.
+    if (D > 128) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qf[ks]));
+    }
     tile_barrier();
 
     f32x16 oacc[DT];
