@@ -1823,15 +1823,17 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // resident workgroups per CU, by the LDS the two tiles of a workgroup take (2 * B * d * 2 bytes of the
   // CU's 160 KB) and its waves: 2 at B = 128, d = 128 (64 KB, 4 waves).  At d = 256 a wave has a SIMD to itself: one
   // workgroup of four waves, or two of two at B = 64.  Two of these share the LDS and the copies of the CU, which a call
-  // of few rows, bound by its longest ones, feels and a longer one does not; beyond 11 rows per CU the lists decide (halve, below;
-  // before it they mostly speak for one, though not always: 32/8 at 5050 tokens).  us of
-  // attention, one -> two: 16/4 heads, 8100 tokens (2032 rows) 313 -> 326, 10001 (2512) 368 -> 388, 12001 (3008) 524 -> 462,
-  // 30016 (7504) 2605 -> 1630; 32/8, 2000 (1024) 90 -> 97, 5050 (2528) 247 -> 219, 8100 (4064) 489 -> 350, 16300 (8160)
-  // 1354 -> 858; 28/4, 4001 (1764) 169 -> 178, 6050 (2660) 249 -> 259; 7/1, 24001 (2632) 252 -> 268.
+  // bound by its longest rows feels and another one does not: from four rows per CU on, where the preparation looks for the
+  // longest row, the lists decide (halve, below); elsewhere it is two beyond 11 rows per CU.  us of estimate and attention, one / two
+  // / by the lists: 16/4 heads, 8100 tokens (2032 rows) 274 / 296 / 275, 10001 (2512) 336 / 359 / 336, 12065 (3024) 420 / 424 / 422,
+  // 30016 (7504) 1968 / 1334 / 1335; 32/8, 2063 (1056) 100 / 108 / 101, 4000 (2016) 183 / 176 / 176, 5050 (2528) 241 / 216 / 217, 8100
+  // (4064) 453 / 340 / 344, 16300 (8160) 1156 / 824 / 825; 28/4, 4001 (1764) 159 / 176 / 159, 6050 (2660) 246 / 245 / 245; 7/1, 24065
+  // (2639) 223 / 247 / 223.
   const int tile_pair = 2 * params->block * d * 2;
   int per_cu = (160 * 1024) / tile_pair;
   per_cu = per_cu > 4 ? 4 : per_cu;
-  const int two_wide_rows = 11 * persistent_grid(0x7fffffff, 1);
+  const bool looks = R <= kPrepMaxRows && heads_in_cache(params, seqs) >= h_kv;
+  const int two_wide_rows = (looks ? 4 : 11) * persistent_grid(0x7fffffff, 1);
   if (d > 128) per_cu = params->block == 64 && R > two_wide_rows ? 2 : 1;
   else if (params->block == 128 && per_cu > 2) per_cu = 2;
   const int grid = persistent_grid(R, per_cu);
@@ -1871,11 +1873,10 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const bool full = grid == persistent_grid(0x7fffffff, 2) && grid % (2 * kXcds) == 0 && grid / (2 * kXcds) <= 32;
   const float alone = params->block == 128 && per_cu == 2 && full ? kAlone : 0.f;
   // Wide rows (d = 256, two workgroups per CU): all have a CU to themselves, so half of the workgroups end, where the longest row
-  // bounds the call, a CU's average work (entries + 3 a row) being less than 1.2 times the longest row.  us of preparation
-  // and attention, one / two per CU, at that ratio: 16/2 heads, 11305 tokens (0.90) 408 / 432, 16/8, 11309 (0.94) 385 / 412, 16/4, 11294 (1.02)
-  // 413 / 438, 28/4, 7568 (1.14) 304 / 325, 8/1, 24071 (1.17) 218 / 233; 4/2, 45368 (1.21) 639 / 605, 3/1, 64020 (1.23) 279 / 260,
-  // 16/4, 12066 (1.25) 530 / 482.  Calls of several phases or more than kPrepMaxRows rows have two, whose preparation does
-  // not look for the longest row (16/16, 11298 (0.95) 632 / 562, 15288 (1.12) 771 / 714).
+  // bounds the call, a CU's average work (entries + 3 a row) being less than 1.2 times the longest row.  us of estimate
+  // and attention, one / two per CU, at that ratio: 16/2 heads, 11305 tokens (0.90) 355 / 393, 16/8, 11309 (0.94) 384 / 401, 8/1, 24071
+  // (1.17) 229 / 245; 4/2, 45368 (1.21) 819 / 846, 16/4, 12066 (1.25) 455 / 434.  Calls of several phases or more than kPrepMaxRows
+  // rows have two, whose preparation does not look for the longest row (16/16, 11298 (0.95) 617 / 546, 15288 (1.12) 746 / 703).
   const float halve = d > 128 && per_cu == 2 && full ? 1.2f : 0.f;
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;

@@ -102,6 +102,12 @@ def test_wide_rows_beyond_one_workgroup_per_cu(h, bidir):
         assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
 
 
+@pytest.mark.parametrize("h,bidir", [(15, False), (16, True)])
+def test_wide_rows_of_short_calls(h, bidir):
+    """975 and 1040 rows: one workgroup per CU, and two or one by the lists."""
+    test_wide_rows_beyond_one_workgroup_per_cu(h, bidir)
+
+
 @pytest.mark.parametrize("dirty", [False, True])
 def test_pair_queues_of_the_separate_kernels(dirty):
     check_pair_plan(33, 11, 250, dirty)  # 8250 rows: the counters of both plans are written by the last launch that fills one
