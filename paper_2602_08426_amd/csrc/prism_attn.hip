@@ -128,7 +128,7 @@ __device__ __forceinline__ int dirty_sequences(const DirtyFlags& f) {
 // Step per listed kv block (each tile buffer is refilled as soon as its last reader is done):
 //     K(j) in LDS | S^T = K Q^T, requests of V(j) between the MFMAs | barrier
 //     online softmax, requests of K(j+1) at its start or in it | wait V(j) | barrier | O^T += V^T P^T | wait K(j+1) | barrier
-// Two buffers per tile (one barrier per step instead of three, both tiles of the next block requested a whole step ahead)
+// Pairs of 64 x 256 have two buffers per tile (AttnCfg).  In the plain forms, where two workgroups share a CU, they
 // fit at 64 x 64, 128 x 64 and 64 x 256 and are no gain over the range: us of attention, one buffer -> two, 32/8 heads: 128 x 64
 // at 8192 tokens 127 -> 123, at 20000 331 -> 345, at 32768 755 -> 790; 64 x 256 at 16320 1374 -> 1432, at 32768 3159 -> 3257;
 // 64 x 64 at 16384 298 -> 303, at 40000 1060 -> 1007.
@@ -161,6 +161,12 @@ struct AttnCfg {
   // 16384 714 / 701 / 697 / 682; pair 64 x 128, 8/2, 60000 605 / 584 / 591 / 592; 64 x 64, 32/8, 16384 305 / 298 / 298 / 316.
   static constexpr int kPiecesInMax = BLK == 128 && D <= 128 ? kPerThread : 0;
   static constexpr int kPiecesInExp = D > 128 ? kPerThread : 0;
+  // Two buffers per tile.  A pair of 256-dim rows has the CU to itself, so nothing fills the gaps where its waves wait for a tile, and
+  // the 160 KB hold both: the copies have a whole step to land, and a step has one barrier instead of three.  us of attention,
+  // one buffer -> two: 16/4 heads, 16384 tokens 515 -> 486, 32/8, 8192 312 -> 304, 8/2, 32768 598 -> 555.  The requests lie over the
+  // MFMAs of S, K and V by turns, one for two MFMAs (one for each MFMA of the first half 518, V's over the exponentials 504).  The
+  // scores of the next block between the instructions of this one's softmax as well: 544; a lone wave is bound by issue there.
+  static constexpr bool kTwo = PAIR && D > 128;
 };
 
 // Asynchronous global -> LDS tile copies (buffer_load_dwordx4 ... lds: every lane fetches 16
@@ -226,6 +232,26 @@ __device__ __forceinline__ void async_load_vt_pieces(__amdgpu_buffer_rsrc_t rs, 
   for (int i = i0; i < i1; ++i)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(lds + (i * C::kThreads + wave_base) * 16), 16,
                                              vt_piece_offset<BLK, D>(i * C::kThreads + t), tile_off, 0, 0);
+}
+
+// One piece of such a copy, written as asm: the compiler, seeing the builtin, would wait for a copy into one of two buffers before
+// it reads the other.  Waited for with wait_async_loads.
+struct TileRsrc {
+  u32x4 w;
+};
+__device__ __forceinline__ TileRsrc make_tile_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t b = (uint64_t)base;
+  TileRsrc r;
+  r.w[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  r.w[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xffffu));
+  r.w[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+  r.w[3] = 0x00020000u;
+  return r;
+}
+__device__ __forceinline__ void async_piece(const TileRsrc& rs, int lane_off, int tile_off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(lane_off), "s"(rs.w),
+               "s"(tile_off)
+               : "m0", "memory");
 }
 
 // Waits on the vector-memory counter, written with the builtin (immediate: vmcnt in bits 3:0,
@@ -368,8 +394,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   using C = AttnCfg<BLK, D, kPair>;
   constexpr int KS = C::kKSteps, DT = C::kDTiles;
   constexpr int KT = BLK / 32;                       // 32-key tiles per kv block
-  __shared__ __attribute__((aligned(16))) char lds_k[C::kTileBytes];
-  __shared__ __attribute__((aligned(16))) char lds_v[C::kTileBytes];
+  constexpr bool kTwo = C::kTwo && !kStreamOnly;
+  __shared__ __attribute__((aligned(16))) char lds_k[C::kTileBytes * (kTwo ? 2 : 1)];
+  __shared__ __attribute__((aligned(16))) char lds_v[C::kTileBytes * (kTwo ? 2 : 1)];
   __shared__ int next_item, next_queue;
   int take = ~0;                                            // the sequences that are this launch's to do
   if (kPair) {
@@ -442,6 +469,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // load in flight will write would force a wait for every older memory operation)
   int4 item_nxt = make_int4(0, 0, 0, 0);
   int pulled_reg = 0;
+  // two buffers per tile: where the current ones start, and this lane's places in pieces 0 and 1 of a K tile and in a piece of V^T
+  int buf = 0;
+  const int k_lane0 = kTwo ? k_piece_offset<BLK, D>(t) : 0, k_lane1 = kTwo ? k_piece_offset<BLK, D>(C::kThreads + t) : 0;
+  const int v_lane = kTwo ? vt_piece_offset<BLK, D>(t) : 0;
 
   for (;;) {
     if (kind_cur == kItemEnd) {
@@ -532,6 +563,30 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     const __amdgpu_buffer_rsrc_t vrs =
         make_rsrc(vt + ((size_t)seqs.s[sq].blk0 * (h / g) + (size_t)kvh * N) * BLK * D, image_head_bytes);
     const int vmax = causal ? u_own : vmax_nc;
+    // With two buffers per tile, step j reads the buffers j & 1, and both tiles of the next block are copied into the others; `buf` is
+    // where they start, and what the lanes' read offsets hold already.
+    TileRsrc krs2 = {}, vrs2 = {};
+    if constexpr (kTwo) {
+      krs2 = make_tile_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
+      vrs2 = make_tile_rsrc(vt + ((size_t)seqs.s[sq].blk0 * (h / g) + (size_t)kvh * N) * BLK * D, image_head_bytes);
+    }
+    auto other_buffer = [&]() __attribute__((always_inline)) {
+      const int by = buf == 0 ? C::kTileBytes : -C::kTileBytes;
+      buf += by;
+#pragma unroll
+      for (int st = 0; st < KS; ++st) koff[st] += by;
+#pragma unroll
+      for (int st = 0; st < KT * 2; ++st) voff[st] += by;
+    };
+    auto copy_k = [&](int blk, int at, int wave_base, int i) __attribute__((always_inline)) {
+      // (16 rows from one piece to the next but one: the same swizzle)
+      async_piece(krs2, (i & 1) ? k_lane1 : k_lane0, blk * C::kTileBytes + (i & ~1) * (C::kThreads * 16),
+                  (uint32_t)(size_t)lds_k + at + (i * C::kThreads + wave_base) * 16);
+    };
+    auto copy_v = [&](int blk, int at, int wave_base, int i) __attribute__((always_inline)) {
+      async_piece(vrs2, v_lane, blk * C::kTileBytes + i * (C::kThreads * 16),
+                  (uint32_t)(size_t)lds_v + at + (i * C::kThreads + wave_base) * 16);
+    };
 
     // Pair rows: the two lists [it, mid) and [mid, end) are walked together, smallest block first;
     // `act` says whose list names the block (bit 0: q-block 2u, bit 1: q-block 2u + 1).
@@ -568,7 +623,15 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
     }
-    async_load_k_pieces<BLK, D, kPair>(krs, v * C::kTileBytes, lds_k, t, first_slot(t), 0, C::kPerThread);
+    if constexpr (kTwo) {
+      const int wave_base = first_slot(t);
+#pragma unroll
+      for (int i = 0; i < C::kPerThread; ++i) copy_k(v, buf, wave_base, i);
+#pragma unroll
+      for (int i = 0; i < C::kPerThread; ++i) copy_v(v, buf, wave_base, i);
+    } else {
+      async_load_k_pieces<BLK, D, kPair>(krs, v * C::kTileBytes, lds_k, t, first_slot(t), 0, C::kPerThread);
+    }
     wait_async_loads();
     // At d = 256 a lane holds 128 accumulators, 64 registers of Q and 32 scores beside the operands.  What the maximum moves
     // in nearly every step, the accumulators, has to be in VGPRs (build.py), and the Q fragments, which only the MFMAs read,
@@ -599,7 +662,14 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       // ---- V(j) -> LDS, requested piece by piece between the MFMAs of S^T, in flight during the softmax ----
       const int wave_base = first_slot(t);
       const bool computes = !kStreamOnly && active;
-      if (!computes) async_load_vt_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, 0, C::kPerThread);
+      if (!computes && !kTwo) async_load_vt_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, 0, C::kPerThread);
+      const int other = C::kTileBytes - buf;
+      if (!computes && kTwo && !kLast) {
+#pragma unroll
+        for (int i = 0; i < C::kPerThread; ++i) copy_k(v_next, other, wave_base, i);
+#pragma unroll
+        for (int i = 0; i < C::kPerThread; ++i) copy_v(v_next, other, wave_base, i);
+      }
 
       f32x16 sacc[KT];
       if (kPair) {
@@ -632,8 +702,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
           }
           constexpr int kEvery = kSteps / C::kPerThread;
           static_assert(kSteps % C::kPerThread == 0, "a piece per kEvery MFMAs");
-          if (i % kEvery == 0)
+          if (!kTwo && i % kEvery == 0)
             async_load_vt_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, i / kEvery, i / kEvery + 1);
+          if (kTwo && !kLast && i % kEvery == 0) copy_k(v_next, other, wave_base, i / kEvery);
+          if (kTwo && !kLast && i % kEvery == kEvery / 2) copy_v(v_next, other, wave_base, i / kEvery);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -641,9 +713,9 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       }
 
       // every wave is done reading K(j): K(j+1) can start now and land during softmax + PV
-      tile_barrier();
+      if (!kTwo) tile_barrier();
       constexpr int kNow = C::kPerThread - C::kPiecesInMax - C::kPiecesInExp;
-      if (!kLast)
+      if (!kLast && !kTwo)
         async_load_k_pieces<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t, wave_base, 0, computes ? kNow : C::kPerThread);
 
       bf16x8 pf[KT][2];
@@ -686,7 +758,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       float mx = -INFINITY;
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
-        if (!kLast && C::kPiecesInMax > 0) {
+        if (!kLast && !kTwo && C::kPiecesInMax > 0) {
           constexpr int kEach = C::kPiecesInMax / KT;
           static_assert(kEach * KT == C::kPiecesInMax, "pieces per 32 keys");
           async_load_k_pieces<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t, wave_base, kNow + kt * kEach, kNow + (kt + 1) * kEach);
@@ -714,7 +786,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       for (int kt = 0; kt < KT; ++kt) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-          if (!kLast && C::kPiecesInExp > 0) {
+          if (!kLast && !kTwo && C::kPiecesInExp > 0) {
             constexpr int kEach = C::kPiecesInExp / (2 * KT), kFirst = kNow + C::kPiecesInMax;
             static_assert(kEach * 2 * KT == C::kPiecesInExp, "pieces per 16 keys");
             async_load_k_pieces<BLK, D, kPair>(krs, v_next * C::kTileBytes, lds_k, t, wave_base,
@@ -741,10 +813,10 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       if (kLast) {
         if (t == 0) next_item = pulled_reg;         // the queue position pulled at the top of the step
         wait_async_loads();                          // this wave's share of V(j) has landed
-      } else {
+      } else if (!kTwo) {
         wait_async_loads_but_last_tile<C::kPerThread>();   // ... while the younger loads of K(j+1) may still be in flight
       }
-      tile_barrier();                                // V(j) complete
+      if (!kTwo || kLast) tile_barrier();            // V(j) complete
 
       if (kLast) {
         // the next row's queue entry, read through a per-lane (vector) address so that it arrives
@@ -782,6 +854,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 
       wait_async_loads();              // this wave's share of K(j+1) (or the next row's entry) has landed
       tile_barrier();                  // K(j+1) complete; everyone is done reading V(j)
+      if (kTwo) other_buffer();
     };
 
     // The list is walked one entry ahead of its use: col_idx[it + 1] is requested here and
@@ -1898,9 +1971,13 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // At d = 64 a tile is 8 KB and the plain kernel is not bound by its copies: the pair form is 5 % slower
   // even on all-ones lists, where the two lists of a pair coincide (750 -> 712 TFLOP/s at 16K tokens;
   // d = 128: 948 -> 993, d = 256: 438 -> 753).
-  constexpr int kPairMinRows = 4096;
+  // At d = 256, where a workgroup of the plain form has two waves for the four SIMDs of its CU, pairs win from 11 rows per CU on: us
+  // of estimate and attention, plain / pairs: 16/4 heads, 8192 tokens (2048 rows) 278 / 294, 8/2, 16384 (2048) 292 / 300, 16/2, 11264
+  // (2816) 374 / 381, 16/4, 11264 (2816) 414 / 392, 28/4, 6656 (2912) 277 / 261, 12/4, 16384 (3072) 321 / 318, 8/2, 24576 (3072) 609 /
+  // 523, 32/8, 6144 (3072) 262 / 253, 28/4, 8192 (3584) 334 / 308, 4/2, 57344 (3584) 924 / 786.
+  const int pair_rows = d > 128 ? 11 * persistent_grid(0x7fffffff, 1) : 4096;
   const bool pair = W.pair_plan != W.pair_items && !stream_only && !(params->flags & PRISM_FLAG_GENERAL_KERNEL) &&
-                    ((R >= kPairMinRows && d >= 128) || (params->flags & PRISM_FLAG_PAIR_KERNEL));
+                    ((R >= pair_rows && d >= 128) || (params->flags & PRISM_FLAG_PAIR_KERNEL));
   const int only_dirty = w64 && seqs.n > 1 ? kDirtySequences : (w64 || pair ? kDirtyCall : kEverything);
   int4* pair_items = reinterpret_cast<int4*>(ws + W.pair_items);
   int32_t* pair_plan = reinterpret_cast<int32_t*>(ws + W.pair_plan);

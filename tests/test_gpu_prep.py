@@ -108,6 +108,40 @@ def test_wide_rows_of_short_calls(h, bidir):
     test_wide_rows_beyond_one_workgroup_per_cu(h, bidir)
 
 
+@pytest.mark.parametrize("h,tail,bidir", [(43, 64, False), (44, 64, False), (44, 7, False), (45, 1, True)])
+def test_wide_pairs(h, tail, bidir):
+    """d = 256, B = 64, 64 blocks: 2752 rows in the plain form, 2816 and 2880 in pairs, whose unions have from one block to all.
+    Every head has the bits of a call on a few heads, which is plain, and agrees with the oracle."""
+    N, B, d = 64, 64, 256
+    L = (N - 1) * B + tail
+    rng = np.random.default_rng(h + tail)
+    g = torch.Generator(device="cuda").manual_seed(h)
+    q, k, v = (torch.randn((n, L, d), generator=g, device="cuda").bfloat16() for n in (h, 1, 1))
+    mask = rng.random((h, N, N)) < np.array([0.0, 0.03, 0.2, 0.9])[np.arange(h) % 4, None, None]
+    mask[:, np.arange(N), np.arange(N)] = True
+    mask[1, :, N - 1] = True
+    mask[5, 10] = False                                    # an empty list beside a full one, and two empty ones
+    mask[5, 20:22] = False
+    if not bidir:
+        mask = np.tril(mask)
+    flags = pb.PRISM_FLAG_BIDIRECTIONAL if bidir else 0
+
+    def run(heads):
+        params = pb.make_params(len(heads), 1, L, B, 128, 192, 0.9, flags, d)
+        rp, ci, cnt = gu.csr_to_device(*orc.mask_to_csr(mask[heads]))
+        return gu.gpu_sparse_attn(params, q[heads].contiguous(), k, v, rp, ci, cnt)
+
+    out, lse = run(range(h))
+    for part in (range(8), range(h - 5, h)):
+        o, s = run(part)
+        assert torch.equal(out[part].view(torch.int16), o.view(torch.int16)) and torch.equal(lse[part], s)
+    Q, K, V = (t.float().cpu().numpy().astype(np.float64) for t in (q, k, v))
+    rows = {(i, u) for i in (0, 1, 2, 3, h - 1) for u in (0, 1, N // 2, N - 1)}
+    ref = orc.block_sparse_attention(Q, K, V, mask, B, rows, causal=not bidir)
+    for (i, u), (ro, _) in ref.items():                    # 2e-2: the bar of the other attention tests
+        assert np.abs(gu.bf16_out_to_f64(out[i, u * B:(u + 1) * B]) - ro).max() <= 2e-2, (i, u)
+
+
 @pytest.mark.parametrize("dirty", [False, True])
 def test_pair_queues_of_the_separate_kernels(dirty):
     check_pair_plan(33, 11, 250, dirty)  # 8250 rows: the counters of both plans are written by the last launch that fills one
