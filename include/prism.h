@@ -125,7 +125,7 @@ const char* prism_status_string(int status);
  *               info[1] = 1 if that number exceeds col_capacity (col_idx then holds only
  *               the entries that fit and must not be used), info[2..3] reserved (0).
  * workspace: prism_estimate_workspace_bytes() bytes.  The last n_q_heads*N*4 of them (rounded up
- *            to 256) hold row counts that short calls keep apart; a buffer without them is taken
+ *            to 256) hold the counts of strips of rows; a buffer without them is taken
  *            too, the call then goes the general way.
  * ---------------------------------------------------------------------------------- */
 int prism_estimate_workspace_bytes(const prism_params* params, size_t* bytes /* host, out */);
@@ -153,7 +153,7 @@ int prism_estimate_bands(const prism_params* params, const prism_bands* bands /*
  * 16 MiB device array inside the library (one copy per GPU, held until the process ends;
  * its address is looked up on the first call on each device, which allocates nothing).
  * Returns PRISM_ERR_TOO_LARGE, with nothing enqueued, when
- * prism_estimate_workspace_bytes(params), less the row counts (see there), exceeds 16 MiB
+ * prism_estimate_workspace_bytes(params), less the counts (see there), exceeds 16 MiB
  * (16 777 216 bytes; the Llama-shaped layer fits up to 32K tokens at B = 128).  The call allocates nothing.  All calls on one GPU
  * share that GPU's array: calls that overlap there (different streams or threads) race and
  * must be serialised by the caller; calls in a row on one stream are fine, nothing needs

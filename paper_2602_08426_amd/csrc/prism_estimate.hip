@@ -5,7 +5,7 @@
 //   scale_kernel       : RMS energies -> tau_z -> 1 / (sqrt(d_z) tau_z) per q-head
 //   select_kernel      : dual-band block logits on bf16 MFMA (pooled vectors split into
 //                        three bf16 terms), row softmax, top-p, union, bit rows
-//   scan/fill kernels  : bit rows -> CSR index lists
+//   compact_kernel     : bit rows -> CSR index lists
 #include "prism_common.h"
 
 #include <mutex>
@@ -634,6 +634,11 @@ constexpr bool kAblNoScores = (PRISM_SELECT_ABLATION & 1) != 0;      // no score
 constexpr bool kAblNoSearch = (PRISM_SELECT_ABLATION & 2) != 0;      // no softmax / top-p search
 constexpr bool kAblNoRefetch = (PRISM_SELECT_ABLATION & 4) != 0;     // pooled-K fragments fetched for a wave's first tile only
 
+// Where the number of set bits of a strip lies: the strips of a sequence in the order of their rows.
+__device__ __forceinline__ size_t strip_index(int h, int tile0, int N, int hq, int strip) {
+  return (size_t)h * tile0 + (size_t)hq * ((N + 15) >> 4) + strip;
+}
+
 // select_flags
 constexpr int kSelCausal = 1;          // key blocks v > u are excluded (block-causal estimation)
 constexpr int kSelForceDiagonal = 2;   // block u of every row is switched on after the union
@@ -643,11 +648,12 @@ template <int MAXCH, bool DUMP, int kRowsPerWave, int kSeqs>
 __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
     BandVectors bv, const float* __restrict__ inv_scale, int h, int h_kv,
     SeqTableOf<kSeqs> seqs, int bs, int dpad_high, int dpad_low, float top_p, int select_flags,
-    uint64_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr,
+    uint64_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr, int32_t* __restrict__ strip_counts,
     float* __restrict__ logits_high, float* __restrict__ logits_low) {
   constexpr int kWaves = kStripRows / kRowsPerWave, kThreads = kWaves * 64;
   extern __shared__ float lds_logits[];
   __shared__ uint64_t lds_bits[kStripRows][kMaxBlocks / 64];
+  __shared__ int s_count;
   // heavy strips (large u) first; the sequences of a group lie longest first
   int sq = 0;
   if (kSeqs > 1)
@@ -671,6 +677,7 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
   if (!DUMP) {
     for (int i = threadIdx.x; i < kStripRows * (kMaxBlocks / 64); i += kThreads)
       (&lds_bits[0][0])[i] = 0ull;
+    if (threadIdx.x == 0) s_count = 0;
   }
 
 #pragma unroll 1
@@ -818,7 +825,14 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
       if ((select_flags & kSelForceSink) && lane == 0) word |= 1ull;
       const int cnt = wave_sum((int)__popcll(word));
       if (lane < W) mask_bits[row * W + lane] = word;
-      if (lane == 0) row_ptr[row + 1] = cnt;
+      if (lane == 0) {
+        if (strip_counts != nullptr) atomicAdd(&s_count, cnt);
+        else row_ptr[row + 1] = cnt;
+      }
+    }
+    if (strip_counts != nullptr) {                   // uniform
+      __syncthreads();
+      if (threadIdx.x == 0) strip_counts[strip_index(h, seqs.s[sq].tile0, N, hq, strip)] = s_count;
     }
   }
 }
@@ -826,7 +840,7 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
 // =====================================================================================
 // The same selection for calls of few strips, whose time is the length of one workgroup's chain: sixteen waves per
 // strip, eight per band, so that the two bands run side by side and a wave owns two rows instead of four; the
-// calibration is done here as well instead of in a launch of its own, and the row counts go to `counts`.
+// calibration is done here as well instead of in a launch of its own.
 // N <= 512 (two logit strips of 33 KB).  Logits and masks have the bits of select_kernel: a tile's MFMAs and a row's
 // sums keep their order.  A workgroup of 16 waves with 90 registers a lane has a CU to itself, so up to 256 strips run
 // at once and the strips beyond start a second round; of select_kernel two workgroups share a CU.  Whole estimate, us, five
@@ -840,16 +854,16 @@ template <int kSeqs>
 __global__ __launch_bounds__(1024) void select_small_kernel(
     BandVectors bv, const float* __restrict__ energy, int h, int h_kv, SeqTableOf<kSeqs> seqs, int bs, int head_dim,
     int dz_high, int dz_low, int dpad_high, int dpad_low, int calibrate, float top_p, int select_flags,
-    uint64_t* __restrict__ mask_bits, int32_t* __restrict__ counts) {
+    uint64_t* __restrict__ mask_bits, int32_t* __restrict__ strip_counts) {
   extern __shared__ float lds_logits[];
   __shared__ uint64_t lds_bits[2][kStripRows][kSmallBlocks / 64];
+  __shared__ int s_count;
   int sq = 0;
   if (kSeqs > 1)
     while (sq + 1 < seqs.n && (int)blockIdx.x >= seqs.s[sq + 1].tile0) ++sq;
   const int N = seqs.s[sq].N;
   const int strip = ((N + 15) >> 4) - 1 - ((int)blockIdx.x - seqs.s[sq].tile0), hq = blockIdx.y;
   mask_bits += seqs.s[sq].mask0;
-  counts += (size_t)h * seqs.s[sq].blk0;
   energy += (size_t)(h + h_kv) * seqs.s[sq].blk0 * 4;
   const size_t q0 = (size_t)h * seqs.s[sq].blk0 * bs, kv0 = kv_band_base(h, h_kv, seqs.nsum, seqs.s[sq].tile0, bs);
   const int kvh = hq / (h / h_kv);
@@ -864,6 +878,7 @@ __global__ __launch_bounds__(1024) void select_small_kernel(
   const int W = (N + 63) >> 6;
   float* const strip_lds = lds_logits + (size_t)z * kStripRows * ld;
   for (int i = threadIdx.x; i < 2 * kStripRows * (kSmallBlocks / 64); i += 1024) (&lds_bits[0][0][0])[i] = 0ull;
+  if (threadIdx.x == 0) s_count = 0;
 
   const int dpad = z == 0 ? dpad_high : dpad_low;
   if (dpad != 0) {                                     // uniform per wave
@@ -938,84 +953,80 @@ __global__ __launch_bounds__(1024) void select_small_kernel(
     if ((select_flags & kSelForceSink) && lane == 0) word |= 1ull;
     const int cnt = wave_sum((int)__popcll(word));
     if (lane < W) mask_bits[row * W + lane] = word;
-    if (lane == 0) counts[row] = cnt;
+    if (lane == 0) atomicAdd(&s_count, cnt);
   }
+  __syncthreads();
+  if (threadIdx.x == 0) strip_counts[strip_index(h, seqs.s[sq].tile0, N, hq, strip)] = s_count;
 }
 
 // =====================================================================================
 // Bit rows -> CSR
 // =====================================================================================
-// Row offsets and column lists in one launch from row counts that lie apart from row_ptr: a workgroup takes 16 rows,
-// adds up all counts in front of them (from the L2, 10 KB on average at the 5120 rows that calls of this form have at
-// most), scans its own and writes their columns, four rows per wave.  For more rows the sums cost more than the launch
-// they save: at 8192 rows 114 instead of 106 us for the whole estimate, at 32768 486 instead of 462 (64 rows per
-// workgroup), so scan_kernel and fill_kernel stay there.
-constexpr int kCompactRows = 16;
-template <int kSeqs>
-__global__ __launch_bounds__(256) void compact_kernel(const uint64_t* __restrict__ mask_bits,
-                                                      const int32_t* __restrict__ counts, int h,
-                                                      SeqTableOf<kSeqs> seqs, int32_t* __restrict__ row_ptr,
-                                                      int32_t* __restrict__ col_idx, int32_t* __restrict__ info) {
-  __shared__ int s_before[4], s_base[kCompactRows];
-  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  int sq = 0, wg = blockIdx.x;
-  if (kSeqs > 1) {
-    while (sq + 1 < seqs.n) {
-      const int n = (h * seqs.s[sq].N + kCompactRows - 1) / kCompactRows;
-      if (wg < n) break;
-      wg -= n;
-      ++sq;
-    }
+// The columns of a row whose word i lane i holds, ascending from col_idx[base] on, by one wave.
+__device__ __forceinline__ void write_columns(uint64_t mine, int W, int64_t base, int64_t capacity, int lane,
+                                              int32_t* __restrict__ col_idx) {
+  const int lo = (int)(uint32_t)mine, hi = (int)(uint32_t)(mine >> 32);
+  for (int i = 0; i < W; ++i) {
+    const uint64_t word = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32) |
+                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i);
+    if (word == 0ull) continue;                      // uniform
+    const int rank = __popcll(word & ((1ull << lane) - 1ull));
+    if (((word >> lane) & 1ull) && base + rank < capacity) col_idx[base + rank] = i * 64 + lane;
+    base += __popcll(word);
   }
-  const int N = seqs.s[sq].N, R = h * N, W = (N + 63) >> 6;
+}
+
+// Row offsets and column lists in one launch, bound by its memory round trips: a workgroup takes a strip, a row a wave, adds up the
+// counts of all strips in front of it, counts its own rows from their bits, and writes offsets and columns.  us of the whole
+// estimate, sums over row counts (short calls) or separate scan and fill (others) -> sums over strip counts: 32/8 heads, 8192 tokens
+// 32.3 -> 30.1, 20011 70.8 -> 68.3, d = 64, 12345 32.8 -> 31.2, the eight packed prompts of perf/cases.py 123.1 -> 118.8, 32768 107.6 -> 105.0,
+// B = 64, 32768 168.7 -> 166.6, 131072 487 -> 480.  (The calibration inside select_kernel as well costs it what its own launch
+// takes: 87.7 -> 93.4 us at 28/4 heads, 65536 tokens.)
+template <int kSeqs>
+__global__ __launch_bounds__(1024) void compact_kernel(const uint64_t* __restrict__ mask_bits,
+                                                       const int32_t* __restrict__ strip_counts, int h,
+                                                       SeqTableOf<kSeqs> seqs, int32_t* __restrict__ row_ptr,
+                                                       int32_t* __restrict__ col_idx, int32_t* __restrict__ info) {
+  __shared__ int s_before[16], s_rows[16];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  int sq = 0, wg = blockIdx.x;                           // the strips of the sequences one behind the other, as the counts
+  if (kSeqs > 1)
+    while (sq + 1 < seqs.n && wg >= h * seqs.s[sq + 1].tile0) ++sq;
+  wg -= h * seqs.s[sq].tile0;
+  const int N = seqs.s[sq].N, W = (N + 63) >> 6, strips = (N + 15) >> 4;
   const int64_t capacity = seqs.s[sq].cap;
-  mask_bits += seqs.s[sq].mask0;
-  counts += (size_t)h * seqs.s[sq].blk0;
+  strip_counts += (size_t)h * seqs.s[sq].tile0;
   row_ptr += seqs.s[sq].row0;
   col_idx += seqs.s[sq].col0;
-  const int r0 = wg * kCompactRows;
+  const int hq = wg / strips, u = (wg - hq * strips) * kStripRows + wave, r = hq * N + u;
+  // requested before the sums; a row past the head's end has no bits
+  const uint64_t mine = u < N && lane < W ? mask_bits[seqs.s[sq].mask0 + (size_t)r * W + lane] : 0ull;
   int part = 0;
-  // this wave's rows, requested before the sums
-  uint64_t words[kCompactRows / 4];
-#pragma unroll
-  for (int j = 0; j < kCompactRows / 4; ++j) {
-    const int r = r0 + wave * (kCompactRows / 4) + j;
-    words[j] = r < R && lane < W ? mask_bits[(size_t)r * W + lane] : 0ull;
-  }
-#pragma unroll 8
-  for (int i = t; i < r0; i += 256) part += counts[i];
+#pragma unroll 4
+  for (int i = t; i < wg; i += 1024) part += strip_counts[i];
   part = wave_sum(part);
-  if (lane == 0) s_before[wave] = part;
+  const int own = wave_sum((int)__popcll(mine));
+  if (lane == 0) {
+    s_before[wave] = part;
+    s_rows[wave] = own;
+  }
   __syncthreads();
-  if (wave == 0) {
-    const bool own = lane < kCompactRows && r0 + lane < R;
-    const int mine = own ? counts[r0 + lane] : 0;
-    const int incl = wave_scan_inclusive(mine) + s_before[0] + s_before[1] + s_before[2] + s_before[3];
-    if (lane < kCompactRows) s_base[lane] = incl - mine;
-    if (own) row_ptr[r0 + lane + 1] = incl;
-    if (lane == 0 && r0 == 0) row_ptr[0] = 0;
-    if (own && r0 + lane == R - 1) {
+  // lane i: the sum over wave i and the row of wave i
+  const int of_wave = lane < 16 ? s_before[lane] + (lane < wave ? s_rows[lane] : 0) : 0;
+  const int begin = wave_sum(of_wave);
+  if (u >= N) return;
+  if (lane == 0) {
+    if (r == 0) row_ptr[0] = 0;
+    row_ptr[r + 1] = begin + own;
+    if (r == h * N - 1) {
       int32_t* out = info + 4 * (size_t)seqs.s[sq].index;
-      out[0] = incl;
-      out[1] = (int64_t)incl > capacity ? 1 : 0;
+      out[0] = begin + own;
+      out[1] = (int64_t)(begin + own) > capacity ? 1 : 0;
       out[2] = 0;
       out[3] = 0;
     }
   }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kCompactRows / 4; ++j) {           // rows past the end have no bits
-    int64_t base = s_base[wave * (kCompactRows / 4) + j];
-    const int lo = (int)(uint32_t)words[j], hi = (int)(uint32_t)(words[j] >> 32);
-    for (int i = 0; i < W; ++i) {
-      const uint64_t word = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32) |
-                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i);
-      if (word == 0ull) continue;                      // uniform
-      const int rank = __popcll(word & ((1ull << lane) - 1ull));
-      if (((word >> lane) & 1ull) && base + rank < capacity) col_idx[base + rank] = i * 64 + lane;
-      base += __popcll(word);
-    }
-  }
+  write_columns(mine, W, begin, capacity, lane, col_idx);
 }
 
 __global__ __launch_bounds__(256) void row_count_kernel(const uint64_t* __restrict__ mask_bits,
@@ -1088,16 +1099,9 @@ __device__ __forceinline__ void scan_resident(int32_t* __restrict__ row_ptr, int
   }
 }
 
-// One workgroup per sequence.
-template <int kSeqs>
-__global__ __launch_bounds__(1024) void scan_kernel(int32_t* __restrict__ row_ptr, int h, SeqTableOf<kSeqs> seqs,
+__global__ __launch_bounds__(1024) void scan_kernel(int32_t* __restrict__ row_ptr, int R, int64_t capacity,
                                                     int32_t* __restrict__ info) {
   __shared__ int wave_tot[2][16 * 16];
-  const SeqInfo sq = seqs.s[kSeqs == 1 ? 0 : blockIdx.x];
-  const int R = h * sq.N;
-  const int64_t capacity = sq.cap;
-  row_ptr += sq.row0;
-  info += 4 * (size_t)sq.index;
   const int chunks = (R + 4095) / 4096;              // uniform
   if (chunks <= 16) {
     if (chunks <= 1) scan_resident<1>(row_ptr, R, capacity, info, wave_tot[0], wave_tot[1]);
@@ -1155,32 +1159,13 @@ __global__ __launch_bounds__(1024) void scan_kernel(int32_t* __restrict__ row_pt
 
 // One wave per row: ascending columns of the set bits.  Lane i fetches word i of the row (one
 // request for the whole row; W <= 32), the words are then taken from registers.
-template <int kSeqs>
-__global__ __launch_bounds__(256) void fill_kernel(const uint64_t* __restrict__ mask_bits, int h,
-                                                   SeqTableOf<kSeqs> seqs,
-                                                   const int32_t* __restrict__ row_ptr,
-                                                   int32_t* __restrict__ col_idx) {
-  int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__global__ __launch_bounds__(256) void fill_kernel(const uint64_t* __restrict__ mask_bits, int R, int W, int64_t capacity,
+                                                   const int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx) {
+  const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (r >= h * seqs.nsum) return;
-  const int sq = seq_of(seqs, r, h);
-  r -= h * seqs.s[sq].blk0;
-  const int W = (seqs.s[sq].N + 63) >> 6;
-  const int64_t capacity = seqs.s[sq].cap;
-  mask_bits += seqs.s[sq].mask0;
-  row_ptr += seqs.s[sq].row0;
-  col_idx += seqs.s[sq].col0;
-  int64_t base = row_ptr[r];
-  const uint64_t mine = lane < W ? mask_bits[(size_t)r * W + lane] : 0ull;
-  const int lo = (int)(uint32_t)mine, hi = (int)(uint32_t)(mine >> 32);
-  for (int i = 0; i < W; ++i) {
-    const uint64_t word = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32) |
-                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i);
-    if (word == 0ull) continue;                      // uniform
-    const int rank = __popcll(word & ((1ull << lane) - 1ull));
-    if (((word >> lane) & 1ull) && base + rank < capacity) col_idx[base + rank] = i * 64 + lane;
-    base += __popcll(word);
-  }
+  if (r >= R) return;
+  const int64_t base = row_ptr[r];
+  write_columns(lane < W ? mask_bits[(size_t)r * W + lane] : 0ull, W, base, capacity, lane, col_idx);
 }
 
 // Index lists of the all-ones mask: row (head,u) = {0..u} (causal) or {0..N-1}.
@@ -1247,7 +1232,7 @@ static int make_band_map(const prism_params* p, const prism_bands* bands, BandMa
 // ---- workspace layout ------------------------------------------------------------
 struct EstimateWs {
   size_t band[2][3], energy, inv_scale, counts, total;
-  size_t least;      // without the row counts: a buffer of this size runs the separate scan and fill kernels
+  size_t least;      // without the strip counts: a buffer of this size runs the separate scan and fill kernels
 };
 // The layout for n sequences of together `blocks` blocks and `tiles` tiles of 16 blocks.
 static EstimateWs estimate_layout(const prism_params* p, size_t n, size_t blocks, size_t tiles) {
@@ -1362,7 +1347,8 @@ static int select_flags_of(const prism_params* p) {
 
 template <int MAXCH, bool DUMP, int kRowsPerWave, int kSeqs>
 static int launch_select_on(const prism_params* p, const SeqTableOf<kSeqs>& seqs, const BandMap& map, char* ws,
-                         const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, float* lh, float* ll, hipStream_t st) {
+                         const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, int32_t* strip_counts, float* lh, float* ll,
+                         hipStream_t st) {
   const size_t lds = (size_t)kStripRows * (((seqs.nmax + 15) / 16) * 16 + 4) * sizeof(float);
   auto kern = select_kernel<MAXCH, DUMP, kRowsPerWave, kSeqs>;
   if (lds > 64 * 1024) {
@@ -1373,48 +1359,43 @@ static int launch_select_on(const prism_params* p, const SeqTableOf<kSeqs>& seqs
   hipLaunchKernelGGL(kern, dim3(seqs.tiles, p->n_q_heads), dim3(kStripRows / kRowsPerWave * 64), lds, st,
                      band_vectors(ws, L),
                      reinterpret_cast<const float*>(ws + L.inv_scale), p->n_q_heads, p->n_kv_heads, seqs,
-                     band_stride(p->head_dim), map.dpad[0], map.dpad[1], p->top_p, select_flags_of(p), mask_bits, row_ptr, lh, ll);
+                     band_stride(p->head_dim), map.dpad[0], map.dpad[1], p->top_p, select_flags_of(p), mask_bits, row_ptr, strip_counts,
+                     lh, ll);
   return launch_status();
 }
 
 template <int MAXCH, bool DUMP, int kRowsPerWave = 4>
 static int launch_select(const prism_params* p, const SeqTable& seqs, const BandMap& map, char* ws,
-                         const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, float* lh, float* ll,
+                         const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, int32_t* strip_counts, float* lh, float* ll,
                          hipStream_t st) {
   if (DUMP || seqs.n == 1)
-    return launch_select_on<MAXCH, DUMP, kRowsPerWave, 1>(p, only_sequence(seqs), map, ws, L, mask_bits, row_ptr, lh, ll, st);
-  return launch_select_on<MAXCH, false, kRowsPerWave, kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, row_ptr, lh, ll, st);
+    return launch_select_on<MAXCH, DUMP, kRowsPerWave, 1>(p, only_sequence(seqs), map, ws, L, mask_bits, row_ptr, strip_counts, lh,
+                                                          ll, st);
+  return launch_select_on<MAXCH, false, kRowsPerWave, kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, row_ptr, strip_counts, lh,
+                                                                     ll, st);
 }
 
-static int run_compact(const prism_params* p, const SeqTable& seqs, const uint64_t* mask_bits, const int32_t* counts,
+static int run_compact(const prism_params* p, const SeqTable& seqs, const uint64_t* mask_bits, const int32_t* strip_counts,
                        int32_t* row_ptr, int32_t* col_idx, int32_t* info, hipStream_t st) {
   const int h = p->n_q_heads;
-  int grid = 0;
-  for (int i = 0; i < seqs.n; ++i) grid += (h * seqs.s[i].N + kCompactRows - 1) / kCompactRows;
+  const dim3 grid(h * seqs.tiles);
   if (seqs.n == 1)
-    hipLaunchKernelGGL(compact_kernel<1>, dim3(grid), dim3(256), 0, st, mask_bits, counts, h, only_sequence(seqs), row_ptr,
+    hipLaunchKernelGGL(compact_kernel<1>, grid, dim3(1024), 0, st, mask_bits, strip_counts, h, only_sequence(seqs), row_ptr,
                        col_idx, info);
   else
-    hipLaunchKernelGGL(compact_kernel<kMaxGroupSeqs>, dim3(grid), dim3(256), 0, st, mask_bits, counts, h, seqs, row_ptr,
+    hipLaunchKernelGGL(compact_kernel<kMaxGroupSeqs>, grid, dim3(1024), 0, st, mask_bits, strip_counts, h, seqs, row_ptr,
                        col_idx, info);
   return launch_status();
 }
 
-static int run_compaction(const prism_params* p, const SeqTable& seqs, const uint64_t* mask_bits, int32_t* row_ptr,
+// One sequence, whose outputs start at the pointers.  count_rows: its row counts are not in row_ptr yet.
+static int run_compaction(const prism_params* p, const SeqInfo& sq, const uint64_t* mask_bits, int32_t* row_ptr,
                           int32_t* col_idx, int32_t* info, bool count_rows, hipStream_t st) {
-  const int h = p->n_q_heads, R = h * seqs.nsum;
-  if (count_rows)                                      // one sequence
-    hipLaunchKernelGGL(row_count_kernel, dim3((R + 255) / 256), dim3(256), 0, st, mask_bits, R, (seqs.nsum + 63) / 64,
-                       row_ptr);
-  if (seqs.n == 1) {
-    const OneSeq one = only_sequence(seqs);
-    hipLaunchKernelGGL(scan_kernel<1>, dim3(1), dim3(1024), 0, st, row_ptr, h, one, info);
-    hipLaunchKernelGGL(fill_kernel<1>, dim3((R + 3) / 4), dim3(256), 0, st, mask_bits, h, one, row_ptr, col_idx);
-  } else {
-    hipLaunchKernelGGL(scan_kernel<kMaxGroupSeqs>, dim3(seqs.n), dim3(1024), 0, st, row_ptr, h, seqs, info);
-    hipLaunchKernelGGL(fill_kernel<kMaxGroupSeqs>, dim3((R + 3) / 4), dim3(256), 0, st, mask_bits, h, seqs, row_ptr,
-                       col_idx);
-  }
+  const int R = p->n_q_heads * sq.N, W = (sq.N + 63) / 64;
+  if (count_rows)
+    hipLaunchKernelGGL(row_count_kernel, dim3((R + 255) / 256), dim3(256), 0, st, mask_bits, R, W, row_ptr);
+  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, row_ptr, R, (int64_t)sq.cap, info);
+  hipLaunchKernelGGL(fill_kernel, dim3((R + 3) / 4), dim3(256), 0, st, mask_bits, R, W, (int64_t)sq.cap, row_ptr, col_idx);
   return launch_status();
 }
 
@@ -1452,7 +1433,7 @@ extern "C" int prism_estimate_workspace_bytes(const prism_params* params, size_t
 
 template <int kSeqs>
 static int run_small_on(const prism_params* p, const SeqTableOf<kSeqs>& seqs, const BandMap& map, char* ws,
-                        const EstimateWs& L, uint64_t* mask_bits, int32_t* counts, hipStream_t st) {
+                        const EstimateWs& L, uint64_t* mask_bits, int32_t* strip_counts, hipStream_t st) {
   const int h = p->n_q_heads;
   const size_t lds = (size_t)2 * kStripRows * (((seqs.nmax + 15) / 16) * 16 + 4) * sizeof(float);
   auto kern = select_small_kernel<kSeqs>;
@@ -1464,13 +1445,13 @@ static int run_small_on(const prism_params* p, const SeqTableOf<kSeqs>& seqs, co
   hipLaunchKernelGGL(kern, dim3(seqs.tiles, h), dim3(1024), lds, st, band_vectors(ws, L),
                      reinterpret_cast<const float*>(ws + L.energy), h, p->n_kv_heads, seqs, band_stride(p->head_dim),
                      p->head_dim, map.dz[0], map.dz[1], map.dpad[0], map.dpad[1],
-                     (p->flags & PRISM_FLAG_NO_CALIBRATION) ? 0 : 1, p->top_p, select_flags_of(p), mask_bits, counts);
+                     (p->flags & PRISM_FLAG_NO_CALIBRATION) ? 0 : 1, p->top_p, select_flags_of(p), mask_bits, strip_counts);
   return launch_status();
 }
 static int run_small(const prism_params* p, const SeqTable& seqs, const BandMap& map, char* ws, const EstimateWs& L,
-                     uint64_t* mask_bits, int32_t* counts, hipStream_t st) {
-  if (seqs.n == 1) return run_small_on<1>(p, only_sequence(seqs), map, ws, L, mask_bits, counts, st);
-  return run_small_on<kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, counts, st);
+                     uint64_t* mask_bits, int32_t* strip_counts, hipStream_t st) {
+  if (seqs.n == 1) return run_small_on<1>(p, only_sequence(seqs), map, ws, L, mask_bits, strip_counts, st);
+  return run_small_on<kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, strip_counts, st);
 }
 
 // Strips * q-heads of the whole call up to which the short form is taken: the second round of its workgroups (see
@@ -1486,26 +1467,27 @@ static int estimate_core(const prism_params* params, const HeadStrides& hs, cons
                          hipStream_t st, const RopeArgs* rope = nullptr, void* q_out = nullptr,
                          void* k_out = nullptr) {
   const EstimateWs L = estimate_layout(params, seqs.n, seqs.nsum, seqs.tiles);
-  // Few strips: three launches instead of five, and a shorter chain per strip (both sides of the rule at
-  // select_small_kernel).  A workspace without room for the row counts goes the general way.
-  const bool small = ws_bytes >= L.total && seqs.nmax <= kSmallBlocks &&
+  // A workspace without room for the counts has the row counts in row_ptr and the separate scan and fill kernels.
+  int32_t* strip_counts = ws_bytes >= L.total ? reinterpret_cast<int32_t*>(ws + L.counts) : nullptr;
+  // Few strips: a launch less, and a shorter chain per strip (both sides of the rule at select_small_kernel).
+  const bool small = strip_counts != nullptr && seqs.nmax <= kSmallBlocks &&
                      (int64_t)seqs.tiles * params->n_q_heads <= kSmallStrips;
   int rc = run_pool_and_scale(params, hs, seqs, map, q, k, ws, L, nullptr, nullptr, nullptr, st, rope, q_out, k_out, !small);
   if (rc != PRISM_OK) return rc;
-  if (small) {
-    int32_t* counts = reinterpret_cast<int32_t*>(ws + L.counts);
-    rc = run_small(params, seqs, map, ws, L, mask_bits, counts, st);
-    if (rc != PRISM_OK) return rc;
-    return run_compact(params, seqs, mask_bits, counts, row_ptr, col_idx, info, st);
-  }
   // up to 1024 blocks: 4 waves of 4 rows, two workgroups per CU; beyond (a 131 KB logit strip, one
   // workgroup per CU, rows of 32 registers): 8 waves of 2 rows (measured 1.89 -> 1.25 ms at N = 2048,
   // while at N = 1024 the 4-wave form is 2 % faster)
-  rc = (seqs.nmax <= 1024)
-           ? launch_select<16, false, 4>(params, seqs, map, ws, L, mask_bits, row_ptr, nullptr, nullptr, st)
-           : launch_select<32, false, 2>(params, seqs, map, ws, L, mask_bits, row_ptr, nullptr, nullptr, st);
+  if (small)
+    rc = run_small(params, seqs, map, ws, L, mask_bits, strip_counts, st);
+  else if (seqs.nmax <= 1024)
+    rc = launch_select<16, false, 4>(params, seqs, map, ws, L, mask_bits, row_ptr, strip_counts, nullptr, nullptr, st);
+  else
+    rc = launch_select<32, false, 2>(params, seqs, map, ws, L, mask_bits, row_ptr, strip_counts, nullptr, nullptr, st);
   if (rc != PRISM_OK) return rc;
-  return run_compaction(params, seqs, mask_bits, row_ptr, col_idx, info, false, st);
+  if (strip_counts != nullptr) return run_compact(params, seqs, mask_bits, strip_counts, row_ptr, col_idx, info, st);
+  const SeqInfo& sq = seqs.s[0];                       // (several sequences come only with a workspace that holds the counts)
+  return run_compaction(params, sq, mask_bits + sq.mask0, row_ptr + sq.row0, col_idx + sq.col0, info + 4 * (size_t)sq.index, false,
+                        st);
 }
 
 extern "C" int prism_estimate_bands(const prism_params* params, const prism_bands* bands,
@@ -1742,7 +1724,7 @@ extern "C" int prism_block_scores_bands(const prism_params* params, const prism_
                           scales, st);
   if (rc != PRISM_OK) return rc;
   if (logits_high == nullptr && logits_low == nullptr) return PRISM_OK;
-  return launch_select<16, true>(params, seqs, map, ws, L, nullptr, nullptr, logits_high, logits_low, st);
+  return launch_select<16, true>(params, seqs, map, ws, L, nullptr, nullptr, nullptr, logits_high, logits_low, st);
 }
 
 extern "C" int prism_block_scores(const prism_params* params, const void* q_bf16,
@@ -1764,7 +1746,7 @@ extern "C" int prism_mask_to_csr(const prism_params* params, const uint64_t* mas
   int rc = check_params(params);
   if (rc != PRISM_OK) return rc;
   if (!mask_bits || !row_ptr || !col_idx || !info || col_capacity < 0) return PRISM_ERR_INVALID_ARG;
-  return run_compaction(params, one_sequence(params, col_capacity), mask_bits, row_ptr, col_idx, info, true,
+  return run_compaction(params, one_sequence(params, col_capacity).s[0], mask_bits, row_ptr, col_idx, info, true,
                         static_cast<hipStream_t>(stream));
 }
 
