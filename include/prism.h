@@ -256,9 +256,10 @@ int prism_dense_csr(const prism_params* params, int32_t* row_ptr, int32_t* col_i
  *                      col_idx (row_ptr values are clamped to it).
  *   out_bf16         : [n_q_heads, L, d] bf16, fully overwritten.
  *   lse              : [n_q_heads, L] float natural-log sum-exp of the scaled scores, or NULL.
- * workspace: prism_sparse_attn_workspace_bytes() bytes (a transposed copy of V plus the
- *            kernel's work queues: one entry per row, ordered by list-length class and
- *            q-head and dealt to the eight XCDs in parts of equal work).
+ * workspace: prism_sparse_attn_workspace_bytes() bytes (the kernel's work queues: one entry
+ *            per row, ordered by list-length class and q-head and dealt to the eight XCDs in
+ *            parts of equal work; an fp16 image of V where a kernel reads one; room for the
+ *            copy of V that prism_v_image leaves).
  * top_p, d_high, d_low and the other flags of `params` are ignored here.
  * ---------------------------------------------------------------------------------- */
 int prism_sparse_attn_workspace_bytes(const prism_params* params, size_t* bytes /* host, out */);
@@ -269,16 +270,16 @@ int prism_sparse_attn(const prism_params* params,
                       void* out_bf16, float* lse,
                       void* workspace, size_t workspace_bytes, void* stream);
 
-/* The two halves of prism_sparse_attn, for callers that reuse one V image for several
+/* prism_sparse_attn in two halves, for callers that reuse one V image for several
  * attention calls (or time the attention kernel alone):
- *   prism_v_image          : writes the transposed, block-tiled copy of V that the attention
- *                            kernel reads into `v_image` (prism_sparse_attn_workspace_bytes()
- *                            bytes, 256-byte aligned).
+ *   prism_v_image          : writes what the attention kernels read of V into `v_image`
+ *                            (prism_sparse_attn_workspace_bytes() bytes, 256-byte aligned).
  *   prism_sparse_attn_pre  : same computation and arguments as prism_sparse_attn, with the
  *                            image in place of V.  The tail of the same buffer (beyond the
  *                            image) is scratch for the kernel's work queue and is rewritten
  *                            by every call, so calls sharing one image must not overlap.
- * prism_sparse_attn(...) == prism_v_image(..., workspace) ; prism_sparse_attn_pre(..., workspace). */
+ * out and lse of prism_sparse_attn(...) are those of prism_v_image(..., workspace) ;
+ * prism_sparse_attn_pre(..., workspace).  prism_sparse_attn itself leaves no image behind. */
 int prism_v_image(const prism_params* params, const void* v_bf16, void* v_image,
                   size_t v_image_bytes, void* stream);
 

@@ -11,8 +11,9 @@
 // In the 32x32 accumulator layout lane l holds query column l%32 and, per 32-key tile,
 // keys 8*(r/4) + 4*(l/32) + r%4 for r = 0..15.  One MFMA K-step of PV therefore consumes
 // keys {16s + 8g + 4*(l/32) + i}; the V^T operand must present the same keys in the same
-// slots, which is achieved by a one-off re-layout of V in HBM (vt_image_kernel): per kv
-// block a [d][B] image whose key positions inside every group of 16 are permuted to
+// slots.  The general kernel reads V as it is given and transposes on the way from LDS to the registers
+// (ds_read_b64_tr_b16 hands a lane four keys of its dim).  The 64-queries-per-wave kernel reads an fp16 image of V^T: per kv
+// block [d][B], whose key positions inside every group of 16 are permuted to
 // pos = 8*hf + 4*g + i  for key = 8*g + 4*hf + i.  A 16-byte LDS read then yields one
 // A operand.
 #include "prism_common.h"
@@ -23,75 +24,69 @@
 namespace prism {
 
 // =====================================================================================
-// V re-layout: V [h_kv, L, d]  ->  image [h_kv, N, d, B] with permuted key positions; keys
-// past the end of a ragged last block are written as zeros.
-// =====================================================================================
-// With vt16 != nullptr a second image with the same layout holds the values as fp16 (the
+// V re-layout: V [h_kv, L, 128], whole blocks  ->  fp16 image [h_kv, N, 128, 128] of V^T with permuted key positions (the
 // 64-queries-per-wave kernel forms its P V product in fp16: 11 significant bits for P instead of 8).
 // Every bf16 value of magnitude in [2^-17, 65504] (and zero) is an fp16 value, so the conversion is
 // exact there; smaller magnitudes lose at most 2^-25 absolute.  A block holding a finite value beyond
 // the fp16 range sets range_flags[kv head * N + block] = 1 (else 0): such inputs go through the
-// general kernel and the bf16 image.
-template <int BLK, int D, int kThreads>
-__device__ __forceinline__ void vt_image_tile(uint16_t (&tile)[BLK][D + 2], int& s_over,
-                                              const uint16_t* __restrict__ src, int cnt,
-                                              uint16_t* __restrict__ dstb, uint16_t* __restrict__ dst16,
-                                              int32_t* __restrict__ range_flag, int flag_value) {
+// general kernel, which reads V itself.
+// =====================================================================================
+constexpr int kImageRows = 128;                      // tokens of a block of the image
+typedef uint16_t ImageTile[kImageRows][kHeadDim + 2];
+template <int kThreads>
+__device__ __forceinline__ void vt_image_tile(ImageTile& tile, int& s_over, const uint16_t* __restrict__ src,
+                                              uint16_t* __restrict__ dst16, int32_t* __restrict__ range_flag, int flag_value) {
   const int t = threadIdx.x;
   if (t == 0) s_over = 0;
-  constexpr int RCH = D / 8;                         // 16-byte chunks per token row
-  for (int idx = t; idx < BLK * RCH; idx += kThreads) {
-    const int row = idx / RCH, c = idx % RCH;
-    u32x4 x = {0u, 0u, 0u, 0u};                       // V is read once: streaming (non-temporal) loads
-    if (row < cnt) x = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (size_t)row * D + c * 8));
-    uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[row][c * 8]);   // 4-byte aligned: row stride 2*D + 4 B
+  constexpr int RCH = kHeadDim / 8;                  // 16-byte chunks per token row
+  for (int idx = t; idx < kImageRows * RCH; idx += kThreads) {
+    const int row = idx / RCH, c = idx % RCH;        // V is read once: streaming (non-temporal) loads
+    const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (size_t)row * kHeadDim + c * 8));
+    uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[row][c * 8]);   // 4-byte aligned: row stride 2*d + 4 B
     dst[0] = x[0]; dst[1] = x[1]; dst[2] = x[2]; dst[3] = x[3];
   }
   __syncthreads();
-  constexpr int CPR = BLK / 8;                       // 16-byte chunks per image row
+  constexpr int CPR = kImageRows / 8;                // 16-byte chunks per image row
   bool over = false;
-  for (int idx = t; idx < D * CPR; idx += kThreads) {
+  for (int idx = t; idx < kHeadDim * CPR; idx += kThreads) {
     const int d = idx / CPR, c = idx % CPR;
-    uint32_t w[4], w16[4];
+    uint32_t w16[4];
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
       // position p = c*8 + e inside the row; group a = p/16, hf = (p/8)&1, g = (p/4)&1, i = p&3
       const int p0 = c * 8 + e, p1 = p0 + 1;
       const int k0 = (p0 & ~15) + 8 * ((p0 >> 2) & 1) + 4 * ((p0 >> 3) & 1) + (p0 & 3);
       const int k1 = (p1 & ~15) + 8 * ((p1 >> 2) & 1) + 4 * ((p1 >> 3) & 1) + (p1 & 3);
-      const uint32_t a = tile[k0][d], b = tile[k1][d];
-      w[e >> 1] = a | (b << 16);
-      if (dst16 != nullptr) {
-        const float fa = bf16_bits_to_float(a), fb = bf16_bits_to_float(b);
-        over |= (fabsf(fa) > 65504.f && fabsf(fa) < INFINITY) || (fabsf(fb) > 65504.f && fabsf(fb) < INFINITY);
-        const _Float16 ha = (_Float16)fa, hb = (_Float16)fb;
-        w16[e >> 1] = (uint32_t)__builtin_bit_cast(uint16_t, ha) | ((uint32_t)__builtin_bit_cast(uint16_t, hb) << 16);
-      }
+      const float fa = bf16_bits_to_float(tile[k0][d]), fb = bf16_bits_to_float(tile[k1][d]);
+      over |= (fabsf(fa) > 65504.f && fabsf(fa) < INFINITY) || (fabsf(fb) > 65504.f && fabsf(fb) < INFINITY);
+      const _Float16 ha = (_Float16)fa, hb = (_Float16)fb;
+      w16[e >> 1] = (uint32_t)__builtin_bit_cast(uint16_t, ha) | ((uint32_t)__builtin_bit_cast(uint16_t, hb) << 16);
     }
-    *reinterpret_cast<uint4*>(dstb + (size_t)d * BLK + c * 8) = make_uint4(w[0], w[1], w[2], w[3]);
-    if (dst16 != nullptr)
-      *reinterpret_cast<uint4*>(dst16 + (size_t)d * BLK + c * 8) = make_uint4(w16[0], w16[1], w16[2], w16[3]);
+    *reinterpret_cast<uint4*>(dst16 + (size_t)d * kImageRows + c * 8) = make_uint4(w16[0], w16[1], w16[2], w16[3]);
   }
-  if (dst16 != nullptr) {
-    if (over) s_over = 1;                            // benign race: every writer stores 1
-    __syncthreads();
-    if (t == 0) *range_flag = s_over != 0 ? flag_value : 0;
-  }
+  if (over) s_over = 1;                              // benign race: every writer stores 1
+  __syncthreads();
+  if (t == 0) *range_flag = s_over != 0 ? flag_value : 0;
 }
 
-template <int BLK, int D>
-__global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restrict__ v,
-                                                       uint16_t* __restrict__ vt, int L, int N,
-                                                       size_t kv_head_stride,
-                                                       uint16_t* __restrict__ vt16,
-                                                       int32_t* __restrict__ range_flags) {
-  __shared__ uint16_t tile[BLK][D + 2];
+__global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restrict__ v, int N, size_t kv_head_stride,
+                                                       uint16_t* __restrict__ vt16, int32_t* __restrict__ range_flags) {
+  __shared__ ImageTile tile;
   __shared__ int s_over;
   const int blk = blockIdx.x, kvh = blockIdx.y;
-  const size_t at = ((size_t)kvh * N + blk) * (size_t)D * BLK;
-  vt_image_tile<BLK, D, 256>(tile, s_over, v + (size_t)kvh * kv_head_stride + (size_t)blk * BLK * D,
-                             min(BLK, L - blk * BLK), vt + at, vt16 != nullptr ? vt16 + at : nullptr,
-                             vt16 != nullptr ? range_flags + kvh * N + blk : nullptr, 1);
+  vt_image_tile<256>(tile, s_over, v + (size_t)kvh * kv_head_stride + (size_t)blk * kImageRows * kHeadDim,
+                     vt16 + ((size_t)kvh * N + blk) * kHeadDim * kImageRows, range_flags + kvh * N + blk, 1);
+}
+
+// The copy of V that prism_v_image leaves for prism_sparse_attn_pre: [h_kv, N * B, d], of which the L tokens are written.
+__global__ __launch_bounds__(256) void v_copy_kernel(const uint16_t* __restrict__ v, size_t chunks, size_t from_stride,
+                                                     size_t to_stride, uint16_t* __restrict__ copy) {
+  const u32x4* from = reinterpret_cast<const u32x4*>(v + (size_t)blockIdx.y * from_stride);
+  u32x4* to = reinterpret_cast<u32x4*>(copy + (size_t)blockIdx.y * to_stride);
+  const size_t at = (size_t)blockIdx.x * 1024 + threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (at + i * 256 < chunks) to[at + i * 256] = __builtin_nontemporal_load(from + at + i * 256);
 }
 
 // A queue entry names its sequence in the high bits of the head number (only where a group holds several).
@@ -122,8 +117,8 @@ __device__ __forceinline__ int dirty_sequences(const DirtyFlags& f) {
 // =====================================================================================
 // Sparse attention kernel.  One workgroup works on one (q-head, q-block) row at a time;
 // BLK/32 waves of 32 queries.
-// LDS: K tile [BLK][d] bf16 and V^T tile [d][BLK] bf16 (d = 64, 128, 256), 16-byte chunks XOR-swizzled by
-// row so that the 16-lane column reads are conflict-free.  Tiles are copied global -> LDS
+// LDS: K tile and V tile [BLK][d] bf16 (d = 64, 128, 256), 16-byte chunks XOR-swizzled by
+// row so that the 16-lane column reads of K and the transposing reads of V are conflict-free.  Tiles are copied global -> LDS
 // asynchronously, without passing through registers.
 // Step per listed kv block (each tile buffer is refilled as soon as its last reader is done):
 //     K(j) in LDS | S^T = K Q^T, requests of V(j) between the MFMAs | barrier
@@ -147,13 +142,12 @@ struct AttnCfg {
   static constexpr int kChunks = kTileBytes / 16;          // 16-byte pieces per tile
   static constexpr int kPerThread = kChunks / kThreads;    // = D / 16 (D / 32 with PAIR)
   static constexpr int kKCpr = D / 8;                      // chunks per K row
-  static constexpr int kVtCpr = BLK / 8;                   // chunks per V^T row
   static constexpr int kDTiles = D / 32;                   // 32-dim tiles of the output
   static constexpr int kKSteps = D / 16;                   // MFMA k-steps of S^T = K Q^T
   static constexpr int kWavesPerSimd = D > 128 ? 1 : 2;    // register budget: 512 or 256 per lane
   // Where the requests of the next K tile go.  A wave that issues all its pieces of a tile in a row stands still until the
   // texture path has taken them, 500 - 1000 cycles of a step (S phase 2770 cycles, PV phase with as many MFMAs 1640).  The
-  // V^T pieces are spread over the S MFMAs in every form; the K pieces over the maximum at B = 128, over the exponentials
+  // V pieces are spread over the S MFMAs in every form; the K pieces over the maximum at B = 128, over the exponentials
   // at d = 256, where no second wave of the SIMD fills the gap; at B = 64 the softmax is too short to hide a later request.
   // us of attention, all in a row / V^T spread / K over the maximum too / K over the exponentials instead:
   // 128 x 128, 32/8 heads, 12345 tokens 281 / 274 / 271 / 270, 40001 1822 / 1752 / 1755 / 1754; 128 x 64, 12345
@@ -198,11 +192,17 @@ __device__ __forceinline__ int k_piece_offset(int p) {
   const int row = p / C::kKCpr;
   return row * (D * 2) + (((p % C::kKCpr) ^ k_row_swizzle<D>(row)) << 4);
 }
+// XOR applied to the 64-byte groups of V-tile row `row`, so that the four keys of a transposing read lie in four bank groups: rows
+// of 128 bytes (d = 64) come two to a 256-byte line.
+template <int D>
+__device__ __forceinline__ int v_row_swizzle(int row) {
+  return D == 64 ? ((row >> 1) & 1) : (row & 3);
+}
 template <int BLK, int D>
-__device__ __forceinline__ int vt_piece_offset(int p) {
+__device__ __forceinline__ int v_piece_offset(int p) {
   using C = AttnCfg<BLK, D>;
-  const int row = p / C::kVtCpr;
-  return row * (BLK * 2) + (((p % C::kVtCpr) ^ (row & (C::kVtCpr - 1))) << 4);
+  const int row = p / C::kKCpr;
+  return row * (D * 2) + (((p % C::kKCpr) ^ (v_row_swizzle<D>(row) << 2)) << 4);
 }
 
 // this wave's first LDS slot of a tile's piece 0, wave-uniform and re-materialised per step so that the per-piece M0
@@ -225,13 +225,13 @@ __device__ __forceinline__ void async_load_k_pieces(__amdgpu_buffer_rsrc_t rs, i
 }
 
 template <int BLK, int D, bool PAIR>
-__device__ __forceinline__ void async_load_vt_pieces(__amdgpu_buffer_rsrc_t rs, int tile_off, char* lds, int t,
+__device__ __forceinline__ void async_load_v_pieces(__amdgpu_buffer_rsrc_t rs, int tile_off, char* lds, int t,
                                                      int wave_base, int i0, int i1) {
   using C = AttnCfg<BLK, D, PAIR>;
 #pragma unroll
   for (int i = i0; i < i1; ++i)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(lds + (i * C::kThreads + wave_base) * 16), 16,
-                                             vt_piece_offset<BLK, D>(i * C::kThreads + t), tile_off, 0, 0);
+                                             v_piece_offset<BLK, D>(i * C::kThreads + t), tile_off, 0, 0);
 }
 
 // One piece of such a copy, written as asm: the compiler, seeing the builtin, would wait for a copy into one of two buffers before
@@ -385,7 +385,7 @@ struct ListWindow {
 enum { kEverything, kDirtyCall, kDirtySequences };
 template <int BLK, bool kStreamOnly, int D, bool kPair, bool kKeepMask>
 __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D, kPair>::kWavesPerSimd)) void sparse_attn_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vt,
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ vals, size_t v_head_stride,
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const int4* __restrict__ items,
     int32_t* __restrict__ plan, PullCounters pulls, DirtyFlags flags,
     uint16_t* __restrict__ out, float* __restrict__ lse, int h, int h_kv, SeqTable seqs,
@@ -417,15 +417,29 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   const float sm_scale = 1.4426950408889634f * (D == 64 ? 0.125f : (D == 128 ? 0.08838834764831845f : 0.0625f));
 
   // LDS read offsets of this lane inside a 32-row slab: row l32, swizzled chunk
-  // (2*step + hf) ^ swizzle(row).  The K tile has d/8 chunks per row; the V^T tile has BLK/8
-  // (for BLK = 128 and d = 128 the two tables coincide).
+  // (2*step + hf) ^ swizzle(row).
   constexpr int kDepth = 8;                                // LDS reads kept in flight
-  int koff[KS], voff[KT * 2];
+  constexpr int kGroups = D > 128 ? 4 : DT;                // 64-byte groups of a V row that the swizzle mixes
+  int koff[KS], voff[kGroups];
 #pragma unroll
   for (int st = 0; st < KS; ++st) koff[st] = l32 * (D * 2) + (((2 * st + hf) ^ k_row_swizzle<D>(l32)) << 4);
+  // V: lane l supplies the address of 4 dims of key 4*hf + (l%16)/4 of a 16-key step, and receives 4 keys of dim l%32.  Two such
+  // reads make an operand that one 16-byte read of a transposed image would be; the kernel takes as long (us of attention alone, image /
+  // this: 128 x 128, 32/8 heads, 20011 tokens 501 / 501, 128 x 64, 12345 183 / 185, pair 64 x 128, 32768 1337 / 1332, pair 64 x 256,
+  // 16/4, 16384 489 / 495), and the image need not be written: preparation and attention 16 heads, 19290 tokens, bidirectional
+  // 458 -> 441, 64 x 128, 32768 1314 -> 1282, 128 x 128, 20011 504 -> 499.
 #pragma unroll
-  for (int st = 0; st < KT * 2; ++st)
-    voff[st] = l32 * (BLK * 2) + (((2 * st + hf) ^ (l32 & (C::kVtCpr - 1))) << 4);
+  for (int i = 0; i < kGroups; ++i) {
+    const int key = 4 * hf + ((lane >> 2) & 3);
+    voff[i] = key * (D * 2) + ((i ^ v_row_swizzle<D>(key)) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+  }
+  // one A operand of O^T += V^T P^T: dims 32*dt ..+31, keys 16*st + {8*g + 4*hf + i}
+  auto v_frag = [&](int dt, int st) __attribute__((always_inline)) {
+    typedef __attribute__((address_space(3))) bf16x4* lv4_t;
+    const char* at = lds_v + voff[dt % kGroups] + (dt / kGroups) * (kGroups * 64) + st * (16 * D * 2);
+    const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lv4_t)at), b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lv4_t)(at + 8 * D * 2));
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
 
   // Persistent workgroups pull rows from per-XCD queues (workgroups are dealt round-robin to the
   // 8 XCDs, and each XCD has its own L2).  A queue runs through neighbouring q-blocks of one
@@ -472,7 +486,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // two buffers per tile: where the current ones start, and this lane's places in pieces 0 and 1 of a K tile and in a piece of V^T
   int buf = 0;
   const int k_lane0 = kTwo ? k_piece_offset<BLK, D>(t) : 0, k_lane1 = kTwo ? k_piece_offset<BLK, D>(C::kThreads + t) : 0;
-  const int v_lane = kTwo ? vt_piece_offset<BLK, D>(t) : 0;
+  const int v_lane = kTwo ? v_piece_offset<BLK, D>(t) : 0;
 
   for (;;) {
     if (kind_cur == kItemEnd) {
@@ -522,7 +536,6 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     const int vmax_nc = N - 1;
     const int tail = L - (N - 1) * BLK;              // tokens in the last block (BLK unless ragged)
     const uint32_t head_bytes = (uint32_t)L * D * 2;
-    const uint32_t image_head_bytes = (uint32_t)N * C::kTileBytes;
     const int32_t* __restrict__ cols = col_idx + seqs.s[sq].col0;
     const int u = cur_y & 0xffff;
     int v = (cur_y >> 16) & 0xffff;
@@ -558,17 +571,16 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 
     // K and V^T of this kv head as buffer resources (tile v starts at byte v * kTileBytes).
     // K is the caller's tensor: rows past L in a ragged last block are outside the resource and
-    // read as zeros.  The V^T image is padded to whole blocks.
+    // read as zeros, as are those of V.
     const __amdgpu_buffer_rsrc_t krs = make_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
-    const __amdgpu_buffer_rsrc_t vrs =
-        make_rsrc(vt + ((size_t)seqs.s[sq].blk0 * (h / g) + (size_t)kvh * N) * BLK * D, image_head_bytes);
+    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(vals + (size_t)kvh * v_head_stride + (size_t)tok0 * D, head_bytes);
     const int vmax = causal ? u_own : vmax_nc;
     // With two buffers per tile, step j reads the buffers j & 1, and both tiles of the next block are copied into the others; `buf` is
     // where they start, and what the lanes' read offsets hold already.
     TileRsrc krs2 = {}, vrs2 = {};
     if constexpr (kTwo) {
       krs2 = make_tile_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
-      vrs2 = make_tile_rsrc(vt + ((size_t)seqs.s[sq].blk0 * (h / g) + (size_t)kvh * N) * BLK * D, image_head_bytes);
+      vrs2 = make_tile_rsrc(vals + (size_t)kvh * v_head_stride + (size_t)tok0 * D, head_bytes);
     }
     auto other_buffer = [&]() __attribute__((always_inline)) {
       const int by = buf == 0 ? C::kTileBytes : -C::kTileBytes;
@@ -576,7 +588,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 #pragma unroll
       for (int st = 0; st < KS; ++st) koff[st] += by;
 #pragma unroll
-      for (int st = 0; st < KT * 2; ++st) voff[st] += by;
+      for (int i = 0; i < kGroups; ++i) voff[i] += by;
     };
     auto copy_k = [&](int blk, int at, int wave_base, int i) __attribute__((always_inline)) {
       // (16 rows from one piece to the next but one: the same swizzle)
@@ -662,7 +674,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       // ---- V(j) -> LDS, requested piece by piece between the MFMAs of S^T, in flight during the softmax ----
       const int wave_base = first_slot(t);
       const bool computes = !kStreamOnly && active;
-      if (!computes && !kTwo) async_load_vt_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, 0, C::kPerThread);
+      if (!computes && !kTwo) async_load_v_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, 0, C::kPerThread);
       const int other = C::kTileBytes - buf;
       if (!computes && kTwo && !kLast) {
 #pragma unroll
@@ -703,7 +715,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
           constexpr int kEvery = kSteps / C::kPerThread;
           static_assert(kSteps % C::kPerThread == 0, "a piece per kEvery MFMAs");
           if (!kTwo && i % kEvery == 0)
-            async_load_vt_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, i / kEvery, i / kEvery + 1);
+            async_load_v_pieces<BLK, D, kPair>(vrs, v * C::kTileBytes, lds_v, t, wave_base, i / kEvery, i / kEvery + 1);
           if (kTwo && !kLast && i % kEvery == 0) copy_k(v_next, other, wave_base, i / kEvery);
           if (kTwo && !kLast && i % kEvery == kEvery / 2) copy_v(v_next, other, wave_base, i / kEvery);
           __builtin_amdgcn_sched_barrier(0);
@@ -836,7 +848,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
         bf16x8 fr[kDepth];
 #pragma unroll
         for (int i = 0; i < kDepth; ++i)
-          fr[i] = *reinterpret_cast<const bf16x8*>(lds_v + (i % DT) * (32 * BLK * 2) + voff[i / DT]);
+          fr[i] = v_frag(i % DT, i / DT);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < kSteps; ++i) {
@@ -844,7 +856,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
           oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % kDepth], pf[st >> 1][st & 1], oacc[dt], 0, 0, 0);
           if (i + kDepth < kSteps) {
             const int j = i + kDepth;
-            fr[i % kDepth] = *reinterpret_cast<const bf16x8*>(lds_v + (j % DT) * (32 * BLK * 2) + voff[j / DT]);
+            fr[i % kDepth] = v_frag(j % DT, j / DT);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -1348,7 +1360,8 @@ __global__ __launch_bounds__(256) void queue_fill_kernel(const int32_t* __restri
 // =====================================================================================
 // Everything in front of the attention kernels in one launch, for calls of up to kPrepMaxRows rows whose kv heads
 // form one phase: workgroup 0 (and 1, where the pair kernel may take the call) builds a queue plan, the next
-// `n_check` workgroups look the lists over, the rest write the V image.  The parts do not depend on each other;
+// `n_check` workgroups look the lists over, the rest write the fp16 image of V, where the 64-queries-per-wave kernel may
+// take the call.  The parts do not depend on each other;
 // the attention kernels read what the list check and the image found through DirtyFlags.
 // Such calls are bound by launches: a kernel with next to no work takes 4.5 us, and as four to nine kernels the same
 // work took 34 of 266 us per layer at 8K tokens and 14 of 47 us at 2K tokens and one head (the attention dispatch has
@@ -1359,8 +1372,8 @@ constexpr int kPrepMaxRows = 8 * kPrepThreads;
 constexpr int kCheckRows = 64;             // rows per list-check workgroup
 struct PrepArgs {
   const int32_t *row_ptr, *col_idx;
-  const uint16_t* v;                       // null: the image is there already
-  uint16_t *vt, *vt16;
+  const uint16_t* v;                       // read for the image of the launch, if it writes one
+  uint16_t* vt16;
   int32_t *range_flags, *check;
   int4 *items, *pair_items;
   int32_t *plan, *pair_plan;
@@ -1370,7 +1383,7 @@ struct PrepArgs {
   float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
   float halve;                             // every row has, where the longest is a CU's average work over this or more (0: no)
   int32_t h, h_kv, n_queues, pair_queues, n_check;
-  uint8_t n_plans, causal, need_sorted, shape;      // shape: block / 64 * 8 + head_dim / 64
+  uint8_t n_plans, causal, need_sorted;
   size_t kv_head_stride;
 };
 
@@ -1627,22 +1640,18 @@ __device__ __forceinline__ void check_rows(const PrepArgs& a, const SeqTable& se
 
 union PrepLds {
   PlanLds plan;
-  uint16_t tile[128][256 + 2];             // 66 KB: of the largest block, two workgroups to a CU all the same
+  ImageTile tile;
 };
 // The part of the V image that belongs to workgroup `wg` of the launch's image workgroups.
-template <int BLK, int D>
 __device__ __forceinline__ void prep_image(PrepLds& lds, int& s_over, const PrepArgs& a, const SeqTable& seqs, int wg) {
   const int s = seq_of(seqs, wg, a.h_kv);
   const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
   const int kvh = rr / N, blk = rr - kvh * N;
-  const size_t at = (size_t)wg * D * BLK;
-  vt_image_tile<BLK, D, kPrepThreads>(
-      *reinterpret_cast<uint16_t(*)[BLK][D + 2]>(&lds), s_over,
-      a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * BLK) * D, min(BLK, seqs.s[s].L - blk * BLK),
-      a.vt + at, a.vt16 != nullptr ? a.vt16 + at : nullptr, a.vt16 != nullptr ? a.range_flags + wg : nullptr, 1 << s);
+  vt_image_tile<kPrepThreads>(lds.tile, s_over,
+                              a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * kImageRows) * kHeadDim,
+                              a.vt16 + (size_t)wg * kHeadDim * kImageRows, a.range_flags + wg, 1 << s);
 }
-// One kernel for all shapes: the plan does not depend on them, and six kernels with its sixteen instances each are 1.1 MB more.
-// The smallest calls feel what lies in front of their work: with the image and the shortest plans first, and without a look
+// The smallest calls feel what lies in front of their work: with the shortest plans first, and without a look
 // at each of sixteen sequences where there is one, 32 rows of one head take 4.3 us instead of 4.9.
 __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTable table) {
   __shared__ PrepLds lds;
@@ -1668,17 +1677,7 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
       return;
     }
     wg -= a.n_check;
-    switch (a.shape) {
-#define PRISM_IMAGE(BLK, D) \
-    case BLK / 64 * 8 + D / 64: prep_image<BLK, D>(lds, s_over, a, seqs, wg); break
-      PRISM_IMAGE(64, 64);
-      PRISM_IMAGE(64, 128);
-      PRISM_IMAGE(64, 256);
-      PRISM_IMAGE(128, 64);
-      PRISM_IMAGE(128, 128);
-      PRISM_IMAGE(128, 256);
-#undef PRISM_IMAGE
-    }
+    prep_image(lds, s_over, a, seqs, wg);
     return;
   }
   const int stride = 1 + wg;
@@ -1712,12 +1711,12 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
 
 using namespace prism;
 
-// ---- workspace layout: [ V image | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
+// ---- workspace layout: [ copy of V (written by prism_v_image only) | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
 //                            bins[2*h*kClasses] | parts[h_kv*kClasses*8] | plan[kPlanInts] |
 //                            fp16 V image | range_flags[h_kv*N]        where the fp16 image is read |
 //                            pair_items[h*N/2] | pair_plan[kPlanInts]  where the pair kernel may run ] ----
 struct AttnWs {
-  size_t image, items, row_rank, row_part, bins, parts, plan, image16, range_flags, pair_items, pair_plan, total;
+  size_t copy, items, row_rank, row_part, bins, parts, plan, image16, range_flags, pair_items, pair_plan, total;
 };
 // The fp16 image exists where the 64-queries-per-wave kernel can take the call: whole blocks only.  Ragged lengths stay
 // with the general kernel, which reads V as it is given: fp16 loses bits of values below 2^-17 and has nothing left of
@@ -1737,7 +1736,7 @@ static AttnWs attn_layout(const prism_params* p, size_t N, bool with16, bool pai
   const size_t image_bytes = (size_t)p->n_kv_heads * N * p->block * p->head_dim * 2;
   AttnWs w;
   size_t off = 0;
-  w.image = off;    off = align_up(off + image_bytes, 256);
+  w.copy = off;     off = align_up(off + image_bytes, 256);
   w.items = off;    off = align_up(off + rows * sizeof(int4), 256);
   w.row_rank = off; off = align_up(off + rows * sizeof(int32_t), 256);
   w.row_part = off; off = align_up(off + rows * sizeof(int32_t), 256);
@@ -1761,6 +1760,8 @@ static AttnWs attn_layout(const prism_params* p, size_t N, bool with16, bool pai
   w.total = off;
   return w;
 }
+// elements between the kv heads of the copy of V that prism_v_image leaves
+static size_t image_head_stride(const prism_params* p) { return (size_t)n_blocks(p) * p->block * p->head_dim; }
 static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), w64_shape(p), pair_shape(p)); }
 
 static int check_image(const prism_params* params, const void* img, size_t bytes) {
@@ -1818,26 +1819,10 @@ extern "C" int prism_sparse_attn_workspace_bytes(const prism_params* params, siz
   return PRISM_OK;
 }
 
-template <int BLK, int D>
-static void launch_vt_image(const prism_params* p, const HeadStrides& hs, const uint16_t* v, uint16_t* vt,
-                            uint16_t* vt16, int32_t* range_flags, hipStream_t st) {
-  const int N = n_blocks(p);
-  hipLaunchKernelGGL((vt_image_kernel<BLK, D>), dim3(N, p->n_kv_heads), dim3(256), 0, st, v, vt, p->seq_len, N,
-                     hs.kv, vt16, range_flags);
-}
-
-static int v_image_core(const prism_params* params, const HeadStrides& hs, const void* v_bf16, uint16_t* vt,
-                        uint16_t* vt16, int32_t* range_flags, hipStream_t st) {
-  const uint16_t* v = (const uint16_t*)v_bf16;
-  if (params->block == 128) {
-    if (params->head_dim == 64) launch_vt_image<128, 64>(params, hs, v, vt, vt16, range_flags, st);
-    else if (params->head_dim == 128) launch_vt_image<128, 128>(params, hs, v, vt, vt16, range_flags, st);
-    else launch_vt_image<128, 256>(params, hs, v, vt, vt16, range_flags, st);
-  } else {
-    if (params->head_dim == 64) launch_vt_image<64, 64>(params, hs, v, vt, vt16, range_flags, st);
-    else if (params->head_dim == 128) launch_vt_image<64, 128>(params, hs, v, vt, vt16, range_flags, st);
-    else launch_vt_image<64, 256>(params, hs, v, vt, vt16, range_flags, st);
-  }
+static int v_image_core(const prism_params* params, const HeadStrides& hs, const uint16_t* v, uint16_t* vt16,
+                        int32_t* range_flags, hipStream_t st) {
+  const int N = n_blocks(params);
+  hipLaunchKernelGGL(vt_image_kernel, dim3(N, params->n_kv_heads), dim3(256), 0, st, v, N, hs.kv, vt16, range_flags);
   return launch_status();
 }
 
@@ -1850,19 +1835,24 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
   if (rc != PRISM_OK) return rc;
   const AttnWs W = attn_ws(params);
   char* ws = static_cast<char*>(v_image);
-  const bool with16 = w64_shape(params);
-  return v_image_core(params, contiguous_heads(params), v_bf16, reinterpret_cast<uint16_t*>(ws + W.image),
-                      with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr,
-                      with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr, static_cast<hipStream_t>(stream));
+  const HeadStrides hs = contiguous_heads(params);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const size_t chunks = hs.kv / 8;                           // 16 bytes each
+  hipLaunchKernelGGL(v_copy_kernel, dim3((unsigned)((chunks + 1023) / 1024), params->n_kv_heads), dim3(256), 0, st,
+                     (const uint16_t*)v_bf16, chunks, hs.kv, image_head_stride(params), reinterpret_cast<uint16_t*>(ws + W.copy));
+  rc = launch_status();
+  if (rc != PRISM_OK || !w64_shape(params)) return rc;
+  return v_image_core(params, hs, (const uint16_t*)v_bf16, reinterpret_cast<uint16_t*>(ws + W.image16),
+                      reinterpret_cast<int32_t*>(ws + W.range_flags), st);
 }
 
 template <int BLK, bool kStreamOnly, int D, bool kPair = false, bool kKeepMask = false>
-static void launch_attn(int grid, hipStream_t st, const PullCounters& pulls, const uint16_t* q, const uint16_t* k, const uint16_t* vt,
+static void launch_attn(int grid, hipStream_t st, const PullCounters& pulls, const uint16_t* q, const uint16_t* k, const uint16_t* v, size_t v_head_stride,
                         const int32_t* row_ptr, const int32_t* col_idx, const int4* items, int32_t* plan,
                         const DirtyFlags& flags, uint16_t* out, float* lse, int h, int h_kv, const SeqTable& seqs,
                         const HeadStrides& hs, int causal, int only_dirty) {
   hipLaunchKernelGGL((sparse_attn_kernel<BLK, kStreamOnly, D, kPair, kKeepMask>), dim3(grid),
-                     dim3(AttnCfg<BLK, D, kPair>::kThreads), 0, st, q, k, vt, row_ptr, col_idx, items, plan,
+                     dim3(AttnCfg<BLK, D, kPair>::kThreads), 0, st, q, k, v, v_head_stride, row_ptr, col_idx, items, plan,
                      pulls, flags, out, lse, h, h_kv, seqs, hs, causal, only_dirty);
 }
 
@@ -1879,8 +1869,8 @@ static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t*
 }
 
 // The whole attention of the sequences in `seqs` (arguments already validated; several sequences only where
-// R <= kPrepMaxRows and one phase, and where w64_shape says the same of all).  `v_bf16`: the V image is written first;
-// null: it is there already.
+// R <= kPrepMaxRows and one phase, and where w64_shape says the same of all).  With `v_bf16` null what prism_v_image left in
+// `ws` takes its place.
 static int attn_core(const prism_params* params, const HeadStrides& hs, const SeqTable& seqs, const AttnWs& W,
                      const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws,
                      const int32_t* row_ptr, const int32_t* col_idx, void* out_bf16, float* lse, hipStream_t st) {
@@ -1954,7 +1944,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
-  uint16_t* vp = reinterpret_cast<uint16_t*>(ws + W.image);
+  // the general kernel reads V itself, or the copy
+  const uint16_t* vp = v_bf16 != nullptr ? (const uint16_t*)v_bf16 : reinterpret_cast<const uint16_t*>(ws + W.copy);
+  const size_t v_head_stride = v_bf16 != nullptr ? hs.kv : image_head_stride(params);
   const bool with16 = w64_shape(params);
   uint16_t* vp16 = with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
   int32_t* range_flags = with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
@@ -1985,11 +1977,12 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   if (pair && pair_grid <= 0) return PRISM_ERR_HIP;
   const int pair_queues = pair_grid < kXcds ? 1 : kXcds;
   const int n_range_flags = w64 ? h_kv * N : 0;
+  const bool writes_image = w64 && v_bf16 != nullptr;
 
-  // One launch prepares the call up to kPrepMaxRows rows in one phase: 13.4 us instead of 34.7 us at 2048 rows (8K
-  // tokens, 32 heads), 24.4 instead of 41.0 at 5024 (20011 tokens: one image, no list check), 39.2 instead of 63.1 at 8192
-  // (32K tokens; the images alone take 13, 22 and 39 us), 5.0 instead of 13.9 at 32 rows.  Beyond, the plan of a single
-  // workgroup would no longer hide behind the image, and the parts run as kernels of their own.
+  // One launch prepares the call up to kPrepMaxRows rows in one phase: 11.6 us instead of 34.7 us at 2048 rows (8K tokens, 32
+  // heads, with the fp16 image), 9.0 without it, 20.7 at 5024 (20011 tokens), 37.8 instead of 63.1 at 8192 with the image (32K
+  // tokens), 31.8 without it, 4.7 instead of 13.9 at 32 rows.  Beyond, a single workgroup would plan for longer than the separate
+  // kernels take.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   // Two sets of pull counters in row_part, which the preparation is done with: of the pair kernel and the one behind it, or
   // of the 64-queries-per-wave kernel and the one behind it.  A short table holds them closer together.
@@ -2005,7 +1998,6 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.row_ptr = row_ptr;
     pa.col_idx = col_idx;
     pa.v = (const uint16_t*)v_bf16;
-    pa.vt = vp;
     pa.vt16 = vp16;
     pa.range_flags = range_flags;
     pa.check = row_rank;
@@ -2015,7 +2007,6 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.pair_plan = pair_plan;
     pa.h = h;
     pa.h_kv = h_kv;
-    pa.shape = (uint8_t)(params->block / 64 * 8 + d / 64);
     pa.causal = (uint8_t)pc.causal;
     pa.n_queues = pc.n_queues;
     pa.pair_queues = pair_queues;
@@ -2030,12 +2021,12 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.halve = halve;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
-    const int prep_grid = pa.n_plans + pa.n_check + (v_bf16 != nullptr ? h_kv * N : 0);
+    const int prep_grid = pa.n_plans + pa.n_check + (writes_image ? h_kv * N : 0);
     hipLaunchKernelGGL(prep_kernel, dim3(prep_grid), dim3(kPrepThreads), 0, st, pa, seqs);
     flags = DirtyFlags{row_rank, range_flags, pa.n_check, n_range_flags};
   } else {
-    if (v_bf16 != nullptr) {
-      const int rc = v_image_core(params, hs, v_bf16, vp, vp16, range_flags, st);
+    if (writes_image) {
+      const int rc = v_image_core(params, hs, vp, vp16, range_flags, st);
       if (rc != PRISM_OK) return rc;
     }
     // (over a thousand rows here: more than kPrepMaxRows, or kv heads that do not fit the memory-side cache together)
@@ -2057,7 +2048,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   }
   if (pair) {
 #define PRISM_PAIR(D)                                                                                        \
-  launch_attn<64, false, D, true>(pair_grid, st, second_pulls, qp, kp, vp, row_ptr, col_idx, pair_items, pair_plan, flags, \
+  launch_attn<64, false, D, true>(pair_grid, st, second_pulls, qp, kp, vp, v_head_stride, row_ptr, col_idx, pair_items, pair_plan, flags, \
                                   op, lse, h, h_kv, seqs, hs, causal, 0)
     if (d == 64) PRISM_PAIR(64);
     else if (d == 128) PRISM_PAIR(128);
@@ -2086,7 +2077,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   // 7968 rows 433 -> 436), and the other shapes are faster without: 64 x 64 at 16448 tokens 413 -> 401, 64 x 256 at 16320
   // 1406 -> 1375, 128 x 64 at 32768 804 -> 795, 128 x 128 at 40001 1669 -> 1662.
 #define PRISM_ATTN(BLK, SO, D, KEEP)                                                                          \
-  launch_attn<BLK, SO, D, false, KEEP>(grid, st, w64 ? second_pulls : pulls, qp, kp, vp, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
+  launch_attn<BLK, SO, D, false, KEEP>(grid, st, w64 ? second_pulls : pulls, qp, kp, vp, v_head_stride, row_ptr, col_idx, items, plan, flags, op, lse, h, h_kv, seqs, \
                           hs, causal, only_dirty)
   if (stream_only) {
     // measurement aid of the d = 128 kernels only
