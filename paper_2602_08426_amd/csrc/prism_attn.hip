@@ -1731,12 +1731,12 @@ static bool w64_shape(const prism_params* p) {
 static bool pair_shape(const prism_params* p) { return p->block == 64 && n_blocks(p) % 2 == 0; }
 
 // The layout for `N` blocks (those of one sequence, or of a group of a packed batch).
-static AttnWs attn_layout(const prism_params* p, size_t N, bool with16, bool pairs) {
+static AttnWs attn_layout(const prism_params* p, size_t N, bool with_copy, bool with16, bool pairs) {
   const size_t rows = (size_t)p->n_q_heads * N;
   const size_t image_bytes = (size_t)p->n_kv_heads * N * p->block * p->head_dim * 2;
   AttnWs w;
   size_t off = 0;
-  w.copy = off;     off = align_up(off + image_bytes, 256);
+  w.copy = off;     off = align_up(off + (with_copy ? image_bytes : 0), 256);
   w.items = off;    off = align_up(off + rows * sizeof(int4), 256);
   w.row_rank = off; off = align_up(off + rows * sizeof(int32_t), 256);
   w.row_part = off; off = align_up(off + rows * sizeof(int32_t), 256);
@@ -1762,7 +1762,7 @@ static AttnWs attn_layout(const prism_params* p, size_t N, bool with16, bool pai
 }
 // elements between the kv heads of the copy of V that prism_v_image leaves
 static size_t image_head_stride(const prism_params* p) { return (size_t)n_blocks(p) * p->block * p->head_dim; }
-static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), w64_shape(p), pair_shape(p)); }
+static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), true, w64_shape(p), pair_shape(p)); }
 
 static int check_image(const prism_params* params, const void* img, size_t bytes) {
   if (img == nullptr || (reinterpret_cast<uintptr_t>(img) & 255u) != 0 ||
@@ -2171,7 +2171,11 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
     ps.seq_len = q.L;
     return w64_shape(&ps);
   };
-  auto layout = [&](const SeqTable& t) { return attn_layout(params, t.nsum, kind(t.s[0]), pairs(t)); };
+  // These calls read V itself and write no copy of it: a group that needs the room has it.
+  auto layout = [&](const SeqTable& t) {
+    const AttnWs w = attn_layout(params, t.nsum, true, kind(t.s[0]), pairs(t));
+    return w.total <= workspace_bytes ? w : attn_layout(params, t.nsum, false, kind(t.s[0]), pairs(t));
+  };
   // Sequences share their launches while the one-launch preparation can take them all, their heads form one phase
   // and the workspace holds them.
   auto fits = [&](const SeqTable& t) {
