@@ -1394,7 +1394,7 @@ struct PlanLds {
   int rows[16][kClasses], work[16][kClasses];       // per wave: totals, then what lies in front of the wave
   float scale[kClasses];                            // parts per unit of work
   int start[kClasses][9];                           // first rank of the class that belongs to part x
-  int before[kClasses][8], qlen[8];
+  int before[kClasses][8], qlen[8], qstart[8];
   int total;                                        // entries + 3 per row (a row costs about three blocks beside its own)
   int above[8];                                     // rows of queue x with that much work
   unsigned alone[8];
@@ -1436,13 +1436,14 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     r.u = (n_of(r.s) >> (stride - 1)) - 1 - (kOne ? rem : rem - (seqs.s[r.s].blk0 >> (stride - 1)));
     return r;
   };
+  auto index = [&](int c) { return (wave * CH + c) * 64 + lane; };
   // The bounds of all rows are requested at once, and at the end the first entries of all lists: two memory round trips
   // for the workgroup.  What remains is a few hundred instructions per 64 rows of a wave on one CU, 9.5 us at 2048 rows
   // (an integer division per row and part and a prefix sum over every class, there or not, took 11.1 us).
   int beg[CH], len[CH];                               // len = -1 past the last row
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    const int i = (wave * CH + c) * 64 + lane;
+    const int i = index(c);
     beg[c] = 0;
     len[c] = -1;
     if (i < R) {
@@ -1454,7 +1455,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   }
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    const int i = (wave * CH + c) * 64 + lane;
+    const int i = index(c);
     if (i < R) {
       const int cap = cap_of(kOne ? 0 : row(i).s);
       const int b = beg[c] < 0 ? 0 : (beg[c] > cap ? cap : beg[c]), e = len[c];
@@ -1495,18 +1496,17 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   if (t < 8) m.alone[t] = m.above[t] = 0;
   if (t == 8) m.total = m.longest = 0;
   __syncthreads();
-  if (t < kClasses) {
-    int r = 0, w = 0;
-    for (int i = 0; i < 16; ++i) {
-      const int nr = m.rows[i][t], nw = m.work[i][t];
-      m.rows[i][t] = r;
-      m.work[i][t] = w;
-      r += nr;
-      w += nw;
+  if (t < 16 * kClasses) {                            // 16 lanes a class, one for each wave
+    const int k = t >> 4, w = t & 15;
+    const int nr = m.rows[w][k], nw = m.work[w][k];
+    const int r = row16_scan_inclusive(nr), work = row16_scan_inclusive(nw);
+    m.rows[w][k] = r - nr;
+    m.work[w][k] = work - nw;
+    if (w == 15) {
+      atomicAdd(&m.total, work + 2 * r);
+      m.scale[k] = work > 0 ? (float)n_queues / (float)work : 0.f;
+      for (int x = 0; x < 9; ++x) m.start[k][x] = r;
     }
-    atomicAdd(&m.total, w + 2 * r);
-    m.scale[t] = w > 0 ? (float)n_queues / (float)w : 0.f;
-    for (int x = 0; x < 9; ++x) m.start[t][x] = r;
   }
   if (a.halve > 0.f) {
     int longest = 0;
@@ -1531,15 +1531,18 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     }
   }
   __syncthreads();
-  if (t < 8) {
-    int run = 0;
-    for (int k = 0; k < kClasses; ++k) {
-      m.before[k][t] = run;
-      run += m.start[k][t + 1] - m.start[k][t];
-    }
-    m.qlen[t] = run;
+  if (t < 16 * 8) {                                   // 16 lanes a queue, one for each class
+    const int x = t >> 4, k = t & 15;
+    const int n = k < kClasses ? m.start[k][x + 1] - m.start[k][x] : 0;
+    const int upto = row16_scan_inclusive(n);
+    if (k < kClasses) m.before[k][x] = upto - n;
+    if (k == 15) m.qlen[x] = upto;
   }
   __syncthreads();
+  // lane x < 8: where queue x starts
+  const int qlen = lane < 8 ? m.qlen[lane] : 0;
+  const int qstart = row16_scan_inclusive(qlen) - qlen;
+  if (lane < 8) m.qstart[lane] = qstart;              // every wave the same
   const bool marks = stride == 1 && (a.alone > 0.f || a.halve > 0.f);     // some row may have a CU to itself
   auto count = [&](unsigned alone) __attribute__((always_inline)) {
     plan[kPlanAlone + t] = (int)alone;
@@ -1549,10 +1552,8 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
     if (more_counters != nullptr) more_counters[t * a.counter_stride] = kOne ? dealt : all;
   };
   if (t < 8) {
-    int start = 0;
-    for (int x = 0; x < t; ++x) start += m.qlen[x];
-    plan[kPlanStart + t] = start;
-    plan[kPlanLen + t] = m.qlen[t];
+    plan[kPlanStart + t] = qstart;
+    plan[kPlanLen + t] = qlen;
     plan[kPlanCounter + t] = 0;
     plan[kPlanFlags + t] = 0;
     if (!marks) count(0);
@@ -1564,16 +1565,15 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
   for (int c = 0; c < CH; ++c) {
     if (len[c] < 0) continue;
     const int k = length_class(len[c]), x = part(cum[c], k);
-    int entry = m.before[k][x] + rank[c] - m.start[k][x];
+    const int entry = m.before[k][x] + rank[c] - m.start[k][x];
     if ((float)len[c] > alone_from) {
       atomicAdd(&m.above[x], 1);
       if (entry < half) atomicOr(&m.alone[x], 1u << entry);
     }
-    for (int y = 0; y < x; ++y) entry += m.qlen[y];
-    rank[c] = entry;
+    rank[c] = m.qstart[x] + entry;
     cum[c] = 0;
     if (stride == 1 && len[c] > 0)
-      cum[c] = a.col_idx[col0_of(kOne ? 0 : row((wave * CH + c) * 64 + lane).s) + beg[c]];
+      cum[c] = a.col_idx[col0_of(kOne ? 0 : row(index(c)).s) + beg[c]];
   }
   if (marks) {
     // (in front of the entries, whose stores the workgroup would wait for at a barrier behind them: 42.8 -> 39.8 us in a
@@ -1587,7 +1587,7 @@ __device__ __forceinline__ void plan_rows(PlanLds& m, const PrepArgs& a, const S
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
     if (len[c] < 0) continue;
-    const Row r = row((wave * CH + c) * 64 + lane);
+    const Row r = row(index(c));
     const int end = beg[c] + len[c];
     int it = beg[c], v = cum[c];
     if (stride == 1) {
@@ -1979,9 +1979,9 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const int n_range_flags = w64 ? h_kv * N : 0;
   const bool writes_image = w64 && v_bf16 != nullptr;
 
-  // One launch prepares the call up to kPrepMaxRows rows in one phase: 11.6 us instead of 34.7 us at 2048 rows (8K tokens, 32
-  // heads, with the fp16 image), 9.0 without it, 20.7 at 5024 (20011 tokens), 37.8 instead of 63.1 at 8192 with the image (32K
-  // tokens), 31.8 without it, 4.7 instead of 13.9 at 32 rows.  Beyond, a single workgroup would plan for longer than the separate
+  // One launch prepares the call up to kPrepMaxRows rows in one phase: 10.8 us instead of 34.7 us at 2048 rows (8K tokens, 32
+  // heads, with the fp16 image), 8.0 without it, 19.6 at 5024 (20011 tokens), 36.1 instead of 63.1 at 8192 with the image (32K
+  // tokens), 30.6 without it, 3.8 instead of 13.9 at 32 rows.  Beyond, a single workgroup would plan for longer than the separate
   // kernels take.
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   // Two sets of pull counters in row_part, which the preparation is done with: of the pair kernel and the one behind it, or

@@ -225,6 +225,14 @@ __device__ __forceinline__ int wave_scan_inclusive(int x) {
   s += dpp_i32<kDppRowBcast31, 0xC>(0, s);
   return s;
 }
+// the same over each 16 lanes
+__device__ __forceinline__ int row16_scan_inclusive(int x) {
+  x += dpp_i32<0x111>(0, x);
+  x += dpp_i32<0x112>(0, x);
+  x += dpp_i32<0x114>(0, x);
+  x += dpp_i32<0x118>(0, x);
+  return x;
+}
 __device__ __forceinline__ int wave_sum(int x) {
   x += dpp_i32<kDppQuadSwap1>(0, x);
   x += dpp_i32<kDppQuadSwap2>(0, x);
