@@ -172,3 +172,38 @@ def test_values_of_any_magnitude_in_a_packed_batch(h, hkv, lens):
         at = slice(cu[s], cu[s + 1])
         for i in (0, h - 1):
             _check_small_values(q[i, at], k[i // (h // hkv), at], v[i // (h // hkv), at], out[i, at])
+
+
+@pytest.mark.parametrize("B,d", [(64, 64), (64, 128), (64, 256), (128, 64), (128, 128), (128, 256)])
+@pytest.mark.parametrize("lens", [[200, 65, 127, 1], [129, 64, 190, 250]])
+def test_values_behind_a_ragged_end_are_not_read(B, d, lens):
+    """V of every other sequence of a packed batch, and of every other head, is NaN or infinite: what lies behind the last token of
+    a sequence leaves no trace in it."""
+    h = 3
+    cu = [0] + np.cumsum(lens).tolist()
+    g = torch.Generator(device="cuda").manual_seed(B + d)
+    q, k, v = (torch.randn((h, cu[-1], d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    bad = torch.tensor([float("nan"), float("inf"), -float("inf")], device="cuda").bfloat16()
+    for i in range(h):
+        for s in range(len(lens)):
+            if (i + s) % 2:
+                v[i, cu[s]:cu[s + 1]] = bad[(i + s) % 3]
+    bands = {64: (32, 48), 128: (64, 96), 256: (128, 192)}[d]
+    params = pb.make_params(h, h, cu[-1], B, *bands, 0.9, 0, d)
+    _, ro, co = pb.prism_varlen_layout(params, cu)
+    rp = torch.zeros(ro[-1], dtype=torch.int32, device="cuda")
+    ci = torch.zeros(co[-1], dtype=torch.int32, device="cuda")
+    for s, L in enumerate(lens):
+        pb.prism_causal_csr(pb.make_params(h, h, L, B, *bands, 0.9, 0, d), rp[ro[s]:], ci[co[s]:], co[s + 1] - co[s])
+    out = torch.empty_like(q)
+    ws = pb.alloc_workspace(pb.prism_sparse_attn_varlen_workspace_bytes(params, cu))
+    pb.prism_sparse_attn_varlen(params, cu, q, k, v, rp, ci, out, None, ws)
+    torch.cuda.synchronize()
+    for s in range(len(lens)):
+        at = slice(cu[s], cu[s + 1])
+        for i in range(h):
+            if (i + s) % 2 == 0:
+                x = (q[i, at].double() @ k[i, at].double().T) / np.sqrt(d)
+                n = cu[s + 1] - cu[s]
+                p = torch.softmax(x.masked_fill(torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1), -np.inf), -1)
+                assert (out[i, at].double() - p @ v[i, at].double()).abs().max() <= OUT_TOL, (i, s)

@@ -98,3 +98,13 @@ def test_estimate_of_a_batch_is_the_same_in_any_workspace(room):
         assert torch.equal(a, b)
     with pytest.raises(pb.PrismError):
         run(least - 256)
+
+
+@pytest.mark.parametrize("lens,h,hkv,B,d", [
+    ([1024, 2048, 1024, 4096, 1024, 512], 8, 2, 128, 128),     # 64 blocks together fit the room of the 32 of the longest
+    ([4096, 4096, 128, 300, 77], 8, 2, 128, 128),              # 65 do not
+    ([1024, 2048, 1000, 4096, 1024, 64], 4, 1, 64, 64),
+    ([1000, 2048, 3000, 640], 4, 4, 64, 256),
+])
+def test_groups_in_the_workspace_that_is_asked_for(lens, h, hkv, B, d):
+    test_groups_equal_single_calls(lens, h, hkv, B, d, False, 0, False)
