@@ -338,7 +338,7 @@ __device__ __forceinline__ float band_inv_scale(const float* __restrict__ energy
 // =====================================================================================
 // Dual-band scoring, softmax, top-p, union (Sec. 3.4 steps 4-5, App. C).
 //
-// One workgroup (4 waves) per (strip of 16 q-blocks, q-head).  Per band:
+// One workgroup (4, 8 or 16 waves) per (strip of 16 q-blocks, q-head).  Per band:
 //   phase A: logits[16][v <= u_max] = Qbar_z Kbar_z^T * inv_scale on
 //            v_mfma_f32_16x16x32_bf16, with x = hi + mid + lo (three bf16 terms) and the
 //            six products of weight >= 2^-16 (fp32 accumulate), written to LDS;
@@ -354,11 +354,10 @@ __device__ __forceinline__ float band_inv_scale(const float* __restrict__ energy
 // =====================================================================================
 constexpr int kStripRows = 16;
 
-// Top-p selection of the four consecutive rows of one band that a wave owns.  Row k has
+// Top-p selection of the one, two or four consecutive rows of one band that a wave owns.  Row k has
 // n0 + k*nstep logits (nstep = 1: block-causal rows, 0: every row sees all N blocks); each row lives in registers: column
-// 64*i + lane in e[k][i].  The four rows are advanced together so that their wave reductions
+// 64*i + lane in e[k][i].  The rows are advanced together so that their wave reductions
 // (dependent DPP chains) overlap.  Selected bits are OR-ed into the rows' LDS bit words.
-// rows per wave: 4 (workgroup of 4 waves) or 2 (8 waves: twice the waves in flight for the same LDS strip)
 
 // lane I of (lo, hi) := the wave-uniform 64-bit word w.  Two lane writes with the lane number as an
 // immediate: no per-lane predicate has to be formed or kept.  The s_nop gives the compare that wrote w
@@ -644,8 +643,12 @@ constexpr int kSelCausal = 1;          // key blocks v > u are excluded (block-c
 constexpr int kSelForceDiagonal = 2;   // block u of every row is switched on after the union
 constexpr int kSelForceSink = 4;       // block 0 of every row is switched on after the union
 
+// Bound by the issue of the search, which one wave alone leaves half empty (its reductions are chains of dependent lane operations): a
+// wave holds at most 32 row registers, so that 128 in all suffice and four waves share a SIMD.  us of the kernel, with 64 row
+// registers, two waves a SIMD and the next tile's fragments requested ahead -> now: 28/4 heads, 65536 tokens 87 -> 67-69; 32/8, B = 64,
+// 32768 94 -> 63; 32/8, 131072 241 -> 190.
 template <int MAXCH, bool DUMP, int kRowsPerWave, int kSeqs>
-__global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
+__global__ __launch_bounds__(kStripRows / kRowsPerWave * 64, MAXCH * kRowsPerWave <= 32 ? 4 : 1) void select_kernel(
     BandVectors bv, const float* __restrict__ inv_scale, int h, int h_kv,
     SeqTableOf<kSeqs> seqs, int bs, int dpad_high, int dpad_low, float top_p, int select_flags,
     uint64_t* __restrict__ mask_bits, int32_t* __restrict__ row_ptr, int32_t* __restrict__ strip_counts,
@@ -702,10 +705,9 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
       const size_t aoff = q0 + ((size_t)hq * N + arow) * bs + k0 * 32 + (lane >> 4) * 8;
       const size_t tile0 = kv_band_offset(kv0, N, bs, kvh - h, 0, 0) + k0 * 512 + lane * 8;   // this lane's piece of tile 0
       const size_t tile_stride = (size_t)16 * bs;
-      // The pass with the number of k-steps and "first pass" as compile-time facts: a fixed number of
-      // loads per tile lets the compiler wait for exactly the fragments of the tile whose MFMAs come next
-      // while those of the tile after it stay in flight.  The B fragments alternate between two register
-      // sets; past the wave's last tile the last tile is fetched once more and not used.
+      // The pass with the number of k-steps and "first pass" as compile-time facts: a fixed number of loads per tile lets the
+      // compiler wait for exactly the fragments that come next.  One set of them: the other three waves of the SIMD have work
+      // while a wave waits for its own.
       auto score_pass = [&](auto kn_tag, auto first_tag) __attribute__((always_inline)) {
         constexpr int KN = decltype(kn_tag)::value;
         constexpr bool FIRST = decltype(first_tag)::value;
@@ -720,7 +722,7 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
           a.l[ks] = *reinterpret_cast<const bf16x8*>(pooled_lo + aoff + ks * 32);
         }
         auto load_b = [&](Frag& f, int ct) __attribute__((always_inline)) {
-          const size_t boff = tile0 + (size_t)min(ct, ntiles - 1) * tile_stride;
+          const size_t boff = tile0 + (size_t)ct * tile_stride;
 #pragma unroll
           for (int ks = 0; ks < KN; ++ks) {
             f.h[ks] = *reinterpret_cast<const bf16x8*>(pooled_hi + boff + ks * 512);
@@ -756,22 +758,10 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
           }
         };
         const bool refetch = !kAblNoRefetch || top_p > 5.f;
-        Frag b0, b1;
-        load_b(b0, wave);
-        if (!refetch) load_b(b1, wave);
-        // (the scheduling barriers keep the fetches of the next tile in front of the MFMAs of this one;
-        // left to itself the scheduler sinks them to their first use to save registers)
-        for (int ct = wave; ct < ntiles; ct += 2 * kWaves) {
-          if (refetch) load_b(b1, ct + kWaves);
-          __builtin_amdgcn_sched_barrier(0);
-          tile(b0, ct);
-          __builtin_amdgcn_sched_barrier(0);
-          if (ct + kWaves < ntiles) {
-            if (refetch) load_b(b0, ct + 2 * kWaves);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(b1, ct + kWaves);
-            __builtin_amdgcn_sched_barrier(0);
-          }
+        Frag b;
+        for (int ct = wave; ct < ntiles; ct += kWaves) {
+          if (refetch || ct == wave) load_b(b, ct);
+          tile(b, ct);
         }
       };
       if (wave < ntiles && (!kAblNoScores || top_p > 5.f)) {
@@ -789,7 +779,7 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
     }
     __syncthreads();
 
-    // ---------------- phase B: each wave selects its four rows ----------------
+    // ---------------- phase B: each wave selects its rows ----------------
     if (!DUMP) {
       const int r0 = wave * kRowsPerWave;
       const int nrows = min(kRowsPerWave, N - (u0 + r0));          // uniform per wave, may be <= 0
@@ -805,9 +795,9 @@ __global__ __launch_bounds__(kStripRows / kRowsPerWave * 64) void select_kernel(
         constexpr int bld = kMaxBlocks / 64;
         if (nmax <= 128) select_rows<2, kRowsPerWave>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
         else if (nmax <= 256) select_rows<4, kRowsPerWave>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
-        else if (nmax <= 512) select_rows<8, kRowsPerWave>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
+        else if (MAXCH <= 8 || nmax <= 512) select_rows<8, kRowsPerWave>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
         else if (MAXCH <= 16 || nmax <= 1024) select_rows<16, kRowsPerWave>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
-        else select_rows<MAXCH, kRowsPerWave>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
+        else if constexpr (MAXCH > 8) select_rows<MAXCH, kRowsPerWave>(lg, ld, n0, nstep, nrows, top_p, lane, bits, bld);
       }
       __syncthreads();                             // LDS logits are reused by the next band
     }
@@ -1368,11 +1358,12 @@ template <int MAXCH, bool DUMP, int kRowsPerWave = 4>
 static int launch_select(const prism_params* p, const SeqTable& seqs, const BandMap& map, char* ws,
                          const EstimateWs& L, uint64_t* mask_bits, int32_t* row_ptr, int32_t* strip_counts, float* lh, float* ll,
                          hipStream_t st) {
-  if (DUMP || seqs.n == 1)
-    return launch_select_on<MAXCH, DUMP, kRowsPerWave, 1>(p, only_sequence(seqs), map, ws, L, mask_bits, row_ptr, strip_counts, lh,
-                                                          ll, st);
-  return launch_select_on<MAXCH, false, kRowsPerWave, kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, row_ptr, strip_counts, lh,
-                                                                     ll, st);
+  if constexpr (!DUMP)
+    if (seqs.n > 1)
+      return launch_select_on<MAXCH, false, kRowsPerWave, kMaxGroupSeqs>(p, seqs, map, ws, L, mask_bits, row_ptr, strip_counts, lh,
+                                                                         ll, st);
+  return launch_select_on<MAXCH, DUMP, kRowsPerWave, 1>(p, only_sequence(seqs), map, ws, L, mask_bits, row_ptr, strip_counts, lh,
+                                                        ll, st);
 }
 
 static int run_compact(const prism_params* p, const SeqTable& seqs, const uint64_t* mask_bits, const int32_t* strip_counts,
@@ -1458,6 +1449,7 @@ static int run_small(const prism_params* p, const SeqTable& seqs, const BandMap&
 // select_small_kernel) may be a quarter full.  All head dims still gain there (5 - 13 % at 320 strips); with d = 256, whose
 // strips take longest, it loses 2 % from 352 on, d <= 128 would gain up to some 450.
 constexpr int64_t kSmallStrips = 320;
+constexpr int64_t kCUs = 256;                          // of the MI355X
 
 // The whole estimate of the sequences in `seqs` (arguments already validated): pooling (+ RoPE when `rope`
 // is given), calibration, selection, compaction.
@@ -1474,15 +1466,26 @@ static int estimate_core(const prism_params* params, const HeadStrides& hs, cons
                      (int64_t)seqs.tiles * params->n_q_heads <= kSmallStrips;
   int rc = run_pool_and_scale(params, hs, seqs, map, q, k, ws, L, nullptr, nullptr, nullptr, st, rope, q_out, k_out, !small);
   if (rc != PRISM_OK) return rc;
-  // up to 1024 blocks: 4 waves of 4 rows, two workgroups per CU; beyond (a 131 KB logit strip, one
-  // workgroup per CU, rows of 32 registers): 8 waves of 2 rows (measured 1.89 -> 1.25 ms at N = 2048,
-  // while at N = 1024 the 4-wave form is 2 % faster)
-  if (small)
-    rc = run_small(params, seqs, map, ws, L, mask_bits, strip_counts, st);
-  else if (seqs.nmax <= 1024)
-    rc = launch_select<16, false, 4>(params, seqs, map, ws, L, mask_bits, row_ptr, strip_counts, nullptr, nullptr, st);
-  else
-    rc = launch_select<32, false, 2>(params, seqs, map, ws, L, mask_bits, row_ptr, strip_counts, nullptr, nullptr, st);
+  // Rows of up to 8 registers a lane (512 blocks): four waves of four rows a strip, or eight of two where the strips are so few that
+  // they would leave SIMDs with less than four waves.  us of the estimate with the rotation, four / eight waves: 28/4 heads, 65536
+  // tokens (896 strips) 276 / 282, 32/8, B = 64, 32768 (1024) 205 / 211, 28/4, 52000 (728) 218.4 / 217.9, 47000 (644) 200 / 198, 40960
+  // (560) 176 / 171, 16/4, 65536 (512) 182 / 168, 32/8, 22000 (352) 116 / 107.
+  // Of up to 16 (1024 blocks): eight waves of two rows, or sixteen of one where every strip has a CU to itself: 32/8, 131072
+  // (2048 strips) 721 / 768, 8/2, 100000 (392) 133 / 135, 7/1, 70000 (245) 87 / 81, 4/1, 100000 (196) 93 / 84.
+  // Beyond (a 131 KB logit strip, one workgroup per CU): sixteen waves of one row (eight of two at half the waves a SIMD 757, now 702;
+  // 28/4, B = 64, 100000).
+  const int64_t strips = (int64_t)seqs.tiles * params->n_q_heads;
+  auto select = [&](auto maxch, auto rows) {
+    return launch_select<decltype(maxch)::value, false, decltype(rows)::value>(params, seqs, map, ws, L, mask_bits, row_ptr, strip_counts,
+                                                                               nullptr, nullptr, st);
+  };
+  using std::integral_constant;
+  if (small) rc = run_small(params, seqs, map, ws, L, mask_bits, strip_counts, st);
+  else if (seqs.nmax <= 512 && strips > 3 * kCUs) rc = select(integral_constant<int, 8>{}, integral_constant<int, 4>{});
+  else if (seqs.nmax <= 512) rc = select(integral_constant<int, 8>{}, integral_constant<int, 2>{});
+  else if (seqs.nmax <= 1024 && strips > kCUs) rc = select(integral_constant<int, 16>{}, integral_constant<int, 2>{});
+  else if (seqs.nmax <= 1024) rc = select(integral_constant<int, 16>{}, integral_constant<int, 1>{});
+  else rc = select(integral_constant<int, 32>{}, integral_constant<int, 1>{});
   if (rc != PRISM_OK) return rc;
   if (strip_counts != nullptr) return run_compact(params, seqs, mask_bits, strip_counts, row_ptr, col_idx, info, st);
   const SeqInfo& sq = seqs.s[0];                       // (several sequences come only with a workspace that holds the counts)

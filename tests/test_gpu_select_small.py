@@ -65,3 +65,39 @@ def test_same_bits_as_the_general_form(h, hkv, N, tail, B, d, bands, p, flags, k
     with pytest.raises(pb.PrismError):
         ws = pb.alloc_workspace(need)[:need - (h * N * 4 + 255) // 256 * 256 - 1]
         pb.prism_estimate(params, q, k, *outs[0][:3], 1, outs[0][3], ws)
+
+
+@pytest.mark.parametrize("h,N,tail,flags", [
+    (50, 256, 64, 0), (47, 257, 1, 0),             # 800 and 799 strips: four waves of four rows
+    (48, 256, 64, 0),                              # 768: eight of two
+    (24, 512, 9, pb.PRISM_FLAG_BIDIRECTIONAL),
+    (26, 497, 64, 0),                              # 832 strips of rows of up to eight registers
+    (8, 513, 64, 0), (7, 513, 5, 0),               # 264: eight of two; 231: sixteen of one
+    (5, 1024, 64, 0), (2, 1024, 3, pb.PRISM_FLAG_BIDIRECTIONAL),
+    (3, 1025, 64, 0), (2, 1100, 7, 0),             # beyond 1024 blocks
+])
+def test_forms_of_the_general_selection(h, N, tail, flags):
+    """Every head of a call has the bits of a call on that head and one other, which takes the short form or sixteen waves of one
+    row, and the lists are those of the bits."""
+    B, L = 64, (N - 1) * 64 + tail
+    g = torch.Generator(device="cuda").manual_seed(N + h)
+    q, k = (torch.randn((n, L, 128), generator=g, device="cuda") for n in (h, 1))
+    for x in (q, k):
+        x += torch.randn((x.shape[0], N, 128), generator=g, device="cuda").repeat_interleave(B, 1)[:, :L] * 0.6
+    q, k = q.bfloat16(), k.bfloat16()
+
+    def run(heads):
+        params = pb.make_params(len(heads), 1, L, B, flags=flags)
+        mask, rp, ci, info = pb.alloc_estimate_outputs(params)
+        pb.prism_estimate(params, q[heads].contiguous(), k, mask, rp, ci, ci.numel(), info,
+                          pb.alloc_workspace(pb.prism_estimate_workspace_bytes(params)))
+        rp2, ci2, info2 = torch.empty_like(rp), torch.empty_like(ci), torch.empty_like(info)
+        pb.prism_mask_to_csr(params, mask, rp2, ci2, ci2.numel(), info2)
+        torch.cuda.synchronize()
+        n = int(info[0])
+        assert torch.equal(rp, rp2) and torch.equal(info, info2) and torch.equal(ci[:n], ci2[:n])
+        return mask.view(len(heads), -1)
+
+    mask = run(list(range(h)))
+    for i in sorted({0, (h - 2) // 2, h - 2}):
+        assert torch.equal(mask[i:i + 2], run([i, i + 1])), i
