@@ -22,13 +22,13 @@ HIPCC_FLAGS = [
     "-Wno-unused-command-line-argument",
     # queue pulls stay plain returning atomics whose result is waited for where it is used
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
-    # accumulators of the compiler's MFMAs stay in VGPRs; at head dim 256, the only kernels with more than 256 registers a
-    # lane, it otherwise puts them in AGPRs and moves each in and out for every rescale (330 of the 746 vector instructions
-    # of a 64 x 256 step, now none)
-    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     # the registers of every kernel, for check_registers
     "-Rpass-analysis=kernel-resource-usage",
 ]
+# of libprism alone (the probes keep their accumulators where the compiler puts them): accumulators of the compiler's MFMAs stay in
+# VGPRs.  At head dim 256, the only kernels with more than 256 registers a lane, it otherwise puts them in AGPRs and moves each in
+# and out for every rescale (330 of the 746 vector instructions of a 64 x 256 step, now none).
+LIB_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 
 
 def _compile(sources: list[str], out_path: str, verbose: bool, extra_flags: list[str] | None) -> str:
@@ -92,7 +92,7 @@ def build_library(verbose: bool = False, extra_flags: list[str] | None = None) -
     if verbose:
         print(gen.stderr.strip(), flush=True)
     _compile(PEAKS_SOURCES, PEAKS_LIB_PATH, verbose, None)
-    return _compile(SOURCES, LIB_PATH, verbose, extra_flags)
+    return _compile(SOURCES, LIB_PATH, verbose, [*LIB_FLAGS, *(extra_flags or [])])
 
 
 SELECT_ABLATION_BITS = {"select_noscores": 1, "select_nosearch": 2, "select_norefetch": 4}
@@ -119,7 +119,7 @@ def build_ablation(experiment: str, out_path: str, verbose: bool = False) -> str
             raise RuntimeError(f"gen_attn_w64.py failed:\n{gen.stderr}")
         hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
         bits = sum(SELECT_ABLATION_BITS.get(tok, 0) for tok in experiment.split())
-        cmd = [hipcc, *HIPCC_FLAGS, f"-DPRISM_SELECT_ABLATION={bits}", "-I", os.path.join(ROOT, "include"), "-I", tmp,
+        cmd = [hipcc, *HIPCC_FLAGS, *LIB_FLAGS, f"-DPRISM_SELECT_ABLATION={bits}", "-I", os.path.join(ROOT, "include"), "-I", tmp,
                *[os.path.join(tmp, s) for s in SOURCES], "-o", out_path]
         if verbose:
             print(" ".join(cmd), flush=True)
