@@ -508,7 +508,7 @@ def main() -> int:
                                         "note": "achieved = counter bytes of the committed profile / launch time of "
                                                 "this run; bytes_per_launch_no_reuse = 64 KB per listed block pair + "
                                                 "Q in + O out, what the kernel would move if no tile were shared"},
-        "roofline_estimate": {"kernel": "prism_estimate (5 kernels; pool_energy_kernel carries the bytes)",
+        "roofline_estimate": {"kernel": "prism_estimate (4 kernels; pool_energy_kernel carries the bytes)",
                               "bound": "hbm", "achieved": round(est_gbs, 1), "peak": PEAK_HBM_GBS,
                               "unit": "GB/s", "frac": round(est_gbs / PEAK_HBM_GBS, 4),
                               "traffic": est_traffic, "traffic_source": est_src,
