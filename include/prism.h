@@ -258,8 +258,7 @@ int prism_dense_csr(const prism_params* params, int32_t* row_ptr, int32_t* col_i
  *   lse              : [n_q_heads, L] float natural-log sum-exp of the scaled scores, or NULL.
  * workspace: prism_sparse_attn_workspace_bytes() bytes (the kernel's work queues: one entry
  *            per row, ordered by list-length class and q-head and dealt to the eight XCDs in
- *            parts of equal work; an fp16 image of V where a kernel reads one; room for the
- *            copy of V that prism_v_image leaves).
+ *            parts of equal work; a copy of V; an fp16 image of it where a kernel reads one).
  * top_p, d_high, d_low and the other flags of `params` are ignored here.
  * ---------------------------------------------------------------------------------- */
 int prism_sparse_attn_workspace_bytes(const prism_params* params, size_t* bytes /* host, out */);
@@ -278,8 +277,8 @@ int prism_sparse_attn(const prism_params* params,
  *                            image in place of V.  The tail of the same buffer (beyond the
  *                            image) is scratch for the kernel's work queue and is rewritten
  *                            by every call, so calls sharing one image must not overlap.
- * out and lse of prism_sparse_attn(...) are those of prism_v_image(..., workspace) ;
- * prism_sparse_attn_pre(..., workspace).  prism_sparse_attn itself leaves no image behind. */
+ * prism_sparse_attn(...) == prism_v_image(..., workspace) ; prism_sparse_attn_pre(..., workspace):
+ * its workspace holds the image of its V afterwards. */
 int prism_v_image(const prism_params* params, const void* v_bf16, void* v_image,
                   size_t v_image_bytes, void* stream);
 

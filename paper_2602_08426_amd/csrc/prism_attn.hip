@@ -1360,8 +1360,8 @@ __global__ __launch_bounds__(256) void queue_fill_kernel(const int32_t* __restri
 // =====================================================================================
 // Everything in front of the attention kernels in one launch, for calls of up to kPrepMaxRows rows whose kv heads
 // form one phase: workgroup 0 (and 1, where the pair kernel may take the call) builds a queue plan, the next
-// `n_check` workgroups look the lists over, the rest write the fp16 image of V, where the 64-queries-per-wave kernel may
-// take the call.  The parts do not depend on each other;
+// `n_check` workgroups look the lists over, the rest write the V image: the fp16 image, where the 64-queries-per-wave kernel may
+// take the call, and the copy that prism_sparse_attn_pre finds.  The parts do not depend on each other;
 // the attention kernels read what the list check and the image found through DirtyFlags.
 // Such calls are bound by launches: a kernel with next to no work takes 4.5 us, and as four to nine kernels the same
 // work took 34 of 266 us per layer at 8K tokens and 14 of 47 us at 2K tokens and one head (the attention dispatch has
@@ -1373,7 +1373,7 @@ constexpr int kCheckRows = 64;             // rows per list-check workgroup
 struct PrepArgs {
   const int32_t *row_ptr, *col_idx;
   const uint16_t* v;                       // read for the image of the launch, if it writes one
-  uint16_t* vt16;
+  uint16_t *vt16, *copy;
   int32_t *range_flags, *check;
   int4 *items, *pair_items;
   int32_t *plan, *pair_plan;
@@ -1382,7 +1382,8 @@ struct PrepArgs {
   int32_t grid, pair_grid;                 // workgroups of the attention kernels
   float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
   float halve;                             // every row has, where the longest is a CU's average work over this or more (0: no)
-  int32_t h, h_kv, n_queues, pair_queues, n_check;
+  int32_t h, h_kv, n_queues, pair_queues, n_check, n_image16;
+  int32_t block, head_dim;
   uint8_t n_plans, causal, need_sorted;
   size_t kv_head_stride;
 };
@@ -1642,7 +1643,7 @@ union PrepLds {
   PlanLds plan;
   ImageTile tile;
 };
-// The part of the V image that belongs to workgroup `wg` of the launch's image workgroups.
+// The part of the fp16 image that belongs to workgroup `wg` of those that write it.
 __device__ __forceinline__ void prep_image(PrepLds& lds, int& s_over, const PrepArgs& a, const SeqTable& seqs, int wg) {
   const int s = seq_of(seqs, wg, a.h_kv);
   const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
@@ -1650,6 +1651,18 @@ __device__ __forceinline__ void prep_image(PrepLds& lds, int& s_over, const Prep
   vt_image_tile<kPrepThreads>(lds.tile, s_over,
                               a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * kImageRows) * kHeadDim,
                               a.vt16 + (size_t)wg * kHeadDim * kImageRows, a.range_flags + wg, 1 << s);
+}
+// The same of the copy: a block of a kv head.
+__device__ __forceinline__ void prep_copy(const PrepArgs& a, const SeqTable& seqs, int wg) {
+  const int s = seq_of(seqs, wg, a.h_kv);
+  const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
+  const int kvh = rr / N, blk = rr - kvh * N;
+  const int chunks = min(a.block, seqs.s[s].L - blk * a.block) * a.head_dim / 8;       // of 16 bytes
+  const u32x4* from = reinterpret_cast<const u32x4*>(
+      a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * a.block) * a.head_dim);
+  u32x4* to = reinterpret_cast<u32x4*>(
+      a.copy + ((size_t)kvh * seqs.nsum + seqs.s[s].blk0 + blk) * ((size_t)a.block * a.head_dim));
+  for (int i = threadIdx.x; i < chunks; i += kPrepThreads) to[i] = __builtin_nontemporal_load(from + i);
 }
 // The smallest calls feel what lies in front of their work: with the shortest plans first, and without a look
 // at each of sixteen sequences where there is one, 32 rows of one head take 4.3 us instead of 4.9.
@@ -1677,7 +1690,8 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
       return;
     }
     wg -= a.n_check;
-    prep_image(lds, s_over, a, seqs, wg);
+    if (wg < a.n_image16) prep_image(lds, s_over, a, seqs, wg);
+    else prep_copy(a, seqs, wg - a.n_image16);
     return;
   }
   const int stride = 1 + wg;
@@ -1711,7 +1725,7 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
 
 using namespace prism;
 
-// ---- workspace layout: [ copy of V (written by prism_v_image only) | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
+// ---- workspace layout: [ copy of V (no room for it in the larger groups of packed batches) | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
 //                            bins[2*h*kClasses] | parts[h_kv*kClasses*8] | plan[kPlanInts] |
 //                            fp16 V image | range_flags[h_kv*N]        where the fp16 image is read |
 //                            pair_items[h*N/2] | pair_plan[kPlanInts]  where the pair kernel may run ] ----
@@ -1760,8 +1774,8 @@ static AttnWs attn_layout(const prism_params* p, size_t N, bool with_copy, bool 
   w.total = off;
   return w;
 }
-// elements between the kv heads of the copy of V that prism_v_image leaves
-static size_t image_head_stride(const prism_params* p) { return (size_t)n_blocks(p) * p->block * p->head_dim; }
+// elements between the kv heads of the copy of V
+static size_t copy_head_stride(const prism_params* p) { return (size_t)n_blocks(p) * p->block * p->head_dim; }
 static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), true, w64_shape(p), pair_shape(p)); }
 
 static int check_image(const prism_params* params, const void* img, size_t bytes) {
@@ -1819,10 +1833,17 @@ extern "C" int prism_sparse_attn_workspace_bytes(const prism_params* params, siz
   return PRISM_OK;
 }
 
-static int v_image_core(const prism_params* params, const HeadStrides& hs, const uint16_t* v, uint16_t* vt16,
-                        int32_t* range_flags, hipStream_t st) {
-  const int N = n_blocks(params);
-  hipLaunchKernelGGL(vt_image_kernel, dim3(N, params->n_kv_heads), dim3(256), 0, st, v, N, hs.kv, vt16, range_flags);
+// The parts of the V image by kernels of their own.
+static int v_image_core(const prism_params* params, const HeadStrides& hs, const void* v_bf16, const AttnWs& W, char* ws,
+                        bool copy, bool image16, hipStream_t st) {
+  const uint16_t* v = (const uint16_t*)v_bf16;
+  const size_t chunks = (size_t)params->seq_len * params->head_dim / 8;     // 16 bytes each
+  if (copy)
+    hipLaunchKernelGGL(v_copy_kernel, dim3((unsigned)((chunks + 1023) / 1024), params->n_kv_heads), dim3(256), 0, st, v, chunks, hs.kv,
+                       copy_head_stride(params), reinterpret_cast<uint16_t*>(ws + W.copy));
+  if (image16)
+    hipLaunchKernelGGL(vt_image_kernel, dim3(n_blocks(params), params->n_kv_heads), dim3(256), 0, st, v, n_blocks(params), hs.kv,
+                       reinterpret_cast<uint16_t*>(ws + W.image16), reinterpret_cast<int32_t*>(ws + W.range_flags));
   return launch_status();
 }
 
@@ -1833,17 +1854,8 @@ extern "C" int prism_v_image(const prism_params* params, const void* v_bf16, voi
   if (!v_bf16) return PRISM_ERR_INVALID_ARG;
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
-  const AttnWs W = attn_ws(params);
-  char* ws = static_cast<char*>(v_image);
-  const HeadStrides hs = contiguous_heads(params);
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  const size_t chunks = hs.kv / 8;                           // 16 bytes each
-  hipLaunchKernelGGL(v_copy_kernel, dim3((unsigned)((chunks + 1023) / 1024), params->n_kv_heads), dim3(256), 0, st,
-                     (const uint16_t*)v_bf16, chunks, hs.kv, image_head_stride(params), reinterpret_cast<uint16_t*>(ws + W.copy));
-  rc = launch_status();
-  if (rc != PRISM_OK || !w64_shape(params)) return rc;
-  return v_image_core(params, hs, (const uint16_t*)v_bf16, reinterpret_cast<uint16_t*>(ws + W.image16),
-                      reinterpret_cast<int32_t*>(ws + W.range_flags), st);
+  return v_image_core(params, contiguous_heads(params), v_bf16, attn_ws(params), static_cast<char*>(v_image),
+                      true, w64_shape(params), static_cast<hipStream_t>(stream));
 }
 
 template <int BLK, bool kStreamOnly, int D, bool kPair = false, bool kKeepMask = false>
@@ -1869,10 +1881,10 @@ static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t*
 }
 
 // The whole attention of the sequences in `seqs` (arguments already validated; several sequences only where
-// R <= kPrepMaxRows and one phase, and where w64_shape says the same of all).  With `v_bf16` null what prism_v_image left in
-// `ws` takes its place.
+// R <= kPrepMaxRows and one phase, and where w64_shape says the same of all).  With `v_bf16` null the V image in `ws` takes
+// its place; with `leaves_image` the call writes that image, whole, whatever it reads of it.
 static int attn_core(const prism_params* params, const HeadStrides& hs, const SeqTable& seqs, const AttnWs& W,
-                     const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws,
+                     const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws, bool leaves_image,
                      const int32_t* row_ptr, const int32_t* col_idx, void* out_bf16, float* lse, hipStream_t st) {
   const int h = params->n_q_heads, h_kv = params->n_kv_heads, d = params->head_dim;
   const int N = seqs.nsum;
@@ -1946,7 +1958,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const uint16_t* kp = (const uint16_t*)k_bf16;
   // the general kernel reads V itself, or the copy
   const uint16_t* vp = v_bf16 != nullptr ? (const uint16_t*)v_bf16 : reinterpret_cast<const uint16_t*>(ws + W.copy);
-  const size_t v_head_stride = v_bf16 != nullptr ? hs.kv : image_head_stride(params);
+  const size_t v_head_stride = v_bf16 != nullptr ? hs.kv : copy_head_stride(params);
   const bool with16 = w64_shape(params);
   uint16_t* vp16 = with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
   int32_t* range_flags = with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
@@ -1977,7 +1989,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   if (pair && pair_grid <= 0) return PRISM_ERR_HIP;
   const int pair_queues = pair_grid < kXcds ? 1 : kXcds;
   const int n_range_flags = w64 ? h_kv * N : 0;
-  const bool writes_image = w64 && v_bf16 != nullptr;
+  const bool writes_image16 = v_bf16 != nullptr && with16 && (w64 || leaves_image);
 
   // One launch prepares the call up to kPrepMaxRows rows in one phase: 10.8 us instead of 34.7 us at 2048 rows (8K tokens, 32
   // heads, with the fp16 image), 8.0 without it, 19.6 at 5024 (20011 tokens), 36.1 instead of 63.1 at 8192 with the image (32K
@@ -1999,6 +2011,10 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.col_idx = col_idx;
     pa.v = (const uint16_t*)v_bf16;
     pa.vt16 = vp16;
+    pa.copy = reinterpret_cast<uint16_t*>(ws + W.copy);
+    pa.n_image16 = writes_image16 ? h_kv * N : 0;
+    pa.block = params->block;
+    pa.head_dim = d;
     pa.range_flags = range_flags;
     pa.check = row_rank;
     pa.items = items;
@@ -2021,12 +2037,12 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.halve = halve;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
-    const int prep_grid = pa.n_plans + pa.n_check + (writes_image ? h_kv * N : 0);
+    const int prep_grid = pa.n_plans + pa.n_check + pa.n_image16 + (leaves_image ? h_kv * N : 0);
     hipLaunchKernelGGL(prep_kernel, dim3(prep_grid), dim3(kPrepThreads), 0, st, pa, seqs);
     flags = DirtyFlags{row_rank, range_flags, pa.n_check, n_range_flags};
   } else {
-    if (writes_image) {
-      const int rc = v_image_core(params, hs, vp, vp16, range_flags, st);
+    if (leaves_image || writes_image16) {
+      const int rc = v_image_core(params, hs, v_bf16, W, ws, leaves_image, writes_image16, st);
       if (rc != PRISM_OK) return rc;
     }
     // (over a thousand rows here: more than kPrepMaxRows, or kv heads that do not fit the memory-side cache together)
@@ -2109,7 +2125,7 @@ extern "C" int prism_sparse_attn_pre(const prism_params* params, const void* q_b
   rc = check_image(params, v_image, v_image_bytes);
   if (rc != PRISM_OK) return rc;
   return attn_core(params, contiguous_heads(params), one_sequence(params, col_count),
-                   attn_ws(params), q_bf16, k_bf16, nullptr, static_cast<char*>(v_image),
+                   attn_ws(params), q_bf16, k_bf16, nullptr, static_cast<char*>(v_image), false,
                    row_ptr, col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
@@ -2124,7 +2140,7 @@ extern "C" int prism_sparse_attn(const prism_params* params, const void* q_bf16,
   rc = check_image(params, workspace, workspace_bytes);
   if (rc != PRISM_OK) return rc;
   return attn_core(params, contiguous_heads(params), one_sequence(params, col_count),
-                   attn_ws(params), q_bf16, k_bf16, v_bf16, static_cast<char*>(workspace), row_ptr,
+                   attn_ws(params), q_bf16, k_bf16, v_bf16, static_cast<char*>(workspace), true, row_ptr,
                    col_idx, out_bf16, lse, static_cast<hipStream_t>(stream));
 }
 
@@ -2189,7 +2205,7 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
     if (t.n == 1) at.s[0].tok0 = 0, at.s[0].row0 = 0, at.s[0].col0 = 0;   // one sequence: through the pointers
     const int64_t ro = t.n > 1 ? 0 : t.s[0].row0, co = t.n > 1 ? 0 : t.s[0].col0;
     return attn_core(&ps, hs, at, layout(t), (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
-                     (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), row_ptr + ro, col_idx + co,
+                     (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), false, row_ptr + ro, col_idx + co,
                      (uint16_t*)out_bf16 + tok * d, lse != nullptr ? lse + tok : nullptr, st);
   };
   return for_each_group(params, cu_seqlens, n_seqs, fits, run);

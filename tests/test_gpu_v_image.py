@@ -1,0 +1,98 @@
+"""The V image that prism_v_image and prism_sparse_attn leave for prism_sparse_attn_pre: every block and head size, whole and ragged
+lengths, clean lists and lists that send a call to the general kernel, one-launch and separate preparation."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import prism_oracle as orc
+from paper_2602_08426_amd import binding as pb
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+# h, h_kv, blocks, tokens of the last one, B, d, kind of lists
+SHAPES = [
+    (6, 3, 9, 64, 64, 64, "clean"), (6, 3, 9, 17, 64, 64, "clean"),
+    (4, 2, 12, 64, 64, 128, "clean"), (5, 5, 9, 1, 64, 128, "clean"),
+    (4, 2, 7, 64, 64, 256, "clean"), (4, 4, 7, 63, 64, 256, "clean"),
+    (44, 44, 64, 64, 64, 256, "clean"), (44, 4, 64, 5, 64, 256, "clean"),        # 2816 rows: pairs with two buffers per tile
+    (44, 4, 64, 64, 64, 256, "skip"),
+    (32, 32, 128, 33, 64, 128, "clean"), (32, 4, 128, 64, 64, 128, "unsorted"),  # 4096 rows: pairs
+    (6, 2, 9, 128, 128, 64, "clean"), (3, 3, 9, 100, 128, 64, "clean"),
+    (6, 2, 9, 128, 128, 128, "clean"), (6, 2, 9, 128, 128, 128, "skip"), (3, 3, 9, 77, 128, 128, "clean"),
+    (3, 3, 9, 128, 128, 128, "large"),                                           # V beyond fp16
+    (6, 2, 5, 128, 128, 256, "clean"), (3, 3, 5, 1, 128, 256, "clean"),
+    (66, 66, 125, 128, 128, 128, "skip"), (66, 66, 125, 40, 128, 64, "clean"),   # 8250 rows: separate kernels
+]
+
+
+def _inputs(h, hkv, N, tail, B, d, kind):
+    L = (N - 1) * B + tail
+    g = torch.Generator(device="cuda").manual_seed(N * B + h + tail)
+    q, k, v = (torch.randn((n, L, d), generator=g, device="cuda").bfloat16() for n in (h, hkv, hkv))
+    if kind == "large":
+        v[-1, L // 2, 3] = 1.0e5
+    rng = np.random.default_rng(h + tail)
+    mask = np.tril(rng.random((h, N, N)) < 0.3)
+    mask[:, np.arange(N), np.arange(N)] = True
+    rp, ci, cnt = gu.csr_to_device(*orc.mask_to_csr(mask))
+    at = int(rp[N])                                        # the last entries of the first q-head's last row
+    if kind == "skip":
+        ci[at - 1] = -1
+    if kind == "unsorted":
+        ci[at - 2:at] = ci[at - 2:at].flip(0)
+    bands = {64: (32, 48), 128: (64, 96), 256: (128, 192)}[d]
+    return pb.make_params(h, hkv, L, B, *bands, 0.9, 0, d), q, k, v, rp, ci, cnt
+
+
+def _same(a, b):
+    return torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
+                       b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32))
+
+
+@pytest.mark.parametrize("h,hkv,N,tail,B,d,kind", SHAPES)
+def test_image_of_either_call_serves_pre(h, hkv, N, tail, B, d, kind):
+    """prism_sparse_attn leaves what prism_v_image leaves: calls of prism_sparse_attn_pre behind either have its bits, also where the
+    first call took another kernel, and out and lse agree with 64-bit attention."""
+    params, q, k, v, rp, ci, cnt = _inputs(h, hkv, N, tail, B, d, kind)
+    need = pb.prism_sparse_attn_workspace_bytes(params)
+    general = pb.make_params(h, hkv, params.seq_len, B, params.d_high, params.d_low, 0.9, pb.PRISM_FLAG_GENERAL_KERNEL, d)
+
+    def pre(p, ws):
+        out = torch.full_like(q, float("nan"))
+        lse = torch.full((h, params.seq_len), float("nan"), device="cuda")
+        pb.prism_sparse_attn_pre(p, q, k, ws, rp, ci, cnt, out, lse)
+        torch.cuda.synchronize()
+        return out, lse
+
+    results = {}
+    for p in (params, general):
+        ws = torch.full((need,), 0x3c, dtype=torch.uint8, device="cuda")
+        out, lse = torch.full_like(q, float("nan")), torch.full((h, params.seq_len), float("nan"), device="cuda")
+        pb.prism_sparse_attn(p, q, k, v, rp, ci, cnt, out, lse, ws)
+        torch.cuda.synchronize()
+        results[p.flags] = (out, lse)
+        for reader in (general, params, general):
+            got = pre(reader, ws)
+            if reader.flags in results:
+                assert all(_same(a, b) for a, b in zip(got, results[reader.flags])), (p.flags, reader.flags)
+            else:
+                results[reader.flags] = got
+    image = torch.full((need,), 0x3c, dtype=torch.uint8, device="cuda")
+    pb.prism_v_image(params, v, image)
+    for p in (params, general):
+        assert all(_same(a, b) for a, b in zip(pre(p, image), results[p.flags])), p.flags
+    rows, counts = rp.cpu().numpy(), ci.cpu().numpy()
+    for i, u in {(0, N - 1), (0, 0), (h - 1, N // 2), (h - 1, N - 1)}:
+        listed = counts[rows[i * N + u]:rows[i * N + u + 1]]
+        t0, t1 = u * B, min((u + 1) * B, params.seq_len)
+        seen = torch.from_numpy(np.isin(np.arange(t1) // B, listed)).cuda()[None, :]
+        seen = seen & (torch.arange(t1, device="cuda")[None, :] <= torch.arange(t0, t1, device="cuda")[:, None])
+        j = i // (h // hkv)
+        x = (q[i, t0:t1].double() @ k[j, :t1].double().T / np.sqrt(d)).masked_fill(~seen, -np.inf)
+        live = seen.any(1)
+        ref = torch.where(live[:, None], torch.nan_to_num(torch.softmax(x, -1)) @ v[j, :t1].double(), 0.0)
+        for out, lse in results.values():
+            # 2e-2: the bar of the other attention tests, for values of that size
+            assert ((out[i, t0:t1].double() - ref).abs() <= 2e-2 * torch.clamp(ref.abs(), min=1.0)).all(), (i, u)
+            assert (lse[i, t0:t1].double() - torch.logsumexp(x, -1))[live].abs().max() <= 2e-3, (i, u)
