@@ -256,6 +256,7 @@ int prism_dense_csr(const prism_params* params, int32_t* row_ptr, int32_t* col_i
  *                      col_idx (row_ptr values are clamped to it).
  *   out_bf16         : [n_q_heads, L, d] bf16, fully overwritten.
  *   lse              : [n_q_heads, L] float natural-log sum-exp of the scaled scores, or NULL.
+ * out and lse may overlap V (all of it is read before the first output is written), but not K.
  * workspace: prism_sparse_attn_workspace_bytes() bytes (the kernel's work queues: one entry
  *            per row, ordered by list-length class and q-head and dealt to the eight XCDs in
  *            parts of equal work; a copy of V; an fp16 image of it where a kernel reads one).

@@ -1956,9 +1956,11 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
-  // the general kernel reads V itself, or the copy
-  const uint16_t* vp = v_bf16 != nullptr ? (const uint16_t*)v_bf16 : reinterpret_cast<const uint16_t*>(ws + W.copy);
-  const size_t v_head_stride = v_bf16 != nullptr ? hs.kv : copy_head_stride(params);
+  // The general kernel reads the copy where there is one: V itself may lie where the outputs go, and its tile copies ask for
+  // 16-byte alignment.
+  const bool reads_copy = v_bf16 == nullptr || leaves_image;
+  const uint16_t* vp = reads_copy ? reinterpret_cast<const uint16_t*>(ws + W.copy) : (const uint16_t*)v_bf16;
+  const size_t v_head_stride = reads_copy ? copy_head_stride(params) : hs.kv;
   const bool with16 = w64_shape(params);
   uint16_t* vp16 = with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
   int32_t* range_flags = with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;

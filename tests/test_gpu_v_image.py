@@ -1,5 +1,6 @@
 """The V image that prism_v_image and prism_sparse_attn leave for prism_sparse_attn_pre: every block and head size, whole and ragged
-lengths, clean lists and lists that send a call to the general kernel, one-launch and separate preparation."""
+lengths, clean lists and lists that send a call to the general kernel, one-launch and separate preparation.  And V in places of its
+own: where the outputs go, and at any alignment."""
 import numpy as np
 import pytest
 import torch
@@ -96,3 +97,22 @@ def test_image_of_either_call_serves_pre(h, hkv, N, tail, B, d, kind):
             # 2e-2: the bar of the other attention tests, for values of that size
             assert ((out[i, t0:t1].double() - ref).abs() <= 2e-2 * torch.clamp(ref.abs(), min=1.0)).all(), (i, u)
             assert (lse[i, t0:t1].double() - torch.logsumexp(x, -1))[live].abs().max() <= 2e-3, (i, u)
+
+
+@pytest.mark.parametrize("h,hkv,N,tail,B,d,kind", SHAPES)
+def test_values_where_the_outputs_go(h, hkv, N, tail, B, d, kind):
+    """V at the start of out, at its end, across its end, across lse, and at an odd address: the bits of a call with buffers apart."""
+    params, q, k, v, rp, ci, cnt = _inputs(h, hkv, N, tail, B, d, kind)
+    ref, ref_lse = gu.gpu_sparse_attn(params, q, k, v, rp, ci, cnt)
+    ws = pb.alloc_workspace(pb.prism_sparse_attn_workspace_bytes(params))
+    n_out, n_v, n_lse = q.numel(), v.numel(), 2 * ref_lse.numel()         # in elements of 2 bytes
+    # where V starts among [out | lse | room]
+    for at in {0, 1, n_out - n_v, n_out - n_v // 2 // 128 * 128, n_out, n_out + n_lse + 1}:
+        buf = torch.zeros(n_out + n_lse + n_v + 8, dtype=torch.bfloat16, device="cuda")
+        out = buf[:n_out].view(q.shape)
+        lse = buf[n_out:n_out + n_lse].view(torch.float32).view(ref_lse.shape)
+        vals = buf[at:at + n_v].view(v.shape)
+        vals.copy_(v)
+        pb.prism_sparse_attn(params, q, k, vals, rp, ci, cnt, out, lse, ws)
+        torch.cuda.synchronize()
+        assert _same(out, ref) and _same(lse, ref_lse), at
