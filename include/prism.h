@@ -313,6 +313,7 @@ int prism_sparse_attn_pre(const prism_params* params,
  * The sequences share the workspace (prism_*_varlen_workspace_bytes: the largest single
  * sequence's need).  Up to 16 sequences that fit it together also share their kernel launches;
  * such groups run one after the other on `stream`.  A larger workspace allows larger groups.
+ * The out and lse of a sequence may overlap its own V (out == v), but not that of another one.
  * Errors: PRISM_ERR_INVALID_ARG for malformed offsets, PRISM_ERR_UNSUPPORTED if a sequence
  * exceeds the per-sequence limits; nothing is launched in either case.
  * ---------------------------------------------------------------------------------- */

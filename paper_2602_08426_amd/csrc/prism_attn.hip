@@ -573,14 +573,14 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
     // K is the caller's tensor: rows past L in a ragged last block are outside the resource and
     // read as zeros, as are those of V.
     const __amdgpu_buffer_rsrc_t krs = make_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
-    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(vals + (size_t)kvh * v_head_stride + (size_t)tok0 * D, head_bytes);
+    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(vals + (size_t)kvh * v_head_stride + (size_t)(tok0 + seqs.s[sq].v_shift) * D, head_bytes);
     const int vmax = causal ? u_own : vmax_nc;
     // With two buffers per tile, step j reads the buffers j & 1, and both tiles of the next block are copied into the others; `buf` is
     // where they start, and what the lanes' read offsets hold already.
     TileRsrc krs2 = {}, vrs2 = {};
     if constexpr (kTwo) {
       krs2 = make_tile_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
-      vrs2 = make_tile_rsrc(vals + (size_t)kvh * v_head_stride + (size_t)tok0 * D, head_bytes);
+      vrs2 = make_tile_rsrc(vals + (size_t)kvh * v_head_stride + (size_t)(tok0 + seqs.s[sq].v_shift) * D, head_bytes);
     }
     auto other_buffer = [&]() __attribute__((always_inline)) {
       const int by = buf == 0 ? C::kTileBytes : -C::kTileBytes;
@@ -1774,8 +1774,8 @@ static AttnWs attn_layout(const prism_params* p, size_t N, bool with_copy, bool 
   w.total = off;
   return w;
 }
-// elements between the kv heads of the copy of V
-static size_t copy_head_stride(const prism_params* p) { return (size_t)n_blocks(p) * p->block * p->head_dim; }
+// elements between the kv heads of the copy of V, whose sequences start with a block each
+static size_t copy_head_stride(const prism_params* p, size_t N) { return N * p->block * p->head_dim; }
 static AttnWs attn_ws(const prism_params* p) { return attn_layout(p, n_blocks(p), true, w64_shape(p), pair_shape(p)); }
 
 static int check_image(const prism_params* params, const void* img, size_t bytes) {
@@ -1840,7 +1840,7 @@ static int v_image_core(const prism_params* params, const HeadStrides& hs, const
   const size_t chunks = (size_t)params->seq_len * params->head_dim / 8;     // 16 bytes each
   if (copy)
     hipLaunchKernelGGL(v_copy_kernel, dim3((unsigned)((chunks + 1023) / 1024), params->n_kv_heads), dim3(256), 0, st, v, chunks, hs.kv,
-                       copy_head_stride(params), reinterpret_cast<uint16_t*>(ws + W.copy));
+                       copy_head_stride(params, n_blocks(params)), reinterpret_cast<uint16_t*>(ws + W.copy));
   if (image16)
     hipLaunchKernelGGL(vt_image_kernel, dim3(n_blocks(params), params->n_kv_heads), dim3(256), 0, st, v, n_blocks(params), hs.kv,
                        reinterpret_cast<uint16_t*>(ws + W.image16), reinterpret_cast<int32_t*>(ws + W.range_flags));
@@ -1882,11 +1882,16 @@ static void build_plan(const PlanCfg& pc, const int32_t* row_ptr, const int32_t*
 
 // The whole attention of the sequences in `seqs` (arguments already validated; several sequences only where
 // R <= kPrepMaxRows and one phase, and where w64_shape says the same of all).  With `v_bf16` null the V image in `ws` takes
-// its place; with `leaves_image` the call writes that image, whole, whatever it reads of it.
-static int attn_core(const prism_params* params, const HeadStrides& hs, const SeqTable& seqs, const AttnWs& W,
-                     const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws, bool leaves_image,
+// its place; with `writes_copy` the call writes that image, whole, whatever it reads of it.
+static int attn_core(const prism_params* params, const HeadStrides& hs, const SeqTable& sequences, const AttnWs& W,
+                     const void* q_bf16, const void* k_bf16, const void* v_bf16, char* ws, bool writes_copy,
                      const int32_t* row_ptr, const int32_t* col_idx, void* out_bf16, float* lse, hipStream_t st) {
   const int h = params->n_q_heads, h_kv = params->n_kv_heads, d = params->head_dim;
+  // The general kernel reads the copy where there is one: V itself may lie where the outputs go, and its tile copies ask for
+  // 16-byte alignment.
+  const bool reads_copy = v_bf16 == nullptr || writes_copy;
+  SeqTable seqs = sequences;
+  for (int i = 0; i < seqs.n; ++i) seqs.s[i].v_shift = reads_copy ? seqs.s[i].blk0 * params->block - seqs.s[i].tok0 : 0;
   const int N = seqs.nsum;
   const int R = h * N;
   int4* items = reinterpret_cast<int4*>(ws + W.items);
@@ -1956,11 +1961,8 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const bool stream_only = (params->flags & PRISM_FLAG_STREAM_ONLY) != 0;
   const uint16_t* qp = (const uint16_t*)q_bf16;
   const uint16_t* kp = (const uint16_t*)k_bf16;
-  // The general kernel reads the copy where there is one: V itself may lie where the outputs go, and its tile copies ask for
-  // 16-byte alignment.
-  const bool reads_copy = v_bf16 == nullptr || leaves_image;
   const uint16_t* vp = reads_copy ? reinterpret_cast<const uint16_t*>(ws + W.copy) : (const uint16_t*)v_bf16;
-  const size_t v_head_stride = reads_copy ? copy_head_stride(params) : hs.kv;
+  const size_t v_head_stride = reads_copy ? copy_head_stride(params, N) : hs.kv;
   const bool with16 = w64_shape(params);
   uint16_t* vp16 = with16 ? reinterpret_cast<uint16_t*>(ws + W.image16) : nullptr;
   int32_t* range_flags = with16 ? reinterpret_cast<int32_t*>(ws + W.range_flags) : nullptr;
@@ -1991,7 +1993,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   if (pair && pair_grid <= 0) return PRISM_ERR_HIP;
   const int pair_queues = pair_grid < kXcds ? 1 : kXcds;
   const int n_range_flags = w64 ? h_kv * N : 0;
-  const bool writes_image16 = v_bf16 != nullptr && with16 && (w64 || leaves_image);
+  const bool writes_image16 = v_bf16 != nullptr && with16 && (w64 || writes_copy);
 
   // One launch prepares the call up to kPrepMaxRows rows in one phase: 10.8 us instead of 34.7 us at 2048 rows (8K tokens, 32
   // heads, with the fp16 image), 8.0 without it, 19.6 at 5024 (20011 tokens), 36.1 instead of 63.1 at 8192 with the image (32K
@@ -2039,12 +2041,12 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.halve = halve;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
-    const int prep_grid = pa.n_plans + pa.n_check + pa.n_image16 + (leaves_image ? h_kv * N : 0);
+    const int prep_grid = pa.n_plans + pa.n_check + pa.n_image16 + (writes_copy ? h_kv * N : 0);
     hipLaunchKernelGGL(prep_kernel, dim3(prep_grid), dim3(kPrepThreads), 0, st, pa, seqs);
     flags = DirtyFlags{row_rank, range_flags, pa.n_check, n_range_flags};
   } else {
-    if (leaves_image || writes_image16) {
-      const int rc = v_image_core(params, hs, v_bf16, W, ws, leaves_image, writes_image16, st);
+    if (writes_copy || writes_image16) {
+      const int rc = v_image_core(params, hs, v_bf16, W, ws, writes_copy, writes_image16, st);
       if (rc != PRISM_OK) return rc;
     }
     // (over a thousand rows here: more than kPrepMaxRows, or kv heads that do not fit the memory-side cache together)
@@ -2189,10 +2191,17 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
     ps.seq_len = q.L;
     return w64_shape(&ps);
   };
-  // These calls read V itself and write no copy of it: a group that needs the room has it.
+  // These calls leave no image and read V itself, where it is aligned for the tile copies and apart from the outputs: a group
+  // that needs the room of a copy has it then.
+  const uintptr_t v0 = reinterpret_cast<uintptr_t>(v_bf16), v1 = v0 + params->n_kv_heads * T * d * 2;
+  auto overlaps = [&](const void* p, size_t bytes) {
+    const uintptr_t p0 = reinterpret_cast<uintptr_t>(p);
+    return p != nullptr && p0 < v1 && v0 < p0 + bytes;
+  };
+  const bool copy = (v0 & 15u) != 0 || overlaps(out_bf16, params->n_q_heads * T * d * 2) || overlaps(lse, params->n_q_heads * T * 4);
   auto layout = [&](const SeqTable& t) {
     const AttnWs w = attn_layout(params, t.nsum, true, kind(t.s[0]), pairs(t));
-    return w.total <= workspace_bytes ? w : attn_layout(params, t.nsum, false, kind(t.s[0]), pairs(t));
+    return copy || w.total <= workspace_bytes ? w : attn_layout(params, t.nsum, false, kind(t.s[0]), pairs(t));
   };
   // Sequences share their launches while the one-launch preparation can take them all, their heads form one phase
   // and the workspace holds them.
@@ -2207,7 +2216,7 @@ extern "C" int prism_sparse_attn_varlen(const prism_params* params, const int32_
     if (t.n == 1) at.s[0].tok0 = 0, at.s[0].row0 = 0, at.s[0].col0 = 0;   // one sequence: through the pointers
     const int64_t ro = t.n > 1 ? 0 : t.s[0].row0, co = t.n > 1 ? 0 : t.s[0].col0;
     return attn_core(&ps, hs, at, layout(t), (const uint16_t*)q_bf16 + tok * d, (const uint16_t*)k_bf16 + tok * d,
-                     (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), false, row_ptr + ro, col_idx + co,
+                     (const uint16_t*)v_bf16 + tok * d, static_cast<char*>(workspace), copy, row_ptr + ro, col_idx + co,
                      (uint16_t*)out_bf16 + tok * d, lse != nullptr ? lse + tok : nullptr, st);
   };
   return for_each_group(params, cu_seqlens, n_seqs, fits, run);

@@ -69,11 +69,11 @@ constexpr int kMaxGroupSeqs = 16;
 struct SeqInfo {
   int32_t tok0;      // first token inside the packed tensors
   int32_t L, N;      // tokens, blocks
+  int32_t v_shift;   // from tok0 to its first token in what the attention reads as V
   int32_t blk0;      // blocks of the sequences in front of it in the group ...
   int32_t tile0;     // ... and their tiles (strips) of 16 blocks
   int32_t cap;       // entries of its col_idx part
   int32_t index;     // its number in the batch
-  int32_t pad;
   int64_t mask0;     // its part of the mask words, of row_ptr and of col_idx starts here
   int64_t row0;
   int64_t col0;

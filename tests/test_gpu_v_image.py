@@ -116,3 +116,46 @@ def test_values_where_the_outputs_go(h, hkv, N, tail, B, d, kind):
         pb.prism_sparse_attn(params, q, k, vals, rp, ci, cnt, out, lse, ws)
         torch.cuda.synchronize()
         assert _same(out, ref) and _same(lse, ref_lse), at
+
+
+@pytest.mark.parametrize("lens,h,hkv,B,d,extra,dirty", [
+    ([1024, 640, 2048, 384, 500, 128 * 9], 4, 4, 128, 128, 0, None),
+    ([1024, 640, 2048, 384, 500, 128 * 9], 8, 2, 128, 128, 64 << 20, "skip"),       # one group of whole blocks, one ragged
+    ([1024, 640, 2048, 384, 500, 128 * 9], 4, 4, 128, 128, 64 << 20, "large"),
+    ([3000, 129, 5, 1025, 641, 1], 4, 4, 128, 64, 64 << 20, None),
+    ([700, 128, 1400], 2, 2, 128, 256, 64 << 20, None),
+    ([64 * 6, 64 * 2, 64 * 10, 64 * 4], 4, 1, 64, 64, 64 << 20, None),
+    ([64 * 40, 64 * 2, 64 * 100, 64 * 4], 32, 32, 64, 128, 256 << 20, None),        # 4672 rows: pairs
+    ([64 * 40 - 9, 64 * 2, 64 * 50, 64 * 4], 32, 8, 64, 256, 256 << 20, None),      # 2944 rows of whole blocks: pairs
+    ([128 * 130, 1000, 128 * 3], 66, 66, 128, 128, 0, "skip"),                      # 8580 rows of one sequence: separate kernels
+])
+def test_values_where_the_outputs_of_a_packed_batch_go(lens, h, hkv, B, d, extra, dirty):
+    """V at the start of out and at an odd address: the bits of a call with buffers apart."""
+    cu = [0] + np.cumsum(lens).tolist()
+    T = cu[-1]
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    q, k, v = (torch.randn((n, T, d), generator=g, device="cuda").bfloat16() for n in (h, hkv, hkv))
+    if dirty == "large":
+        v[0, cu[1] + 5, 3] = 1.0e5
+    bands = {64: (32, 48), 128: (64, 96), 256: (128, 192)}[d]
+    params = pb.make_params(h, hkv, T, B, *bands, 0.9, 0, d)
+    _, ro, co = pb.prism_varlen_layout(params, cu)
+    rp = torch.zeros(ro[-1], dtype=torch.int32, device="cuda")
+    ci = torch.zeros(co[-1], dtype=torch.int32, device="cuda")
+    for s, L in enumerate(lens):
+        pb.prism_causal_csr(pb.make_params(h, hkv, L, B, *bands, 0.9, 0, d), rp[ro[s]:], ci[co[s]:], co[s + 1] - co[s])
+    if dirty == "skip":
+        ci[co[0]] = -1
+    ws = pb.alloc_workspace(pb.prism_sparse_attn_varlen_workspace_bytes(params, cu) + extra)
+    ref, ref_lse = torch.full_like(q, float("nan")), torch.full((h, T), float("nan"), device="cuda")
+    pb.prism_sparse_attn_varlen(params, cu, q, k, v, rp, ci, ref, ref_lse, ws)
+    torch.cuda.synchronize()
+    assert not torch.isnan(ref.float()).any()
+    n_out, n_v = q.numel(), v.numel()
+    for at in (0, n_out + 1):
+        buf = torch.zeros(n_out + n_v + 8, dtype=torch.bfloat16, device="cuda")
+        out, vals, lse = buf[:n_out].view(q.shape), buf[at:at + n_v].view(v.shape), torch.zeros_like(ref_lse)
+        vals.copy_(v)
+        pb.prism_sparse_attn_varlen(params, cu, q, k, vals, rp, ci, out, lse, ws)
+        torch.cuda.synchronize()
+        assert _same(out, ref) and _same(lse, ref_lse), at
