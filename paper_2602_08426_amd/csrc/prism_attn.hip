@@ -29,19 +29,21 @@ namespace prism {
 // Every bf16 value of magnitude in [2^-17, 65504] (and zero) is an fp16 value, so the conversion is
 // exact there; smaller magnitudes lose at most 2^-25 absolute.  A block holding a finite value beyond
 // the fp16 range sets range_flags[kv head * N + block] = 1 (else 0): such inputs go through the
-// general kernel, which reads V itself.
+// general kernel, which reads V or its copy.  Where both are written, the copy is stored from the registers that V passes through.
 // =====================================================================================
 constexpr int kImageRows = 128;                      // tokens of a block of the image
 typedef uint16_t ImageTile[kImageRows][kHeadDim + 2];
 template <int kThreads>
 __device__ __forceinline__ void vt_image_tile(ImageTile& tile, int& s_over, const uint16_t* __restrict__ src,
-                                              uint16_t* __restrict__ dst16, int32_t* __restrict__ range_flag, int flag_value) {
+                                              uint16_t* __restrict__ copy, uint16_t* __restrict__ dst16,
+                                              int32_t* __restrict__ range_flag, int flag_value) {
   const int t = threadIdx.x;
   if (t == 0) s_over = 0;
   constexpr int RCH = kHeadDim / 8;                  // 16-byte chunks per token row
   for (int idx = t; idx < kImageRows * RCH; idx += kThreads) {
     const int row = idx / RCH, c = idx % RCH;        // V is read once: streaming (non-temporal) loads
     const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (size_t)row * kHeadDim + c * 8));
+    if (copy != nullptr) *reinterpret_cast<u32x4*>(copy + (size_t)row * kHeadDim + c * 8) = x;
     uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[row][c * 8]);   // 4-byte aligned: row stride 2*d + 4 B
     dst[0] = x[0]; dst[1] = x[1]; dst[2] = x[2]; dst[3] = x[3];
   }
@@ -70,15 +72,16 @@ __device__ __forceinline__ void vt_image_tile(ImageTile& tile, int& s_over, cons
 }
 
 __global__ __launch_bounds__(256) void vt_image_kernel(const uint16_t* __restrict__ v, int N, size_t kv_head_stride,
-                                                       uint16_t* __restrict__ vt16, int32_t* __restrict__ range_flags) {
+                                                       uint16_t* __restrict__ copy, uint16_t* __restrict__ vt16, int32_t* __restrict__ range_flags) {
   __shared__ ImageTile tile;
   __shared__ int s_over;
   const int blk = blockIdx.x, kvh = blockIdx.y;
+  const size_t at = ((size_t)kvh * N + blk) * kHeadDim * kImageRows;
   vt_image_tile<256>(tile, s_over, v + (size_t)kvh * kv_head_stride + (size_t)blk * kImageRows * kHeadDim,
-                     vt16 + ((size_t)kvh * N + blk) * kHeadDim * kImageRows, range_flags + kvh * N + blk, 1);
+                     copy != nullptr ? copy + at : nullptr, vt16 + at, range_flags + kvh * N + blk, 1);
 }
 
-// The copy of V that prism_v_image leaves for prism_sparse_attn_pre: [h_kv, N * B, d], of which the L tokens are written.
+// The copy of V alone: [h_kv, N * B, d], of which the L tokens are written.
 __global__ __launch_bounds__(256) void v_copy_kernel(const uint16_t* __restrict__ v, size_t chunks, size_t from_stride,
                                                      size_t to_stride, uint16_t* __restrict__ copy) {
   const u32x4* from = reinterpret_cast<const u32x4*>(v + (size_t)blockIdx.y * from_stride);
@@ -1360,8 +1363,8 @@ __global__ __launch_bounds__(256) void queue_fill_kernel(const int32_t* __restri
 // =====================================================================================
 // Everything in front of the attention kernels in one launch, for calls of up to kPrepMaxRows rows whose kv heads
 // form one phase: workgroup 0 (and 1, where the pair kernel may take the call) builds a queue plan, the next
-// `n_check` workgroups look the lists over, the rest write the V image: the fp16 image, where the 64-queries-per-wave kernel may
-// take the call, and the copy that prism_sparse_attn_pre finds.  The parts do not depend on each other;
+// `n_check` workgroups look the lists over, the rest write the V image: the fp16 image and the copy, or the copy alone where the
+// 64-queries-per-wave kernel cannot take the call.  The parts do not depend on each other;
 // the attention kernels read what the list check and the image found through DirtyFlags.
 // Such calls are bound by launches: a kernel with next to no work takes 4.5 us, and as four to nine kernels the same
 // work took 34 of 266 us per layer at 8K tokens and 14 of 47 us at 2K tokens and one head (the attention dispatch has
@@ -1373,7 +1376,7 @@ constexpr int kCheckRows = 64;             // rows per list-check workgroup
 struct PrepArgs {
   const int32_t *row_ptr, *col_idx;
   const uint16_t* v;                       // read for the image of the launch, if it writes one
-  uint16_t *vt16, *copy;
+  uint16_t *vt16, *copy;                   // null: not written
   int32_t *range_flags, *check;
   int4 *items, *pair_items;
   int32_t *plan, *pair_plan;
@@ -1382,7 +1385,7 @@ struct PrepArgs {
   int32_t grid, pair_grid;                 // workgroups of the attention kernels
   float alone;                             // a row this many times the work of an average workgroup has a CU to itself (0: none)
   float halve;                             // every row has, where the longest is a CU's average work over this or more (0: no)
-  int32_t h, h_kv, n_queues, pair_queues, n_check, n_image16;
+  int32_t h, h_kv, n_queues, pair_queues, n_check;
   int32_t block, head_dim;
   uint8_t n_plans, causal, need_sorted;
   size_t kv_head_stride;
@@ -1643,16 +1646,21 @@ union PrepLds {
   PlanLds plan;
   ImageTile tile;
 };
-// The part of the fp16 image that belongs to workgroup `wg` of those that write it.
+// Where block `blk` of a sequence lies in a kv head of the copy.
+__device__ __forceinline__ uint16_t* copy_block(const PrepArgs& a, const SeqTable& seqs, int kvh, int s, int blk) {
+  return a.copy + ((size_t)kvh * seqs.nsum + seqs.s[s].blk0 + blk) * ((size_t)a.block * a.head_dim);
+}
+// The part of the V image that belongs to workgroup `wg` of the launch's image workgroups: with the fp16 image ...
 __device__ __forceinline__ void prep_image(PrepLds& lds, int& s_over, const PrepArgs& a, const SeqTable& seqs, int wg) {
   const int s = seq_of(seqs, wg, a.h_kv);
   const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
   const int kvh = rr / N, blk = rr - kvh * N;
   vt_image_tile<kPrepThreads>(lds.tile, s_over,
                               a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * kImageRows) * kHeadDim,
+                              a.copy != nullptr ? copy_block(a, seqs, kvh, s, blk) : nullptr,
                               a.vt16 + (size_t)wg * kHeadDim * kImageRows, a.range_flags + wg, 1 << s);
 }
-// The same of the copy: a block of a kv head.
+// ... and the copy alone.
 __device__ __forceinline__ void prep_copy(const PrepArgs& a, const SeqTable& seqs, int wg) {
   const int s = seq_of(seqs, wg, a.h_kv);
   const int rr = wg - a.h_kv * seqs.s[s].blk0, N = seqs.s[s].N;
@@ -1660,8 +1668,7 @@ __device__ __forceinline__ void prep_copy(const PrepArgs& a, const SeqTable& seq
   const int chunks = min(a.block, seqs.s[s].L - blk * a.block) * a.head_dim / 8;       // of 16 bytes
   const u32x4* from = reinterpret_cast<const u32x4*>(
       a.v + (size_t)kvh * a.kv_head_stride + ((size_t)seqs.s[s].tok0 + (size_t)blk * a.block) * a.head_dim);
-  u32x4* to = reinterpret_cast<u32x4*>(
-      a.copy + ((size_t)kvh * seqs.nsum + seqs.s[s].blk0 + blk) * ((size_t)a.block * a.head_dim));
+  u32x4* to = reinterpret_cast<u32x4*>(copy_block(a, seqs, kvh, s, blk));
   for (int i = threadIdx.x; i < chunks; i += kPrepThreads) to[i] = __builtin_nontemporal_load(from + i);
 }
 // The smallest calls feel what lies in front of their work: with the shortest plans first, and without a look
@@ -1690,8 +1697,8 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
       return;
     }
     wg -= a.n_check;
-    if (wg < a.n_image16) prep_image(lds, s_over, a, seqs, wg);
-    else prep_copy(a, seqs, wg - a.n_image16);
+    if (a.vt16 != nullptr) prep_image(lds, s_over, a, seqs, wg);
+    else prep_copy(a, seqs, wg);
     return;
   }
   const int stride = 1 + wg;
@@ -1838,11 +1845,12 @@ static int v_image_core(const prism_params* params, const HeadStrides& hs, const
                         bool copy, bool image16, hipStream_t st) {
   const uint16_t* v = (const uint16_t*)v_bf16;
   const size_t chunks = (size_t)params->seq_len * params->head_dim / 8;     // 16 bytes each
-  if (copy)
+  uint16_t* to = copy ? reinterpret_cast<uint16_t*>(ws + W.copy) : nullptr;
+  if (copy && !image16)
     hipLaunchKernelGGL(v_copy_kernel, dim3((unsigned)((chunks + 1023) / 1024), params->n_kv_heads), dim3(256), 0, st, v, chunks, hs.kv,
-                       copy_head_stride(params, n_blocks(params)), reinterpret_cast<uint16_t*>(ws + W.copy));
+                       copy_head_stride(params, n_blocks(params)), to);
   if (image16)
-    hipLaunchKernelGGL(vt_image_kernel, dim3(n_blocks(params), params->n_kv_heads), dim3(256), 0, st, v, n_blocks(params), hs.kv,
+    hipLaunchKernelGGL(vt_image_kernel, dim3(n_blocks(params), params->n_kv_heads), dim3(256), 0, st, v, n_blocks(params), hs.kv, to,
                        reinterpret_cast<uint16_t*>(ws + W.image16), reinterpret_cast<int32_t*>(ws + W.range_flags));
   return launch_status();
 }
@@ -2014,9 +2022,8 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.row_ptr = row_ptr;
     pa.col_idx = col_idx;
     pa.v = (const uint16_t*)v_bf16;
-    pa.vt16 = vp16;
-    pa.copy = reinterpret_cast<uint16_t*>(ws + W.copy);
-    pa.n_image16 = writes_image16 ? h_kv * N : 0;
+    pa.vt16 = writes_image16 ? vp16 : nullptr;
+    pa.copy = writes_copy ? reinterpret_cast<uint16_t*>(ws + W.copy) : nullptr;
     pa.block = params->block;
     pa.head_dim = d;
     pa.range_flags = range_flags;
@@ -2041,7 +2048,7 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
     pa.halve = halve;
     pa.pair_grid = pair_grid;
     pa.kv_head_stride = hs.kv;
-    const int prep_grid = pa.n_plans + pa.n_check + pa.n_image16 + (writes_copy ? h_kv * N : 0);
+    const int prep_grid = pa.n_plans + pa.n_check + (writes_copy || writes_image16 ? h_kv * N : 0);
     hipLaunchKernelGGL(prep_kernel, dim3(prep_grid), dim3(kPrepThreads), 0, st, pa, seqs);
     flags = DirtyFlags{row_rank, range_flags, pa.n_check, n_range_flags};
   } else {
