@@ -6,7 +6,9 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import prism_oracle as orc
 from paper_2602_08426_amd import binding as pb
+from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
@@ -78,7 +80,8 @@ def test_same_bits_as_the_general_form(h, hkv, N, tail, B, d, bands, p, flags, k
 ])
 def test_forms_of_the_general_selection(h, N, tail, flags):
     """Every head of a call has the bits of a call on that head and one other, which takes the short form or sixteen waves of one
-    row, and the lists are those of the bits."""
+    row, and the lists are those of the bits.  Calls that have sixteen waves of one row themselves (7 heads of 513 blocks, 2 of 1024,
+    and all beyond 1024) are held against the oracle in the test below."""
     B, L = 64, (N - 1) * 64 + tail
     g = torch.Generator(device="cuda").manual_seed(N + h)
     q, k = (torch.randn((n, L, 128), generator=g, device="cuda") for n in (h, 1))
@@ -101,3 +104,28 @@ def test_forms_of_the_general_selection(h, N, tail, flags):
     mask = run(list(range(h)))
     for i in sorted({0, (h - 2) // 2, h - 2}):
         assert torch.equal(mask[i:i + 2], run([i, i + 1])), i
+
+
+@pytest.mark.parametrize("h,N,tail,d,flags", [
+    (50, 250, 9, 256, 0),                                   # 800 strips: four waves of four rows
+    (30, 300, 64, 256, pb.PRISM_FLAG_BIDIRECTIONAL),        # 570: eight of two
+    (8, 600, 64, 64, 0), (8, 520, 3, 256, 0),               # 304 and 264: eight of two rows of up to 1024
+    (7, 513, 5, 128, 0), (2, 1024, 3, 128, pb.PRISM_FLAG_BIDIRECTIONAL), (2, 700, 64, 256, 0),      # sixteen of one
+    (3, 1025, 64, 128, 0), (2, 1100, 7, 128, 0), (2, 1040, 64, 64, pb.PRISM_FLAG_BIDIRECTIONAL), (2, 1030, 1, 256, 0),
+])
+def test_general_selection_agrees_with_the_oracle(h, N, tail, d, flags):
+    """The first and the last head: the blocks that the oracle selects, outside its margin at the cut."""
+    B, L = 64, (N - 1) * 64 + tail
+    g = torch.Generator(device="cuda").manual_seed(N + h)
+    q, k = (torch.randn((n, L, d), generator=g, device="cuda") for n in (h, 1))
+    for x in (q, k):
+        x += torch.randn((x.shape[0], N, d), generator=g, device="cuda").repeat_interleave(B, 1)[:, :L] * 0.6
+    q, k = q.bfloat16(), k.bfloat16()
+    bands = {64: (32, 48), 128: (64, 96), 256: (128, 192)}[d]
+    res = gu.gpu_estimate(pb.make_params(h, 1, L, B, *bands, 0.95, flags, d), q, k)
+    sel = orc.prism_select(q[[0, h - 1]].double().cpu().numpy(), k.double().cpu().numpy(), *bands, B, 0.95,
+                           causal=not flags & pb.PRISM_FLAG_BIDIRECTIONAL)
+    tol = orc.selection_tolerance(sel, 0.95)
+    mask = res["mask"][[0, h - 1]]
+    assert not (tol.must & ~mask).any() and not (tol.must_not & mask).any()
+    assert tol.dont_care_fraction < 0.02

@@ -159,3 +159,58 @@ def test_values_where_the_outputs_of_a_packed_batch_go(lens, h, hkv, B, d, extra
         pb.prism_sparse_attn_varlen(params, cu, q, k, vals, rp, ci, out, lse, ws)
         torch.cuda.synchronize()
         assert _same(out, ref) and _same(lse, ref_lse), at
+
+
+@pytest.mark.parametrize("h,hkv,N,tail,B,d,kind", [s for s in SHAPES if s[3] < s[4] and s[1] > 1])
+def test_nothing_behind_a_ragged_end_of_a_head_is_read(h, hkv, N, tail, B, d, kind):
+    """The workspace full of NaN, V of every other kv head NaN or infinite: the other heads keep their bits."""
+    params, q, k, v, rp, ci, cnt = _inputs(h, hkv, N, tail, B, d, kind)
+    ref, ref_lse = gu.gpu_sparse_attn(params, q, k, v, rp, ci, cnt)
+    out, lse = torch.empty_like(ref), torch.empty_like(ref_lse)
+    for first, value in ((0, float("nan")), (1, float("inf"))):
+        vals = v.clone()
+        vals[first::2] = value
+        ws = torch.full((pb.prism_sparse_attn_workspace_bytes(params),), 0xff, dtype=torch.uint8, device="cuda")
+        pb.prism_sparse_attn(params, q, k, vals, rp, ci, cnt, out, lse, ws)
+        torch.cuda.synchronize()
+        clean = torch.arange(h, device="cuda") // (h // hkv) % 2 != first
+        assert _same(out[clean], ref[clean]) and _same(lse, ref_lse)
+
+
+@pytest.mark.parametrize("lens,h,hkv,B,d", [
+    ([64 * 39 + 5, 64 * 47 + 63, 64 * 2 - 1], 32, 8, 64, 256),      # 2880 rows in one group: pairs with two buffers per tile
+    ([64 * 79 + 5, 64 * 47 + 63, 64 * 2 - 1], 32, 8, 64, 128),      # 4160: pairs
+    ([64 * 20 + 5, 64 * 30, 64 * 7 - 1], 16, 4, 64, 256),           # plain
+])
+def test_nothing_behind_a_ragged_end_of_a_sequence_is_read(lens, h, hkv, B, d):
+    """V of every other sequence NaN or infinite, read as it is given and by way of the copy: the other sequences keep their bits."""
+    cu = [0] + np.cumsum(lens).tolist()
+    T = cu[-1]
+    g = torch.Generator(device="cuda").manual_seed(T)
+    q, k, v = (torch.randn((n, T, d), generator=g, device="cuda").bfloat16() for n in (h, hkv, hkv))
+    bands = {128: (64, 96), 256: (128, 192)}[d]
+    params = pb.make_params(h, hkv, T, B, *bands, 0.9, 0, d)
+    _, ro, co = pb.prism_varlen_layout(params, cu)
+    rp, ci = (torch.zeros(n, dtype=torch.int32, device="cuda") for n in (ro[-1], co[-1]))
+    for s, L in enumerate(lens):
+        pb.prism_causal_csr(pb.make_params(h, hkv, L, B, *bands, 0.9, 0, d), rp[ro[s]:], ci[co[s]:], co[s + 1] - co[s])
+    need = pb.prism_sparse_attn_varlen_workspace_bytes(params, cu) + (256 << 20)
+
+    def run(vals):
+        out = torch.full_like(q, float("nan"))
+        ws = torch.full((need,), 0xff, dtype=torch.uint8, device="cuda")
+        pb.prism_sparse_attn_varlen(params, cu, q, k, vals, rp, ci, out, None, ws)
+        torch.cuda.synchronize()
+        return out
+
+    ref = run(v)
+    for first, value in ((0, float("nan")), (1, -float("inf"))):
+        for at in (0, 1):
+            buf = torch.zeros(v.numel() + 8, dtype=torch.bfloat16, device="cuda")
+            vals = buf[at:at + v.numel()].view(v.shape)
+            vals.copy_(v)
+            for s in range(first, len(lens), 2):
+                vals[:, cu[s]:cu[s + 1]] = value
+            out = run(vals)
+            for s in range(1 - first, len(lens), 2):
+                assert _same(out[:, cu[s]:cu[s + 1]].contiguous(), ref[:, cu[s]:cu[s + 1]].contiguous()), (s, at)
