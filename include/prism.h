@@ -61,7 +61,7 @@ typedef enum prism_status {
                                           use the pair kernel wherever the shape allows it (an even number
                                           of blocks), also for problems too small for it to pay */
 #define PRISM_FLAG_STREAM_ONLY 0x40000000u /* measurement aid for prism_sparse_attn(_pre): run the
-                                          kernel's K / V^T tile copies, waits and scheduling without
+                                          kernel's K / V tile copies, waits and scheduling without
                                           its arithmetic; the outputs are then meaningless.  Shows how
                                           long the memory side of a call takes on its own.  Head dim
                                           128 only (PRISM_ERR_UNSUPPORTED otherwise). */

@@ -11,7 +11,7 @@
 // In the 32x32 accumulator layout lane l holds query column l%32 and, per 32-key tile,
 // keys 8*(r/4) + 4*(l/32) + r%4 for r = 0..15.  One MFMA K-step of PV therefore consumes
 // keys {16s + 8g + 4*(l/32) + i}; the V^T operand must present the same keys in the same
-// slots.  The general kernel reads V as it is given and transposes on the way from LDS to the registers
+// slots.  The general kernel reads V, or a plain copy of it, and transposes on the way from LDS to the registers
 // (ds_read_b64_tr_b16 hands a lane four keys of its dim).  The 64-queries-per-wave kernel reads an fp16 image of V^T: per kv
 // block [d][B], whose key positions inside every group of 16 are permuted to
 // pos = 8*hf + 4*g + i  for key = 8*g + 4*hf + i.  A 16-byte LDS read then yields one
@@ -29,7 +29,8 @@ namespace prism {
 // Every bf16 value of magnitude in [2^-17, 65504] (and zero) is an fp16 value, so the conversion is
 // exact there; smaller magnitudes lose at most 2^-25 absolute.  A block holding a finite value beyond
 // the fp16 range sets range_flags[kv head * N + block] = 1 (else 0): such inputs go through the
-// general kernel, which reads V or its copy.  Where both are written, the copy is stored from the registers that V passes through.
+// general kernel, which reads V or its copy.  Bound by the bytes: where both are written, the copy is stored from the registers that V
+// passes through (us, two kernels / one: 32/8 heads, 8192 tokens 16.1 / 13.0, 32768 50.6 / 38.1, 131072 194.6 / 145.1).
 // =====================================================================================
 constexpr int kImageRows = 128;                      // tokens of a block of the image
 typedef uint16_t ImageTile[kImageRows][kHeadDim + 2];
@@ -152,7 +153,7 @@ struct AttnCfg {
   // texture path has taken them, 500 - 1000 cycles of a step (S phase 2770 cycles, PV phase with as many MFMAs 1640).  The
   // V pieces are spread over the S MFMAs in every form; the K pieces over the maximum at B = 128, over the exponentials
   // at d = 256, where no second wave of the SIMD fills the gap; at B = 64 the softmax is too short to hide a later request.
-  // us of attention, all in a row / V^T spread / K over the maximum too / K over the exponentials instead:
+  // us of attention, all in a row / V spread / K over the maximum too / K over the exponentials instead:
   // 128 x 128, 32/8 heads, 12345 tokens 281 / 274 / 271 / 270, 40001 1822 / 1752 / 1755 / 1754; 128 x 64, 12345
   // 195 / 189 / 186 / 183, 28001 591 / 592 / 590 / 605; 128 x 256, 4/4 heads, 16384 216 / 201 / 192 / 187; pair 64 x 256, 16/4,
   // 16384 714 / 701 / 697 / 682; pair 64 x 128, 8/2, 60000 605 / 584 / 591 / 592; 64 x 64, 32/8, 16384 305 / 298 / 298 / 316.
@@ -427,10 +428,11 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
 #pragma unroll
   for (int st = 0; st < KS; ++st) koff[st] = l32 * (D * 2) + (((2 * st + hf) ^ k_row_swizzle<D>(l32)) << 4);
   // V: lane l supplies the address of 4 dims of key 4*hf + (l%16)/4 of a 16-key step, and receives 4 keys of dim l%32.  Two such
-  // reads make an operand that one 16-byte read of a transposed image would be; the kernel takes as long (us of attention alone, image /
-  // this: 128 x 128, 32/8 heads, 20011 tokens 501 / 501, 128 x 64, 12345 183 / 185, pair 64 x 128, 32768 1337 / 1332, pair 64 x 256,
-  // 16/4, 16384 489 / 495), and the image need not be written: preparation and attention 16 heads, 19290 tokens, bidirectional
-  // 458 -> 441, 64 x 128, 32768 1314 -> 1282, 128 x 128, 20011 504 -> 499.
+  // reads make an operand that one 16-byte read of a transposed image would be, at no more than 1 % (us of attention on an image that
+  // is there, transposed / as given: 128 x 128, 32/8 heads, 20011 tokens 612.8 / 614.2, 16 heads, 19290, bidirectional 514.7 / 516.1,
+  // 128 x 64, 8192 119.2 / 119.7, 12345 192.5 / 193.8, 32768 981.3 / 980.8, 8/2, 40000 289.1 / 292.3, 64 x 64, 16384 310.5 / 312.3, 32000
+  // 932 / 929, pair 64 x 128, 32768 1478 / 1469, 16 heads, 30000 986 / 982).  Packed batches then need no image, and the others a plain copy:
+  // preparation and attention, image / copy: 128 x 128, 20011 627 / 629, bidirectional 19290 535 / 530, 64 x 128, 32768 1545 / 1525.
 #pragma unroll
   for (int i = 0; i < kGroups; ++i) {
     const int key = 4 * hf + ((lane >> 2) & 3);
@@ -486,7 +488,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
   // load in flight will write would force a wait for every older memory operation)
   int4 item_nxt = make_int4(0, 0, 0, 0);
   int pulled_reg = 0;
-  // two buffers per tile: where the current ones start, and this lane's places in pieces 0 and 1 of a K tile and in a piece of V^T
+  // two buffers per tile: where the current ones start, and this lane's places in pieces 0 and 1 of a K tile and in a piece of V
   int buf = 0;
   const int k_lane0 = kTwo ? k_piece_offset<BLK, D>(t) : 0, k_lane1 = kTwo ? k_piece_offset<BLK, D>(C::kThreads + t) : 0;
   const int v_lane = kTwo ? v_piece_offset<BLK, D>(t) : 0;
@@ -572,7 +574,7 @@ __global__ __launch_bounds__((AttnCfg<BLK, D, kPair>::kThreads), (AttnCfg<BLK, D
       continue;
     }
 
-    // K and V^T of this kv head as buffer resources (tile v starts at byte v * kTileBytes).
+    // K and V of this kv head as buffer resources (tile v starts at byte v * kTileBytes).
     // K is the caller's tensor: rows past L in a ragged last block are outside the resource and
     // read as zeros, as are those of V.
     const __amdgpu_buffer_rsrc_t krs = make_rsrc(k + (size_t)kvh * hs.kv + (size_t)tok0 * D, head_bytes);
@@ -1124,8 +1126,8 @@ __global__ __launch_bounds__(256) void queue_validate_kernel(const int32_t* __re
 // through the long rows of a phase first and its short rows last (no long row is started at the
 // end of the call), and the queues hold equal work.
 //   phase = kv head / heads_per_phase: the kv heads are taken a few at a time so that the K and
-//       V^T of the heads in flight fit the 256 MB memory-side cache (at 128K tokens a kv head is
-//       67 MB of K + V^T and all eight do not fit).
+//       V of the heads in flight fit the 256 MB memory-side cache (at 128K tokens a kv head is
+//       67 MB of K + V and all eight do not fit).
 //   class: list length in (512, ..], (256, 512], (128, 256], ... (1, 2], [0, 1].
 //   queue_count_kernel  (one workgroup per q-head): rows and work of the head per class.
 //   queue_rank_kernel   (one workgroup per q-head): every row's rank in its group and its part,
@@ -1732,7 +1734,8 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(PrepArgs a, SeqTa
 
 using namespace prism;
 
-// ---- workspace layout: [ copy of V (no room for it in the larger groups of packed batches) | items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
+// ---- workspace layout: [ copy of V        (packed batches: where they read one, or have room)
+//                            items[h*N] (queue entries) | row_rank[h*N] | row_part[h*N] |
 //                            bins[2*h*kClasses] | parts[h_kv*kClasses*8] | plan[kPlanInts] |
 //                            fp16 V image | range_flags[h_kv*N]        where the fp16 image is read |
 //                            pair_items[h*N/2] | pair_plan[kPlanInts]  where the pair kernel may run ] ----
@@ -1813,11 +1816,11 @@ static int device_facts(DeviceFacts* out) {
   return PRISM_OK;
 }
 
-// The memory-side cache holds 256 MB; the K and V^T of the kv heads that are in flight together are
+// The memory-side cache holds 256 MB; the K and V of the kv heads that are in flight together are
 // kept to kCacheBudgetBytes of it.
 constexpr size_t kCacheBudgetBytes = (size_t)160 << 20;
 
-// kv heads whose K and V^T fit that budget together, at least one
+// kv heads whose K and V fit that budget together, at least one
 static int heads_in_cache(const prism_params* p, const SeqTable& seqs) {
   size_t tokens = 0;
   for (int i = 0; i < seqs.n; ++i) tokens += seqs.s[i].L;
@@ -2003,10 +2006,12 @@ static int attn_core(const prism_params* params, const HeadStrides& hs, const Se
   const int n_range_flags = w64 ? h_kv * N : 0;
   const bool writes_image16 = v_bf16 != nullptr && with16 && (w64 || writes_copy);
 
-  // One launch prepares the call up to kPrepMaxRows rows in one phase: 10.8 us instead of 34.7 us at 2048 rows (8K tokens, 32
-  // heads, with the fp16 image), 8.0 without it, 19.6 at 5024 (20011 tokens), 36.1 instead of 63.1 at 8192 with the image (32K
-  // tokens), 30.6 without it, 3.8 instead of 13.9 at 32 rows.  Beyond, a single workgroup would plan for longer than the separate
-  // kernels take.
+  // One launch prepares the call up to kPrepMaxRows rows in one phase: the V image is written beside the plan of a single workgroup.  us,
+  // one launch / separate kernels, B = 128, 32/8 heads, copy and fp16 image: 2048 rows 14.0 / 35.9, 4096 27.1 / 45.1, 8192 47.2 / 61.7; the copy
+  // alone (ragged): 2048 10.3 / 28.4, 4096 21.4 / 32.9, 5024 28.4 / 33.7, 8192 39.3 / 42.3; with a plan of pairs: B = 64, 8192 31.6 / 52.6, d = 256,
+  // 4096 22.1 / 50.8; 32 rows 4.2.  Beyond, the plan takes longer than the image.  Calls that write none (prism_sparse_attn_pre, most packed
+  // batches) would have their line lower: 2048 rows 10 / 18, 4096 17.0 / 18.6, 5024 21.9 / 18.6, 8192 32.4 / 18.8, of calls of 700 - 1300 us
+  // (attention and all, 5024 677 / 673, 8192 1275 / 1280, where the separate kernels plan no row with a CU to itself).
   DirtyFlags flags = {plan + kPlanFlags, nullptr, 1, 0};
   // Two sets of pull counters in row_part, which the preparation is done with: of the pair kernel and the one behind it, or
   // of the 64-queries-per-wave kernel and the one behind it.  A short table holds them closer together.

@@ -1470,8 +1470,12 @@ static int estimate_core(const prism_params* params, const HeadStrides& hs, cons
   // they would leave SIMDs with less than four waves.  us of the estimate with the rotation, four / eight waves: 28/4 heads, 65536
   // tokens (896 strips) 276 / 282, 32/8, B = 64, 32768 (1024) 205 / 211, 28/4, 52000 (728) 218.4 / 217.9, 47000 (644) 200 / 198, 40960
   // (560) 176 / 171, 16/4, 65536 (512) 182 / 168, 32/8, 22000 (352) 116 / 107.
+  // The other head dims, without the rotation, lie on either side of that line: d = 256, 32/8, 40960 (640) 216.6 / 219.2, 49152 (768) 251 /
+  // 259, 65536 (1024) 333 / 352, 22000 (352) 128 / 121; d = 64, 52000 (832) 110 / 105, 65536 130 / 138, 16/4, 65536 (512) 87 / 71.
   // Of up to 16 (1024 blocks): eight waves of two rows, or sixteen of one where every strip has a CU to itself: 32/8, 131072
-  // (2048 strips) 721 / 768, 8/2, 100000 (392) 133 / 135, 7/1, 70000 (245) 87 / 81, 4/1, 100000 (196) 93 / 84.
+  // (2048 strips) 721 / 768, 8/2, 100000 (392) 133 / 135, 7/1, 70000 (245) 87 / 81, 4/1, 100000 (196) 93 / 84; d = 256, 8/2, 100000 163 /
+  // 169, B = 64, 60000 (472) 136 / 144, 4/1, 65536 (256) 99 / 89; d = 64, 8/2, 100000 75.9 / 75.2, 16/4, 130000 (1024) 163 / 169, B = 64,
+  // 4/1, 60000 (236) 59 / 48.
   // Beyond (a 131 KB logit strip, one workgroup per CU): sixteen waves of one row (eight of two at half the waves a SIMD 757, now 702;
   // 28/4, B = 64, 100000).
   const int64_t strips = (int64_t)seqs.tiles * params->n_q_heads;
