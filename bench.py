@@ -443,7 +443,7 @@ def main() -> int:
     exec_tflops = flop_exec / (ms_attn * 1e-3) / 1e12
     # the attention kernel against the memory roof: bytes that crossed the L2 <-> fabric boundary
     # per launch (rocprofv3 counters of the committed profile of this workload) over the launch time
-    # measured here.  The no-reuse bytes (K and V^T tile per listed block, Q in, O out) are kept
+    # measured here.  The no-reuse bytes (K and V tile per listed block, Q in, O out) are kept
     # beside it as the algorithmic figure; rows that share tiles are served by the L2s.
     w64 = (B == 128 and L % 128 == 0)
     pair = (B == 64 and N % 2 == 0 and h * N >= 4096)       # two q-blocks per workgroup (pair kernel)
