@@ -970,7 +970,9 @@ __device__ __forceinline__ void write_columns(uint64_t mine, int W, int64_t base
 // counts of all strips in front of it, counts its own rows from their bits, and writes offsets and columns.  us of the whole
 // estimate, sums over row counts (short calls) or separate scan and fill (others) -> sums over strip counts: 32/8 heads, 8192 tokens
 // 32.3 -> 30.1, 20011 70.8 -> 68.3, d = 64, 12345 32.8 -> 31.2, the eight packed prompts of perf/cases.py 123.1 -> 118.8, 32768 107.6 -> 105.0,
-// B = 64, 32768 168.7 -> 166.6, 131072 487 -> 480.  (The calibration inside select_kernel as well costs it what its own launch
+// B = 64, 32768 168.7 -> 166.6, 131072 487 -> 480.  The sums in front grow with the square of the strips and still cost less than
+// the two launches where heads are many and short (estimates as they were / with the selection's forms too): 16384 heads of 8 blocks 1843 /
+// 1518, 32768 of one 741 / 690, 65000 of one 1357 / 1332.  (The calibration inside select_kernel as well costs it what its own launch
 // takes: 87.7 -> 93.4 us at 28/4 heads, 65536 tokens.)
 template <int kSeqs>
 __global__ __launch_bounds__(1024) void compact_kernel(const uint64_t* __restrict__ mask_bits,
